@@ -1,0 +1,200 @@
+"""What is measured: the calls a user of the library makes, from one decode GEMV to a prefill of
+hundreds of rows, through the public entry points (paper_2407_00088_amd.runner.LinearLUT and
+tmac_mpgemv_fused_multi).
+
+A case is a dict of plain values:
+
+  call   "fused"     one decode launch, tables built in the kernel (LinearLUT.forward_fused)
+         "two_call"  table precompute, then the look-ups (LinearLUT.forward)
+         "one_call"  either layout, any number of rows (LinearLUT.forward_one_call)
+         "multi"     several matrices in one launch (tmac_mpgemv_fused_multi): (M, M), (F, M), (M, F)
+         "block"     the seven projections of a decoder block in four launches, replayed from a HIP
+                     graph: Q, K, V (M x M) in one, O (M x M), gate and up (F x M) in one, down (M x F)
+  act    "f16", "i8" (int8 activations with one scale per row against ternary weights with one scale
+         per tensor: exact integer arithmetic), "tq" (fp16 activations, tables quantised to int8)
+  N rows of activations, M x K weights of `bits` bits, a scale and zero per `group` elements of a row
+  (group == K: one per row; 0: one per tensor), `out` "f32" or "f16".
+"""
+import math
+
+import numpy as np
+import torch
+
+import paper_2407_00088_amd as T
+from paper_2407_00088_amd import binding as B
+from paper_2407_00088_amd.runner import LinearLUT
+
+BIGGEST_WEIGHTS = 28672 * 8192          # elements of the largest weight matrix
+BIGGEST_PRODUCT = 13824 * 5120 * 511    # largest N M K
+
+
+def listed():
+    return [
+        # smallest call: nothing but launch and latency
+        dict(name="decode_tiny", call="fused", act="f16", N=1, M=256, K=256, bits=2, group=32, out="f32"),
+        # one projection of a 7B-sized decoder, the two documented calls one after the other
+        dict(name="decode_two_call", call="two_call", act="f16", N=1, M=4096, K=4096, bits=4, group=128, out="f32"),
+        # odd sizes, three bits, small groups
+        dict(name="decode_ragged", call="fused", act="f16", N=1, M=5003, K=3232, bits=3, group=32, out="f32"),
+        # token generation: all projections of a 7B-sized decoder block, replayed as a serving loop does
+        dict(name="decode_block", call="block", act="f16", N=1, M=4096, F=11008, bits=4, group=128, out="f32"),
+        # ternary weights, int8 activations: the three shapes of a 3B-sized model in one launch
+        dict(name="decode_ternary", call="multi", act="i8", N=1, M=3200, F=8640, bits=2, group=0, out="f32"),
+        # the largest single decode GEMV
+        dict(name="decode_large", call="fused", act="f16", N=1, M=28672, K=8192, bits=4, group=128, out="f16"),
+        # a few users or a few speculated tokens at once, in the decode layout
+        dict(name="batch_4", call="fused", act="f16", N=4, M=4096, K=4096, bits=4, group=128, out="f32"),
+        # batched decode
+        dict(name="batch_16", call="one_call", act="f16", N=16, M=11008, K=4096, bits=4, group=128, out="f16"),
+        # batched decode at odd sizes, small groups
+        dict(name="batch_45_ragged", call="two_call", act="f16", N=45, M=4099, K=3232, bits=3, group=32, out="f32"),
+        # prefill, the paper's sequence length
+        dict(name="prefill_256", call="two_call", act="f16", N=256, M=5120, K=5120, bits=4, group=128, out="f32"),
+        # ternary prefill, exact integers
+        dict(name="prefill_ternary", call="one_call", act="i8", N=128, M=8640, K=3200, bits=2, group=0, out="f32"),
+        # the largest: an odd number of rows on the widest layer
+        dict(name="prefill_511", call="one_call", act="f16", N=511, M=13824, K=5120, bits=2, group=128, out="f32"),
+    ]
+
+
+def _log_int(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    call = rng.choice(["fused", "fused", "two_call", "two_call", "one_call", "one_call", "multi", "block"])
+    bits = rng.choice([1, 2, 3, 4, 4])
+    if call in ("multi", "block"):
+        ternary = call == "multi" and rng.random() < 0.4
+        M = 128 * _log_int(rng, 8, 32)
+        c = dict(call=call, act="i8" if ternary else "f16", N=1, M=M, F=128 * int(M / 128 * rng.uniform(2.5, 3.0)),
+                 bits=2 if ternary else bits, group=0 if ternary else rng.choice([64, 128]), out="f32")
+        return c
+    if call == "fused":
+        N = rng.choice([1, 1, 1, 2, 3, 5, 8])
+    elif call == "two_call":
+        N = rng.choice([1, 2, 4, _log_int(rng, 9, 64), _log_int(rng, 65, 511), _log_int(rng, 65, 511)])
+    else:
+        N = rng.choice([1, 8, _log_int(rng, 9, 32), _log_int(rng, 33, 64), _log_int(rng, 65, 511)])
+    act = rng.choice(["f16", "f16", "f16", "i8"] + (["tq"] if call == "fused" else []))
+    while True:
+        M, K = _log_int(rng, 256, 28672), 32 * _log_int(rng, 8, 430)
+        if M * K <= BIGGEST_WEIGHTS // 4 and M * K * N <= BIGGEST_PRODUCT:
+            break
+    if act == "i8":
+        return dict(call=call, act=act, N=N, M=M, K=K, bits=2, group=0, out="f32")
+    group = rng.choice([g for g in (32, 64, 128, 128, 128, K) if K % g == 0])
+    return dict(call=call, act=act, N=N, M=M, K=K, bits=bits, group=group, out=rng.choice(["f32", "f32", "f16"]))
+
+
+def _shapes(case):
+    if "F" not in case:
+        return [(case["M"], case["K"])]
+    h, f = case["M"], case["F"]
+    if case["call"] == "multi":
+        return [(h, h), (f, h), (h, f)]
+    return [(h, h), (h, h), (h, h), (h, h), (f, h), (f, h), (h, f)]
+
+
+def _weights(case, M, K, gen):
+    """Packed weights on the GPU: uniform codes (ternary: -1, 0, +1 with 1/4, 1/2, 1/4), scales in
+    [0.01, 0.1], zeros anywhere between the smallest and the largest code."""
+    bits, group = case["bits"], case["group"]
+    kw = dict(max_N=case["N"], int_path=case["act"] == "i8")
+    if group == 0:
+        q = (torch.randint(0, 4, (M, K), dtype=torch.uint8, device="cuda", generator=gen) + 1) // 2
+        return LinearLUT(M, K, bits, 0, q.cpu().numpy(), zero_point=1.0, weight_scale=0.02, **kw)
+    q = torch.randint(0, 1 << bits, (M, K), dtype=torch.uint8, device="cuda", generator=gen)
+    s = torch.rand((M, K // group), device="cuda", generator=gen) * 0.09 + 0.01
+    z = torch.rand((M, K // group), device="cuda", generator=gen) * ((1 << bits) - 1)
+    return LinearLUT(M, K, bits, group, q.cpu().numpy(), s.half().cpu().numpy(), z.half().cpu().numpy(), **kw)
+
+
+def _activations(case, K, gen):
+    """Gaussian with a few large channels, as a transformer's hidden states have them; int8: quantised
+    per row to its largest magnitude."""
+    a = torch.randn((case["N"], K), device="cuda", generator=gen)
+    a *= torch.where(torch.rand((1, K), device="cuda", generator=gen) < 0.002, 30.0, 1.0)
+    if case["act"] != "i8":
+        return a.half(), None
+    scale = a.abs().amax(dim=1) / 127.0
+    return torch.round(a / scale[:, None]).clamp(-127, 127).to(torch.int8), scale
+
+
+def prepare(case, seed):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    shapes = _shapes(case)
+    lins = [_weights(case, M, K, gen) for M, K in shapes]
+    out_t, dt = (B.TMAC_OUT_F16, torch.float16) if case["out"] == "f16" else (B.TMAC_OUT_F32, torch.float32)
+    state = dict(call=case["call"], lins=lins, out_t=out_t, tq=B.TMAC_ACT_F16_TQ if case["act"] == "tq" else None)
+    if len(shapes) == 1:
+        state["A"], state["scale"] = _activations(case, shapes[0][1], gen)
+        return state
+    outs = [torch.empty((case["N"], M), dtype=dt, device="cuda") for M, _ in shapes]
+    state["outs"] = outs
+    if case["call"] == "multi":
+        acts = {K: _activations(case, K, gen) for K in sorted({K for _, K in shapes})}
+        state["items"] = [(lin.desc, lin.packed, *acts[lin.K][:1], o, acts[lin.K][1], lin.weight_scale)
+                          for lin, o in zip(lins, outs)]
+        return state
+    # a decoder block: what lies between the projections (norms, attention, activation) is not part of
+    # this library, so each launch has an input of its own
+    h, f = case["M"], case["F"]
+    x = [_activations(case, K, gen)[0] for K in (h, h, h, f)]
+    state["x"] = x
+
+    def item(i, a):
+        return lins[i].desc, lins[i].packed, a, outs[i]
+
+    def step():
+        T.tmac_mpgemv_fused_multi([item(0, x[0]), item(1, x[0]), item(2, x[0])], 1, out_t)
+        lins[3].mpgemv_fused(x[1], 1, outs[3], out_t)
+        T.tmac_mpgemv_fused_multi([item(4, x[2]), item(5, x[2])], 1, out_t)
+        lins[6].mpgemv_fused(x[3], 1, outs[6], out_t)
+
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        step()
+    side.synchronize()
+    state["graph"] = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(state["graph"], stream=side):
+        step()
+    return state
+
+
+def run(state):
+    call, lins = state["call"], state["lins"]
+    if call == "block":
+        state["graph"].replay()
+        return state["outs"]
+    if call == "multi":
+        T.tmac_mpgemv_fused_multi(state["items"], state["items"][0][2].shape[0], state["out_t"])
+        return state["outs"]
+    if call == "fused":
+        return lins[0].forward_fused(state["A"], out_t=state["out_t"], act_scale=state["scale"], act=state["tq"])
+    if call == "two_call":
+        return lins[0].forward(state["A"], out_t=state["out_t"], act_scale=state["scale"])
+    return lins[0].forward_one_call(state["A"], out_t=state["out_t"], act_scale=state["scale"])
+
+
+def work(case):
+    """Indices, scales and zeros, activations and results, each moved once."""
+    N, nbytes, flops = case["N"], 0, 0
+    for M, K in _shapes(case):
+        group = case["group"]
+        nbytes += M * K * case["bits"] // 8 + (M * (K // group) * 4 if group else 0)
+        nbytes += N * K * (1 if case["act"] == "i8" else 2) + N * M * (2 if case["out"] == "f16" else 4)
+        flops += 2 * N * M * K
+    return {"bytes": nbytes, "flops": flops}
+
+
+def tolerance(case):
+    """Against the product in 64 bits the listed cases are off by 2.3e-4 to 4.1e-4 (2-norm: fp16 table
+    entries and chunk sums), the worst single result by 3.0e-3 of the root mean square; four times that."""
+    if case["act"] == "i8":
+        return "exact"           # integers, then two roundings in a fixed order
+    if case["act"] == "tq":
+        return {"rel": 1e-3}     # the same int8 entries but for ties at half-integers (2e-4 each)
+    return {"rel": 1.6e-3, "max": 1.2e-2}
