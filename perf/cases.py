@@ -96,18 +96,25 @@ def _shapes(case):
     return [(h, h), (h, h), (h, h), (h, h), (f, h), (f, h), (h, f)]
 
 
-def _weights(case, M, K, gen):
-    """Packed weights on the GPU: uniform codes (ternary: -1, 0, +1 with 1/4, 1/2, 1/4), scales in
-    [0.01, 0.1], zeros anywhere between the smallest and the largest code."""
+def _codes(case, M, K, gen):
+    """Uniform codes (ternary: -1, 0, +1 with 1/4, 1/2, 1/4), scales in [0.01, 0.1], zeros anywhere
+    between the smallest and the largest code; scales and zeros None where the tensor has one of each."""
     bits, group = case["bits"], case["group"]
-    kw = dict(max_N=case["N"], int_path=case["act"] == "i8")
     if group == 0:
-        q = (torch.randint(0, 4, (M, K), dtype=torch.uint8, device="cuda", generator=gen) + 1) // 2
-        return LinearLUT(M, K, bits, 0, q.cpu().numpy(), zero_point=1.0, weight_scale=0.02, **kw)
+        return (torch.randint(0, 4, (M, K), dtype=torch.uint8, device="cuda", generator=gen) + 1) // 2, None, None
     q = torch.randint(0, 1 << bits, (M, K), dtype=torch.uint8, device="cuda", generator=gen)
     s = torch.rand((M, K // group), device="cuda", generator=gen) * 0.09 + 0.01
     z = torch.rand((M, K // group), device="cuda", generator=gen) * ((1 << bits) - 1)
-    return LinearLUT(M, K, bits, group, q.cpu().numpy(), s.half().cpu().numpy(), z.half().cpu().numpy(), **kw)
+    return q, s.half(), z.half()
+
+
+def _weights(case, M, K, gen):
+    """Packed weights on the GPU."""
+    q, s, z = _codes(case, M, K, gen)
+    kw = dict(max_N=case["N"], int_path=case["act"] == "i8")
+    if s is None:
+        return LinearLUT(M, K, case["bits"], 0, q.cpu().numpy(), zero_point=1.0, weight_scale=0.02, **kw)
+    return LinearLUT(M, K, case["bits"], case["group"], q.cpu().numpy(), s.cpu().numpy(), z.cpu().numpy(), **kw)
 
 
 def _activations(case, K, gen):
@@ -177,6 +184,37 @@ def run(state):
     if call == "two_call":
         return lins[0].forward(state["A"], out_t=state["out_t"], act_scale=state["scale"])
     return lins[0].forward_one_call(state["A"], out_t=state["out_t"], act_scale=state["scale"])
+
+
+def exact(case, seed):
+    """The product of the activations with the de-quantised weights in 64 bits, laid out as `run` returns it."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    shapes = _shapes(case)
+    raw = [_codes(case, M, K, gen) for M, K in shapes]        # the order of the draws is that of prepare
+    if len(shapes) == 1:
+        acts = [_activations(case, shapes[0][1], gen)]
+    elif case["call"] == "multi":
+        by_k = {K: _activations(case, K, gen) for K in sorted({K for _, K in shapes})}
+        acts = [by_k[K] for _, K in shapes]
+    else:
+        h, f = case["M"], case["F"]
+        x = [_activations(case, K, gen) for K in (h, h, h, f)]
+        acts = [x[0], x[0], x[0], x[1], x[2], x[2], x[3]]
+    outs = []
+    for (M, K), (q, s, z), (a, scale) in zip(shapes, raw, acts):
+        a, out = a.double(), torch.empty((case["N"], M), dtype=torch.float64, device="cuda")
+        for lo in range(0, M, 4096):                          # (a few GB of 64-bit weights at a time)
+            w = q[lo:lo + 4096].double()
+            if s is None:
+                # whole numbers, then the two roundings of the entry point: by the row's scale, by the tensor's
+                r = (a @ (w - 1.0).t()).float() * scale[:, None]
+                out[:, lo:lo + 4096] = (r * torch.tensor(0.02, dtype=torch.float32, device="cuda")).double()
+                continue
+            s64, z64 = (t[lo:lo + 4096].double().repeat_interleave(case["group"], dim=1) for t in (s, z))
+            out[:, lo:lo + 4096] = a @ (s64 * (w - z64)).t()
+        outs.append(out)
+    return outs[0] if len(shapes) == 1 else outs
 
 
 def work(case):
