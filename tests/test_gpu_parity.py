@@ -1111,6 +1111,28 @@ def test_many_rows_two_n_tiles_per_workgroup(T, torch, N, bits, group):
     check_int(T, torch, pt, layout=L3)
 
 
+@pytest.mark.parametrize("off,ldo_extra", [(0, 1), (1, 3), (2, 2), (0, 0)])
+def test_slice_sums_four_outputs_per_thread(T, torch, off, ldo_extra):
+    """Calls of at least 2^19 outputs add their K slices four outputs to a thread: M that is no multiple of
+    four, output pointers and leading dimensions that allow one store per thread, every other one, or none;
+    fp32, fp16 (the rounded fp32 result) and exact int32 outputs, nothing written outside the rows."""
+    N, M, K = 127, 4163, 1024                                       # four slices
+    p = wl.make_ternary(0, 1460 + off, N, M, K, name="wide_sum")
+    lin = make_lin(p, L3)
+    A, s_a = torch.from_numpy(p.act_q).cuda(), torch.from_numpy(p.act_scale).cuda()
+    ref_i = orc.ternary_int_matmul(p.act_q, p.q, 1)
+    ref_f = orc.int_path_output_f32(ref_i, p.act_scale, p.weight_scale)
+    lin.precompute(A)
+    for out_t, dt, want in ((T.TMAC_OUT_I32, torch.int32, ref_i.astype(np.int32)), (T.TMAC_OUT_F32, torch.float32, ref_f),
+                            (T.TMAC_OUT_F16, torch.float16, ref_f.astype(np.float16))):
+        flat = torch.full((N * (M + ldo_extra) + off + 8,), 77, dtype=dt, device="cuda")
+        rows = flat[off: off + N * (M + ldo_extra)].view(N, M + ldo_extra)
+        lin.mpgemm(N, rows[:, :M], out_t, act_scale=s_a)
+        assert np.array_equal(rows[:, :M].cpu().numpy(), want), (out_t, off, ldo_extra)
+        assert bool((rows[:, M:] == 77).all()) and bool((flat[:off] == 77).all())
+        assert bool((flat[off + N * (M + ldo_extra):] == 77).all())
+
+
 def test_large_call_takes_two_row_tiles_per_workgroup_by_default(T, torch):
     """From about 8000 wavefronts on (here 8192 x 8192: 1024 row tiles x 8 waves) the register-table
     kernel serves 16 rows per workgroup unless told otherwise: the default call, the call with 8 rows
