@@ -15,7 +15,8 @@
 //     the indices of eight consecutive tables, and two mask-and-shift operations turn them into
 //     the byte offsets of the entries (even and odd tables) four at a time.
 //   * Aggregation: the eight entries of a chunk and plane are added as packed 16-bit pairs, two
-//     activation rows per instruction, then widened.  Exact for integer tables.  For fp16 tables
+//     activation rows per instruction, then widened.  Exact for integer tables (32-bit additions of
+//     biased pairs, two entries per instruction: rows_int_bias).  For fp16 tables
 //     this is this library's own choice and it is lossy (three fp16 roundings per chunk sum: about
 //     1.5e-4 -> 3.4e-4 relative error, still a sixth of the 2e-3 bar); it is not the paper's "fast
 //     8-bit aggregation" (Section 4), an integer averaging trick that is not built here.
@@ -121,10 +122,27 @@ struct RowsShape {
 };
 
 
+// Integer tables in LDS hold their entries plus 128 g, which makes them non-negative 16-bit values
+// (|entry| <= 128 g), so that two of them side by side in a dword are added by plain 32-bit additions
+// without a carry from one to the other: v_add3_u32 adds two entries' pairs in the time v_pk_add_i16
+// takes for one (1.8 ns per wavefront and SIMD each).  The 32 / g entries of a chunk and plane add up to
+// their sum plus ROWS_CHUNK_BIAS, at most twice that; planes 0..2 fit 16 bits together with their
+// weights 1, 2, 4 (7 * 8192 < 65536).
+constexpr int rows_int_bias(int g) { return 128 * g; }
+constexpr int ROWS_CHUNK_BIAS = 4096;  // (32 / g) * 128 g
+
+// l += (one half of pair) * W: the widening of a 16-bit sum, one instruction
+template <int W>
+__device__ __forceinline__ void rows_widen(int& l0, int& l1, uint32_t pair) {
+  asm("v_mad_u32_u16 %0, %1, %2, %0" : "+v"(l0) : "v"(pair), "n"(W));
+  asm("v_mad_u32_u16 %0, %1, %2, %0 op_sel:[1,0,0,0]" : "+v"(l1) : "v"(pair), "n"(W));
+}
+
 // Algorithm 1 Precompute for one (activation row, LUT group of four) inside a lookup kernel: the
 // eight entries 8h..8h+7 of the table, as four dwords of two 16-bit entries, with the arithmetic
 // of the stand-alone precompute kernel ((+-a0 +- a1) + (+-a2 - a3), every addition in fp16;
-// entries 8..15 are the negated entries 7..0: mirror consolidation, Section 3.3).
+// entries 8..15 are the negated entries 7..0: mirror consolidation, Section 3.3).  Integer entries come
+// with their bias (rows_int_bias).
 template <bool IS_INT>
 __device__ __forceinline__ ru32x4v rows_build_half_table(const void* A, int64_t lda, int n, int kg, int h, bool live) {
   uint32_t low[4];  // entries 0..7
@@ -140,7 +158,7 @@ __device__ __forceinline__ ru32x4v rows_build_half_table(const void* A, int64_t 
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
       const int x = h ? -e[7 - 2 * d] : e[2 * d], y = h ? -e[6 - 2 * d] : e[2 * d + 1];
-      low[d] = ((uint32_t)x & 0xffffu) | ((uint32_t)y << 16);
+      low[d] = ((uint32_t)x + ((uint32_t)y << 16)) + (uint32_t)rows_int_bias(4) * 0x10001u;
     }
     return ru32x4v{low[0], low[1], low[2], low[3]};
   } else {
@@ -159,7 +177,8 @@ __device__ __forceinline__ ru32x4v rows_build_half_table(const void* A, int64_t 
 // Stage a K slice of tables into LDS: the LUT buffer holds them in the LDS layout, so this is a copy,
 // `per` 16-byte pieces per thread, all loads requested before the first store; consecutive lanes
 // write consecutive 16 bytes (no bank conflicts).  Tables from kg_end on are written as zeros.
-template <int NT, int G, int BYTES>
+// Integer entries get their bias on the way.
+template <bool IS_INT, int NT, int G, int BYTES>
 __device__ __forceinline__ void rows_stage_copy(const RowsParams& p, char* tab, int ntile, int kg0, int kg_end) {
   using Sh = RowsShape<NT, G>;
   constexpr int THREADS = 64 * ROWS_WAVES, PER = BYTES / 16 / THREADS;
@@ -178,7 +197,13 @@ __device__ __forceinline__ void rows_stage_copy(const RowsParams& p, char* tab, 
   for (int i = 0; i < PER; ++i) {
     const int off = (i * THREADS + (int)threadIdx.x) * 16;
     const ru32x4v z = {0u, 0u, 0u, 0u};
-    *reinterpret_cast<ru32x4v*>(tab + off) = off < live_bytes ? v[i] : z;
+    ru32x4v e = off < live_bytes ? v[i] : z;
+    if constexpr (IS_INT) {
+      constexpr short be = (short)rows_int_bias(G);
+#pragma unroll
+      for (int d = 0; d < 4; ++d) e[d] = __builtin_bit_cast(uint32_t, (rs2v)(__builtin_bit_cast(rs2v, (uint32_t)e[d]) + rs2v{be, be}));
+    }
+    *reinterpret_cast<ru32x4v*>(tab + off) = e;
   }
 }
 
@@ -229,6 +254,7 @@ __device__ __forceinline__ void rows_chunk(const uint32_t (&x)[BITS], uint32_t c
   // rounds of 16 LDS reads (one, two or four planes at g = 2, 4, 8): the hardware counts at
   // most 15 outstanding LDS operations exactly, so a round's reads can be consumed as they return
   constexpr int PL = 16 / (TPC * OCT);
+  uint32_t c[OCT * HD];  // integer tables: planes 0..2 with their weights, as biased 16-bit pairs
 #pragma unroll
   for (int b0 = 0; b0 < BITS; b0 += PL) {
     uint32_t e[PL][TPC][OCT * HD];
@@ -275,11 +301,11 @@ __device__ __forceinline__ void rows_chunk(const uint32_t (&x)[BITS], uint32_t c
       }
     }
     __builtin_amdgcn_sched_barrier(0);  // keep the reads above the accumulation
-    // The entries of a plane (one per table of the chunk) are added pairwise as packed 16-bit
-    // values, two activation rows per instruction: exact for the integer tables (|sum| <= 4096),
-    // log2(32/g) roundings to fp16 for the fp16 tables (lossy, this library's choice: the widening
-    // happens once per chunk and plane); the chunk sum then enters the 32-bit sum of the
-    // quantisation group times 2^plane.
+    // fp16 tables: the entries of a plane (one per table of the chunk) are added pairwise as packed
+    // fp16 values, two activation rows per instruction: log2(32/g) roundings to fp16 (lossy, this
+    // library's choice: the widening happens once per chunk and plane); the chunk sum then enters the
+    // 32-bit sum of the quantisation group times 2^plane.  Integer tables: exact, see rows_int_bias; the
+    // biases of a chunk, ROWS_CHUNK_BIAS * (2^BITS - 1), are in L's start value.
 #pragma unroll
     for (int bb = 0; bb < PL; ++bb) {
       const int b = b0 + bb;
@@ -287,12 +313,15 @@ __device__ __forceinline__ void rows_chunk(const uint32_t (&x)[BITS], uint32_t c
 #pragma unroll
       for (int u = 0; u < OCT * HD; ++u) {
         if constexpr (IS_INT) {
-          rs2v q[TPC];
+          uint32_t q = e[bb][0][u];
 #pragma unroll
-          for (int j = 0; j < TPC; ++j) q[j] = __builtin_bit_cast(rs2v, e[bb][j][u]);
-          tree_sum(q);
-          L[2 * u] += (int)q[0].x << b;
-          L[2 * u + 1] += (int)q[0].y << b;
+          for (int j = 1; j < TPC; ++j) q += e[bb][j][u];
+          if (b < 3) {
+            c[u] = b == 0 ? q : c[u] + (q << b);
+            if (b == (BITS < 3 ? BITS - 1 : 2)) rows_widen<1>(L[2 * u], L[2 * u + 1], c[u]);
+          } else {
+            rows_widen<8>(L[2 * u], L[2 * u + 1], q);
+          }
         } else {
           rh2v q[TPC];
 #pragma unroll
@@ -305,6 +334,51 @@ __device__ __forceinline__ void rows_chunk(const uint32_t (&x)[BITS], uint32_t c
       }
     }
     __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// The same for integer tables in the many-row kernel's usual shape (eight activation rows, g = 4), in
+// rounds of the eight reads of one plane and row set instead of sixteen: a round's entries take 32
+// registers, which leaves room for more wavefronts, and a SIMD's wavefronts cover each other's reads.
+// Bound by the look-up rate of LDS and the vector ALUs about equally: per plane and 16 activation rows
+// sixteen reads (110 ns with four wavefronts on the CU's four SIMDs) and 11 address, 32 adding and 8 to
+// 16 widening instructions (95 ns).  128 rows x 8640 x 3200 at 2 bit: 67.8 us with packed 16-bit adds,
+// 60.4 with rounds of sixteen reads, 53.8 like this (next round's reads ahead of a round's sums: 60.0).
+// fp16 tables gain nothing from the shorter rounds (the vector ALUs bind there).
+template <int BITS, int OCT, int OSTRIDE>
+__device__ __forceinline__ void rows_chunk_int(const uint32_t (&x)[BITS], uint32_t cbase, int (&L)[8 * OCT]) {
+  using Sh = RowsShape<8, 4>;
+  constexpr int TPC = Sh::TPC, HD = Sh::HD, TB = Sh::TB;
+  uint32_t c[OCT * HD];  // planes 0..2 with their weights, as biased 16-bit pairs
+#pragma unroll
+  for (int b = 0; b < BITS; ++b) {
+    const uint32_t even = (x[b] << 4) & 0xF0F0F0F0u, odd = x[b] & 0xF0F0F0F0u;
+    uint32_t a[TPC];
+#pragma unroll
+    for (int j = 0; j < TPC; ++j) a[j] = __builtin_amdgcn_perm(j & 1 ? odd : even, cbase, 0x0C020100u + 4u + (uint32_t)(j / 2));
+#pragma unroll
+    for (int o = 0; o < OCT; ++o) {
+      ru32x4v e[TPC];
+#pragma unroll
+      for (int j = 0; j < TPC; ++j) e[j] = *reinterpret_cast<rows_lds_u32x4*>(a[j] + j * TB + o * OSTRIDE);
+      __builtin_amdgcn_sched_barrier(0);  // keep the reads above the accumulation
+#pragma unroll
+      for (int u = 0; u < HD; ++u) {
+        uint32_t q = e[0][u];
+#pragma unroll
+        for (int j = 1; j < TPC; ++j) q += e[j][u];
+        int& l0 = L[8 * o + 2 * u];
+        int& l1 = L[8 * o + 2 * u + 1];
+        uint32_t& cc = c[o * HD + u];
+        if (b < 3) {
+          cc = b == 0 ? q : cc + (q << b);
+          if (b == (BITS < 3 ? BITS - 1 : 2)) rows_widen<1>(l0, l1, cc);
+        } else {
+          rows_widen<8>(l0, l1, q);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
   }
 }
 
@@ -387,7 +461,7 @@ __global__ __launch_bounds__(64 * ROWS_WAVES) void mpgemm_rows_kernel(const Rows
   float acc[NTT];
   AccT L[NTT];
 #pragma unroll
-  for (int t = 0; t < NTT; ++t) { acc[t] = 0.f; L[t] = 0; }
+  for (int t = 0; t < NTT; ++t) acc[t] = 0.f;
   float w[4] = {p.pw[0], p.pw[1], p.pw[2], p.pw[3]};
 
   auto load_idx = [&](int c, uint32_t (&x)[BITS]) {
@@ -408,22 +482,27 @@ __global__ __launch_bounds__(64 * ROWS_WAVES) void mpgemm_rows_kernel(const Rows
   const int cz0 = blockIdx.z * p.cps, cz1 = min(cz0 + p.cps, p.n_chunks);
   const int kg_end = min(cz1 * TPC, p.KG);  // tables beyond it are read as zero
   int gq = p.grouped ? cz0 / p.cpg : 0, cg = 0;  // current quantisation group, chunks done in it (wave-uniform)
-  // {scale, zero} of the lane's row and the activation sums of a group, requested one group ahead
+  // {scale, zero} of the lane's row and the activation sums of a group (wave-uniform: scalar registers):
+  // requested one group ahead for fp tables, which need them when the group starts, and when the group
+  // starts for integer tables, which need them when it ends
   uint32_t szv = 0, szv_next = 0;
-  float Sg[NTT], Sg_next[NTT];
+  AccT Sg[NTT], Sg_next[NTT];
   auto load_group = [&](int g) {
     const int gc = min(g, p.nq - 1);
     szv_next = my_sz[(size_t)gc * 64];
 #pragma unroll
     for (int t = 0; t < NTT; ++t) {
       const int n = min(n0 + t, p.N - 1);
-      if constexpr (IS_INT) Sg_next[t] = (float)static_cast<const int*>(p.S)[(size_t)n * p.nq + gc];
-      else Sg_next[t] = static_cast<const float*>(p.S)[(size_t)n * p.nq + gc];
+      Sg_next[t] = static_cast<const AccT*>(p.S)[(size_t)n * p.nq + gc];
     }
   };
 #pragma unroll
-  for (int t = 0; t < NTT; ++t) Sg[t] = Sg_next[t] = 0.f;
-  if (p.grouped) load_group(gq);
+  for (int t = 0; t < NTT; ++t) Sg[t] = Sg_next[t] = 0;
+  if (p.grouped && !IS_INT) load_group(gq);
+  // (integer tables: minus the biases of the chunks that enter one sum, a group's or this workgroup's)
+  const AccT L0 = IS_INT ? (AccT)(-ROWS_CHUNK_BIAS * ((1 << BITS) - 1) * (p.grouped ? p.cpg : cz1 - cz0)) : (AccT)0;
+#pragma unroll
+  for (int t = 0; t < NTT; ++t) L[t] = L0;
   uint32_t xn[BITS];
   load_idx(cz0, xn);
 
@@ -435,7 +514,7 @@ __global__ __launch_bounds__(64 * ROWS_WAVES) void mpgemm_rows_kernel(const Rows
       const int last8 = (p.N + NT - 1) / NT - 1;  // last n tile of the LUT buffer (a second row set past it repeats it)
 #pragma unroll
       for (int o = 0; o < OCT; ++o)
-        rows_stage_copy<NT, G, OSTRIDE>(p, tab + o * OSTRIDE, min((int)blockIdx.x * OCT + o, last8), c0 * TPC, kg_end);
+        rows_stage_copy<IS_INT, NT, G, OSTRIDE>(p, tab + o * OSTRIDE, min((int)blockIdx.x * OCT + o, last8), c0 * TPC, kg_end);
     }
     __syncthreads();
 
@@ -449,7 +528,8 @@ __global__ __launch_bounds__(64 * ROWS_WAVES) void mpgemm_rows_kernel(const Rows
       for (int b = 0; b < BITS; ++b) x[b] = xn[b];
       if (c + 1 < cz1) load_idx(c + 1, xn);  // next chunk's indices, one chunk ahead
       if (p.grouped && cg == 0 && gq < p.nq) {  // (chunks in the K padding belong to no group)
-        // a group starts: its scale/zero and activation sums have been requested a group ago
+        if constexpr (IS_INT) load_group(gq);
+        // (fp tables: the group's scale/zero and activation sums have been requested a group ago)
         szv = szv_next;
 #pragma unroll
         for (int t = 0; t < NTT; ++t) Sg[t] = Sg_next[t];
@@ -464,18 +544,22 @@ __global__ __launch_bounds__(64 * ROWS_WAVES) void mpgemm_rows_kernel(const Rows
         }
         // (the requests for the next group come after the last use of this group's values, so that they
         // can land in the same registers and nobody has to wait for them before the next group starts)
-        __builtin_amdgcn_sched_barrier(0);
-        load_group(gq + 1);
+        if constexpr (!IS_INT) {
+          __builtin_amdgcn_sched_barrier(0);
+          load_group(gq + 1);
+        }
       }
-      rows_chunk<IS_INT, BITS, NT, G, AccT, OCT, OSTRIDE>(x, lds0 + (uint32_t)(c - c0) * (uint32_t)CB, L, w);
+      const uint32_t cbase = lds0 + (uint32_t)(c - c0) * (uint32_t)CB;
+      if constexpr (IS_INT && NT == 8 && G == 4) rows_chunk_int<BITS, OCT, OSTRIDE>(x, cbase, L);
+      else rows_chunk<IS_INT, BITS, NT, G, AccT, OCT, OSTRIDE>(x, cbase, L, w);
       if (p.grouped && gq < p.nq && ++cg == p.cpg) {
         if constexpr (IS_INT) {
           const float s = __half2float(__ushort_as_half((uint16_t)(szv & 0xffffu)));
           const float z = __half2float(__ushort_as_half((uint16_t)(szv >> 16)));
 #pragma unroll
           for (int t = 0; t < NTT; ++t) {
-            acc[t] = fmaf(s, fmaf(p.mid - z, Sg[t], 0.5f * (float)L[t]), acc[t]);
-            L[t] = 0;
+            acc[t] = fmaf(s, fmaf(p.mid - z, (float)Sg[t], 0.5f * (float)L[t]), acc[t]);
+            L[t] = L0;
           }
         }
         cg = 0;
@@ -687,7 +771,7 @@ __global__ __launch_bounds__(64 * ROWS_WAVES) void mpgemm_rows8_kernel(const Row
     for (int it = threadIdx.x; it < R8_CH * Sh::CB / (8 * Sh::ES); it += 64 * ROWS_WAVES)
       rows_stage_item<NT, G, IS_INT>(p, tab, it, n0, cz0 * Sh::TPC, kg_end);
   } else {
-  rows_stage_copy<NT, G, R8_CH * Sh::CB>(p, tab, un.nt, cz0 * Sh::TPC, kg_end);
+  rows_stage_copy<IS_INT, NT, G, R8_CH * Sh::CB>(p, tab, un.nt, cz0 * Sh::TPC, kg_end);
   if (p.grouped && threadIdx.x < R8_CH * NT) {
     const int c = threadIdx.x / NT, t = threadIdx.x % NT;
     const int gq = min((cz0 + c) >> p.cpg_log2, p.nq - 1);
@@ -701,8 +785,10 @@ __global__ __launch_bounds__(64 * ROWS_WAVES) void mpgemm_rows8_kernel(const Row
   // 3. the chunks, straight-line
   float acc[NT];
   AccT L[NT];
+  // (integer tables: minus the biases of the chunks that enter one sum, a group's or this workgroup's)
+  const AccT L0 = IS_INT ? (AccT)(-ROWS_CHUNK_BIAS * ((1 << BITS) - 1) * (p.grouped ? 1 << p.cpg_log2 : nc)) : (AccT)0;
 #pragma unroll
-  for (int t = 0; t < NT; ++t) { acc[t] = 0.f; L[t] = 0; }
+  for (int t = 0; t < NT; ++t) { acc[t] = 0.f; L[t] = L0; }
   const int cmask = (1 << p.cpg_log2) - 1;
 #pragma unroll
   for (int c = 0; c < R8_CH; ++c) {
@@ -715,7 +801,7 @@ __global__ __launch_bounds__(64 * ROWS_WAVES) void mpgemm_rows8_kernel(const Row
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
           acc[t] = fmaf(s, fmaf(p.mid - z, sS[c][t], 0.5f * (float)L[t]), acc[t]);
-          L[t] = 0;
+          L[t] = L0;
         }
       }
     }

@@ -275,6 +275,28 @@ def test_int_path_extreme_values_four_bit_long_k(T, torch):
         assert np.array_equal(got.astype(np.int64), ref), layout
 
 
+@pytest.mark.parametrize("g", [2, 4, 8])
+@pytest.mark.parametrize("bits", [1, 2, 3, 4])
+@pytest.mark.parametrize("N", [3, 8, 73])
+def test_integer_sums_of_pairs_at_their_limits(T, torch, N, bits, g):
+    """Integer look-ups are added two activation rows to a dword, entries made non-negative by a bias:
+    rows of -128, 127 and both alternating (the largest entries of either sign, next to each other in a
+    dword) against all-zero, all-one and random codes stay exact for every bit-width and table size, with
+    K ending inside a chunk and inside a K slice."""
+    M, K = 70, 1032
+    rng = np.random.default_rng(97 + bits)
+    q = rng.integers(0, 1 << bits, size=(M, K), dtype=np.uint8)
+    q[0], q[1] = 0, (1 << bits) - 1
+    q[2, ::2], q[2, 1::2] = 0, (1 << bits) - 1
+    a_q = rng.integers(-128, 128, size=(N, K)).astype(np.int8)
+    a_q[0], a_q[1] = -128, 127
+    a_q[2, ::2], a_q[2, 1::2] = -128, 127
+    p = wl.Problem("pairs", 0, N, M, K, bits, 0, q, None, None, weight_scale=0.5, zero_point=1.0, act_q=a_q,
+                   act_scale=np.full(N, 0.5, np.float32))
+    ref = orc.ternary_int_matmul(a_q, q, 1)
+    assert np.array_equal(run_g(T, torch, p, g, int_out=T.TMAC_OUT_I32).astype(np.int64), ref)
+
+
 def test_int_tables_with_group_scales(T, torch, layout):
     """int8 activations against group-quantised 4-bit weights (W4A8): exact integer group sums,
     fp32 scale application; compared with the fp64 product of the de-quantised operands."""
