@@ -7,6 +7,11 @@
 
 #include "tmac.h"
 
+#if defined(__HIPCC__)
+#include <hip/hip_fp16.h>
+#include <hip/hip_runtime.h>
+#endif
+
 namespace tmac {
 
 constexpr uint32_t TMAC_MAGIC = 0x43414D54u;  // "TMAC"
@@ -154,6 +159,41 @@ __device__ inline __attribute__((always_inline)) float sum4_f16(uint32_t x01, ui
   asm("v_dot2_f32_f16 %0, %1, %2, 0" : "=v"(s) : "v"(x01), "s"(0x3C003C00u));
   return __builtin_amdgcn_fdot2(__builtin_bit_cast(tmac_h2, x23), ones, s, false);
 }
+// One wavefront per (n, quantisation group): the group sum S[n][gq] = sum of its activations,
+// four elements per lane and step (the row base, lda and the group size are multiples of 4),
+// then a butterfly.
+// BY16: stored as [set of 16 rows][group][16 rows] instead of [row][group].
+template <bool IS_INT, bool BY16 = false>
+__device__ inline __attribute__((always_inline)) void group_sums_wave(const void* __restrict__ A_, int N, int64_t lda,
+                                                void* __restrict__ S_, int Geff, int nq, int wave) {
+  const int lane = threadIdx.x & 63;
+  if (wave >= N * nq) return;
+  const int n = wave / nq, gq = wave % nq;
+  const size_t at = BY16 ? ((size_t)(n >> 4) * nq + gq) * 16 + (n & 15) : (size_t)wave;
+  const int64_t base = n * lda + (int64_t)gq * Geff;
+  if constexpr (IS_INT) {
+    const uint32_t* a = reinterpret_cast<const uint32_t*>(static_cast<const int8_t*>(A_) + base);
+    int s = 0;
+    for (int k4 = lane; 4 * k4 < Geff; k4 += 64) s = __builtin_amdgcn_sdot4((int)a[k4], 0x01010101, s, false);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    if (lane == 0) static_cast<int*>(S_)[at] = s;
+  } else {
+    const uint2* a = reinterpret_cast<const uint2*>(static_cast<const __half*>(A_) + base);
+    float s = 0.f;
+    for (int k4 = lane; 4 * k4 < Geff; k4 += 64) {
+      const uint2 v = a[k4];
+      const float a0 = __half2float(__ushort_as_half((uint16_t)(v.x & 0xffffu)));
+      const float a1 = __half2float(__ushort_as_half((uint16_t)(v.x >> 16)));
+      const float a2 = __half2float(__ushort_as_half((uint16_t)(v.y & 0xffffu)));
+      const float a3 = __half2float(__ushort_as_half((uint16_t)(v.y >> 16)));
+      s += (a0 + a1) + (a2 + a3);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    if (lane == 0) static_cast<float*>(S_)[at] = s;
+  }
+}
 #endif
 
 // Register-table decode kernel (layout 2); defined in tmac_perm.hip.  Arguments are those of
@@ -178,14 +218,23 @@ struct RowsPlan {
   bool eight;                 // slices of eight chunks: the kernel pair for few activation rows serves the call
   size_t part_bytes, ctr_bytes;  // workspace: partial sums (0 when slices == 1); ctr_bytes is always 0
   size_t srow_bytes;             // ... and the slices' sums of every activation row (eight-chunk plans)
+  // fp16 tables as fixed-point numbers (see rows_fix_kernel); fix == false: none of it
+  bool fix;
+  int fix_cps, fix_slices, fix_tiles;               // chunks per K slice, K slices, sets of 16 activation rows
+  // inside the same workspace: partial sums, tables, their units, the group sums
+  size_t fix_part_bytes, fix_tab_bytes, fix_scale_bytes;
+  size_t bytes() const { return part_bytes + ctr_bytes + srow_bytes; }
 };
 RowsPlan rows_plan(const tmac_wdesc* desc, int N);
 bool rows_builds_tables(const tmac_wdesc* desc, int N);
 // Returns a tmac_status value.  lut_dev NULL: tables built in the kernel from A_dev (where
-// rows_builds_tables(desc, N) holds).
+// rows_builds_tables(desc, N) holds, or, with fixed_from_act, rows_fixed_point(desc, N)).
 int launch_rows_gemm(const tmac_wdesc* desc, const void* packed_dev, const void* lut_dev, const void* A_dev,
                      int64_t lda, int lut_t, int N, const float* act_scale_dev, float weight_scale, void* out_dev,
-                     int out_t, int64_t ldo, void* workspace_dev, size_t workspace_bytes, void* stream);
+                     int out_t, int64_t ldo, void* workspace_dev, size_t workspace_bytes, void* stream,
+                     bool fixed_from_act = false);
+// Whether a call with fp16 tables turns them into fixed-point numbers.
+bool rows_fixed_point(const tmac_wdesc* desc, int N);
 
 // Records the last HIP error of this thread (diagnostics for TMAC_EHIP).
 void note_hip_error(int hip_error);

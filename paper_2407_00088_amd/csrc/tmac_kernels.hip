@@ -39,40 +39,6 @@ static void fill_ptrs(Tuple& t, void** ptrs, std::index_sequence<I...>) {
 // ------------------------------------------------------------------------------------------
 // Table precompute
 // ------------------------------------------------------------------------------------------
-// One wavefront per (n, quantisation group): the group sum S[n][gq] = sum of its activations,
-// four elements per lane and step (the row base, lda and the group size are multiples of 4),
-// then a butterfly.
-template <bool IS_INT>
-__device__ __forceinline__ void group_sums_wave(const void* __restrict__ A_, int N, int64_t lda,
-                                                void* __restrict__ S_, int Geff, int nq, int wave) {
-  const int lane = threadIdx.x & 63;
-  if (wave >= N * nq) return;
-  const int n = wave / nq, gq = wave % nq;
-  const int64_t base = n * lda + (int64_t)gq * Geff;
-  if constexpr (IS_INT) {
-    const uint32_t* a = reinterpret_cast<const uint32_t*>(static_cast<const int8_t*>(A_) + base);
-    int s = 0;
-    for (int k4 = lane; 4 * k4 < Geff; k4 += 64) s = __builtin_amdgcn_sdot4((int)a[k4], 0x01010101, s, false);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-    if (lane == 0) static_cast<int*>(S_)[wave] = s;
-  } else {
-    const uint2* a = reinterpret_cast<const uint2*>(static_cast<const __half*>(A_) + base);
-    float s = 0.f;
-    for (int k4 = lane; 4 * k4 < Geff; k4 += 64) {
-      const uint2 v = a[k4];
-      const float a0 = __half2float(__ushort_as_half((uint16_t)(v.x & 0xffffu)));
-      const float a1 = __half2float(__ushort_as_half((uint16_t)(v.x >> 16)));
-      const float a2 = __half2float(__ushort_as_half((uint16_t)(v.y & 0xffffu)));
-      const float a3 = __half2float(__ushort_as_half((uint16_t)(v.y >> 16)));
-      s += (a0 + a1) + (a2 + a3);
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-    if (lane == 0) static_cast<float*>(S_)[wave] = s;
-  }
-}
-
 // The tables as the batched kernels keep them in LDS: [n tile][KG][2^G][NT] 16-bit entries, NT
 // activation rows side by side per entry, so that staging a K slice is a plain copy.  Thread `id`
 // builds the two consecutive entries 2 id, 2 id + 1 (counted over [n tile][KG][2^G]) for the NT
@@ -485,7 +451,7 @@ extern "C" size_t tmac_workspace_bytes(const tmac_wdesc* desc, int32_t N) {
   if (!desc_valid(desc) || N <= 0) return 0;
   if (desc->layout == TMAC_LAYOUT_R8U16) return 256;  // the register-table kernel uses none
   const RowsPlan pl = rows_plan(desc, N);
-  return pl.part_bytes + pl.ctr_bytes + pl.srow_bytes + 256;
+  return pl.bytes() + 256;
 }
 
 extern "C" tmac_status tmac_mpgemm_ex(const tmac_wdesc* desc, const void* packed_dev, const void* lut_dev,
@@ -660,6 +626,12 @@ extern "C" tmac_status tmac_mpgemm_fused(const tmac_wdesc* desc, const void* pac
                                                       weight_scale, out_dev, (int)out, ldo, workspace_dev, ws, stream));
   }
   void* lut_dev = static_cast<char*>(workspace_dev) + ws;
+  if (act == TMAC_ACT_F16 && desc->layout == TMAC_LAYOUT_R64K32 && rows_fixed_point(desc, N)) {
+    // fixed-point tables and group sums straight from the activations (the LUT buffer stays unused)
+    if (lda % 4 != 0) return TMAC_EINVAL;
+    return static_cast<tmac_status>(launch_rows_gemm(desc, packed_dev, nullptr, A_dev, lda, (int)lt, N, act_scale_dev,
+                                                      weight_scale, out_dev, (int)out, ldo, workspace_dev, ws, stream, true));
+  }
   const tmac_status st = tmac_precompute_lut(A_dev, act, N, desc->K, lda, desc->g, desc->group, lt, lut_dev, lutb, stream);
   if (st != TMAC_OK) return st;
   return tmac_mpgemm(desc, packed_dev, lut_dev, lt, N, act_scale_dev, weight_scale, out_dev, out, ldo, workspace_dev,

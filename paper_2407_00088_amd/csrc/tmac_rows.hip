@@ -51,6 +51,9 @@ namespace tmac {
 typedef uint32_t ru32x4v __attribute__((ext_vector_type(4)));
 typedef uint32_t ru32x2v __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) char rows_lds_char;
+// wave-uniform data that no running kernel writes: read through scalar loads into scalar registers
+typedef __attribute__((address_space(4))) const float rows_const_float;
+__device__ __forceinline__ rows_const_float* rows_const(const void* p) { return (rows_const_float*)(uintptr_t)p; }
 typedef __attribute__((address_space(3))) const ru32x2v rows_lds_u32x2;
 typedef __attribute__((address_space(3))) const ru32x4v rows_lds_u32x4;
 
@@ -63,6 +66,9 @@ typedef __attribute__((address_space(3))) const ru32x4v rows_lds_u32x4;
 constexpr int ROWS_WAVES = TMAC_ROWS_WAVES;  // 64-row tiles per workgroup
 constexpr int ROWS_TARGET_WGS = TMAC_ROWS_TARGET_WGS;  // K is split until a call has about this many workgroups
 constexpr int ROWS_LDS = 32768;     // bytes of tables per LDS slice: 1024 k for 4 activation rows, 512 k for 8
+constexpr int ROWS_FIX_TARGET_WGS = 2048;  // eight workgroups per CU
+constexpr int ROWS_FIX_LEAST_WGS = 640;    // fewer leave the chip idle
+constexpr int ROWS_FIX_MIN_N = 64;  // activation rows from which tables are turned into fixed-point numbers (rows_plan)
 constexpr int ROWS_NT_WIDE = 8;     // activation rows per workgroup when there are enough of them
 constexpr int ROWS_NT_NARROW = 4;   // ... and otherwise
 constexpr int64_t ROWS_SUM_WIDE = 1 << 19;  // outputs from which the slice sums go four to a thread (two wavefronts per SIMD)
@@ -95,6 +101,8 @@ struct RowsParams {
   float pw[4];             // plane weights 1, 2, 4, 8: kernel arguments, so that plane 0 also takes the
                            // fused convert-multiply-add (a literal 1.0 would be folded into cvt + add)
   int out_t;
+  int bits;
+  const float* fix_scale;  // fixed-point tables, else null: [set of 16 rows][128-k block][16] value of one unit (negative: fp16 entries)
 };
 
 // 32-k chunks of tables one LDS slice holds, for LUT group size g and nt activation rows
@@ -839,6 +847,36 @@ __global__ __launch_bounds__(64 * ROWS_WAVES) void mpgemm_rows8_kernel(const Row
   }
 }
 
+// What the blocks that kept their fp16 entries (see rows_fix_kernel) contribute to output (n, m), looked
+// up from memory with the additions of the general kernel.
+__device__ __forceinline__ float rows_raw_blocks(const RowsParams& p, const float* unit, int n, int m) {
+  float sum = 0.f;
+  const int tile = m >> 6, r = m & 63;
+#pragma unroll 1
+  for (int c = 0; c < p.n_chunks; ++c) {
+    if (!(unit[(size_t)(c >> 2) * 16] < 0.f)) continue;
+    float hs = 1.f;
+    if (p.grouped) {
+      if (c / p.cpg >= p.nq) break;  // chunks in the K padding belong to no group
+      hs = 0.5f * __half2float(__ushort_as_half((uint16_t)(p.sz[((size_t)tile * p.nq + c / p.cpg) * 64 + r] & 0xffffu)));
+    }
+#pragma unroll 1
+    for (int b = 0; b < p.bits; ++b) {
+      const uint32_t x = p.idx[(((size_t)tile * p.n_chunks + c) * 64 + r) * p.bits + b];
+      rh2v q[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const size_t ent = ((size_t)(n >> 3) * p.KG + c * 8 + j) * 16 + ((x >> (4 * j)) & 15u);
+        q[j].x = __builtin_bit_cast(_Float16, p.tables[ent * 8 + (n & 7)]);
+        q[j].y = (_Float16)0.f;
+      }
+      tree_sum(q);
+      sum = fmaf((float)q[0].x, hs * p.pw[b], sum);
+    }
+  }
+  return sum;
+}
+
 // Adds the partial sums [nz][N][Mp] of the K slices in slice order and finishes: VEC outputs per
 // thread.  Bound by memory traffic.  Everything the thread needs is requested before the first wait
 // (scales and zeros, the activation scale, the row sum or its per-slice parts, the partial sums of a
@@ -852,6 +890,19 @@ __global__ __launch_bounds__(256) void rows_sum_kernel(const RowsParams p, int n
   const uint32_t id = blockIdx.x * 256u + threadIdx.x;   // (launch_rows_sum checks that the ids fit)
   const uint32_t per_row = (uint32_t)p.Mp / VEC;
   const int n = (int)(id / per_row), m0 = (int)(id % per_row) * VEC;
+  // fixed-point tables: does any block of the sets of rows this wavefront works for keep its fp16 entries?
+  // Usually none does, which takes one load per lane (all lanes take part: before any of them returns)
+  bool raw = false;
+  if constexpr (!IS_INT) {
+    if (p.fix_scale) {
+      const int nblk = p.KG / 32;
+      const int first = __builtin_amdgcn_readfirstlane(min(n, p.N - 1)) >> 4;
+      const int last = __builtin_amdgcn_readlane(min(n, p.N - 1), 63) >> 4;
+      bool some = false;
+      for (int b = first * nblk + (int)(threadIdx.x & 63); b < (last + 1) * nblk; b += 64) some |= p.fix_scale[(size_t)b * 16] < 0.f;
+      raw = __any(some);
+    }
+  }
   if (n >= p.N || m0 >= p.M) return;
   const bool raw_int = IS_INT && !p.grouped;
   const float* src = p.ws_part + (size_t)n * p.Mp + m0;
@@ -906,6 +957,13 @@ __global__ __launch_bounds__(256) void rows_sum_kernel(const RowsParams p, int n
     else if (left > 4) { round(sl0, std::integral_constant<int, 8>()); sl0 += 8; }
     else { round(sl0, std::integral_constant<int, 4>()); sl0 += 4; }
   }
+  if constexpr (!IS_INT) {
+    if (raw) {
+      const float* const unit = p.fix_scale + (size_t)(n >> 4) * (p.KG / 32) * 16;
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) sf[i] += rows_raw_blocks(p, unit, n, m0 + i);
+    }
+  }
   uint32_t res[VEC];
 #pragma unroll
   for (int i = 0; i < VEC; ++i) {
@@ -953,6 +1011,312 @@ static hipError_t launch_rows_sum(const RowsParams& p, int nz, hipStream_t st) {
   const void* fn = wide ? reinterpret_cast<const void*>(rows_sum_kernel<IS_INT, 4>)
                         : reinterpret_cast<const void*>(rows_sum_kernel<IS_INT, 1>);
   return hipLaunchKernel(fn, dim3((unsigned)blocks), dim3(256), args, 0, st);
+}
+
+// ------------------------------------------------------------------------------------------
+// fp16 tables as fixed-point numbers
+// ------------------------------------------------------------------------------------------
+// With fp16 tables and many look-ups the vector ALUs bind: v_pk_add_f16 takes 1.8 ns per wavefront and
+// SIMD for one entry of two activation rows, and a plane's sum takes three fp16 roundings.  Large calls
+// therefore turn the tables into 16-bit integers first, one power of precision for each (activation row,
+// 128 k): the unit is the largest sum that one chunk's eight entries can reach, divided by
+// ROWS_FIX_MAX, so that the eight entries of any chunk and plane add up within 16 bits, exactly, with
+// two entries per v_add3_u32.  What is rounded is each entry, once, to 2^-15 of the largest sum of a
+// chunk, where fp16 sums round to 2^-11 of every partial sum: 256 rows x 5120 x 5120 at 4 bit is off
+// by 2.3e-4 instead of 3.5e-4.
+// In memory and LDS an entry pair is the number (hi + B) * 65536 + lo + B modulo 2^32 (B =
+// ROWS_FIX_BIAS): additions of whole dwords are exact, and the sum of a chunk's eight pairs has two
+// clean halves, sum + 32768.
+// A 128-k block in which some row's entries are not finite keeps its fp16 entries (fix_scale negative
+// for the set's 16 rows); the look-up kernel takes nothing from it, and rows_sum_kernel looks it up from
+// memory with fp16 additions, so that infinities and NaNs come out as they do in the general kernel.
+constexpr int ROWS_FIX_BIAS = 4096;
+constexpr float ROWS_FIX_MAX = 32700.f;  // + 8 roundings of half a unit stays below 32767
+
+// One workgroup: the 32 tables of a 128-k block for 16 activation rows; thread = the table of a pair of
+// rows, wavefront = the eight tables of a chunk, so that a chunk's largest sum is three exchanges away.
+// Entries 0..7 are looked at, the others are their negatives (Section 3.3).  FROM_ACT: entries from the
+// activations (with the fp16 additions of the precompute kernel: both routes hold the same numbers), and
+// further workgroups for the group sums; else from the LUT buffer, whose group sums are copied into the
+// order the look-up kernel reads, [set of 16 rows][group][16].  Bound by launch and memory: 21 MB of
+// tables written at 511 rows of K = 5120, 9.5 us (one thread per entry of a table: 21).
+template <bool FROM_ACT>
+__global__ __launch_bounds__(256) void rows_fix_kernel(const RowsParams p, uint32_t* __restrict__ fix, float* __restrict__ scale,
+                                                       float* __restrict__ sums, int Geff, int lut_nt, int n_fix) {
+  if constexpr (FROM_ACT) {
+    if ((int)blockIdx.x >= n_fix) {
+      group_sums_wave<false, true>(p.A, p.N, p.lda, sums, Geff, p.nq, ((int)blockIdx.x - n_fix) * 4 + (threadIdx.x >> 6));
+      return;
+    }
+  }
+  typedef unsigned short us2v __attribute__((ext_vector_type(2)));
+  constexpr int TD = 64 + 4, OD = 32 * TD + 32;    // dwords from table to table and set half to set half: conflict-free writes
+  __shared__ __attribute__((aligned(16))) uint32_t stage[2 * OD];
+  __shared__ float smax[4][16];                    // [chunk][row]: largest sum of the chunk's eight entries
+  const int nblk = p.KG / 32;
+  const int set = blockIdx.x / nblk, blk = blockIdx.x % nblk;
+  const int u = threadIdx.x & 7, tb = threadIdx.x >> 3, wave = threadIdx.x >> 6;
+  const int kg = blk * 32 + tb, n = set * 16 + 2 * u;
+  uint32_t v[8];                                   // entries 0..7 of rows n (low half) and n + 1
+  if constexpr (FROM_ACT) {
+    uint32_t t0[4], t1[4];
+    ru32x2v a0 = {0u, 0u}, a1 = {0u, 0u};
+    if (4 * kg < p.K) {
+      const __half* const at = static_cast<const __half*>(p.A) + 4 * kg;
+      if (n < p.N) a0 = *reinterpret_cast<const ru32x2v*>(at + n * p.lda);
+      if (n + 1 < p.N) a1 = *reinterpret_cast<const ru32x2v*>(at + (n + 1) * p.lda);
+    }
+    half_table_f16(a0.x, a0.y, t0);
+    half_table_f16(a1.x, a1.y, t1);
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      v[2 * d] = __builtin_amdgcn_perm(t1[d], t0[d], 0x05040100u);
+      v[2 * d + 1] = __builtin_amdgcn_perm(t1[d], t0[d], 0x07060302u);
+    }
+  } else {
+    const int tile = n / lut_nt;                   // the buffer's n tiles are eight or four rows wide
+    const uint16_t* const at = p.tables + ((size_t)tile * p.KG + kg) * 16 * lut_nt + n % lut_nt;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = tile * lut_nt < p.N ? *reinterpret_cast<const uint32_t*>(at + e * lut_nt) : 0u;
+    const int r = set * 16 + (int)threadIdx.x;
+    if (threadIdx.x < 16 && r < p.N)
+      for (int gq = blk; gq < p.nq; gq += nblk) sums[((size_t)set * p.nq + gq) * 16 + threadIdx.x] = static_cast<const float*>(p.S)[(size_t)r * p.nq + gq];
+  }
+  // fp16 magnitudes compare as integers, infinities and NaNs on top
+  us2v m = __builtin_bit_cast(us2v, v[0] & 0x7fff7fffu);
+#pragma unroll
+  for (int e = 1; e < 8; ++e) m = __builtin_elementwise_max(m, __builtin_bit_cast(us2v, v[e] & 0x7fff7fffu));
+  float b0 = __half2float(__ushort_as_half(m.x)), b1 = __half2float(__ushort_as_half(m.y));
+#pragma unroll
+  for (int o = 8; o < 64; o <<= 1) {
+    b0 += __shfl_xor(b0, o);
+    b1 += __shfl_xor(b1, o);
+  }
+  if ((threadIdx.x & 63) < 8) {
+    smax[wave][2 * u] = b0;
+    smax[wave][2 * u + 1] = b1;
+  }
+  __syncthreads();
+  float f[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    float b = smax[0][2 * u + h];
+    bool bad = !(b <= 1e30f);
+#pragma unroll
+    for (int c = 1; c < 4; ++c) {
+      bad |= !(smax[c][2 * u + h] <= 1e30f);
+      b = fmaxf(b, smax[c][2 * u + h]);
+    }
+    f[h] = bad ? -1.f : b;
+  }
+  const bool raw = __any(f[0] < 0.f || f[1] < 0.f);  // (every wavefront sees all 16 rows)
+  if (threadIdx.x < 8) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) scale[((size_t)set * nblk + blk) * 16 + 2 * u + h] = raw ? -1.f : f[h] / ROWS_FIX_MAX;
+  }
+  const float f0 = f[0] > 0.f ? ROWS_FIX_MAX / f[0] : 0.f, f1 = f[1] > 0.f ? ROWS_FIX_MAX / f[1] : 0.f;
+  uint32_t* const dst = stage + (u >> 2) * OD + tb * TD + (u & 3);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    // nearest integer, ties to even: the low bits of x f + 1.5 * 2^23
+    const rh2v x = __builtin_bit_cast(rh2v, v[e]);
+    const uint32_t i0 = __float_as_uint(fmaf((float)x.x, f0, 12582912.f)), i1 = __float_as_uint(fmaf((float)x.y, f1, 12582912.f));
+    // two signed halves side by side -> hi * 65536 + lo, then the bias of both
+    uint32_t d = (__builtin_amdgcn_perm(i1, i0, 0x05040100u) ^ 0x8000u) + ((uint32_t)ROWS_FIX_BIAS * 0x10001u - 0x8000u);
+    uint32_t neg = 2u * ROWS_FIX_BIAS * 0x10001u - d;
+    if (raw) {
+      d = v[e];
+      neg = v[e] ^ 0x80008000u;
+    }
+    dst[e * 4] = d;
+    dst[(15 - e) * 4] = neg;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int o = i >> 1, q = (i & 1) * 256 + (int)threadIdx.x;  // 16-byte piece of the half's 32 tables
+    const int t8 = set * 2 + o;
+    if (t8 * 8 < p.N)
+      *reinterpret_cast<ru32x4v*>(fix + ((size_t)t8 * p.KG + blk * 32) * 64 + q * 4) =
+          *reinterpret_cast<const ru32x4v*>(stage + o * OD + (q >> 4) * TD + (q & 15) * 4);
+  }
+}
+
+// The look-ups of one 32-k chunk for two sets of eight activation rows, in rounds of the eight reads of
+// one plane and row set (see rows_chunk_int): L += the planes' sums, and their biases, times the planes'
+// weights.
+template <int BITS, int OSTRIDE>
+__device__ __forceinline__ void rows_chunk_fix(const uint32_t (&x)[BITS], uint32_t cbase, int (&L)[16]) {
+  using Sh = RowsShape<8, 4>;
+  constexpr int TPC = Sh::TPC, HD = Sh::HD, TB = Sh::TB;
+  auto plane = [&](auto bc) {
+    constexpr int b = decltype(bc)::value;
+    const uint32_t even = (x[b] << 4) & 0xF0F0F0F0u, odd = x[b] & 0xF0F0F0F0u;
+    uint32_t a[TPC];
+#pragma unroll
+    for (int j = 0; j < TPC; ++j) a[j] = __builtin_amdgcn_perm(j & 1 ? odd : even, cbase, 0x0C020100u + 4u + (uint32_t)(j / 2));
+#pragma unroll
+    for (int o = 0; o < 2; ++o) {
+      ru32x4v e[TPC];
+#pragma unroll
+      for (int j = 0; j < TPC; ++j) e[j] = *reinterpret_cast<rows_lds_u32x4*>(a[j] + j * TB + o * OSTRIDE);
+      __builtin_amdgcn_sched_barrier(0);  // keep the reads above the accumulation
+#pragma unroll
+      for (int u = 0; u < HD; ++u) {
+        uint32_t q = e[0][u];
+#pragma unroll
+        for (int j = 1; j < TPC; ++j) q += e[j][u];
+        rows_widen<1 << b>(L[8 * o + 2 * u], L[8 * o + 2 * u + 1], q);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  plane(std::integral_constant<int, 0>());
+  if constexpr (BITS > 1) plane(std::integral_constant<int, 1>());
+  if constexpr (BITS > 2) plane(std::integral_constant<int, 2>());
+  if constexpr (BITS > 3) plane(std::integral_constant<int, 3>());
+}
+
+// mpgemm_rows_kernel for fixed-point tables: two sets of eight activation rows per workgroup, tables
+// from the workspace (written by rows_fix_kernel), results through the workspace to rows_sum_kernel even
+// where there is one K slice only (finishing here as well costs 40 registers).  The integer sums of a quantisation group and 128-k
+// block are converted once and multiplied by the block's unit and half the group's scale.  Bound by the
+// look-up rate of LDS and the vector ALUs about equally, each about 70 % busy (see rows_chunk_int).  The
+// whole call at 256 rows x 5120 x 5120, 4 bit: 139 us against 163 with fp16 tables; 511 rows x 13824 x
+// 5120, 2 bit: 378 against 426.  (Tables of eight chunks staged with a wait: 143, 401; five wavefronts
+// per SIMD: 141, 391 -> 157, 440; next round's reads ahead: 160, 455.)
+template <int BITS>
+__global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_fix_kernel(const RowsParams p) {
+  using Sh = RowsShape<8, 4>;
+  constexpr int CB = Sh::CB, OSTRIDE = 4 * CB;
+  __shared__ __attribute__((aligned(2048))) char tab[2 * OSTRIDE];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n0 = blockIdx.x * 16;
+  const int tile_raw = blockIdx.y * ROWS_WAVES + wave;
+  const bool tile_ok = tile_raw < p.n_tiles;
+  const int tile = tile_ok ? tile_raw : p.n_tiles - 1;  // clamped: loads stay in range, stores are masked
+  const uint32_t* my_idx = p.idx + ((size_t)tile * p.n_chunks * 64 + lane) * BITS;
+  const uint32_t* my_sz = p.sz + (size_t)tile * p.nq * 64 + lane;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)((rows_lds_char*)tab);
+  rows_const_float* const fix_scale = rows_const(p.fix_scale) + (size_t)blockIdx.x * (p.KG / 32) * 16;
+  rows_const_float* const sums = rows_const(p.S) + (size_t)blockIdx.x * p.nq * 16;
+  const int cz0 = blockIdx.z * p.cps, cz1 = min(cz0 + p.cps, p.n_chunks);
+
+  float acc[16];
+#pragma unroll
+  for (int t = 0; t < 16; ++t) acc[t] = 0.f;
+  auto load_idx = [&](int c, uint32_t (&x)[BITS]) {
+    const uint32_t* src = my_idx + (size_t)c * 64 * BITS;
+    if constexpr (BITS == 4) {
+      const ru32x4v v = *reinterpret_cast<const ru32x4v*>(src);
+      x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
+    } else if constexpr (BITS == 2) {
+      const ru32x2v v = *reinterpret_cast<const ru32x2v*>(src);
+      x[0] = v.x; x[1] = v.y;
+    } else {
+#pragma unroll
+      for (int b = 0; b < BITS; ++b) x[b] = src[b];
+    }
+  };
+  int gq = p.grouped ? cz0 / p.cpg : 0, cg = 0;  // current quantisation group, chunks done in it (wave-uniform)
+  float hs = 1.f;                                // half the group's scale (1: one scale per row or tensor, applied at the end)
+  uint32_t szv_next = p.grouped ? my_sz[(size_t)min(gq, p.nq - 1) * 64] : 0u;
+  float unit[16];  // the block's units (wave-uniform); 0 where it kept its fp16 entries
+  uint32_t xn[BITS];
+  load_idx(cz0, xn);
+
+  // the tables of a 128-k block, 8 KB for each set of eight rows, are requested while the block before it
+  // is looked up
+  const int last8 = (p.N + 7) / 8 - 1;  // (a second row set past it repeats it)
+  const char* const src0 = reinterpret_cast<const char*>(p.tables) + (size_t)(blockIdx.x * 2) * p.KG * Sh::TB + threadIdx.x * 16;
+  const char* const src1 = reinterpret_cast<const char*>(p.tables) + (size_t)min((int)blockIdx.x * 2 + 1, last8) * p.KG * Sh::TB + threadIdx.x * 16;
+  ru32x4v next[4];
+  auto request = [&](int c) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      next[i] = *reinterpret_cast<const ru32x4v*>(src0 + (size_t)c * CB + i * 4096);
+      next[2 + i] = *reinterpret_cast<const ru32x4v*>(src1 + (size_t)c * CB + i * 4096);
+    }
+  };
+  request(cz0);
+  for (int c0 = cz0; c0 < cz1; c0 += 4) {
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) *reinterpret_cast<ru32x4v*>(tab + (i >> 1) * OSTRIDE + (i & 1) * 4096 + threadIdx.x * 16) = next[i];
+    __syncthreads();
+    if (c0 + 4 < cz1) request(c0 + 4);
+#pragma unroll
+    for (int t = 0; t < 16; ++t) unit[t] = __int_as_float(max(__float_as_int(fix_scale[(c0 >> 2) * 16 + t]), 0));
+    int L[16];
+    bool first = true;
+    for (int c = c0; c < c0 + 4; ++c) {
+      uint32_t x[BITS];
+#pragma unroll
+      for (int b = 0; b < BITS; ++b) x[b] = xn[b];
+      load_idx(min(c + 1, cz1 - 1), xn);  // next chunk's indices, one chunk ahead
+      if (p.grouped && cg == 0 && gq < p.nq) {  // a group starts (chunks in the K padding belong to none)
+        const float s = __half2float(__ushort_as_half((uint16_t)(szv_next & 0xffffu)));
+        const float z = __half2float(__ushort_as_half((uint16_t)(szv_next >> 16)));
+        hs = 0.5f * s;
+        const float bz = s * (p.mid - z);
+#pragma unroll
+        for (int t = 0; t < 16; ++t)  // bias term of Section 4's linear transform
+          acc[t] = fmaf(bz, sums[(size_t)gq * 16 + t], acc[t]);
+        szv_next = my_sz[(size_t)min(gq + 1, p.nq - 1) * 64];
+      }
+      if (first) {  // sums start at minus the biases of the chunks they will hold
+        int chunks = 4 - (c & 3);
+        if (p.grouped && gq < p.nq) chunks = min(chunks, p.cpg - cg);
+        const int L0 = -chunks * (32768 * ((1 << BITS) - 1));
+#pragma unroll
+        for (int t = 0; t < 16; ++t) L[t] = L0;
+      }
+      rows_chunk_fix<BITS, OSTRIDE>(x, lds0 + (uint32_t)(c - c0) * (uint32_t)CB, L);
+      const bool group_ends = p.grouped && gq < p.nq && ++cg == p.cpg;
+      first = group_ends || (c & 3) == 3;
+      if (first) {
+#pragma unroll
+        for (int t = 0; t < 16; ++t) acc[t] = fmaf((float)L[t], unit[t] * hs, acc[t]);
+      }
+      if (group_ends) {
+        cg = 0;
+        ++gq;
+      }
+    }
+  }
+
+  const int m = tile_raw * 64 + lane;
+  if (!tile_ok) return;
+#pragma unroll
+  for (int t = 0; t < 16; ++t)
+    if (n0 + t < p.N) p.ws_part[((size_t)blockIdx.z * p.N + n0 + t) * p.Mp + (size_t)m] = acc[t];
+}
+
+// Tables to fixed point, look-ups, slice sums.
+static hipError_t launch_rows_fix(const RowsParams& p, const RowsPlan& pl, int bits, bool from_act, int Geff, int lut_nt,
+                                  uint32_t* fix, float* scale, float* sums, hipStream_t st) {
+  RowsParams local = p;
+  int n_fix = pl.fix_tiles * (p.KG / 32);
+  const int64_t blocks = n_fix + (from_act ? ((int64_t)p.N * p.nq + 3) / 4 : 0);
+  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+  void* args[] = {&local, &fix, &scale, &sums, &Geff, &lut_nt, &n_fix};
+  hipError_t e = hipLaunchKernel(from_act ? reinterpret_cast<const void*>(rows_fix_kernel<true>)
+                                          : reinterpret_cast<const void*>(rows_fix_kernel<false>),
+                                 dim3((unsigned)blocks), dim3(256), args, 0, st);
+  if (e != hipSuccess) return e;
+  local.tables = reinterpret_cast<const uint16_t*>(fix);
+  local.fix_scale = scale;
+  local.S = sums;
+  local.cps = pl.fix_cps;
+  const void* fn = bits == 2   ? reinterpret_cast<const void*>(mpgemm_fix_kernel<2>)
+                   : bits == 3 ? reinterpret_cast<const void*>(mpgemm_fix_kernel<3>)
+                               : reinterpret_cast<const void*>(mpgemm_fix_kernel<4>);
+  void* args2[] = {&local};
+  e = hipLaunchKernel(fn, dim3(pl.fix_tiles, (p.n_tiles + ROWS_WAVES - 1) / ROWS_WAVES, pl.fix_slices), dim3(64 * ROWS_WAVES),
+                      args2, 0, st);
+  if (e != hipSuccess) return e;
+  return launch_rows_sum<false>(local, pl.fix_slices, st);
 }
 
 template <bool IS_INT, int BITS, int NT, bool FUSED>
@@ -1019,6 +1383,9 @@ static RowsPlan rows_plan_oct(const tmac_wdesc* desc, int N, int oct) {
   pl.slices = (ge.n_chunks + cps - 1) / cps;
   pl.part_bytes = pl.slices > 1 ? ((size_t)pl.slices * N * ge.Mp * 4 + 255) / 256 * 256 : 0;
   pl.ctr_bytes = 0;  // (no arrival counters: the slices meet in rows_sum_kernel)
+  pl.fix = false;
+  pl.fix_cps = pl.fix_slices = pl.fix_tiles = 0;
+  pl.fix_part_bytes = pl.fix_tab_bytes = pl.fix_scale_bytes = 0;
   pl.srow_bytes = pl.eight ? ((size_t)pl.slices * N * 4 + 255) / 256 * 256 : 0;
   return pl;
 }
@@ -1027,12 +1394,59 @@ static RowsPlan rows_plan_oct(const tmac_wdesc* desc, int N, int oct) {
 // reads.  Measured against one n tile per workgroup (precompute + lookup, 4 bit): 13824 x 5120 even
 // at 48 rows, 7 % ahead at 64, 9 % at 96, 6 % at 128 and beyond; 4096 x 4096, where the eight-chunk
 // kernel pair serves up to 192 rows, behind below 96 rows, even at 96, 4 % ahead at 128.
-RowsPlan rows_plan(const tmac_wdesc* desc, int N) {
+static RowsPlan rows_plan_plain(const tmac_wdesc* desc, int N) {
   const RowsPlan one = rows_plan_oct(desc, N, 1);
   const bool can = desc->g == 4 && one.nt == ROWS_NT_WIDE;
   if (can && (N >= 128 || (N >= 64 && !one.eight))) return rows_plan_oct(desc, N, 2);
   return one;
 }
+
+// Fixed-point tables (fp16 tables only) serve the calls whose partial sums would not fit the library's
+// own array: those are the large ones, and tmac_mpgemm_noalloc, whose results are tmac_mpgemm's bit for
+// bit, refuses exactly these.  The workspace keeps its size: K is split into fewer slices, and the
+// tables take the room of the others' partial sums (a call where that leaves no slice keeps fp16 tables).
+//
+// The extra launch that converts the tables wants look-ups to pay for it.  Measured against the general
+// kernels: 64 rows x 11008 x 4096 at 4 bit 70.0 us against 79.0, 80 rows 84.0 against 96.3; at 4096 x
+// 4096, where the eight-chunk kernel pair is the other side, 1.00 / 0.98 / 1.09 times as fast at 64 / 80 /
+// 96 rows (1.1e9, 1.3e9, 1.6e9 look-ups), 0.985 at 130 rows and 2 bit against the general kernel (1.1e9); with 40 rows there are too few workgroups (0.77 to 1.02), and
+// at 1 bit it is 0.93 to 1.05 times as fast: tables and launches weigh four times as much there.
+// K is split until a call has about eight workgroups per CU.
+RowsPlan rows_plan(const tmac_wdesc* desc, int N) {
+  RowsPlan pl = rows_plan_plain(desc, N);
+  const size_t room = pl.part_bytes + pl.ctr_bytes + pl.srow_bytes;
+  if (desc->g != 4 || desc->bits < 2 || N < ROWS_FIX_MIN_N || room <= (size_t)TMAC_NOALLOC_MAX_WORKSPACE) return pl;
+  const Geometry ge = geometry(desc);
+  if ((double)N * ge.Mp * (ge.Kp / 4) * desc->bits < (pl.eight ? 1.5e9 : 1.1e9)) return pl;
+  const bool one_group = (desc->group == 0 || desc->group == desc->K);
+  const int cpg = (one_group || desc->group < 32) ? 1 : desc->group / 32;
+  int unit = 4;  // whole 128-k blocks, whole groups
+  while (unit % cpg) unit += 4;
+  const int tiles = (N + 15) / 16;
+  const int64_t pairs = (int64_t)tiles * pl.row_blocks;
+  const size_t slice = (size_t)N * ge.Mp * 4;
+  const size_t tab = (size_t)((N + 7) / 8) * (ge.Kp / 4) * 256, scale = (size_t)tiles * (ge.Kp / 128) * 64;
+  const size_t sums = (size_t)tiles * (one_group ? 1 : desc->K / desc->group) * 64;
+  const int want = (int)((ROWS_FIX_TARGET_WGS + pairs - 1) / pairs);
+  for (int cps = ((ge.n_chunks + want - 1) / want + unit - 1) / unit * unit;; cps += unit) {
+    const int slices = (ge.n_chunks + cps - 1) / cps;
+    const size_t part = ((size_t)slices * slice + 255) / 256 * 256;
+    if (part + tab + scale + sums <= room) {
+      if (pairs * slices < ROWS_FIX_LEAST_WGS) return pl;
+      pl.fix = true;
+      pl.fix_cps = cps;
+      pl.fix_slices = slices;
+      pl.fix_tiles = tiles;
+      pl.fix_part_bytes = part;
+      pl.fix_tab_bytes = tab;
+      pl.fix_scale_bytes = scale;
+      return pl;
+    }
+    if (slices == 1) return pl;
+  }
+}
+
+bool rows_fixed_point(const tmac_wdesc* desc, int N) { return desc->g == 4 && rows_plan(desc, N).fix; }
 
 // Whether a call builds its tables inside the lookup kernel when it is given activations instead
 // of a LUT buffer: the eight-chunk kernel, up to 32 activation rows (every
@@ -1046,10 +1460,12 @@ bool rows_builds_tables(const tmac_wdesc* desc, int N) {
 // rows_builds_tables says so).
 int launch_rows_gemm(const tmac_wdesc* desc, const void* packed_dev, const void* lut_dev, const void* A_dev,
                      int64_t lda, int lut_t, int N, const float* act_scale_dev, float weight_scale, void* out_dev,
-                     int out_t, int64_t ldo, void* workspace_dev, size_t workspace_bytes, void* stream) {
+                     int out_t, int64_t ldo, void* workspace_dev, size_t workspace_bytes, void* stream, bool fixed_from_act) {
   if (lut_t != TMAC_LUT_F16 && lut_t != TMAC_LUT_I16) return TMAC_EUNSUPPORTED;
-  const bool fused = (lut_dev == nullptr);
+  const bool from_act = (lut_dev == nullptr && fixed_from_act);  // fixed-point tables from the activations
+  const bool fused = (lut_dev == nullptr && !from_act);
   if (fused && (!A_dev || !rows_builds_tables(desc, N))) return TMAC_EUNSUPPORTED;
+  if (from_act && (!A_dev || lut_t != TMAC_LUT_F16 || !rows_fixed_point(desc, N))) return TMAC_EUNSUPPORTED;
   const Geometry ge = geometry(desc);
   LutGeom lg;
   if (!lut_geom(N, desc->K, desc->g, desc->group, lut_t, &lg)) return TMAC_EINVAL;
@@ -1057,9 +1473,9 @@ int launch_rows_gemm(const tmac_wdesc* desc, const void* packed_dev, const void*
   const bool one_group = (desc->group == 0 || desc->group == desc->K);
   const RowsPlan pl = rows_plan(desc, N);
   if (pl.n_tiles_n > 0x7fffffff || pl.row_blocks > 65535 || pl.slices > 65535) return TMAC_EUNSUPPORTED;
-  if (pl.slices > 1) {
+  if (pl.bytes() > 0) {
     if (!workspace_dev) return TMAC_EINVAL;
-    if (workspace_bytes < pl.part_bytes + pl.ctr_bytes + pl.srow_bytes) return TMAC_ESIZE;
+    if (workspace_bytes < pl.bytes()) return TMAC_ESIZE;
   }
   // int32 accumulators: |L| <= 128 * (2^b - 1) * K must stay below 2^31
   if (is_int && (double)128.0 * ((1 << desc->bits) - 1) * desc->K >= 2147483647.0) return TMAC_EUNSUPPORTED;
@@ -1069,7 +1485,7 @@ int launch_rows_gemm(const tmac_wdesc* desc, const void* packed_dev, const void*
   p.idx = reinterpret_cast<const uint32_t*>(blob + ge.idx_off);
   p.sz = reinterpret_cast<const uint32_t*>(blob + ge.sz_off);
   p.tables = static_cast<const uint16_t*>(lut_dev);
-  p.S = fused ? nullptr : static_cast<const char*>(lut_dev) + lg.s_off;
+  p.S = lut_dev == nullptr ? nullptr : static_cast<const char*>(lut_dev) + lg.s_off;
   p.A = A_dev;
   p.lda = lda;
   p.K = desc->K;
@@ -1104,7 +1520,14 @@ int launch_rows_gemm(const tmac_wdesc* desc, const void* packed_dev, const void*
   if (out_t == TMAC_OUT_I32 && !p.int_exact) return TMAC_EINVAL;
   hipStream_t st = static_cast<hipStream_t>(stream);
   hipError_t e;
-  if (fused) e = is_int ? launch_rows8_nt<true, true>(p, pl.nt, desc->bits, st) : launch_rows8_nt<false, true>(p, pl.nt, desc->bits, st);
+  p.fix_scale = nullptr;
+  p.bits = desc->bits;
+  if (pl.fix && !is_int && !fused) {
+    char* const tab = static_cast<char*>(workspace_dev) + pl.fix_part_bytes;
+    e = launch_rows_fix(p, pl, desc->bits, from_act, lg.Geff, lg.NT, reinterpret_cast<uint32_t*>(tab),
+                        reinterpret_cast<float*>(tab + pl.fix_tab_bytes),
+                        reinterpret_cast<float*>(tab + pl.fix_tab_bytes + pl.fix_scale_bytes), st);
+  } else if (fused) e = is_int ? launch_rows8_nt<true, true>(p, pl.nt, desc->bits, st) : launch_rows8_nt<false, true>(p, pl.nt, desc->bits, st);
   else if (pl.eight) e = is_int ? launch_rows8_nt<true>(p, pl.nt, desc->bits, st) : launch_rows8_nt<false>(p, pl.nt, desc->bits, st);
   else e = is_int ? launch_rows_nt<true>(p, desc->g, pl.nt, pl.oct, desc->bits, st) : launch_rows_nt<false>(p, desc->g, pl.nt, pl.oct, desc->bits, st);
   if (e != hipSuccess) {

@@ -1155,6 +1155,69 @@ def test_slice_sums_four_outputs_per_thread(T, torch, off, ldo_extra):
         assert bool((flat[off + N * (M + ldo_extra):] == 77).all())
 
 
+FIXED_POINT_SHAPES = [  # N, M, K, bits, group (-1: per row, 0: per tensor): large calls (rows_plan's rule)
+    (72, 5200, 4096, 4, 128), (65, 5900, 8192, 2, 32), (79, 6001, 7488, 3, 96), (130, 2700, 8224, 2, 32),
+    (64, 3000, 8200, 4, -1), (80, 3100, 8192, 3, 0), (71, 5000, 8192, 2, 512)]
+
+
+@pytest.mark.parametrize("N,M,K,bits,group", FIXED_POINT_SHAPES)
+def test_large_calls_with_fixed_point_tables(T, torch, N, M, K, bits, group):
+    """Large calls turn their fp16 tables into 16-bit integers with one unit per activation row and 128 k:
+    against the oracle, closer than the fp16 sums they replace (3.5e-4 to 4.1e-4 from 4 bit to 2 bit; the
+    table entries' own roundings, which stay, give 2.1e-4 to 2.5e-4, and half a unit of 2^-15 of a chunk's
+    largest sum per entry adds about 1e-4 in quadrature), with sizes that end inside a set of 16 rows, a tile of 64
+    weight rows, a chunk, a 128-k block and a K slice, groups of 1, 3, 4 and 16 chunks and none; both
+    entry points hold the same tables and give the same bits."""
+    from paper_2407_00088_amd.runner import from_problem
+    rng = np.random.default_rng(1500 + N)
+    if group == 0:
+        p = wl.Problem("fix", 0, N, M, K, bits, 0, wl.uniform_codes(rng, M, K, bits), None, None, weight_scale=0.05,
+                       zero_point=3.0, act=wl.gaussian_act(rng, N, K))
+    else:
+        p = wl.make_grouped(0, 1500 + N, N, M, K, bits, K if group < 0 else group, name="fix")
+    act = p.act.astype(np.float32)
+    act[:, rng.random(K) < 0.002] *= 30                      # a few large channels
+    act[1] = 0                                                # a row of zeros, one of subnormals, one with gaps
+    act[2] *= 2.0 ** -22
+    act[3, : K // 2] = 0
+    p.act = act.astype(np.float16)
+    lin = from_problem(p, layout=L3)
+    assert T.tmac_workspace_bytes(lin.desc, N) > 8 * 2 ** 20 + 256
+    A = torch.from_numpy(p.act).cuda()
+    two, one = lin.forward(A), lin.forward_one_call(A)
+    assert torch.equal(two, one)
+    got, ref = two.cpu().numpy(), oracle_fp(p)
+    # (over many rows; a single row with half its activations zero and a few large ones has a norm of its own,
+    # and is held to the bound of every output below)
+    err = orc.rel_frobenius(got[4:], ref[4:])
+    print(f"fixed point {N}x{M}x{K} w{bits}: {err:.2e}", flush=True)
+    assert err <= 3.4e-4
+    assert not got[1].any()
+    assert_elementwise(got, ref, p)
+
+
+def test_fixed_point_tables_leave_infinities_and_nans_alone(T, torch):
+    """A 128-k block in which some table entry is not finite keeps its fp16 entries: rows with an infinity, a
+    NaN, or activations whose sums overflow fp16 come out as in a small call of the same rows (which goes
+    through the general kernels), and their neighbours stay finite and correct."""
+    from paper_2407_00088_amd.runner import from_problem
+    N, M, K, bits, group = 130, 2700, 8192, 2, 128
+    p = wl.make_grouped(0, 1590, N, M, K, bits, group, name="nonfinite")
+    p.act[3, 100], p.act[5, 8191], p.act[20, 4000] = np.inf, -np.inf, np.nan
+    p.act[40, 512:516] = 30000.0
+    lin = from_problem(p, layout=L3)
+    A = torch.from_numpy(p.act).cuda()
+    odd = [3, 5, 20, 40]
+    small = lin.forward(A[odd].contiguous()).cpu().numpy()
+    for got in (lin.forward(A).cpu().numpy(), lin.forward_one_call(A).cpu().numpy()):
+        assert np.array_equal(np.isnan(got[odd]), np.isnan(small)) and np.isnan(small).any()
+        assert np.array_equal(np.isposinf(got[odd]), np.isposinf(small)) and np.isposinf(small).any()
+        assert np.array_equal(np.isneginf(got[odd]), np.isneginf(small)) and np.isneginf(small).any()
+        rest = [n for n in range(N) if n not in odd]
+        ref = orc.mpgemm_definition(p.act[rest], p.q, p.scales, p.zeros, group)
+        assert orc.rel_frobenius(got[rest], ref) <= 4e-4
+
+
 def test_large_call_takes_two_row_tiles_per_workgroup_by_default(T, torch):
     """From about 8000 wavefronts on (here 8192 x 8192: 1024 row tiles x 8 waves) the register-table
     kernel serves 16 rows per workgroup unless told otherwise: the default call, the call with 8 rows
