@@ -9,10 +9,15 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import struct
 from dataclasses import dataclass
 from typing import Optional
 
 import numpy as np
+# torch bundles its own HIP runtime (same soname as ROCm's).  Import torch before the library is loaded
+# so that it binds to that one runtime instead of pulling a second copy from /opt/rocm: two runtimes
+# in one process do not share streams or devices.
+import torch
 
 _PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG_DIR, "libtmac_hip.so")
@@ -52,6 +57,10 @@ class tmac_gemv_item(C.Structure):
                 ("out_dev", C.c_void_p), ("ldo", C.c_int64)]
 
 
+_ITEM_FORMAT = "PPPqPf4xPq"  # tmac_gemv_item as struct spells it
+assert struct.calcsize("@" + _ITEM_FORMAT) == C.sizeof(tmac_gemv_item)
+
+
 class TmacError(RuntimeError):
     def __init__(self, status: int, where: str):
         self.status = status
@@ -64,10 +73,6 @@ def _load() -> C.CDLL:
         raise ImportError(
             f"{LIB_PATH} is not built; run `python -c 'import __graft_entry__ as g; g.build()'` "
             "(there is no CPU or PyTorch fallback for the HIP path)")
-    # torch bundles its own HIP runtime (same soname as ROCm's).  Import torch first so that the
-    # library binds to that one runtime instead of pulling a second copy from /opt/rocm: two
-    # runtimes in one process do not share streams or devices.
-    import torch  # noqa: F401
     lib = C.CDLL(LIB_PATH)
     P, I32, I64, SZ, F = C.c_void_p, C.c_int32, C.c_int64, C.c_size_t, C.c_float
     D = C.POINTER(tmac_wdesc)
@@ -186,24 +191,26 @@ def tmac_blob_check(desc: tmac_wdesc, header: np.ndarray) -> int:
     return int(lib.tmac_blob_check(C.byref(desc), _np_ptr(h)))
 
 
-def _stream_ptr(stream) -> Optional[int]:
-    if stream is None:
-        import torch
-        stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream)
+def _stream_ptr(stream) -> int:
+    """The stream's handle; None = the current stream of the current device (asked for by its handle:
+    building a torch.cuda.Stream object for it took 2.8 us of a call's 10)."""
+    if stream is not None:
+        return stream.cuda_stream
+    if not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def tmac_precompute_lut(A, N: int, K: int, group: int, lut: int, lut_buf, act: Optional[int] = None,
                         lda: Optional[int] = None, g: int = 4, stream=None) -> None:
     """A: device tensor (fp16 or int8) [N, K]; lut_buf: device uint8 tensor of tmac_lut_bytes."""
-    import torch
     if act is None:
         act = TMAC_ACT_I8 if A.dtype == torch.int8 else TMAC_ACT_F16
     _check_act_dtype(A, act)
     if lda is None:
         lda = A.stride(0) if A.dim() == 2 else K
-    _check(lib.tmac_precompute_lut(C.c_void_p(A.data_ptr()), act, N, K, lda, g, group, lut,
-                                   C.c_void_p(lut_buf.data_ptr()), lut_buf.numel() * lut_buf.element_size(),
+    _check(lib.tmac_precompute_lut(A.data_ptr(), act, N, K, lda, g, group, lut,
+                                   lut_buf.data_ptr(), lut_buf.numel() * lut_buf.element_size(),
                                    _stream_ptr(stream)), "tmac_precompute_lut")
 
 
@@ -213,11 +220,11 @@ def tmac_mpgemm(desc: tmac_wdesc, packed, lut_buf, lut: int, N: int, out, out_t:
     """packed / lut_buf / out / workspace / act_scale: device tensors."""
     if ldo is None:
         ldo = out.stride(0) if out.dim() == 2 else desc.M
-    ws_ptr = C.c_void_p(workspace.data_ptr()) if workspace is not None else None
+    ws_ptr = workspace.data_ptr() if workspace is not None else None
     ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    as_ptr = C.c_void_p(act_scale.data_ptr()) if act_scale is not None else None
-    args = [C.byref(desc), C.c_void_p(packed.data_ptr()), C.c_void_p(lut_buf.data_ptr()), lut, N, as_ptr,
-            C.c_float(weight_scale), C.c_void_p(out.data_ptr()), out_t, ldo, ws_ptr, ws_bytes,
+    as_ptr = act_scale.data_ptr() if act_scale is not None else None
+    args = [desc, packed.data_ptr(), lut_buf.data_ptr(), lut, N, as_ptr,
+            weight_scale, out.data_ptr(), out_t, ldo, ws_ptr, ws_bytes,
             _stream_ptr(stream)]
     if tuning is None:
         _check(lib.tmac_mpgemm(*args), "tmac_mpgemm")
@@ -230,16 +237,15 @@ def tmac_mpgemm_noalloc(desc: tmac_wdesc, packed, lut_buf, lut: int, N: int, out
     """tmac_mpgemm without a workspace (the library's own fixed array takes the partial sums)."""
     if ldo is None:
         ldo = out.stride(0) if out.dim() == 2 else desc.M
-    as_ptr = C.c_void_p(act_scale.data_ptr()) if act_scale is not None else None
-    _check(lib.tmac_mpgemm_noalloc(C.byref(desc), C.c_void_p(packed.data_ptr()), C.c_void_p(lut_buf.data_ptr()), lut,
-                                   N, as_ptr, C.c_float(weight_scale), C.c_void_p(out.data_ptr()), out_t, ldo,
+    as_ptr = act_scale.data_ptr() if act_scale is not None else None
+    _check(lib.tmac_mpgemm_noalloc(desc, packed.data_ptr(), lut_buf.data_ptr(), lut,
+                                   N, as_ptr, weight_scale, out.data_ptr(), out_t, ldo,
                                    _stream_ptr(stream)), "tmac_mpgemm_noalloc")
 
 
 def _check_act_dtype(A, act: int) -> None:
     """The C ABI takes the activation type on trust; a tensor of another element size would be read
     out of range."""
-    import torch
     want = torch.int8 if act == TMAC_ACT_I8 else torch.float16
     if A.dtype != want:
         raise ValueError(f"activation type {act} needs a {want} tensor, got {A.dtype}")
@@ -249,7 +255,6 @@ def tmac_mpgemv_fused(desc: tmac_wdesc, packed, A, N: int, out, out_t: int, act:
                       lda: Optional[int] = None, act_scale=None, weight_scale: float = 1.0,
                       ldo: Optional[int] = None, stream=None, tuning: Optional[tmac_tuning] = None) -> None:
     """packed / A / out / act_scale: device tensors; A fp16 or int8 [N, K]."""
-    import torch
     if act is None:
         act = TMAC_ACT_I8 if A.dtype == torch.int8 else TMAC_ACT_F16
     _check_act_dtype(A, act)
@@ -257,9 +262,9 @@ def tmac_mpgemv_fused(desc: tmac_wdesc, packed, A, N: int, out, out_t: int, act:
         lda = A.stride(0) if A.dim() == 2 else desc.K
     if ldo is None:
         ldo = out.stride(0) if out.dim() == 2 else desc.M
-    as_ptr = C.c_void_p(act_scale.data_ptr()) if act_scale is not None else None
-    args = [C.byref(desc), C.c_void_p(packed.data_ptr()), C.c_void_p(A.data_ptr()), act, N, lda, as_ptr,
-            C.c_float(weight_scale), C.c_void_p(out.data_ptr()), out_t, ldo, _stream_ptr(stream)]
+    as_ptr = act_scale.data_ptr() if act_scale is not None else None
+    args = [desc, packed.data_ptr(), A.data_ptr(), act, N, lda, as_ptr,
+            weight_scale, out.data_ptr(), out_t, ldo, _stream_ptr(stream)]
     if tuning is None:
         _check(lib.tmac_mpgemv_fused(*args), "tmac_mpgemv_fused")
     else:
@@ -270,34 +275,35 @@ def tmac_mpgemv_fused_multi(items, N: int, out_t: int, act: Optional[int] = None
                             tuning: Optional[tmac_tuning] = None) -> None:
     """items: sequence of (desc, packed, A, out[, act_scale[, weight_scale]]) with device tensors;
     one launch serves them all."""
-    import torch
     n = len(items)
     arr = (tmac_gemv_item * max(n, 1))()
-    for i, it in enumerate(items):
+    fields = []
+    for it in items:
         desc, packed, A, out = it[:4]
         act_scale = it[4] if len(it) > 4 else None
         wscale = it[5] if len(it) > 5 else 1.0
-        a_act = TMAC_ACT_I8 if A.dtype == torch.int8 else TMAC_ACT_F16
         if act is None:
-            act = a_act
+            act = TMAC_ACT_I8 if A.dtype == torch.int8 else TMAC_ACT_F16
         _check_act_dtype(A, act)
-        arr[i] = tmac_gemv_item(C.pointer(desc), packed.data_ptr(), A.data_ptr(),
-                                A.stride(0) if A.dim() == 2 else desc.K,
-                                act_scale.data_ptr() if act_scale is not None else None, float(wscale),
-                                out.data_ptr(), out.stride(0) if out.dim() == 2 else desc.M)
+        if not isinstance(desc, tmac_wdesc):
+            raise TypeError(f"expected a tmac_wdesc, got {type(desc).__name__}")
+        fields += (C.addressof(desc), packed.data_ptr(), A.data_ptr(), A.stride(0) if A.dim() == 2 else desc.K,
+                   act_scale.data_ptr() if act_scale is not None else 0, wscale,
+                   out.data_ptr(), out.stride(0) if out.dim() == 2 else desc.M)
+    # (all items' fields at once: one ctypes object per item costs five times as much)
+    struct.pack_into("@" + _ITEM_FORMAT * n, arr, 0, *fields)
     _check(lib.tmac_mpgemv_fused_multi(arr, n, TMAC_ACT_F16 if act is None else act, N, out_t, _stream_ptr(stream),
                                        C.byref(tuning) if tuning is not None else None), "tmac_mpgemv_fused_multi")
 
 
 def tmac_fused_workspace_bytes(desc: tmac_wdesc, N: int, act: int) -> int:
-    return int(lib.tmac_fused_workspace_bytes(C.byref(desc), N, act))
+    return int(lib.tmac_fused_workspace_bytes(desc, N, act))
 
 
 def tmac_mpgemm_fused(desc: tmac_wdesc, packed, A, N: int, out, out_t: int, workspace, act: Optional[int] = None,
                       lda: Optional[int] = None, act_scale=None, weight_scale: float = 1.0,
                       ldo: Optional[int] = None, stream=None) -> None:
     """packed / A / out / act_scale / workspace: device tensors; A fp16 or int8 [N, K]."""
-    import torch
     if act is None:
         act = TMAC_ACT_I8 if A.dtype == torch.int8 else TMAC_ACT_F16
     _check_act_dtype(A, act)
@@ -305,10 +311,10 @@ def tmac_mpgemm_fused(desc: tmac_wdesc, packed, A, N: int, out, out_t: int, work
         lda = A.stride(0) if A.dim() == 2 else desc.K
     if ldo is None:
         ldo = out.stride(0) if out.dim() == 2 else desc.M
-    as_ptr = C.c_void_p(act_scale.data_ptr()) if act_scale is not None else None
-    _check(lib.tmac_mpgemm_fused(C.byref(desc), C.c_void_p(packed.data_ptr()), C.c_void_p(A.data_ptr()), act, N, lda,
-                                 as_ptr, C.c_float(weight_scale), C.c_void_p(out.data_ptr()), out_t, ldo,
-                                 C.c_void_p(workspace.data_ptr()), workspace.numel() * workspace.element_size(),
+    as_ptr = act_scale.data_ptr() if act_scale is not None else None
+    _check(lib.tmac_mpgemm_fused(desc, packed.data_ptr(), A.data_ptr(), act, N, lda,
+                                 as_ptr, weight_scale, out.data_ptr(), out_t, ldo,
+                                 workspace.data_ptr(), workspace.numel() * workspace.element_size(),
                                  _stream_ptr(stream)), "tmac_mpgemm_fused")
 
 

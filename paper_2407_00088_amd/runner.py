@@ -4,8 +4,11 @@ from __future__ import annotations
 from typing import Optional
 
 import numpy as np
+import torch
 
 from . import binding as B
+
+_OUT_DTYPE = {B.TMAC_OUT_F32: torch.float32, B.TMAC_OUT_F16: torch.float16, B.TMAC_OUT_I32: torch.int32}
 
 DECODE_MAX_N = 8  # up to this many activation rows the register-table layout is the default
 
@@ -24,7 +27,6 @@ class LinearLUT:
                  zero_point: float = 0.0, weight_scale: float = 1.0, int_path: bool = False,
                  max_N: int = 1, device: str = "cuda", packed_host: Optional[np.ndarray] = None,
                  layout: Optional[int] = None, lut_t: Optional[int] = None, g: int = 4):
-        import torch
         self.torch = torch
         self.device = device
         # LUT group sizes other than 4 exist in the batched layout only
@@ -65,38 +67,37 @@ class LinearLUT:
 
     def mpgemm_fused(self, A, N: int, out, out_t: int = B.TMAC_OUT_F32, act_scale=None, stream=None, packed=None):
         """One call for either layout (tmac_mpgemm_fused); its workspace is allocated on first use."""
-        act = B.TMAC_ACT_I8 if A.dtype == self.torch.int8 else B.TMAC_ACT_F16
-        need = B.tmac_fused_workspace_bytes_max(self.desc, self.max_N, act)
-        if need == 0:
-            raise B.TmacError(B.TMAC_EUNSUPPORTED, "tmac_fused_workspace_bytes_max")
-        if getattr(self, "fused_ws", None) is None or self.fused_ws.numel() < need:
-            self.fused_ws = self.torch.full((max(need, 256),), 0xA5, dtype=self.torch.uint8, device=self.device)
+        act = B.TMAC_ACT_I8 if A.dtype == torch.int8 else B.TMAC_ACT_F16
+        need = B.tmac_fused_workspace_bytes(self.desc, N, act) if 0 < N <= self.max_N else 0
+        ws = getattr(self, "fused_ws", None)
+        if need == 0 or ws is None or ws.numel() < need:
+            # first use (or a size this holder was not made for): a workspace for every N up to max_N, whose
+            # size takes a pass over all of them
+            need = B.tmac_fused_workspace_bytes_max(self.desc, self.max_N, act)
+            if need == 0:
+                raise B.TmacError(B.TMAC_EUNSUPPORTED, "tmac_fused_workspace_bytes_max")
+            if ws is None or ws.numel() < need:
+                self.fused_ws = torch.full((max(need, 256),), 0xA5, dtype=torch.uint8, device=self.device)
         B.tmac_mpgemm_fused(self.desc, self.packed if packed is None else packed, A, N, out, out_t, self.fused_ws,
                             act_scale=act_scale, weight_scale=self.weight_scale, stream=stream)
 
     def forward_one_call(self, A, out_t: int = B.TMAC_OUT_F32, act_scale=None):
-        torch = self.torch
         N = A.shape[0]
         assert N <= self.max_N
-        dt = {B.TMAC_OUT_F32: torch.float32, B.TMAC_OUT_F16: torch.float16, B.TMAC_OUT_I32: torch.int32}[out_t]
-        out = torch.empty((N, self.M), dtype=dt, device=self.device)
+        out = torch.empty((N, self.M), dtype=_OUT_DTYPE[out_t], device=self.device)
         self.mpgemm_fused(A, N, out, out_t, act_scale=act_scale)
         return out
 
     def forward_fused(self, A, out_t: int = B.TMAC_OUT_F32, act_scale=None, tuning=None, act=None):
-        torch = self.torch
         N = A.shape[0]
-        dt = {B.TMAC_OUT_F32: torch.float32, B.TMAC_OUT_F16: torch.float16, B.TMAC_OUT_I32: torch.int32}[out_t]
-        out = torch.empty((N, self.M), dtype=dt, device=self.device)
+        out = torch.empty((N, self.M), dtype=_OUT_DTYPE[out_t], device=self.device)
         self.mpgemv_fused(A, N, out, out_t, act_scale=act_scale, tuning=tuning, act=act)
         return out
 
     def forward(self, A, out_t: int = B.TMAC_OUT_F32, act_scale=None, tuning=None):
-        torch = self.torch
         N = A.shape[0]
         assert N <= self.max_N
-        dt = {B.TMAC_OUT_F32: torch.float32, B.TMAC_OUT_F16: torch.float16, B.TMAC_OUT_I32: torch.int32}[out_t]
-        out = torch.empty((N, self.M), dtype=dt, device=self.device)
+        out = torch.empty((N, self.M), dtype=_OUT_DTYPE[out_t], device=self.device)
         self.precompute(A, N)
         self.mpgemm(N, out, out_t, act_scale=act_scale, tuning=tuning)
         return out
