@@ -276,6 +276,7 @@ def tmac_mpgemv_fused_multi(items, N: int, out_t: int, act: Optional[int] = None
     """items: sequence of (desc, packed, A, out[, act_scale[, weight_scale]]) with device tensors;
     one launch serves them all."""
     n = len(items)
+    items = list(items)  # a sequence may make its tuples on access: what the library reads by address lives until it returns
     arr = (tmac_gemv_item * max(n, 1))()
     fields = []
     for it in items:

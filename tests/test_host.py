@@ -5,6 +5,8 @@ import ctypes as C
 import os
 import re
 import struct
+import weakref
+from types import SimpleNamespace
 
 import numpy as np
 import pytest
@@ -318,6 +320,39 @@ def test_fused_call_refuses_sizes_beyond_its_index_arithmetic_before_launch():
     # int8 activations with one scale per row: the row sum travels in fp32 and must stay below 2^24
     long_int = T.wdesc(8, 1 << 18, 2, 0, layout=B.TMAC_LAYOUT_R8U16)
     assert call(long_int, act=B.TMAC_ACT_I8) == B.TMAC_EUNSUPPORTED
+
+
+class _LazyItems:
+    """A sequence of matrices that makes each descriptor and tuple when it is asked for it."""
+
+    def __init__(self, sizes, made):
+        self.sizes, self.made = sizes, made
+
+    def __len__(self):
+        return len(self.sizes)
+
+    def __getitem__(self, i):
+        import torch
+        M = self.sizes[i]                                         # (IndexError past the end)
+        d = T.wdesc(M, 256, 4, 128, layout=B.TMAC_LAYOUT_R8U16)
+        t = torch.zeros((1, 256), dtype=torch.float16)
+        self.made += [weakref.ref(d), weakref.ref(t)]
+        return d, torch.zeros(64, dtype=torch.uint8), t, torch.zeros((1, M))
+
+
+def test_multi_keeps_items_made_on_access_alive_until_the_library_returns(monkeypatch):
+    """tmac_mpgemv_fused_multi hands the library addresses of descriptors and tensors: those of a sequence
+    that makes its tuples on access are still there when the library reads them (a stub in its place)."""
+    seen = []
+
+    def stub(arr, n, *rest):
+        assert made and all(r() is not None for r in made), "freed before the call"
+        seen.extend(arr[i].desc.contents.M for i in range(n))
+        return B.TMAC_OK
+    made = []
+    monkeypatch.setattr(B.lib, "tmac_mpgemv_fused_multi", stub)
+    B.tmac_mpgemv_fused_multi(_LazyItems([256, 320, 384], made), 1, B.TMAC_OUT_F32, stream=SimpleNamespace(cuda_stream=0))
+    assert seen == [256, 320, 384]
 
 
 def test_bench_refuses_more_than_one_gpu():
