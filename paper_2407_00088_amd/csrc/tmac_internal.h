@@ -221,9 +221,13 @@ struct RowsPlan {
   // fp16 tables as fixed-point numbers (see rows_fix_kernel); fix == false: none of it
   bool fix;
   int fix_cps, fix_slices, fix_tiles;               // chunks per K slice, K slices, sets of 16 activation rows
+  int fix_shift;                                    // 2: a unit per 128-k block, 0: per chunk
   // inside the same workspace: partial sums, tables, their units, the group sums
-  size_t fix_part_bytes, fix_tab_bytes, fix_scale_bytes;
-  size_t bytes() const { return part_bytes + ctr_bytes + srow_bytes; }
+  size_t fix_part_bytes, fix_tab_bytes, fix_scale_bytes, fix_sums_bytes;
+  size_t bytes() const {
+    const size_t plain = part_bytes + ctr_bytes + srow_bytes, fixed = fix_part_bytes + fix_tab_bytes + fix_scale_bytes + fix_sums_bytes;
+    return fixed > plain ? fixed : plain;  // (fixed is 0 without fixed-point tables; integer tables keep the plain plan)
+  }
 };
 RowsPlan rows_plan(const tmac_wdesc* desc, int N);
 bool rows_builds_tables(const tmac_wdesc* desc, int N);

@@ -102,7 +102,8 @@ struct RowsParams {
                            // fused convert-multiply-add (a literal 1.0 would be folded into cvt + add)
   int out_t;
   int bits;
-  const float* fix_scale;  // fixed-point tables, else null: [set of 16 rows][128-k block][16] value of one unit (negative: fp16 entries)
+  const float* fix_scale;  // fixed-point tables, else null: [set of 16 rows][chunk >> fix_shift][16] value of one unit (negative: fp16 entries)
+  int fix_shift;           // 2: one unit per 128-k block, 0: one per chunk (see rows_fix_kernel)
 };
 
 // 32-k chunks of tables one LDS slice holds, for LUT group size g and nt activation rows
@@ -854,7 +855,7 @@ __device__ __forceinline__ float rows_raw_blocks(const RowsParams& p, const floa
   const int tile = m >> 6, r = m & 63;
 #pragma unroll 1
   for (int c = 0; c < p.n_chunks; ++c) {
-    if (!(unit[(size_t)(c >> 2) * 16] < 0.f)) continue;
+    if (!(unit[(size_t)(c >> p.fix_shift) * 16] < 0.f)) continue;
     float hs = 1.f;
     if (p.grouped) {
       if (c / p.cpg >= p.nq) break;  // chunks in the K padding belong to no group
@@ -895,7 +896,7 @@ __global__ __launch_bounds__(256) void rows_sum_kernel(const RowsParams p, int n
   bool raw = false;
   if constexpr (!IS_INT) {
     if (p.fix_scale) {
-      const int nblk = p.KG / 32;
+      const int nblk = p.n_chunks >> p.fix_shift;
       const int first = __builtin_amdgcn_readfirstlane(min(n, p.N - 1)) >> 4;
       const int last = __builtin_amdgcn_readlane(min(n, p.N - 1), 63) >> 4;
       bool some = false;
@@ -959,7 +960,7 @@ __global__ __launch_bounds__(256) void rows_sum_kernel(const RowsParams p, int n
   }
   if constexpr (!IS_INT) {
     if (raw) {
-      const float* const unit = p.fix_scale + (size_t)(n >> 4) * (p.KG / 32) * 16;
+      const float* const unit = p.fix_scale + (size_t)(n >> 4) * (p.n_chunks >> p.fix_shift) * 16;
 #pragma unroll
       for (int i = 0; i < VEC; ++i) sf[i] += rows_raw_blocks(p, unit, n, m0 + i);
     }
@@ -1018,17 +1019,22 @@ static hipError_t launch_rows_sum(const RowsParams& p, int nz, hipStream_t st) {
 // ------------------------------------------------------------------------------------------
 // With fp16 tables and many look-ups the vector ALUs bind: v_pk_add_f16 takes 1.8 ns per wavefront and
 // SIMD for one entry of two activation rows, and a plane's sum takes three fp16 roundings.  Large calls
-// therefore turn the tables into 16-bit integers first, one power of precision for each (activation row,
-// 128 k): the unit is the largest sum that one chunk's eight entries can reach, divided by
-// ROWS_FIX_MAX, so that the eight entries of any chunk and plane add up within 16 bits, exactly, with
-// two entries per v_add3_u32.  What is rounded is each entry, once, to 2^-15 of the largest sum of a
-// chunk, where fp16 sums round to 2^-11 of every partial sum: 256 rows x 5120 x 5120 at 4 bit is off
-// by 2.3e-4 instead of 3.5e-4.
+// therefore turn the tables into 16-bit integers first, with one unit for each (activation row,
+// quantisation group of at most 128 k): the unit is the largest sum that one chunk's eight entries can
+// reach, divided by ROWS_FIX_MAX, so that the eight entries of any chunk and plane add up within 16 bits,
+// exactly, with two entries per v_add3_u32.  What is rounded is each entry, once, to 2^-15 of the largest
+// sum of a chunk, where fp16 sums round to 2^-11 of every partial sum: 256 rows x 5120 x 5120 at 4 bit is
+// off by 2.3e-4 instead of 3.5e-4.
+// A unit never spans two groups: with group scales that undo the size of the activations (one group's
+// activations 30 times its neighbours', its scales a thirtieth) one unit for the four groups of a
+// 128-k block was off by 2.3e-3, one for each is by 2.4e-4, like groups of one size.  Groups of whole 128-k
+// blocks (or none) have one unit per block; others have one stored per chunk, the same for the chunks of a
+// block that one group holds.
 // In memory and LDS an entry pair is the number (hi + B) * 65536 + lo + B modulo 2^32 (B =
 // ROWS_FIX_BIAS): additions of whole dwords are exact, and the sum of a chunk's eight pairs has two
 // clean halves, sum + 32768.
-// A 128-k block in which some row's entries are not finite keeps its fp16 entries (fix_scale negative
-// for the set's 16 rows); the look-up kernel takes nothing from it, and rows_sum_kernel looks it up from
+// Chunks of one unit in which some row's entries are not finite keep their fp16 entries (fix_scale negative
+// for the set's 16 rows); the look-up kernel takes nothing from them, and rows_sum_kernel looks them up from
 // memory with fp16 additions, so that infinities and NaNs come out as they do in the general kernel.
 constexpr int ROWS_FIX_BIAS = 4096;
 constexpr float ROWS_FIX_MAX = 32700.f;  // + 8 roundings of half a unit stays below 32767
@@ -1055,7 +1061,7 @@ __global__ __launch_bounds__(256) void rows_fix_kernel(const RowsParams p, uint3
   __shared__ float smax[4][16];                    // [chunk][row]: largest sum of the chunk's eight entries
   const int nblk = p.KG / 32;
   const int set = blockIdx.x / nblk, blk = blockIdx.x % nblk;
-  const int u = threadIdx.x & 7, tb = threadIdx.x >> 3, wave = threadIdx.x >> 6;
+  const int u = threadIdx.x & 7, tb = threadIdx.x >> 3, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int kg = blk * 32 + tb, n = set * 16 + 2 * u;
   uint32_t v[8];                                   // entries 0..7 of rows n (low half) and n + 1
   if constexpr (FROM_ACT) {
@@ -1096,23 +1102,31 @@ __global__ __launch_bounds__(256) void rows_fix_kernel(const RowsParams p, uint3
     smax[wave][2 * u] = b0;
     smax[wave][2 * u + 1] = b1;
   }
+  // the chunks of the block that share the unit of this wavefront's chunk: those of its group
+  int u0 = 0, u1 = 4;
+  if (p.fix_shift == 0) {
+    u0 = (blk * 4 + wave) / p.cpg * p.cpg - blk * 4;
+    u1 = u0 + p.cpg;
+  }
   __syncthreads();
   float f[2];
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
-    float b = smax[0][2 * u + h];
-    bool bad = !(b <= 1e30f);
+    float b = 0.f;
+    bool bad = false;
 #pragma unroll
-    for (int c = 1; c < 4; ++c) {
-      bad |= !(smax[c][2 * u + h] <= 1e30f);
-      b = fmaxf(b, smax[c][2 * u + h]);
+    for (int c = 0; c < 4; ++c) {
+      const float sum = c >= u0 && c < u1 ? smax[c][2 * u + h] : 0.f;
+      bad |= !(sum <= 1e30f);
+      b = fmaxf(b, sum);
     }
     f[h] = bad ? -1.f : b;
   }
   const bool raw = __any(f[0] < 0.f || f[1] < 0.f);  // (every wavefront sees all 16 rows)
-  if (threadIdx.x < 8) {
+  if ((threadIdx.x & 63) < 8 && (wave == 0 || p.fix_shift == 0)) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) scale[((size_t)set * nblk + blk) * 16 + 2 * u + h] = raw ? -1.f : f[h] / ROWS_FIX_MAX;
+    for (int h = 0; h < 2; ++h)
+      scale[((size_t)set * (p.n_chunks >> p.fix_shift) + ((blk * 4 + wave) >> p.fix_shift)) * 16 + 2 * u + h] = raw ? -1.f : f[h] / ROWS_FIX_MAX;
   }
   const float f0 = f[0] > 0.f ? ROWS_FIX_MAX / f[0] : 0.f, f1 = f[1] > 0.f ? ROWS_FIX_MAX / f[1] : 0.f;
   uint32_t* const dst = stage + (u >> 2) * OD + tb * TD + (u & 3);
@@ -1180,7 +1194,7 @@ __device__ __forceinline__ void rows_chunk_fix(const uint32_t (&x)[BITS], uint32
 // mpgemm_rows_kernel for fixed-point tables: two sets of eight activation rows per workgroup, tables
 // from the workspace (written by rows_fix_kernel), results through the workspace to rows_sum_kernel even
 // where there is one K slice only (finishing here as well costs 40 registers).  The integer sums of a quantisation group and 128-k
-// block are converted once and multiplied by the block's unit and half the group's scale.  Bound by the
+// block are converted once and multiplied by their unit and half the group's scale.  Bound by the
 // look-up rate of LDS and the vector ALUs about equally, each about 70 % busy (see rows_chunk_int).  The
 // whole call at 256 rows x 5120 x 5120, 4 bit: 139 us against 163 with fp16 tables; 511 rows x 13824 x
 // 5120, 2 bit: 378 against 426.  (Tables of eight chunks staged with a wait: 143, 401; five wavefronts
@@ -1199,7 +1213,8 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_fix_kernel(const Ro
   const uint32_t* my_idx = p.idx + ((size_t)tile * p.n_chunks * 64 + lane) * BITS;
   const uint32_t* my_sz = p.sz + (size_t)tile * p.nq * 64 + lane;
   const uint32_t lds0 = (uint32_t)(uintptr_t)((rows_lds_char*)tab);
-  rows_const_float* const fix_scale = rows_const(p.fix_scale) + (size_t)blockIdx.x * (p.KG / 32) * 16;
+  const int shift = p.fix_shift;
+  rows_const_float* const fix_scale = rows_const(p.fix_scale) + (size_t)blockIdx.x * (p.n_chunks >> shift) * 16;
   rows_const_float* const sums = rows_const(p.S) + (size_t)blockIdx.x * p.nq * 16;
   const int cz0 = blockIdx.z * p.cps, cz1 = min(cz0 + p.cps, p.n_chunks);
 
@@ -1222,7 +1237,7 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_fix_kernel(const Ro
   int gq = p.grouped ? cz0 / p.cpg : 0, cg = 0;  // current quantisation group, chunks done in it (wave-uniform)
   float hs = 1.f;                                // half the group's scale (1: one scale per row or tensor, applied at the end)
   uint32_t szv_next = p.grouped ? my_sz[(size_t)min(gq, p.nq - 1) * 64] : 0u;
-  float unit[16];  // the block's units (wave-uniform); 0 where it kept its fp16 entries
+  float unit[16];  // units of the sums in progress (wave-uniform); 0 where they kept their fp16 entries
   uint32_t xn[BITS];
   load_idx(cz0, xn);
 
@@ -1246,8 +1261,6 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_fix_kernel(const Ro
     for (int i = 0; i < 4; ++i) *reinterpret_cast<ru32x4v*>(tab + (i >> 1) * OSTRIDE + (i & 1) * 4096 + threadIdx.x * 16) = next[i];
     __syncthreads();
     if (c0 + 4 < cz1) request(c0 + 4);
-#pragma unroll
-    for (int t = 0; t < 16; ++t) unit[t] = __int_as_float(max(__float_as_int(fix_scale[(c0 >> 2) * 16 + t]), 0));
     int L[16];
     bool first = true;
     for (int c = c0; c < c0 + 4; ++c) {
@@ -1266,6 +1279,8 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_fix_kernel(const Ro
         szv_next = my_sz[(size_t)min(gq + 1, p.nq - 1) * 64];
       }
       if (first) {  // sums start at minus the biases of the chunks they will hold
+#pragma unroll
+        for (int t = 0; t < 16; ++t) unit[t] = __int_as_float(max(__float_as_int(fix_scale[(c >> shift) * 16 + t]), 0));
         int chunks = 4 - (c & 3);
         if (p.grouped && gq < p.nq) chunks = min(chunks, p.cpg - cg);
         const int L0 = -chunks * (32768 * ((1 << BITS) - 1));
@@ -1384,8 +1399,8 @@ static RowsPlan rows_plan_oct(const tmac_wdesc* desc, int N, int oct) {
   pl.part_bytes = pl.slices > 1 ? ((size_t)pl.slices * N * ge.Mp * 4 + 255) / 256 * 256 : 0;
   pl.ctr_bytes = 0;  // (no arrival counters: the slices meet in rows_sum_kernel)
   pl.fix = false;
-  pl.fix_cps = pl.fix_slices = pl.fix_tiles = 0;
-  pl.fix_part_bytes = pl.fix_tab_bytes = pl.fix_scale_bytes = 0;
+  pl.fix_cps = pl.fix_slices = pl.fix_tiles = pl.fix_shift = 0;
+  pl.fix_part_bytes = pl.fix_tab_bytes = pl.fix_scale_bytes = pl.fix_sums_bytes = 0;
   pl.srow_bytes = pl.eight ? ((size_t)pl.slices * N * 4 + 255) / 256 * 256 : 0;
   return pl;
 }
@@ -1403,8 +1418,9 @@ static RowsPlan rows_plan_plain(const tmac_wdesc* desc, int N) {
 
 // Fixed-point tables (fp16 tables only) serve the calls whose partial sums would not fit the library's
 // own array: those are the large ones, and tmac_mpgemm_noalloc, whose results are tmac_mpgemm's bit for
-// bit, refuses exactly these.  The workspace keeps its size: K is split into fewer slices, and the
-// tables take the room of the others' partial sums (a call where that leaves no slice keeps fp16 tables).
+// bit, refuses exactly these.  K is split into fewer slices, and the tables take the room of the others'
+// partial sums (a call where that leaves no slice keeps fp16 tables); only the units of groups below 128 k
+// may add to the workspace's size.
 //
 // The extra launch that converts the tables wants look-ups to pay for it.  Measured against the general
 // kernels: 64 rows x 11008 x 4096 at 4 bit 70.0 us against 79.0, 80 rows 84.0 against 96.3; at 4096 x
@@ -1425,7 +1441,9 @@ RowsPlan rows_plan(const tmac_wdesc* desc, int N) {
   const int tiles = (N + 15) / 16;
   const int64_t pairs = (int64_t)tiles * pl.row_blocks;
   const size_t slice = (size_t)N * ge.Mp * 4;
-  const size_t tab = (size_t)((N + 7) / 8) * (ge.Kp / 4) * 256, scale = (size_t)tiles * (ge.Kp / 128) * 64;
+  // units: one per 128-k block where no block holds parts of two groups, else one per chunk
+  const int shift = (one_group || cpg % 4 == 0) ? 2 : 0;
+  const size_t tab = (size_t)((N + 7) / 8) * (ge.Kp / 4) * 256, scale = (size_t)tiles * (ge.n_chunks >> 2) * 64;
   const size_t sums = (size_t)tiles * (one_group ? 1 : desc->K / desc->group) * 64;
   const int want = (int)((ROWS_FIX_TARGET_WGS + pairs - 1) / pairs);
   for (int cps = ((ge.n_chunks + want - 1) / want + unit - 1) / unit * unit;; cps += unit) {
@@ -1439,7 +1457,9 @@ RowsPlan rows_plan(const tmac_wdesc* desc, int N) {
       pl.fix_tiles = tiles;
       pl.fix_part_bytes = part;
       pl.fix_tab_bytes = tab;
-      pl.fix_scale_bytes = scale;
+      pl.fix_scale_bytes = scale * (shift == 0 ? 4 : 1);
+      pl.fix_sums_bytes = sums;
+      pl.fix_shift = shift;
       return pl;
     }
     if (slices == 1) return pl;
@@ -1521,6 +1541,7 @@ int launch_rows_gemm(const tmac_wdesc* desc, const void* packed_dev, const void*
   hipStream_t st = static_cast<hipStream_t>(stream);
   hipError_t e;
   p.fix_scale = nullptr;
+  p.fix_shift = pl.fix_shift;
   p.bits = desc->bits;
   if (pl.fix && !is_int && !fused) {
     char* const tab = static_cast<char*>(workspace_dev) + pl.fix_part_bytes;

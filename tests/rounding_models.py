@@ -1,7 +1,7 @@
 """Models of the roundings the HIP kernels take on the fp16 path (test helpers, not the oracle).
 
 The oracle (``oracle/tmac_oracle.py``) holds what the paper defines: the exact product and the
-LUT formulation of Algorithm 1 in fp64.  The kernels round in two places of their own choosing,
+LUT formulation of Algorithm 1 in fp64.  The kernels round in three places of their own choosing,
 and these functions replay exactly those roundings on the CPU so that a GPU test can tell "the
 kernel does the arithmetic it says it does" (agreement to a few 1e-8) from "the result is inside
 the 2e-3 bar" (which a wrong kernel could also be):
@@ -12,6 +12,8 @@ the 2e-3 bar" (which a wrong kernel could also be):
 * ``lookup_sum_narrow`` / ``lut_mpgemm_narrow``: the batched kernels add the eight entries that a
   32-k chunk gives one bit plane in fp16 before widening.  This is the library's own choice and it
   is lossy; the paper's "fast 8-bit aggregation" (Section 4) is a different, integer technique.
+* ``lut_mpgemm_fixed``: large calls round the entries once more, to 16-bit integers with one unit per
+  activation row and quantisation group of at most 128 k; every sum is exact from there on.
 
 They build on the oracle's exact steps (bit planes, indices, group sums) and are pinned by
 ``tests/test_rounding_models.py``.
@@ -112,3 +114,42 @@ def lut_mpgemm_narrow(act, q, bits, scales, zeros, group, g=4, tables_per_sum=8)
     for i, plane in enumerate(orc.bit_planes(q, bits)):
         Lsum += (2.0 ** i) * lookup_sum_narrow(lut, orc.group_indices(plane, g), group // g, tables_per_sum)
     return _finish(Lsum, S, s, z, bits)
+
+
+def _scales_and_zeros(M, K, scales, zeros, group, weight_scale, zero_point):
+    if group == 0:
+        return np.full((M, 1), np.float64(weight_scale)), np.full((M, 1), np.float64(zero_point)), K
+    return np.asarray(scales).astype(np.float64), np.asarray(zeros).astype(np.float64), group
+
+
+def fixed_point_tables(act, group, g=4):
+    """fp16 tables rounded to multiples of one unit per (activation row, stretch of K that lies in one
+    quantisation group and one 128-k block): the largest sum of eight entries a 32-k chunk of the stretch
+    can reach, divided by 32700 (fp32); nearest integer, ties to even.  K is padded to 128 with zeros."""
+    lut = precompute_lut_fp16_tree(act, g).astype(np.float64)
+    N, KG, E = lut.shape
+    lut = np.concatenate([lut, np.zeros((N, -KG % 32, E))], axis=1)
+    C, cpg = lut.shape[1] // 8, max(group // 32, 1)
+    sums = np.abs(lut).max(2).reshape(N, C, 8).sum(2).astype(np.float32)
+    top = sums.copy()
+    for c in range(C):
+        same = [d for d in range(c // 4 * 4, c // 4 * 4 + 4) if d // cpg == c // cpg]
+        top[:, c] = sums[:, same].max(1)
+    with np.errstate(divide="ignore"):
+        factor = np.where(top > 0, np.float32(32700) / top, np.float32(0))
+    unit = (top / np.float32(32700)).astype(np.float64)
+    ints = np.rint(lut * np.repeat(factor.astype(np.float64), 8, axis=1)[:, :, None])
+    assert np.abs(np.abs(ints).max(2).reshape(N, C, 8).sum(2)).max() < 32768
+    return (ints * np.repeat(unit, 8, axis=1)[:, :, None])[:, :KG]
+
+
+def lut_mpgemm_fixed(act, q, bits, scales=None, zeros=None, group=0, weight_scale=1.0, zero_point=0.0):
+    """The LUT route with the tables of ``fixed_point_tables``; sums in fp64."""
+    q = np.asarray(q)
+    M, K = q.shape
+    s, z, G = _scales_and_zeros(M, K, scales, zeros, group, weight_scale, zero_point)
+    lut = fixed_point_tables(act, G)
+    Lsum = np.zeros((lut.shape[0], M, K // G), dtype=np.float64)
+    for i, plane in enumerate(orc.bit_planes(q, bits)):
+        Lsum += (2.0 ** i) * orc.lookup_sum(lut, orc.group_indices(plane, 4), G // 4).astype(np.float64)
+    return _finish(Lsum, orc.group_sums(act, G).astype(np.float64), s, z, bits)

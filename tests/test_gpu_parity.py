@@ -1196,6 +1196,32 @@ def test_large_calls_with_fixed_point_tables(T, torch, N, M, K, bits, group):
     assert_elementwise(got, ref, p)
 
 
+@pytest.mark.parametrize("N,M,K,bits,group", [(80, 4600, 4096, 4, 32), (130, 2700, 8224, 2, 32), (66, 4100, 8192, 3, 64),
+                                              (79, 6001, 7488, 3, 96), (128, 4096, 4096, 4, 128)])
+def test_fixed_point_units_stay_inside_quantisation_groups(T, torch, N, M, K, bits, group):
+    """Group scales that undo the size of the group's activations (up to 300 times from one group to another):
+    the tables of a large call have a unit of their own in each group, so that the error is what it is for
+    groups of one size, and the arithmetic is that of the rounding model (fp32 sums of K / 32 terms: 3e-6;
+    fp16 sums would differ from it by 3e-4)."""
+    from test_rounding_models import unequal_groups
+    from paper_2407_00088_amd.runner import from_problem
+    rng = np.random.default_rng(1610 + group)
+    act, q, s, z = unequal_groups(rng, N, M, K, bits, group, 300.0)
+    p = wl.Problem("unequal", 0, N, M, K, bits, group, q, s, z, act=act)
+    lin = from_problem(p, layout=L3)
+    A = torch.from_numpy(act).cuda()
+    two, one = lin.forward(A), lin.forward_one_call(A)
+    assert torch.equal(two, one)
+    got, ref = two.cpu().numpy(), oracle_fp(p)
+    err = orc.rel_frobenius(got, ref)
+    rows, cols = [0, 17, N - 1], np.r_[0:70, M - 70:M]
+    model = rm.lut_mpgemm_fixed(act[rows], q[cols], bits, s[cols], z[cols], group)
+    off = orc.rel_frobenius(got[np.ix_(rows, cols)], model)
+    print(f"unequal groups {N}x{M}x{K} w{bits} g{group}: {err:.2e}, from the model {off:.2e}", flush=True)
+    assert err <= 3.4e-4
+    assert off <= 3e-6
+
+
 def test_fixed_point_tables_leave_infinities_and_nans_alone(T, torch):
     """A 128-k block in which some table entry is not finite keeps its fp16 entries: rows with an infinity, a
     NaN, or activations whose sums overflow fp16 come out as in a small call of the same rows (which goes

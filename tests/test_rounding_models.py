@@ -99,3 +99,32 @@ def test_fp16_routes_keep_their_error_on_heavy_tailed_activations():
         e_tree = orc.rel_frobenius(rm.lut_mpgemm_fp16_tree(a, q, b, s, z, group=G), ref)
         e_narrow = orc.rel_frobenius(rm.lut_mpgemm_narrow(a, q, b, s, z, G), ref)
         assert e_tree < 5e-4 and e_narrow < 7e-4, (name, e_tree, e_narrow)
+
+
+# ------------------------------------------------ fixed-point tables of large calls ----
+
+def unequal_groups(rng, N, M, K, bits, group, ratio):
+    """Activations whose size changes from group to group by up to `ratio` and scales that undo it: every
+    group weighs the same in the result.  Returns (act, q, scales, zeros)."""
+    nq = K // group
+    size = ratio ** rng.uniform(-0.5, 0.5, size=nq)
+    act = (rng.standard_normal((N, K)) * np.repeat(size, group)).astype(np.float16)
+    s = (rng.uniform(0.01, 0.1, size=(M, nq)) / size).astype(np.float16)
+    z = rng.uniform(0, 2 ** bits - 1, size=(M, nq)).astype(np.float16)
+    return act, rng.integers(0, 1 << bits, size=(M, K), dtype=np.uint8), s, z
+
+
+def test_fixed_point_tables_err_less_than_fp16_sums():
+    """One unit per activation row and quantisation group (of at most 128 k): closer to the product than fp16
+    chunk sums for every group size, also with group sizes and scales that undo each other and with outlier
+    channels, which one unit for several groups would not be (2e-3 and more)."""
+    rng = np.random.default_rng(96)
+    M, K = 48, 2048
+    for bits, group in ((2, 32), (4, 32), (4, 64), (3, 128), (4, 512), (2, 2048)):
+        for ratio in (1.0, 30.0, 1000.0):
+            act, q, s, z = unequal_groups(rng, 4, M, K, bits, group, ratio)
+            act[2:] *= np.where(rng.random(K) < 0.002, 30, 1).astype(np.float16)
+            ref = orc.mpgemm_definition(act, q, s, z, group)
+            fixed = orc.rel_frobenius(rm.lut_mpgemm_fixed(act, q, bits, s, z, group), ref)
+            narrow = orc.rel_frobenius(rm.lut_mpgemm_narrow(act, q, bits, s, z, group), ref)
+            assert fixed < narrow and fixed < 4e-4, (bits, group, ratio, fixed, narrow)
