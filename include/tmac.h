@@ -63,7 +63,8 @@ typedef enum { TMAC_ACT_F16 = 0, TMAC_ACT_I8 = 1, TMAC_ACT_F16_TQ = 2 } tmac_act
  *                 entries up as 16-bit integers, rounded once to 2^-15 of the largest sum of
  *                 eight entries in each (activation row, quantisation group of at most 128 k), whose
  *                 sums are exact: closer to the product than sums in fp16, unless those are exact
- *                 (small whole numbers).  Entries that are not finite are looked up as they are.
+ *                 (small whole numbers).  Where a row's entries are not all finite, that row's
+ *                 fp16 entries are looked up; other rows' results do not change.
  *   TMAC_LUT_I16: entries are exact int16 sums of int8 activations (|T| <= 4*127); all
  *                 aggregation is int32 and the result is bit-exact.
  *   TMAC_LUT_I8Q: table quantisation (Section 3.3): entries of fp16 activations' tables rounded

@@ -232,7 +232,8 @@ struct RowsPlan {
 RowsPlan rows_plan(const tmac_wdesc* desc, int N);
 bool rows_builds_tables(const tmac_wdesc* desc, int N);
 // Returns a tmac_status value.  lut_dev NULL: tables built in the kernel from A_dev (where
-// rows_builds_tables(desc, N) holds, or, with fixed_from_act, rows_fixed_point(desc, N)).
+// rows_builds_tables(desc, N) holds).  fixed_from_act: fixed-point tables built from A_dev (where
+// rows_fixed_point(desc, N) holds); lut_dev is room of a LUT buffer's size.
 int launch_rows_gemm(const tmac_wdesc* desc, const void* packed_dev, const void* lut_dev, const void* A_dev,
                      int64_t lda, int lut_t, int N, const float* act_scale_dev, float weight_scale, void* out_dev,
                      int out_t, int64_t ldo, void* workspace_dev, size_t workspace_bytes, void* stream,

@@ -627,9 +627,10 @@ extern "C" tmac_status tmac_mpgemm_fused(const tmac_wdesc* desc, const void* pac
   }
   void* lut_dev = static_cast<char*>(workspace_dev) + ws;
   if (act == TMAC_ACT_F16 && desc->layout == TMAC_LAYOUT_R64K32 && rows_fixed_point(desc, N)) {
-    // fixed-point tables and group sums straight from the activations (the LUT buffer stays unused)
+    // fixed-point tables and group sums straight from the activations (the LUT buffer holds only tables that
+    // are not finite)
     if (lda % 4 != 0) return TMAC_EINVAL;
-    return static_cast<tmac_status>(launch_rows_gemm(desc, packed_dev, nullptr, A_dev, lda, (int)lt, N, act_scale_dev,
+    return static_cast<tmac_status>(launch_rows_gemm(desc, packed_dev, lut_dev, A_dev, lda, (int)lt, N, act_scale_dev,
                                                       weight_scale, out_dev, (int)out, ldo, workspace_dev, ws, stream, true));
   }
   const tmac_status st = tmac_precompute_lut(A_dev, act, N, desc->K, lda, desc->g, desc->group, lt, lut_dev, lutb, stream);

@@ -101,9 +101,9 @@ struct RowsParams {
   float pw[4];             // plane weights 1, 2, 4, 8: kernel arguments, so that plane 0 also takes the
                            // fused convert-multiply-add (a literal 1.0 would be folded into cvt + add)
   int out_t;
-  int bits;
-  const float* fix_scale;  // fixed-point tables, else null: [set of 16 rows][chunk >> fix_shift][16] value of one unit (negative: fp16 entries)
+  const float* fix_scale;  // fixed-point tables: [set of 16 rows][chunk >> fix_shift][16] value of one unit (-0: entries not finite)
   int fix_shift;           // 2: one unit per 128-k block, 0: one per chunk (see rows_fix_kernel)
+  uint16_t* raw;           // ... and the fp16 tables, as in a LUT buffer, where a unit is -0
 };
 
 // 32-k chunks of tables one LDS slice holds, for LUT group size g and nt activation rows
@@ -848,36 +848,6 @@ __global__ __launch_bounds__(64 * ROWS_WAVES) void mpgemm_rows8_kernel(const Row
   }
 }
 
-// What the blocks that kept their fp16 entries (see rows_fix_kernel) contribute to output (n, m), looked
-// up from memory with the additions of the general kernel.
-__device__ __forceinline__ float rows_raw_blocks(const RowsParams& p, const float* unit, int n, int m) {
-  float sum = 0.f;
-  const int tile = m >> 6, r = m & 63;
-#pragma unroll 1
-  for (int c = 0; c < p.n_chunks; ++c) {
-    if (!(unit[(size_t)(c >> p.fix_shift) * 16] < 0.f)) continue;
-    float hs = 1.f;
-    if (p.grouped) {
-      if (c / p.cpg >= p.nq) break;  // chunks in the K padding belong to no group
-      hs = 0.5f * __half2float(__ushort_as_half((uint16_t)(p.sz[((size_t)tile * p.nq + c / p.cpg) * 64 + r] & 0xffffu)));
-    }
-#pragma unroll 1
-    for (int b = 0; b < p.bits; ++b) {
-      const uint32_t x = p.idx[(((size_t)tile * p.n_chunks + c) * 64 + r) * p.bits + b];
-      rh2v q[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const size_t ent = ((size_t)(n >> 3) * p.KG + c * 8 + j) * 16 + ((x >> (4 * j)) & 15u);
-        q[j].x = __builtin_bit_cast(_Float16, p.tables[ent * 8 + (n & 7)]);
-        q[j].y = (_Float16)0.f;
-      }
-      tree_sum(q);
-      sum = fmaf((float)q[0].x, hs * p.pw[b], sum);
-    }
-  }
-  return sum;
-}
-
 // Adds the partial sums [nz][N][Mp] of the K slices in slice order and finishes: VEC outputs per
 // thread.  Bound by memory traffic.  Everything the thread needs is requested before the first wait
 // (scales and zeros, the activation scale, the row sum or its per-slice parts, the partial sums of a
@@ -891,19 +861,6 @@ __global__ __launch_bounds__(256) void rows_sum_kernel(const RowsParams p, int n
   const uint32_t id = blockIdx.x * 256u + threadIdx.x;   // (launch_rows_sum checks that the ids fit)
   const uint32_t per_row = (uint32_t)p.Mp / VEC;
   const int n = (int)(id / per_row), m0 = (int)(id % per_row) * VEC;
-  // fixed-point tables: does any block of the sets of rows this wavefront works for keep its fp16 entries?
-  // Usually none does, which takes one load per lane (all lanes take part: before any of them returns)
-  bool raw = false;
-  if constexpr (!IS_INT) {
-    if (p.fix_scale) {
-      const int nblk = p.n_chunks >> p.fix_shift;
-      const int first = __builtin_amdgcn_readfirstlane(min(n, p.N - 1)) >> 4;
-      const int last = __builtin_amdgcn_readlane(min(n, p.N - 1), 63) >> 4;
-      bool some = false;
-      for (int b = first * nblk + (int)(threadIdx.x & 63); b < (last + 1) * nblk; b += 64) some |= p.fix_scale[(size_t)b * 16] < 0.f;
-      raw = __any(some);
-    }
-  }
   if (n >= p.N || m0 >= p.M) return;
   const bool raw_int = IS_INT && !p.grouped;
   const float* src = p.ws_part + (size_t)n * p.Mp + m0;
@@ -957,13 +914,6 @@ __global__ __launch_bounds__(256) void rows_sum_kernel(const RowsParams p, int n
     if (VEC == 1 && left > 8) { round(sl0, std::integral_constant<int, 16>()); sl0 += 16; }
     else if (left > 4) { round(sl0, std::integral_constant<int, 8>()); sl0 += 8; }
     else { round(sl0, std::integral_constant<int, 4>()); sl0 += 4; }
-  }
-  if constexpr (!IS_INT) {
-    if (raw) {
-      const float* const unit = p.fix_scale + (size_t)(n >> 4) * (p.n_chunks >> p.fix_shift) * 16;
-#pragma unroll
-      for (int i = 0; i < VEC; ++i) sf[i] += rows_raw_blocks(p, unit, n, m0 + i);
-    }
   }
   uint32_t res[VEC];
 #pragma unroll
@@ -1033,9 +983,11 @@ static hipError_t launch_rows_sum(const RowsParams& p, int nz, hipStream_t st) {
 // In memory and LDS an entry pair is the number (hi + B) * 65536 + lo + B modulo 2^32 (B =
 // ROWS_FIX_BIAS): additions of whole dwords are exact, and the sum of a chunk's eight pairs has two
 // clean halves, sum + 32768.
-// Chunks of one unit in which some row's entries are not finite keep their fp16 entries (fix_scale negative
-// for the set's 16 rows); the look-up kernel takes nothing from them, and rows_sum_kernel looks them up from
-// memory with fp16 additions, so that infinities and NaNs come out as they do in the general kernel.
+// Where an activation row's entries are not all finite, the chunks of that unit hold zeros for this row and
+// the unit is -0; mpgemm_fix_kernel adds what their fp16 entries give, with fp16 additions, so that
+// infinities and NaNs come out as they do in the general kernel (rows_add_raw).  Other rows do not notice.
+// The fp16 entries are read from the LUT buffer; a call that builds the integers from the activations writes
+// those blocks into the buffer's place in its workspace.
 constexpr int ROWS_FIX_BIAS = 4096;
 constexpr float ROWS_FIX_MAX = 32700.f;  // + 8 roundings of half a unit stays below 32767
 
@@ -1110,25 +1062,30 @@ __global__ __launch_bounds__(256) void rows_fix_kernel(const RowsParams p, uint3
   }
   __syncthreads();
   float f[2];
+  bool any_bad = false;  // in any chunk of the block
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     float b = 0.f;
     bool bad = false;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-      const float sum = c >= u0 && c < u1 ? smax[c][2 * u + h] : 0.f;
-      bad |= !(sum <= 1e30f);
-      b = fmaxf(b, sum);
+      const float sum = smax[c][2 * u + h];
+      const bool fin = sum <= 1e30f;
+      any_bad |= !fin;
+      if (c >= u0 && c < u1) {
+        bad |= !fin;
+        b = fmaxf(b, sum);
+      }
     }
     f[h] = bad ? -1.f : b;
   }
-  const bool raw = __any(f[0] < 0.f || f[1] < 0.f);  // (every wavefront sees all 16 rows)
   if ((threadIdx.x & 63) < 8 && (wave == 0 || p.fix_shift == 0)) {
 #pragma unroll
     for (int h = 0; h < 2; ++h)
-      scale[((size_t)set * (p.n_chunks >> p.fix_shift) + ((blk * 4 + wave) >> p.fix_shift)) * 16 + 2 * u + h] = raw ? -1.f : f[h] / ROWS_FIX_MAX;
+      scale[((size_t)set * (p.n_chunks >> p.fix_shift) + ((blk * 4 + wave) >> p.fix_shift)) * 16 + 2 * u + h] = f[h] < 0.f ? -0.f : f[h] / ROWS_FIX_MAX;
   }
   const float f0 = f[0] > 0.f ? ROWS_FIX_MAX / f[0] : 0.f, f1 = f[1] > 0.f ? ROWS_FIX_MAX / f[1] : 0.f;
+  const uint32_t keep = (f[0] < 0.f ? 0u : 0xffffu) | (f[1] < 0.f ? 0u : 0xffff0000u);
   uint32_t* const dst = stage + (u >> 2) * OD + tb * TD + (u & 3);
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
@@ -1136,23 +1093,32 @@ __global__ __launch_bounds__(256) void rows_fix_kernel(const RowsParams p, uint3
     const rh2v x = __builtin_bit_cast(rh2v, v[e]);
     const uint32_t i0 = __float_as_uint(fmaf((float)x.x, f0, 12582912.f)), i1 = __float_as_uint(fmaf((float)x.y, f1, 12582912.f));
     // two signed halves side by side -> hi * 65536 + lo, then the bias of both
-    uint32_t d = (__builtin_amdgcn_perm(i1, i0, 0x05040100u) ^ 0x8000u) + ((uint32_t)ROWS_FIX_BIAS * 0x10001u - 0x8000u);
-    uint32_t neg = 2u * ROWS_FIX_BIAS * 0x10001u - d;
-    if (raw) {
-      d = v[e];
-      neg = v[e] ^ 0x80008000u;
-    }
+    const uint32_t d = ((__builtin_amdgcn_perm(i1, i0, 0x05040100u) & keep) ^ 0x8000u) + ((uint32_t)ROWS_FIX_BIAS * 0x10001u - 0x8000u);
     dst[e * 4] = d;
-    dst[(15 - e) * 4] = neg;
+    dst[(15 - e) * 4] = 2u * ROWS_FIX_BIAS * 0x10001u - d;
   }
-  __syncthreads();
+  auto store = [&](uint32_t* to) {
+    __syncthreads();
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int o = i >> 1, q = (i & 1) * 256 + (int)threadIdx.x;  // 16-byte piece of the half's 32 tables
-    const int t8 = set * 2 + o;
-    if (t8 * 8 < p.N)
-      *reinterpret_cast<ru32x4v*>(fix + ((size_t)t8 * p.KG + blk * 32) * 64 + q * 4) =
-          *reinterpret_cast<const ru32x4v*>(stage + o * OD + (q >> 4) * TD + (q & 15) * 4);
+    for (int i = 0; i < 4; ++i) {
+      const int o = i >> 1, q = (i & 1) * 256 + (int)threadIdx.x;  // 16-byte piece of the half's 32 tables
+      const int t8 = set * 2 + o;
+      if (t8 * 8 < p.N)
+        *reinterpret_cast<ru32x4v*>(to + ((size_t)t8 * p.KG + blk * 32) * 64 + q * 4) =
+            *reinterpret_cast<const ru32x4v*>(stage + o * OD + (q >> 4) * TD + (q & 15) * 4);
+    }
+  };
+  store(fix);
+  if constexpr (FROM_ACT) {
+    if (__any(any_bad)) {  // (the same in all wavefronts: each sees the sums of every row and chunk)
+      __syncthreads();
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        dst[e * 4] = v[e];
+        dst[(15 - e) * 4] = v[e] ^ 0x80008000u;
+      }
+      store(reinterpret_cast<uint32_t*>(p.raw));
+    }
   }
 }
 
@@ -1189,6 +1155,70 @@ __device__ __forceinline__ void rows_chunk_fix(const uint32_t (&x)[BITS], uint32
   if constexpr (BITS > 1) plane(std::integral_constant<int, 1>());
   if constexpr (BITS > 2) plane(std::integral_constant<int, 2>());
   if constexpr (BITS > 3) plane(std::integral_constant<int, 3>());
+}
+
+// What the chunks whose unit is -0 (see above) contribute to activation rows n0 .. n0 + 15 of the lane's
+// weight row, added to its own partial sums: the fp16 entries of eight rows at a time, with the additions of
+// the general kernel.  Only a wavefront that met such a unit comes here.  A row is done once its sum is NaN
+// in all lanes, which a NaN anywhere takes one chunk for and infinities usually not many more, since the
+// planes' signs differ.
+// 256 rows x 5120 x 5120 at 4 bit: 142 us with finite rows, 143 with one NaN, 151 with one row of NaNs, 168 with
+// all rows (fp16 tables throughout: 165); 511 x 13824 x 5120 at 2 bit: 366, 370, 408, 421 (454).
+template <int BITS>
+__device__ __forceinline__ void rows_add_raw(const RowsParams& p, const float* unit, const uint32_t* idx, const uint32_t* sz, int n0,
+                                             int cz0, int cz1, float* part, bool live) {
+  const int lane = threadIdx.x & 63, shift = p.fix_shift;
+  const int units = (cz1 - cz0) >> shift;  // (a K slice is a number of 128-k blocks)
+  unit += (size_t)(cz0 >> shift) * 16;
+#pragma unroll 1
+  for (int o = 0; o < 2 && n0 + 8 * o < p.N; ++o) {
+    const uint16_t* const tables = p.raw + (size_t)((n0 >> 3) + o) * p.KG * 128;
+    uint32_t open = (1u << min(p.N - n0 - 8 * o, 8)) - 1u, some = 0;  // rows not NaN everywhere yet, rows with such units
+    float sum[8];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) sum[r] = 0.f;
+#pragma unroll 1
+    for (int u0 = 0; u0 < units && open; u0 += 8) {
+      const int u = u0 + (lane >> 3);
+      uint64_t marks = __ballot(u < units && __float_as_int(unit[(size_t)min(u, units - 1) * 16 + 8 * o + (lane & 7)]) < 0);
+#pragma unroll 1
+      for (int c = cz0 + (u0 << shift), left = 1 << shift; marks; ++c) {
+        const uint32_t rows = (uint32_t)marks & open;
+        if (p.grouped && c / p.cpg >= p.nq) break;  // chunks in the K padding belong to no group
+        if (rows) {
+          some |= rows;
+          const float hs = p.grouped ? 0.5f * __half2float(__ushort_as_half((uint16_t)(sz[(size_t)(c / p.cpg) * 64] & 0xffffu))) : 1.f;
+#pragma unroll
+          for (int b = 0; b < BITS; ++b) {
+            const uint32_t x = idx[(size_t)c * 64 * BITS + b];
+            ru32x4v e[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+              e[j] = *reinterpret_cast<const ru32x4v*>(tables + ((size_t)(c * 8 + j) * 16 + ((x >> (4 * j)) & 15u)) * 8);
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+              rh2v q[8];
+#pragma unroll
+              for (int j = 0; j < 8; ++j) q[j] = __builtin_bit_cast(rh2v, (uint32_t)e[j][d]);
+              tree_sum(q);
+              if (rows >> (2 * d) & 1u) sum[2 * d] = fmaf((float)q[0].x, hs * p.pw[b], sum[2 * d]);
+              if (rows >> (2 * d + 1) & 1u) sum[2 * d + 1] = fmaf((float)q[0].y, hs * p.pw[b], sum[2 * d + 1]);
+            }
+          }
+#pragma unroll
+          for (int r = 0; r < 8; ++r)
+            if (__all(sum[r] != sum[r] || !live)) open &= ~(1u << r);
+        }
+        if (--left == 0) {
+          left = 1 << shift;
+          marks >>= 8;
+        }
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+      if (some >> r & 1u) part[(size_t)(8 * o + r) * p.Mp] += sum[r];
+  }
 }
 
 // mpgemm_rows_kernel for fixed-point tables: two sets of eight activation rows per workgroup, tables
@@ -1237,7 +1267,8 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_fix_kernel(const Ro
   int gq = p.grouped ? cz0 / p.cpg : 0, cg = 0;  // current quantisation group, chunks done in it (wave-uniform)
   float hs = 1.f;                                // half the group's scale (1: one scale per row or tensor, applied at the end)
   uint32_t szv_next = p.grouped ? my_sz[(size_t)min(gq, p.nq - 1) * 64] : 0u;
-  float unit[16];  // units of the sums in progress (wave-uniform); 0 where they kept their fp16 entries
+  float unit[16];  // units of the sums in progress (wave-uniform); -0 where entries are not finite
+  int flag = 0;    // negative once there was such a unit
   uint32_t xn[BITS];
   load_idx(cz0, xn);
 
@@ -1280,7 +1311,7 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_fix_kernel(const Ro
       }
       if (first) {  // sums start at minus the biases of the chunks they will hold
 #pragma unroll
-        for (int t = 0; t < 16; ++t) unit[t] = __int_as_float(max(__float_as_int(fix_scale[(c >> shift) * 16 + t]), 0));
+        for (int t = 0; t < 16; ++t) flag |= __float_as_int(unit[t] = fix_scale[(c >> shift) * 16 + t]);
         int chunks = 4 - (c & 3);
         if (p.grouped && gq < p.nq) chunks = min(chunks, p.cpg - cg);
         const int L0 = -chunks * (32768 * ((1 << BITS) - 1));
@@ -1306,12 +1337,16 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_fix_kernel(const Ro
 #pragma unroll
   for (int t = 0; t < 16; ++t)
     if (n0 + t < p.N) p.ws_part[((size_t)blockIdx.z * p.N + n0 + t) * p.Mp + (size_t)m] = acc[t];
+  if (flag < 0)
+    rows_add_raw<BITS>(p, p.fix_scale + (size_t)blockIdx.x * (p.n_chunks >> shift) * 16, my_idx, my_sz, n0,
+                       cz0, cz1, p.ws_part + ((size_t)blockIdx.z * p.N + n0) * p.Mp + m, m < p.M);
 }
 
 // Tables to fixed point, look-ups, slice sums.
 static hipError_t launch_rows_fix(const RowsParams& p, const RowsPlan& pl, int bits, bool from_act, int Geff, int lut_nt,
                                   uint32_t* fix, float* scale, float* sums, hipStream_t st) {
   RowsParams local = p;
+  local.raw = const_cast<uint16_t*>(p.tables);  // (written only where the tables are built here)
   int n_fix = pl.fix_tiles * (p.KG / 32);
   const int64_t blocks = n_fix + (from_act ? ((int64_t)p.N * p.nq + 3) / 4 : 0);
   if (blocks > 0x7fffffff) return hipErrorInvalidValue;
@@ -1477,15 +1512,15 @@ bool rows_builds_tables(const tmac_wdesc* desc, int N) {
 }
 
 // lut_dev: buffer of tmac_precompute_lut, or NULL with A_dev / lda given (only where
-// rows_builds_tables says so).
+// rows_builds_tables says so), or with fixed_from_act room for such a buffer, and A_dev / lda.
 int launch_rows_gemm(const tmac_wdesc* desc, const void* packed_dev, const void* lut_dev, const void* A_dev,
                      int64_t lda, int lut_t, int N, const float* act_scale_dev, float weight_scale, void* out_dev,
                      int out_t, int64_t ldo, void* workspace_dev, size_t workspace_bytes, void* stream, bool fixed_from_act) {
   if (lut_t != TMAC_LUT_F16 && lut_t != TMAC_LUT_I16) return TMAC_EUNSUPPORTED;
-  const bool from_act = (lut_dev == nullptr && fixed_from_act);  // fixed-point tables from the activations
-  const bool fused = (lut_dev == nullptr && !from_act);
+  const bool from_act = fixed_from_act;  // fixed-point tables from the activations; lut_dev: room for a LUT buffer
+  const bool fused = (lut_dev == nullptr);
   if (fused && (!A_dev || !rows_builds_tables(desc, N))) return TMAC_EUNSUPPORTED;
-  if (from_act && (!A_dev || lut_t != TMAC_LUT_F16 || !rows_fixed_point(desc, N))) return TMAC_EUNSUPPORTED;
+  if (from_act && (!lut_dev || !A_dev || lut_t != TMAC_LUT_F16 || !rows_fixed_point(desc, N))) return TMAC_EUNSUPPORTED;
   const Geometry ge = geometry(desc);
   LutGeom lg;
   if (!lut_geom(N, desc->K, desc->g, desc->group, lut_t, &lg)) return TMAC_EINVAL;
@@ -1542,7 +1577,7 @@ int launch_rows_gemm(const tmac_wdesc* desc, const void* packed_dev, const void*
   hipError_t e;
   p.fix_scale = nullptr;
   p.fix_shift = pl.fix_shift;
-  p.bits = desc->bits;
+  p.raw = nullptr;
   if (pl.fix && !is_int && !fused) {
     char* const tab = static_cast<char*>(workspace_dev) + pl.fix_part_bytes;
     e = launch_rows_fix(p, pl, desc->bits, from_act, lg.Geff, lg.NT, reinterpret_cast<uint32_t*>(tab),

@@ -1244,6 +1244,46 @@ def test_fixed_point_tables_leave_infinities_and_nans_alone(T, torch):
         assert orc.rel_frobenius(got[rest], ref) <= 4e-4
 
 
+@pytest.mark.parametrize("bits,K,group", [(2, 8192, 128), (3, 8160, 96), (4, 8192, 512), (4, 8224, 32), (2, 8200, -1),
+                                          (3, 8192, 0)])
+def test_fixed_point_rows_do_not_depend_on_rows_that_are_not_finite(T, torch, bits, K, group):
+    """Infinities, NaNs and sums beyond fp16 in some rows of a large call: the other rows keep their results bit
+    for bit, and the rows themselves come out as in a small call (general kernels, fp16 tables): infinities and
+    NaNs in the same places, finite results to the fp16 sums' rounding; groups of 1, 3, 4 and 16 chunks and none."""
+    from paper_2407_00088_amd.runner import from_problem
+    rng = np.random.default_rng(1650 + bits + K)
+    N, M = 130, 2700
+    if group == 0:
+        p = wl.Problem("nonfinite", 0, N, M, K, bits, 0, wl.uniform_codes(rng, M, K, bits), None, None, weight_scale=0.05,
+                       zero_point=3.0, act=wl.gaussian_act(rng, N, K))
+    else:
+        p = wl.make_grouped(0, 1650 + bits, N, M, K, bits, K if group < 0 else group, name="nonfinite")
+    p.q[7], p.q[9] = 0, (1 << bits) - 1                       # rows where infinities of one sign stay infinite
+    lin = from_problem(p, layout=L3)
+    A = torch.from_numpy(p.act).cuda()
+    clean = lin.forward(A)
+    B_ = A.clone()
+    B_[3, 100], B_[5, K - 1], B_[20, 4000], B_[129, 8] = float("inf"), -float("inf"), float("nan"), float("inf")
+    B_[40, 512:516], B_[41, 5000:5004] = 30000.0, -30000.0   # a sum of four beyond fp16 in one table
+    B_[64] = float("nan")
+    B_[77, : K // 2] = float("inf")
+    odd = [3, 5, 20, 40, 41, 64, 77, 129]
+    rest = [n for n in range(N) if n not in odd]
+    small = lin.forward(B_[odd].contiguous())
+    two, one = lin.forward(B_), lin.forward_one_call(B_)
+    for got in (two, one):
+        assert torch.equal(got[rest], clean[rest])
+        for kind in (torch.isnan, torch.isposinf, torch.isneginf):
+            assert torch.equal(kind(got[odd]), kind(small)) and bool(kind(small).any())
+        for i, n in enumerate(odd):
+            fin = torch.isfinite(small[i])
+            if bool(fin.any()):
+                a, b = got[n][fin].double(), small[i][fin].double()
+                # (two roundings of the same product, 2.5e-4 and 4e-4 off it)
+                assert float((a - b).norm() / b.norm()) <= 1e-3, n
+    assert torch.equal(torch.nan_to_num(two, nan=1e30), torch.nan_to_num(one, nan=1e30))
+
+
 def test_large_call_takes_two_row_tiles_per_workgroup_by_default(T, torch):
     """From about 8000 wavefronts on (here 8192 x 8192: 1024 row tiles x 8 waves) the register-table
     kernel serves 16 rows per workgroup unless told otherwise: the default call, the call with 8 rows
