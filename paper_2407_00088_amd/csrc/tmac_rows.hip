@@ -852,10 +852,12 @@ __global__ __launch_bounds__(64 * ROWS_WAVES) void mpgemm_rows8_kernel(const Row
 // thread.  Bound by memory traffic.  Everything the thread needs is requested before the first wait
 // (scales and zeros, the activation scale, the row sum or its per-slice parts, the partial sums of a
 // round of slices), so that a call pays one round trip to memory, not one per operand.  Many outputs go
-// four to a thread (one 16-byte load per slice and one store) in rounds of eight or four slices: 511 x
-// 13824 outputs from three slices 17.5 us (113 MB: 6.5 TB/s) against 50.3 with one output per thread
-// and sixteen clamped requests whatever the number of slices, 256 x 5120 from ten 10.2 against 12.7,
-// 128 x 8640 from thirteen 11.6 against 11.1.  Few outputs go one to a thread in rounds of sixteen.
+// four to a thread (one 16-byte load per slice and one store) in rounds of eight or four slices, few one
+// to a thread in rounds of sixteen.  Four against one, us: 511 x 8640 outputs from two slices 10.2 against
+// 16.3, from four 14.4 against 17.9; 256 x 3200 from nine to seventeen 7.4 to 10.8 against 7.5 to 11.2;
+// 64 x 8640 from thirteen 7.0 against 8.5; 100 x 5504 from 22 9.6 against 10.3.  The number of slices decides
+// nothing: of sixteen shapes with two to 34 one lost, 128 x 8640 from thirteen (11.8 against 11.2, also
+// with the last five taken as four and one).  96 x 3200, below the line, is even at 8.9.
 template <bool IS_INT, int VEC>
 __global__ __launch_bounds__(256) void rows_sum_kernel(const RowsParams p, int nz) {
   const uint32_t id = blockIdx.x * 256u + threadIdx.x;   // (launch_rows_sum checks that the ids fit)
