@@ -1002,7 +1002,7 @@ constexpr float ROWS_FIX_MAX = 32700.f;  // + 8 roundings of half a unit stays b
 // tables written at 511 rows of K = 5120, 9.5 us (one thread per entry of a table: 21).
 template <bool FROM_ACT>
 __global__ __launch_bounds__(256) void rows_fix_kernel(const RowsParams p, uint32_t* __restrict__ fix, float* __restrict__ scale,
-                                                       float* __restrict__ sums, int Geff, int lut_nt, int n_fix) {
+                                                       float* __restrict__ sums, int Geff, int n_fix) {
   if constexpr (FROM_ACT) {
     if ((int)blockIdx.x >= n_fix) {
       group_sums_wave<false, true>(p.A, p.N, p.lda, sums, Geff, p.nq, ((int)blockIdx.x - n_fix) * 4 + (threadIdx.x >> 6));
@@ -1034,10 +1034,10 @@ __global__ __launch_bounds__(256) void rows_fix_kernel(const RowsParams p, uint3
       v[2 * d + 1] = __builtin_amdgcn_perm(t1[d], t0[d], 0x07060302u);
     }
   } else {
-    const int tile = n / lut_nt;                   // the buffer's n tiles are eight or four rows wide
-    const uint16_t* const at = p.tables + ((size_t)tile * p.KG + kg) * 16 * lut_nt + n % lut_nt;
+    const int tile = n >> 3;                       // (n tiles of eight rows: rows_plan)
+    const uint16_t* const at = p.tables + ((size_t)tile * p.KG + kg) * 128 + (n & 7);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = tile * lut_nt < p.N ? *reinterpret_cast<const uint32_t*>(at + e * lut_nt) : 0u;
+    for (int e = 0; e < 8; ++e) v[e] = tile * 8 < p.N ? *reinterpret_cast<const uint32_t*>(at + e * 8) : 0u;
     const int r = set * 16 + (int)threadIdx.x;
     if (threadIdx.x < 16 && r < p.N)
       for (int gq = blk; gq < p.nq; gq += nblk) sums[((size_t)set * p.nq + gq) * 16 + threadIdx.x] = static_cast<const float*>(p.S)[(size_t)r * p.nq + gq];
@@ -1345,14 +1345,14 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_fix_kernel(const Ro
 }
 
 // Tables to fixed point, look-ups, slice sums.
-static hipError_t launch_rows_fix(const RowsParams& p, const RowsPlan& pl, int bits, bool from_act, int Geff, int lut_nt,
+static hipError_t launch_rows_fix(const RowsParams& p, const RowsPlan& pl, int bits, bool from_act, int Geff,
                                   uint32_t* fix, float* scale, float* sums, hipStream_t st) {
   RowsParams local = p;
   local.raw = const_cast<uint16_t*>(p.tables);  // (written only where the tables are built here)
   int n_fix = pl.fix_tiles * (p.KG / 32);
   const int64_t blocks = n_fix + (from_act ? ((int64_t)p.N * p.nq + 3) / 4 : 0);
   if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-  void* args[] = {&local, &fix, &scale, &sums, &Geff, &lut_nt, &n_fix};
+  void* args[] = {&local, &fix, &scale, &sums, &Geff, &n_fix};
   hipError_t e = hipLaunchKernel(from_act ? reinterpret_cast<const void*>(rows_fix_kernel<true>)
                                           : reinterpret_cast<const void*>(rows_fix_kernel<false>),
                                  dim3((unsigned)blocks), dim3(256), args, 0, st);
@@ -1468,7 +1468,7 @@ static RowsPlan rows_plan_plain(const tmac_wdesc* desc, int N) {
 RowsPlan rows_plan(const tmac_wdesc* desc, int N) {
   RowsPlan pl = rows_plan_plain(desc, N);
   const size_t room = pl.part_bytes + pl.ctr_bytes + pl.srow_bytes;
-  if (desc->g != 4 || desc->bits < 2 || N < ROWS_FIX_MIN_N || room <= (size_t)TMAC_NOALLOC_MAX_WORKSPACE) return pl;
+  if (pl.nt != ROWS_NT_WIDE || desc->g != 4 || desc->bits < 2 || N < ROWS_FIX_MIN_N || room <= (size_t)TMAC_NOALLOC_MAX_WORKSPACE) return pl;
   const Geometry ge = geometry(desc);
   if ((double)N * ge.Mp * (ge.Kp / 4) * desc->bits < (pl.eight ? 1.5e9 : 1.1e9)) return pl;
   const bool one_group = (desc->group == 0 || desc->group == desc->K);
@@ -1582,7 +1582,7 @@ int launch_rows_gemm(const tmac_wdesc* desc, const void* packed_dev, const void*
   p.raw = nullptr;
   if (pl.fix && !is_int && !fused) {
     char* const tab = static_cast<char*>(workspace_dev) + pl.fix_part_bytes;
-    e = launch_rows_fix(p, pl, desc->bits, from_act, lg.Geff, lg.NT, reinterpret_cast<uint32_t*>(tab),
+    e = launch_rows_fix(p, pl, desc->bits, from_act, lg.Geff, reinterpret_cast<uint32_t*>(tab),
                         reinterpret_cast<float*>(tab + pl.fix_tab_bytes),
                         reinterpret_cast<float*>(tab + pl.fix_tab_bytes + pl.fix_scale_bytes), st);
   } else if (fused) e = is_int ? launch_rows8_nt<true, true>(p, pl.nt, desc->bits, st) : launch_rows8_nt<false, true>(p, pl.nt, desc->bits, st);
