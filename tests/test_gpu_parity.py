@@ -1244,6 +1244,44 @@ def test_fixed_point_tables_leave_infinities_and_nans_alone(T, torch):
         assert orc.rel_frobenius(got[rest], ref) <= 4e-4
 
 
+@pytest.mark.parametrize("N,M,K,bits,group", [(359, 8336, 384, 4, 128), (401, 7947, 320, 4, 64), (399, 8024, 320, 4, -1),
+                                              (72, 5201, 4096, 4, 128), (256, 2700, 4096, 2, 0)])
+def test_fixed_point_one_slice_and_output_forms(T, torch, N, M, K, bits, group):
+    """Fixed-point tables with one K slice (the first three shapes: one set of partial sums still goes through
+    the workspace) and with several: the arithmetic of the rounding model (which says that this route was
+    taken: fp16 sums are 3e-4 off it), fp16 outputs, an activation scale, and rows wider than M."""
+    from paper_2407_00088_amd.runner import from_problem
+    rng = np.random.default_rng(1700 + N)
+    if group == 0:
+        p = wl.Problem("forms", 0, N, M, K, bits, 0, wl.uniform_codes(rng, M, K, bits), None, None, weight_scale=0.05,
+                       zero_point=1.5, act=wl.gaussian_act(rng, N, K))
+    else:
+        p = wl.make_grouped(0, 1700 + N, N, M, K, bits, K if group < 0 else group, name="forms")
+    lin = from_problem(p, layout=L3)
+    A = torch.from_numpy(p.act).cuda()
+    plain = lin.forward(A)
+    rows, cols = [0, 15, 16, N - 1], np.r_[0:70, M - 70:M]
+    sub = lambda x: None if x is None else x[cols]
+    model = rm.lut_mpgemm_fixed(p.act[rows], p.q[cols], bits, sub(p.scales), sub(p.zeros), p.group, p.weight_scale, p.zero_point)
+    off = orc.rel_frobenius(plain.cpu().numpy()[np.ix_(rows, cols)], model)
+    print(f"forms {N}x{M}x{K} w{bits} g{group}: from the model {off:.2e}", flush=True)
+    assert off <= 3e-6                                         # fp32 sums of at most K / 32 terms
+    assert torch.equal(lin.forward(A, out_t=T.TMAC_OUT_F16), plain.half())
+    assert torch.equal(lin.forward_one_call(A, out_t=T.TMAC_OUT_F16), plain.half())
+    s_a = torch.rand(N, device="cuda") + 0.5
+    assert torch.equal(lin.forward(A, act_scale=s_a), plain * s_a[:, None])
+    assert torch.equal(lin.forward_one_call(A, act_scale=s_a), plain * s_a[:, None])
+    lin.precompute(A)
+    for extra in (1, 4):
+        flat = torch.full((N, M + extra), 77.0, device="cuda")
+        lin.mpgemm(N, flat[:, :M], T.TMAC_OUT_F32)
+        assert torch.equal(flat[:, :M], plain) and bool((flat[:, M:] == 77).all())
+    wide = torch.zeros((N, K + 4), dtype=torch.float16, device="cuda")   # activations with a leading dimension
+    wide[:, :K] = A
+    wide[:, K:] = float("nan")
+    assert torch.equal(lin.forward_one_call(wide[:, :K]), plain)
+
+
 @pytest.mark.parametrize("bits,K,group", [(2, 8192, 128), (3, 8160, 96), (4, 8192, 512), (4, 8224, 32), (2, 8200, -1),
                                           (3, 8192, 0)])
 def test_fixed_point_rows_do_not_depend_on_rows_that_are_not_finite(T, torch, bits, K, group):
