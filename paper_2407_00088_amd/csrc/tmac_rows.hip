@@ -68,6 +68,7 @@ constexpr int ROWS_TARGET_WGS = TMAC_ROWS_TARGET_WGS;  // K is split until a cal
 constexpr int ROWS_LDS = 32768;     // bytes of tables per LDS slice: 1024 k for 4 activation rows, 512 k for 8
 constexpr int ROWS_FIX_TARGET_WGS = 2048;  // eight workgroups per CU
 constexpr int ROWS_FIX_LEAST_WGS = 640;    // fewer leave the chip idle
+constexpr int ROWS_FIX_SPLIT = 16;         // chunks: a longer K slice is split even if the workspace grows (rows_plan)
 constexpr int ROWS_FIX_MIN_N = 64;  // activation rows from which tables are turned into fixed-point numbers (rows_plan)
 constexpr int ROWS_NT_WIDE = 8;     // activation rows per workgroup when there are enough of them
 constexpr int ROWS_NT_NARROW = 4;   // ... and otherwise
@@ -1453,18 +1454,26 @@ static RowsPlan rows_plan_plain(const tmac_wdesc* desc, int N) {
   return one;
 }
 
-// Fixed-point tables (fp16 tables only) serve the calls whose partial sums would not fit the library's
-// own array: those are the large ones, and tmac_mpgemm_noalloc, whose results are tmac_mpgemm's bit for
-// bit, refuses exactly these.  K is split into fewer slices, and the tables take the room of the others'
-// partial sums (a call where that leaves no slice keeps fp16 tables); only the units of groups below 128 k
-// may add to the workspace's size.
+// Fixed-point tables (fp16 tables only) serve calls whose partial sums would not fit the library's own
+// array: tmac_mpgemm_noalloc, whose results are tmac_mpgemm's bit for bit, refuses exactly these.  (Calls
+// with so many workgroups that the plain plan leaves K whole have no partial sums and keep fp16 tables, as do
+// calls whose tables would not fit into the partial sums' room beside one slice's and those that would fill
+// less than two thirds of the chip there: K long against M, where the tables weigh most.)
+//
+// The tables take the room of partial sums: K is split into fewer slices, about eight workgroups per CU.  Where
+// that room allows fewer still, slices of more than ROWS_FIX_SPLIT chunks are split all the same and the
+// workspace grows: two to five slices where eight workgroups per CU wanted seven to eighteen took up to 15 %
+// longer than fp16 tables (460 rows x 2836 x 9536, 3 bit, groups of 64: 293 us in three slices, 250 in six, 271
+// with fp16 tables; 539 x 1386 x 7872, 4 bit, groups of 64: 200, 180, 183).  Eighty such calls: 1.03 times as fast
+// as fp16 tables without it, 1.09 with it.  Shorter slices are not worth it (255 x 15975 x 320: 46 us with
+// what the room allows, 50 in three slices).
 //
 // The extra launch that converts the tables wants look-ups to pay for it.  Measured against the general
 // kernels: 64 rows x 11008 x 4096 at 4 bit 70.0 us against 79.0, 80 rows 84.0 against 96.3; at 4096 x
 // 4096, where the eight-chunk kernel pair is the other side, 1.00 / 0.98 / 1.09 times as fast at 64 / 80 /
-// 96 rows (1.1e9, 1.3e9, 1.6e9 look-ups), 0.985 at 130 rows and 2 bit against the general kernel (1.1e9); with 40 rows there are too few workgroups (0.77 to 1.02), and
-// at 1 bit it is 0.93 to 1.05 times as fast: tables and launches weigh four times as much there.
-// K is split until a call has about eight workgroups per CU.
+// 96 rows (1.1e9, 1.3e9, 1.6e9 look-ups), 0.985 at 130 rows and 2 bit against the general kernel (1.1e9);
+// with 40 rows there are too few workgroups (0.77 to 1.02), and at 1 bit it is 0.93 to 1.05 times as fast:
+// tables and launches weigh four times as much there.
 RowsPlan rows_plan(const tmac_wdesc* desc, int N) {
   RowsPlan pl = rows_plan_plain(desc, N);
   const size_t room = pl.part_bytes + pl.ctr_bytes + pl.srow_bytes;
@@ -1483,24 +1492,27 @@ RowsPlan rows_plan(const tmac_wdesc* desc, int N) {
   const size_t tab = (size_t)((N + 7) / 8) * (ge.Kp / 4) * 256, scale = (size_t)tiles * (ge.n_chunks >> 2) * 64;
   const size_t sums = (size_t)tiles * (one_group ? 1 : desc->K / desc->group) * 64;
   const int want = (int)((ROWS_FIX_TARGET_WGS + pairs - 1) / pairs);
-  for (int cps = ((ge.n_chunks + want - 1) / want + unit - 1) / unit * unit;; cps += unit) {
-    const int slices = (ge.n_chunks + cps - 1) / cps;
-    const size_t part = ((size_t)slices * slice + 255) / 256 * 256;
-    if (part + tab + scale + sums <= room) {
-      if (pairs * slices < ROWS_FIX_LEAST_WGS) return pl;
-      pl.fix = true;
-      pl.fix_cps = cps;
-      pl.fix_slices = slices;
-      pl.fix_tiles = tiles;
-      pl.fix_part_bytes = part;
-      pl.fix_tab_bytes = tab;
-      pl.fix_scale_bytes = scale * (shift == 0 ? 4 : 1);
-      pl.fix_sums_bytes = sums;
-      pl.fix_shift = shift;
-      return pl;
-    }
-    if (slices == 1) return pl;
+  const int cps = ((ge.n_chunks + want - 1) / want + unit - 1) / unit * unit;
+  auto slices_of = [&](int c) { return (ge.n_chunks + c - 1) / c; };
+  auto part_of = [&](int c) { return ((size_t)slices_of(c) * slice + 255) / 256 * 256; };
+  int least = cps;  // the least chunks per slice that leave room for the tables
+  while (part_of(least) + tab + scale + sums > room) {
+    if (slices_of(least) == 1) return pl;
+    least += unit;
   }
+  if (pairs * slices_of(least) < ROWS_FIX_LEAST_WGS) return pl;
+  int use = least;
+  while (use > cps && use > ROWS_FIX_SPLIT) use -= unit;
+  pl.fix = true;
+  pl.fix_cps = use;
+  pl.fix_slices = slices_of(use);
+  pl.fix_tiles = tiles;
+  pl.fix_part_bytes = part_of(use);
+  pl.fix_tab_bytes = tab;
+  pl.fix_scale_bytes = scale * (shift == 0 ? 4 : 1);
+  pl.fix_sums_bytes = sums;
+  pl.fix_shift = shift;
+  return pl;
 }
 
 bool rows_fixed_point(const tmac_wdesc* desc, int N) { return desc->g == 4 && rows_plan(desc, N).fix; }

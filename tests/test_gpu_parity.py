@@ -1245,10 +1245,11 @@ def test_fixed_point_tables_leave_infinities_and_nans_alone(T, torch):
 
 
 @pytest.mark.parametrize("N,M,K,bits,group", [(359, 8336, 384, 4, 128), (401, 7947, 320, 4, 64), (399, 8024, 320, 4, -1),
-                                              (72, 5201, 4096, 4, 128), (256, 2700, 4096, 2, 0)])
+                                              (72, 5201, 4096, 4, 128), (256, 2700, 4096, 2, 0), (271, 919, 12032, 2, 128)])
 def test_fixed_point_one_slice_and_output_forms(T, torch, N, M, K, bits, group):
     """Fixed-point tables with one K slice (the first three shapes: one set of partial sums still goes through
-    the workspace) and with several: the arithmetic of the rounding model (which says that this route was
+    the workspace), with several, and with more than the plain plan's workspace has room for (the last shape;
+    nothing is written past the size asked for): the arithmetic of the rounding model (which says that this route was
     taken: fp16 sums are 3e-4 off it), fp16 outputs, an activation scale, and rows wider than M."""
     from paper_2407_00088_amd.runner import from_problem
     rng = np.random.default_rng(1700 + N)
@@ -1259,7 +1260,11 @@ def test_fixed_point_one_slice_and_output_forms(T, torch, N, M, K, bits, group):
         p = wl.make_grouped(0, 1700 + N, N, M, K, bits, K if group < 0 else group, name="forms")
     lin = from_problem(p, layout=L3)
     A = torch.from_numpy(p.act).cuda()
+    need = T.tmac_workspace_bytes(lin.desc, N)
+    room = torch.full((need + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+    lin.workspace = room[:need]
     plain = lin.forward(A)
+    assert bool((room[need:] == 0xA5).all())
     rows, cols = [0, 15, 16, N - 1], np.r_[0:70, M - 70:M]
     sub = lambda x: None if x is None else x[cols]
     model = rm.lut_mpgemm_fixed(p.act[rows], p.q[cols], bits, sub(p.scales), sub(p.zeros), p.group, p.weight_scale, p.zero_point)
