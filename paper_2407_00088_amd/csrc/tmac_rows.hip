@@ -148,6 +148,13 @@ __device__ __forceinline__ void rows_widen(int& l0, int& l1, uint32_t pair) {
   asm("v_mad_u32_u16 %0, %1, %2, %0 op_sel:[1,0,0,0]" : "+v"(l1) : "v"(pair), "n"(W));
 }
 
+// l = start + (one half of pair) * W
+template <int W>
+__device__ __forceinline__ void rows_widen_from(int& l0, int& l1, uint32_t pair, int start) {
+  asm("v_mad_u32_u16 %0, %1, %2, %3" : "=v"(l0) : "v"(pair), "n"(W), "s"(start));
+  asm("v_mad_u32_u16 %0, %1, %2, %3 op_sel:[1,0,0,0]" : "=v"(l1) : "v"(pair), "n"(W), "s"(start));
+}
+
 // Algorithm 1 Precompute for one (activation row, LUT group of four) inside a lookup kernel: the
 // eight entries 8h..8h+7 of the table, as four dwords of two 16-bit entries, with the arithmetic
 // of the stand-alone precompute kernel ((+-a0 +- a1) + (+-a2 - a3), every addition in fp16;
@@ -1127,9 +1134,9 @@ __global__ __launch_bounds__(256) void rows_fix_kernel(const RowsParams p, uint3
 
 // The look-ups of one 32-k chunk for two sets of eight activation rows, in rounds of the eight reads of
 // one plane and row set (see rows_chunk_int): L += the planes' sums, and their biases, times the planes'
-// weights.
-template <int BITS, int OSTRIDE>
-__device__ __forceinline__ void rows_chunk_fix(const uint32_t (&x)[BITS], uint32_t cbase, int (&L)[16]) {
+// weights.  START: L begins at `start`.
+template <int BITS, int OSTRIDE, bool START>
+__device__ __forceinline__ void rows_chunk_fix(const uint32_t (&x)[BITS], uint32_t cbase, int (&L)[16], int start = 0) {
   using Sh = RowsShape<8, 4>;
   constexpr int TPC = Sh::TPC, HD = Sh::HD, TB = Sh::TB;
   auto plane = [&](auto bc) {
@@ -1149,7 +1156,8 @@ __device__ __forceinline__ void rows_chunk_fix(const uint32_t (&x)[BITS], uint32
         uint32_t q = e[0][u];
 #pragma unroll
         for (int j = 1; j < TPC; ++j) q += e[j][u];
-        rows_widen<1 << b>(L[8 * o + 2 * u], L[8 * o + 2 * u + 1], q);
+        if constexpr (START && b == 0) rows_widen_from<1>(L[8 * o + 2 * u], L[8 * o + 2 * u + 1], q, start);
+        else rows_widen<1 << b>(L[8 * o + 2 * u], L[8 * o + 2 * u + 1], q);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -1226,13 +1234,17 @@ __device__ __forceinline__ void rows_add_raw(const RowsParams& p, const float* u
 
 // mpgemm_rows_kernel for fixed-point tables: two sets of eight activation rows per workgroup, tables
 // from the workspace (written by rows_fix_kernel), results through the workspace to rows_sum_kernel even
-// where there is one K slice only (finishing here as well costs 40 registers).  The integer sums of a quantisation group and 128-k
-// block are converted once and multiplied by their unit and half the group's scale.  Bound by the
-// look-up rate of LDS and the vector ALUs about equally, each about 70 % busy (see rows_chunk_int).  The
-// whole call at 256 rows x 5120 x 5120, 4 bit: 139 us against 163 with fp16 tables; 511 rows x 13824 x
-// 5120, 2 bit: 378 against 426.  (Tables of eight chunks staged with a wait: 143, 401; five wavefronts
-// per SIMD: 141, 391 -> 157, 440; next round's reads ahead: 160, 455.)
-template <int BITS>
+// where there is one K slice only (finishing here as well costs 40 registers).  The integer sums of a
+// quantisation group and 128-k block are converted once and multiplied by their unit and half the group's
+// scale.  Bound by the look-up rate of LDS and the vector ALUs about equally, each about 70 % busy (see
+// rows_chunk_int).  The whole call at 256 rows x 5120 x 5120, 4 bit: 141 us against 164 with fp16 tables;
+// 511 rows x 13824 x 5120, 2 bit: 365 against 449.  (Tables of eight chunks staged with a wait: 143, 401;
+// five wavefronts per SIMD: 141, 391 -> 157, 440; next round's reads ahead: 160, 455.)
+// SOLO: groups of 32 k, every chunk a group and a unit of its own.  The first plane starts from the constant
+// and units and group sums are asked for before the chunk's look-ups and used after them: 511 rows x 13824 x
+// 5120 at 2 bit 424 us against 460 with the general loop (fp16 tables 499), 295 x 8881 x 6496 260 against 293
+// (272), 256 x 5120 x 13824 at 4 bit 377 against 399 (413).
+template <int BITS, bool SOLO>
 __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_fix_kernel(const RowsParams p) {
   using Sh = RowsShape<8, 4>;
   constexpr int CB = Sh::CB, OSTRIDE = 4 * CB;
@@ -1246,7 +1258,7 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_fix_kernel(const Ro
   const uint32_t* my_idx = p.idx + ((size_t)tile * p.n_chunks * 64 + lane) * BITS;
   const uint32_t* my_sz = p.sz + (size_t)tile * p.nq * 64 + lane;
   const uint32_t lds0 = (uint32_t)(uintptr_t)((rows_lds_char*)tab);
-  const int shift = p.fix_shift;
+  const int shift = SOLO ? 0 : p.fix_shift;
   rows_const_float* const fix_scale = rows_const(p.fix_scale) + (size_t)blockIdx.x * (p.n_chunks >> shift) * 16;
   rows_const_float* const sums = rows_const(p.S) + (size_t)blockIdx.x * p.nq * 16;
   const int cz0 = blockIdx.z * p.cps, cz1 = min(cz0 + p.cps, p.n_chunks);
@@ -1302,6 +1314,25 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_fix_kernel(const Ro
 #pragma unroll
       for (int b = 0; b < BITS; ++b) x[b] = xn[b];
       load_idx(min(c + 1, cz1 - 1), xn);  // next chunk's indices, one chunk ahead
+      if constexpr (SOLO) {
+        if (c >= p.nq) break;  // (chunks in the K padding belong to no group)
+        const float s = __half2float(__ushort_as_half((uint16_t)(szv_next & 0xffffu)));
+        const float z = __half2float(__ushort_as_half((uint16_t)(szv_next >> 16)));
+        szv_next = my_sz[(size_t)min(c + 1, p.nq - 1) * 64];
+        float sum[16];
+#pragma unroll
+        for (int t = 0; t < 16; ++t) {
+          flag |= __float_as_int(unit[t] = fix_scale[(size_t)c * 16 + t]);
+          sum[t] = sums[(size_t)c * 16 + t];
+        }
+        rows_chunk_fix<BITS, OSTRIDE, true>(x, lds0 + (uint32_t)(c - c0) * (uint32_t)CB, L, -32768 * ((1 << BITS) - 1));
+        // half the scale times (look-ups + bias term), the latter as in Section 4's linear transform
+        const float bz = 2.f * (p.mid - z);
+        hs = 0.5f * s;
+#pragma unroll
+        for (int t = 0; t < 16; ++t) acc[t] = fmaf(hs, fmaf((float)L[t], unit[t], bz * sum[t]), acc[t]);
+        continue;
+      }
       if (p.grouped && cg == 0 && gq < p.nq) {  // a group starts (chunks in the K padding belong to none)
         const float s = __half2float(__ushort_as_half((uint16_t)(szv_next & 0xffffu)));
         const float z = __half2float(__ushort_as_half((uint16_t)(szv_next >> 16)));
@@ -1321,7 +1352,7 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_fix_kernel(const Ro
 #pragma unroll
         for (int t = 0; t < 16; ++t) L[t] = L0;
       }
-      rows_chunk_fix<BITS, OSTRIDE>(x, lds0 + (uint32_t)(c - c0) * (uint32_t)CB, L);
+      rows_chunk_fix<BITS, OSTRIDE, false>(x, lds0 + (uint32_t)(c - c0) * (uint32_t)CB, L);
       const bool group_ends = p.grouped && gq < p.nq && ++cg == p.cpg;
       first = group_ends || (c & 3) == 3;
       if (first) {
@@ -1345,6 +1376,13 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_fix_kernel(const Ro
                        cz0, cz1, p.ws_part + ((size_t)blockIdx.z * p.N + n0) * p.Mp + m, m < p.M);
 }
 
+template <bool SOLO>
+static const void* rows_fix_lookup(int bits) {
+  return bits == 2   ? reinterpret_cast<const void*>(mpgemm_fix_kernel<2, SOLO>)
+         : bits == 3 ? reinterpret_cast<const void*>(mpgemm_fix_kernel<3, SOLO>)
+                     : reinterpret_cast<const void*>(mpgemm_fix_kernel<4, SOLO>);
+}
+
 // Tables to fixed point, look-ups, slice sums.
 static hipError_t launch_rows_fix(const RowsParams& p, const RowsPlan& pl, int bits, bool from_act, int Geff,
                                   uint32_t* fix, float* scale, float* sums, hipStream_t st) {
@@ -1362,9 +1400,7 @@ static hipError_t launch_rows_fix(const RowsParams& p, const RowsPlan& pl, int b
   local.fix_scale = scale;
   local.S = sums;
   local.cps = pl.fix_cps;
-  const void* fn = bits == 2   ? reinterpret_cast<const void*>(mpgemm_fix_kernel<2>)
-                   : bits == 3 ? reinterpret_cast<const void*>(mpgemm_fix_kernel<3>)
-                               : reinterpret_cast<const void*>(mpgemm_fix_kernel<4>);
+  const void* fn = (p.grouped && p.cpg == 1) ? rows_fix_lookup<true>(bits) : rows_fix_lookup<false>(bits);
   void* args2[] = {&local};
   e = hipLaunchKernel(fn, dim3(pl.fix_tiles, (p.n_tiles + ROWS_WAVES - 1) / ROWS_WAVES, pl.fix_slices), dim3(64 * ROWS_WAVES),
                       args2, 0, st);
