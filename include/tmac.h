@@ -59,7 +59,10 @@ typedef enum { TMAC_ACT_F16 = 0, TMAC_ACT_I8 = 1, TMAC_ACT_F16_TQ = 2 } tmac_act
  *   TMAC_LUT_F16: entries are signed sums of fp16 activations formed with fp16 additions (see
  *                 tmac_precompute_lut; results within 2e-3 relative Frobenius error of the fp64
  *                 product).
- *                 Large calls of the batched kernels (64 activation rows and more) look the
+ *                 Calls of the batched kernels with g = 4, 2 to 4 bits, 64 activation rows or more
+ *                 and more than about 1.1e9 look-ups (N M K bits / 4), for which tmac_mpgemm_noalloc
+ *                 returns TMAC_ESIZE, look (unless K is so long against M that the tables would
+ *                 weigh most; see rows_plan in csrc/tmac_rows.hip for the exact line) the
  *                 entries up as 16-bit integers, rounded once to 2^-15 of the largest sum of
  *                 eight entries in each (activation row, quantisation group of at most 128 k), whose
  *                 sums are exact: closer to the product than sums in fp16, unless those are exact
@@ -265,10 +268,11 @@ tmac_status tmac_mpgemv_fused(const tmac_wdesc* desc, const void* packed_dev, co
  * traffic): layout 2 with K % 16 == 0 (this is then tmac_mpgemv_fused), and layout 3 with g = 4,
  * K % 8 == 0, a group size that divides 256 (or one scale per row or tensor), and at most 32
  * activation rows in a call that is cut into K slices of 256 (the case a separate precompute
- * launch costs most).  Every other call
- * runs tmac_precompute_lut into the second region of the workspace and tmac_mpgemm after it
- * (layout 2 with K % 16 != 0 or an unsupported group size: at most 64 activation rows, beyond
- * that TMAC_EUNSUPPORTED and a size of 0).
+ * launch costs most).  Every other call runs tmac_precompute_lut into the second region of the
+ * workspace and tmac_mpgemm after it, or, where the entries are looked up as integers
+ * (TMAC_LUT_F16 above), builds those from the activations and uses the second region only for tables
+ * that are not finite (layout 2 with K % 16 != 0 or an unsupported group size: at most 64 activation
+ * rows, beyond that TMAC_EUNSUPPORTED and a size of 0).
  *   A_dev          [N,K] fp16 or int8, 16-byte aligned; leading dimension lda a multiple of 8
  *                  where the tables are built in the kernel (16 for int8 with layout 2), else as
  *                  for tmac_precompute_lut
