@@ -1245,9 +1245,10 @@ def test_fixed_point_tables_leave_infinities_and_nans_alone(T, torch):
 
 
 @pytest.mark.parametrize("N,M,K,bits,group", [(359, 8336, 384, 4, 128), (401, 7947, 320, 4, 64), (399, 8024, 320, 4, -1),
+                                              (399, 8024, 320, 4, 32),
                                               (72, 5201, 4096, 4, 128), (256, 2700, 4096, 2, 0), (271, 919, 12032, 2, 128)])
 def test_fixed_point_one_slice_and_output_forms(T, torch, N, M, K, bits, group):
-    """Fixed-point tables with one K slice (the first three shapes: one set of partial sums still goes through
+    """Fixed-point tables with one K slice (the first four shapes: one set of partial sums still goes through
     the workspace), with several, and with more than the plain plan's workspace has room for (the last shape;
     nothing is written past the size asked for): the arithmetic of the rounding model (which says that this route was
     taken: fp16 sums are 3e-4 off it), fp16 outputs, an activation scale, and rows wider than M."""
