@@ -59,11 +59,11 @@ typedef enum { TMAC_ACT_F16 = 0, TMAC_ACT_I8 = 1, TMAC_ACT_F16_TQ = 2 } tmac_act
  *   TMAC_LUT_F16: entries are signed sums of fp16 activations formed with fp16 additions (see
  *                 tmac_precompute_lut; results within 2e-3 relative Frobenius error of the fp64
  *                 product).
- *                 Calls of the batched kernels with g = 4, 2 to 4 bits, 64 activation rows or more
- *                 and more than about 1.1e9 look-ups (N M K bits / 4), for which tmac_mpgemm_noalloc
- *                 returns TMAC_ESIZE, look (unless K is so long against M that the tables would
- *                 weigh most; see rows_plan in csrc/tmac_rows.hip for the exact line) the
- *                 entries up as 16-bit integers, rounded once to 2^-15 of the largest sum of
+ *                 Calls of the batched kernels with g = 4, 2 to 4 bits, nine activation rows or more
+ *                 and more than about 0.75e9 look-ups (N M K bits / 4; tmac_mpgemm_fused: 0.3e9), or
+ *                 1.1e9 with groups that are no multiple of 128, look (unless K is so long against M
+ *                 that the tables would weigh most; see rows_plan in csrc/tmac_rows.hip for the exact
+ *                 lines) the entries up as 16-bit integers, rounded once to 2^-15 of the largest sum of
  *                 eight entries in each (activation row, quantisation group of at most 128 k), whose
  *                 sums are exact: closer to the product than sums in fp16, unless those are exact
  *                 (small whole numbers).  Where a row's entries are not all finite, that row's
@@ -271,11 +271,12 @@ tmac_status tmac_mpgemv_fused(const tmac_wdesc* desc, const void* packed_dev, co
  * launch costs most).  Every other call runs tmac_precompute_lut into the second region of the
  * workspace and tmac_mpgemm after it, or, where the entries are looked up as integers
  * (TMAC_LUT_F16 above), builds those from the activations and uses the second region only for tables
- * that are not finite (layout 2 with K % 16 != 0 or an unsupported group size: at most 64 activation
+ * that are not finite; it does so from fewer look-ups on than tmac_mpgemm, which reads its tables from
+ * a LUT buffer: between the two lines its results are the closer ones (layout 2 with K % 16 != 0 or an unsupported group size: at most 64 activation
  * rows, beyond that TMAC_EUNSUPPORTED and a size of 0).
  *   A_dev          [N,K] fp16 or int8, 16-byte aligned; leading dimension lda a multiple of 8
- *                  where the tables are built in the kernel (16 for int8 with layout 2), else as
- *                  for tmac_precompute_lut
+ *                  where a kernel could build the tables as above (16 for int8 with layout 2), else
+ *                  as for tmac_precompute_lut
  *   workspace_dev  tmac_fused_workspace_bytes(desc, N, act) bytes, 16-byte aligned, contents
  *                  arbitrary (its first region is tmac_mpgemm's workspace); calls that share it
  *                  must not overlap in time

@@ -221,6 +221,8 @@ struct RowsPlan {
   // fp16 tables as fixed-point numbers (see rows_fix_kernel); fix == false: none of it
   bool fix;
   int fix_cps, fix_slices, fix_tiles;               // chunks per K slice, K slices, sets of 16 activation rows
+  int run_wgs, run_total;                           // the same for integer tables
+  int fix_wgs, fix_total;                           // workgroups and chunks of the run (RowsShare); 0: K slices
   int fix_shift;                                    // 2: a unit per 128-k block, 0: per chunk
   // inside the same workspace: partial sums, tables, their units, the group sums
   size_t fix_part_bytes, fix_tab_bytes, fix_scale_bytes, fix_sums_bytes;
@@ -229,17 +231,19 @@ struct RowsPlan {
     return fixed > plain ? fixed : plain;  // (fixed is 0 without fixed-point tables; integer tables keep the plain plan)
   }
 };
-RowsPlan rows_plan(const tmac_wdesc* desc, int N);
-bool rows_builds_tables(const tmac_wdesc* desc, int N);
+// from_act: the call brings activations, not a LUT buffer (tmac_mpgemm_fused)
+RowsPlan rows_plan(const tmac_wdesc* desc, int N, bool from_act = false);
+bool rows_reads_eight(const tmac_wdesc* desc, int N);
+bool rows_builds_tables(const tmac_wdesc* desc, int N, bool is_int);
 // Returns a tmac_status value.  lut_dev NULL: tables built in the kernel from A_dev (where
-// rows_builds_tables(desc, N) holds).  fixed_from_act: fixed-point tables built from A_dev (where
-// rows_fixed_point(desc, N) holds); lut_dev is room of a LUT buffer's size.
+// rows_builds_tables(desc, N, is_int) holds).  fixed_from_act: fixed-point tables built from A_dev (where
+// rows_fixed_from_act(desc, N) holds); lut_dev is room of a LUT buffer's size.
 int launch_rows_gemm(const tmac_wdesc* desc, const void* packed_dev, const void* lut_dev, const void* A_dev,
                      int64_t lda, int lut_t, int N, const float* act_scale_dev, float weight_scale, void* out_dev,
                      int out_t, int64_t ldo, void* workspace_dev, size_t workspace_bytes, void* stream,
                      bool fixed_from_act = false);
-// Whether a call with fp16 tables turns them into fixed-point numbers.
-bool rows_fixed_point(const tmac_wdesc* desc, int N);
+// Whether a call that brings fp16 activations builds fixed-point tables from them.
+bool rows_fixed_from_act(const tmac_wdesc* desc, int N);
 
 // Records the last HIP error of this thread (diagnostics for TMAC_EHIP).
 void note_hip_error(int hip_error);

@@ -585,9 +585,10 @@ extern "C" tmac_status tmac_mpgemv_fused(const tmac_wdesc* desc, const void* pac
 static bool fused_regions(const tmac_wdesc* desc, int N, tmac_act_t act, size_t* ws, size_t* lut) {
   if (!desc_valid(desc) || N <= 0 || (act != TMAC_ACT_F16 && act != TMAC_ACT_I8 && act != TMAC_ACT_F16_TQ)) return false;
   const tmac_lut_t lt = (act == TMAC_ACT_I8) ? TMAC_LUT_I16 : TMAC_LUT_F16;
-  *ws = (tmac_workspace_bytes(desc, N) + 255) / 256 * 256;
+  const bool fixed = act == TMAC_ACT_F16 && desc->layout == TMAC_LAYOUT_R64K32 && rows_fixed_from_act(desc, N);
+  *ws = ((fixed ? rows_plan(desc, N, true).bytes() + 256 : tmac_workspace_bytes(desc, N)) + 255) / 256 * 256;
   const bool in_kernel = (desc->layout == TMAC_LAYOUT_R8U16) ? (desc->K % 16 == 0 && group_supported(desc))
-                                                             : (group_supported(desc) && rows_builds_tables(desc, N));
+                                                             : (group_supported(desc) && rows_builds_tables(desc, N, act == TMAC_ACT_I8));
   // (int8 tables are quantised inside the register-table kernel only)
   if (act == TMAC_ACT_F16_TQ && !(in_kernel && desc->layout == TMAC_LAYOUT_R8U16)) return false;
   // (the register-table kernel reads its tables from a LUT buffer for at most TMAC_DECODE_MAX_ROWS rows)
@@ -614,7 +615,8 @@ extern "C" tmac_status tmac_mpgemm_fused(const tmac_wdesc* desc, const void* pac
   if (out != TMAC_OUT_F32 && out != TMAC_OUT_F16 && out != TMAC_OUT_I32) return TMAC_EINVAL;
   if (!aligned16(packed_dev) || !aligned16(A_dev) || !aligned16(workspace_dev)) return TMAC_EINVAL;
   if (ldo < desc->M || lda < desc->K) return TMAC_EINVAL;
-  if (lutb == 0 && lda % 8 != 0) return TMAC_EINVAL;  // the kernels read eight activations per load
+  // the kernels that build tables in place read eight activations per load
+  if ((lutb == 0 || (desc->layout == TMAC_LAYOUT_R64K32 && rows_reads_eight(desc, N))) && lda % 8 != 0) return TMAC_EINVAL;
   if (!group_supported(desc)) return TMAC_EUNSUPPORTED;
   if (workspace_bytes < ws + lutb) return TMAC_ESIZE;
   const tmac_lut_t lt = (act == TMAC_ACT_I8) ? TMAC_LUT_I16 : TMAC_LUT_F16;
@@ -626,7 +628,7 @@ extern "C" tmac_status tmac_mpgemm_fused(const tmac_wdesc* desc, const void* pac
                                                       weight_scale, out_dev, (int)out, ldo, workspace_dev, ws, stream));
   }
   void* lut_dev = static_cast<char*>(workspace_dev) + ws;
-  if (act == TMAC_ACT_F16 && desc->layout == TMAC_LAYOUT_R64K32 && rows_fixed_point(desc, N)) {
+  if (act == TMAC_ACT_F16 && desc->layout == TMAC_LAYOUT_R64K32 && rows_fixed_from_act(desc, N)) {
     // fixed-point tables and group sums straight from the activations (the LUT buffer holds only tables that
     // are not finite)
     if (lda % 4 != 0) return TMAC_EINVAL;

@@ -68,6 +68,12 @@ constexpr int ROWS_TARGET_WGS = TMAC_ROWS_TARGET_WGS;  // K is split until a cal
 constexpr int ROWS_LDS = 32768;     // bytes of tables per LDS slice: 1024 k for 4 activation rows, 512 k for 8
 constexpr int ROWS_FIX_TARGET_WGS = 2048;  // eight workgroups per CU
 constexpr int ROWS_FIX_LEAST_WGS = 640;    // fewer leave the chip idle
+constexpr int ROWS_RUN_WGS = 1024;         // four workgroups (one wavefront per SIMD each) per CU: what the chip holds at once
+constexpr int ROWS_RUN_INT_CHUNKS = 12288; // chunks of pairs (RowsShare) from which the run serves a call: integer tables,
+constexpr int ROWS_RUN_ACT_CHUNKS = 5000;  // ... fp16 tables built from activations, more than 32 rows,
+constexpr int ROWS_RUN_ACT_FEW = 24576;    // ... times the bits, up to 32 rows,
+constexpr double ROWS_RUN_LUT_LOOKUPS = 0.75e9;  // ... fp16 tables from a LUT buffer: look-ups,
+constexpr int ROWS_RUN_LUT_ROWS = 1536;    // ... and weight rows times bits (rows_plan)
 constexpr int ROWS_FIX_SPLIT = 16;         // chunks: a longer K slice is split even if the workspace grows (rows_plan)
 constexpr int ROWS_FIX_MIN_N = 64;  // activation rows from which tables are turned into fixed-point numbers (rows_plan)
 constexpr int ROWS_NT_WIDE = 8;     // activation rows per workgroup when there are enough of them
@@ -76,6 +82,26 @@ constexpr int64_t ROWS_SUM_WIDE = 1 << 19;  // outputs from which the slice sums
 
 typedef _Float16 rh2v __attribute__((ext_vector_type(2)));
 typedef short rs2v __attribute__((ext_vector_type(2)));
+
+// The call as one run of chunks, dealt out evenly.  A pair is a block of 256 weight rows and a set of 16
+// activation rows; the pairs' chunks follow each other, weight rows fastest, and workgroup w takes the chunks
+// [w total / wgs, (w + 1) total / wgs) of the run, whatever pairs they belong to.  What it has of one pair is
+// one part of that pair's sums; a pair's parts are numbered from its first workgroup.
+struct RowsShare {
+  uint32_t wgs, per, more;      // workgroups, chunks of each; the first `more` take one more
+  uint32_t row_blocks, chunks;  // blocks of 256 weight rows, chunks of a pair
+  uint32_t inv_row_blocks, inv_chunks;  // rows_inverse() of the two
+  __device__ uint32_t start(uint32_t wg) const { return wg * per + min(wg, more); }
+  __device__ uint32_t owner(uint32_t chunk) const {
+    const uint32_t head = more * (per + 1);
+    return chunk < head ? chunk / (per + 1) : more + (chunk - head) / per;
+  }
+  __device__ uint32_t first(uint32_t pair) const { return owner(pair * chunks); }
+  __device__ int parts(uint32_t pair) const { return (int)(owner((pair + 1) * chunks - 1) - first(pair)) + 1; }
+};
+// n / d = the high half of n * rows_inverse(d) for n d < 2^32 and d > 1; d == 1: 0, which rows_div takes for it
+inline uint32_t rows_inverse(uint32_t d) { return (uint32_t)((0x100000000ull + d - 1) / d); }
+__device__ __forceinline__ uint32_t rows_div(uint32_t n, uint32_t inverse) { return inverse ? __umulhi(n, inverse) : n; }
 
 struct RowsParams {
   const uint32_t* idx;     // [n_tiles][n_chunks][64][bits] dwords
@@ -105,6 +131,8 @@ struct RowsParams {
   const float* fix_scale;  // fixed-point tables: [set of 16 rows][chunk >> fix_shift][16] value of one unit (-0: entries not finite)
   int fix_shift;           // 2: one unit per 128-k block, 0: one per chunk (see rows_fix_kernel)
   uint16_t* raw;           // ... and the fp16 tables, as in a LUT buffer, where a unit is -0
+  int lut_nt, raw_nt;      // activation rows of an n tile of the LUT buffer, 4 or 8 (rows_nt), and of raw
+  RowsShare share;         // ... and which part of the call a workgroup serves (wgs == 0: K slices of equal length)
 };
 
 // 32-k chunks of tables one LDS slice holds, for LUT group size g and nt activation rows
@@ -630,7 +658,7 @@ __global__ __launch_bounds__(64 * ROWS_WAVES) void mpgemm_rows_kernel(const Rows
   }
 }
 
-template <bool IS_INT>
+template <bool IS_INT, bool RUN = false>
 static hipError_t launch_rows_sum(const RowsParams& p, int nz, hipStream_t st);
 
 template <bool IS_INT, int BITS, int NT, int G, int OCT>
@@ -866,12 +894,14 @@ __global__ __launch_bounds__(64 * ROWS_WAVES) void mpgemm_rows8_kernel(const Row
 // 64 x 8640 from thirteen 7.0 against 8.5; 100 x 5504 from 22 9.6 against 10.3.  The number of slices decides
 // nothing: of sixteen shapes with two to 34 one lost, 128 x 8640 from thirteen (11.8 against 11.2, also
 // with the last five taken as four and one).  96 x 3200, below the line, is even at 8.9.
-template <bool IS_INT, int VEC>
+// RUN: the parts of a run of chunks, whose number changes from pair to pair (nz is not used).
+template <bool IS_INT, int VEC, bool RUN>
 __global__ __launch_bounds__(256) void rows_sum_kernel(const RowsParams p, int nz) {
   const uint32_t id = blockIdx.x * 256u + threadIdx.x;   // (launch_rows_sum checks that the ids fit)
   const uint32_t per_row = (uint32_t)p.Mp / VEC;
   const int n = (int)(id / per_row), m0 = (int)(id % per_row) * VEC;
   if (n >= p.N || m0 >= p.M) return;
+  if constexpr (RUN) nz = p.share.parts((uint32_t)(n >> 4) * p.share.row_blocks + (uint32_t)(m0 >> 8));
   const bool raw_int = IS_INT && !p.grouped;
   const float* src = p.ws_part + (size_t)n * p.Mp + m0;
   const size_t stride = (size_t)p.N * p.Mp;
@@ -961,7 +991,7 @@ __global__ __launch_bounds__(256) void rows_sum_kernel(const RowsParams p, int n
   }
 }
 
-template <bool IS_INT>
+template <bool IS_INT, bool RUN>
 static hipError_t launch_rows_sum(const RowsParams& p, int nz, hipStream_t st) {
   RowsParams local = p;
   void* args[] = {&local, &nz};
@@ -969,8 +999,8 @@ static hipError_t launch_rows_sum(const RowsParams& p, int nz, hipStream_t st) {
   const bool wide = outs >= ROWS_SUM_WIDE;
   const int64_t blocks = (outs / (wide ? 4 : 1) + 255) / 256;  // (Mp is a multiple of 64)
   if (blocks > 0x00ffffff) return hipErrorInvalidValue;        // (ids of 32 bits; their partial sums alone would be 64 GB)
-  const void* fn = wide ? reinterpret_cast<const void*>(rows_sum_kernel<IS_INT, 4>)
-                        : reinterpret_cast<const void*>(rows_sum_kernel<IS_INT, 1>);
+  const void* fn = wide ? reinterpret_cast<const void*>(rows_sum_kernel<IS_INT, 4, RUN>)
+                        : reinterpret_cast<const void*>(rows_sum_kernel<IS_INT, 1, RUN>);
   return hipLaunchKernel(fn, dim3((unsigned)blocks), dim3(256), args, 0, st);
 }
 
@@ -1042,10 +1072,10 @@ __global__ __launch_bounds__(256) void rows_fix_kernel(const RowsParams p, uint3
       v[2 * d + 1] = __builtin_amdgcn_perm(t1[d], t0[d], 0x07060302u);
     }
   } else {
-    const int tile = n >> 3;                       // (n tiles of eight rows: rows_plan)
-    const uint16_t* const at = p.tables + ((size_t)tile * p.KG + kg) * 128 + (n & 7);
+    const int tile = n / p.lut_nt;
+    const uint16_t* const at = p.tables + ((size_t)tile * p.KG + kg) * (16 * p.lut_nt) + (n & (p.lut_nt - 1));
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = tile * 8 < p.N ? *reinterpret_cast<const uint32_t*>(at + e * 8) : 0u;
+    for (int e = 0; e < 8; ++e) v[e] = tile * p.lut_nt < p.N ? *reinterpret_cast<const uint32_t*>(at + e * p.lut_nt) : 0u;
     const int r = set * 16 + (int)threadIdx.x;
     if (threadIdx.x < 16 && r < p.N)
       for (int gq = blk; gq < p.nq; gq += nblk) sums[((size_t)set * p.nq + gq) * 16 + threadIdx.x] = static_cast<const float*>(p.S)[(size_t)r * p.nq + gq];
@@ -1179,11 +1209,14 @@ template <int BITS>
 __device__ __forceinline__ void rows_add_raw(const RowsParams& p, const float* unit, const uint32_t* idx, const uint32_t* sz, int n0,
                                              int cz0, int cz1, float* part, bool live) {
   const int lane = threadIdx.x & 63, shift = p.fix_shift;
-  const int units = (cz1 - cz0) >> shift;  // (a K slice is a number of 128-k blocks)
+  const int units = ((cz1 + (1 << shift) - 1) >> shift) - (cz0 >> shift);  // (the first and last may be other workgroups' in part)
   unit += (size_t)(cz0 >> shift) * 16;
 #pragma unroll 1
   for (int o = 0; o < 2 && n0 + 8 * o < p.N; ++o) {
+    // (a LUT buffer's n tiles may be four rows wide: then the second half comes from the next tile)
+    const bool narrow = p.raw_nt == 4;
     const uint16_t* const tables = p.raw + (size_t)((n0 >> 3) + o) * p.KG * 128;
+    const uint16_t* const upper = (n0 >> 2) + 2 * o + 1 < (p.N + 3) >> 2 ? tables + (size_t)p.KG * 64 : tables;
     uint32_t open = (1u << min(p.N - n0 - 8 * o, 8)) - 1u, some = 0;  // rows not NaN everywhere yet, rows with such units
     float sum[8];
 #pragma unroll
@@ -1193,27 +1226,35 @@ __device__ __forceinline__ void rows_add_raw(const RowsParams& p, const float* u
       const int u = u0 + (lane >> 3);
       uint64_t marks = __ballot(u < units && __float_as_int(unit[(size_t)min(u, units - 1) * 16 + 8 * o + (lane & 7)]) < 0);
 #pragma unroll 1
-      for (int c = cz0 + (u0 << shift), left = 1 << shift; marks; ++c) {
-        const uint32_t rows = (uint32_t)marks & open;
+      for (int c = ((cz0 >> shift) + u0) << shift, left = 1 << shift; marks; ++c) {
+        const uint32_t rows = c >= cz0 && c < cz1 ? (uint32_t)marks & open : 0u;
         if (p.grouped && c / p.cpg >= p.nq) break;  // chunks in the K padding belong to no group
         if (rows) {
           some |= rows;
           const float hs = p.grouped ? 0.5f * __half2float(__ushort_as_half((uint16_t)(sz[(size_t)(c / p.cpg) * 64] & 0xffffu))) : 1.f;
-#pragma unroll
+#pragma unroll 1
           for (int b = 0; b < BITS; ++b) {
             const uint32_t x = idx[(size_t)c * 64 * BITS + b];
+            const float w = (float)(1 << b);
             ru32x4v e[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j)
-              e[j] = *reinterpret_cast<const ru32x4v*>(tables + ((size_t)(c * 8 + j) * 16 + ((x >> (4 * j)) & 15u)) * 8);
+            for (int j = 0; j < 8; ++j) {
+              const size_t entry = (size_t)(c * 8 + j) * 16 + ((x >> (4 * j)) & 15u);
+              if (narrow) {
+                const ru32x2v lo = *reinterpret_cast<const ru32x2v*>(tables + entry * 4), hi = *reinterpret_cast<const ru32x2v*>(upper + entry * 4);
+                e[j] = ru32x4v{lo.x, lo.y, hi.x, hi.y};
+              } else {
+                e[j] = *reinterpret_cast<const ru32x4v*>(tables + entry * 8);
+              }
+            }
 #pragma unroll
             for (int d = 0; d < 4; ++d) {
               rh2v q[8];
 #pragma unroll
               for (int j = 0; j < 8; ++j) q[j] = __builtin_bit_cast(rh2v, (uint32_t)e[j][d]);
               tree_sum(q);
-              if (rows >> (2 * d) & 1u) sum[2 * d] = fmaf((float)q[0].x, hs * p.pw[b], sum[2 * d]);
-              if (rows >> (2 * d + 1) & 1u) sum[2 * d + 1] = fmaf((float)q[0].y, hs * p.pw[b], sum[2 * d + 1]);
+              if (rows >> (2 * d) & 1u) sum[2 * d] = fmaf((float)q[0].x, hs * w, sum[2 * d]);
+              if (rows >> (2 * d + 1) & 1u) sum[2 * d + 1] = fmaf((float)q[0].y, hs * w, sum[2 * d + 1]);
             }
           }
 #pragma unroll
@@ -1376,6 +1417,220 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_fix_kernel(const Ro
                        cz0, cz1, p.ws_part + ((size_t)blockIdx.z * p.N + n0) * p.Mp + m, m < p.M);
 }
 
+// The same where every 128-k block lies in one quantisation group (or there is one scale per row or tensor), and
+// for integer tables with one scale per row or tensor: the call as one run of chunks (RowsShare), an equal share
+// for each of the 1024 workgroups that the chip holds at once, instead of two to four rounds of workgroups whose
+// last is nearly empty.  Bound by the look-up rate of LDS (rows_chunk_int); what a call takes beyond it is the
+// start of the stream (9 us of a 16 row call without any look-up), the tables and the slice sums.
+// Shares alone are slower than rounds (256 rows x 5120 x 5120, 4 bit: 148 us against 137; 511 x 13824 x 5120, 2 bit:
+// 388 against 365; no matter how the pairs are ordered): a SIMD serves its oldest wavefront first, so one workgroup
+// of a CU is done after three quarters of the time and its place stays empty (12.2 wavefronts per CU on average, of
+// 16).  Wavefronts that are behind therefore get a higher priority.  Indices are requested two chunks ahead, at one
+// and two bits, whose chunks are over sooner, four (511 x 13824 x 5120: 351 us, two 356).
+// Us before (K slices of equal length) and now: 256 x 5120 x 5120, 4 bit 135.8, 132.3; 511 x 13824 x 5120, 2 bit
+// 362.4, 351; ternary 128 x 8640 x 3200 56.4, 50.2, 256 x 3200 x 8640 99.1, 94.2; against fp16 sums 48 x 11008 x
+// 4096, 4 bit 75.0, 57.9, 64 x 4096 x 4096 43.5, 36.1, 300 x 700 x 8192 71.8, 59.5.
+// (The chunk loop not unrolled, indices handed from register to register: 53 and 382 us for the ternary and the 2-bit
+// call of 511 rows; a copy of it without the bounds of a share: 53.7 and 353.)
+template <int BITS, bool IS_INT>
+__global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_run_kernel(const RowsParams p) {
+  using Sh = RowsShape<8, 4>;
+  constexpr int CB = Sh::CB, OSTRIDE = 4 * CB;
+  constexpr int BIAS = IS_INT ? ROWS_CHUNK_BIAS : 32768;  // of a chunk's sum, per plane weight
+  __shared__ __attribute__((aligned(2048))) char tab[2 * OSTRIDE];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // (gridDim.x is a multiple of 8: neighbours in the run share an XCD and its L2)
+  const uint32_t wg = (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  if (wg >= p.share.wgs) return;
+  const uint32_t at0 = p.share.start(wg);
+  const int todo = (int)(p.share.start(wg + 1) - at0);
+  if (todo <= 0) return;
+  const int chunks = (int)p.share.chunks, row_blocks = (int)p.share.row_blocks;
+  const int pair0 = (int)rows_div(at0, p.share.inv_chunks), c00 = (int)(at0 - (uint32_t)pair0 * p.share.chunks);
+  const uint32_t lds0 = (uint32_t)(uintptr_t)((rows_lds_char*)tab);
+  const int last8 = (p.N + 7) / 8 - 1;  // (a second row set past it repeats it)
+  const int bpg = p.cpg >> 2;           // blocks per quantisation group
+
+  auto tile_of = [&](int rb) { return min(rb * ROWS_WAVES + wave, p.n_tiles - 1); };  // (clamped: loads stay in range, stores are masked)
+  auto load_idx = [&](const uint32_t* base, uint32_t (&x)[BITS]) {
+    const uint32_t* src = base + (uint32_t)lane * BITS;
+    if constexpr (BITS == 4) {
+      const ru32x4v v = *reinterpret_cast<const ru32x4v*>(src);
+      x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
+    } else if constexpr (BITS == 2) {
+      const ru32x2v v = *reinterpret_cast<const ru32x2v*>(src);
+      x[0] = v.x; x[1] = v.y;
+    } else {
+#pragma unroll
+      for (int b = 0; b < BITS; ++b) x[b] = src[b];
+    }
+  };
+  // the tables of a 128-k block, 8 KB for each set of eight rows, are requested while the block before it is
+  // looked up, a chunk's indices two chunks ahead
+  ru32x4v next[4];
+  auto request = [&](int set, int blk) {
+    const char* const b0 = reinterpret_cast<const char*>(p.tables) + ((size_t)(set * 2) * p.KG + blk * 32) * Sh::TB;
+    const char* const b1 = reinterpret_cast<const char*>(p.tables) + ((size_t)min(set * 2 + 1, last8) * p.KG + blk * 32) * Sh::TB;
+    const uint32_t o = threadIdx.x * 16;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      next[i] = *reinterpret_cast<const ru32x4v*>(b0 + o + i * 4096);
+      next[2 + i] = *reinterpret_cast<const ru32x4v*>(b1 + o + i * 4096);
+    }
+  };
+  int set = (int)rows_div((uint32_t)pair0, p.share.inv_row_blocks), rb = pair0 - set * row_blocks, c = c00, left = todo, flag = 0;
+  const uint32_t* idx = p.idx + ((size_t)tile_of(rb) * chunks + (c & ~3)) * 64 * BITS;
+  constexpr int AHEAD = BITS <= 2 ? 4 : 2;
+  uint32_t x[AHEAD][BITS];
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i) load_idx(idx + ((c & (4 - AHEAD)) + i) * 64 * BITS, x[i]);
+  request(set, c >> 2);
+  while (true) {  // the parts of this workgroup, pair by pair
+    const int end = min(chunks, c + left);
+    left -= end - c;
+    const int n0 = set * 16, tile_raw = rb * ROWS_WAVES + wave;
+    const uint32_t* const my_sz = p.sz + (size_t)tile_of(rb) * p.nq * 64 + lane;
+    rows_const_float* fix_scale = rows_const(p.fix_scale) + ((size_t)set * (chunks >> 2) + (c >> 2)) * 16;
+    rows_const_float* const sums = rows_const(p.S) + (size_t)set * p.nq * 16;
+    const int rb_n = rb + 1 == row_blocks ? 0 : rb + 1, set_n = rb + 1 == row_blocks ? set + 1 : set;  // the next pair
+    const uint32_t* const idx_n = p.idx + (size_t)tile_of(rb_n) * chunks * 64 * BITS;
+    float acc[16];
+    int L[16];
+#pragma unroll
+    for (int t = 0; t < 16; ++t) {
+      acc[t] = 0.f;
+      L[t] = -(end - c) * (BIAS * ((1 << BITS) - 1));  // (fixed point: set anew in every block)
+    }
+    int gq = 0, bg = 0;  // quantisation group, its block
+    float hs = 1.f;      // half the group's scale (1: one scale per row or tensor, applied at the end)
+    uint32_t szv = 0;
+    bool enter = !IS_INT && p.grouped != 0;
+    if (enter) {
+      gq = (c >> 2) / bpg;
+      bg = (c >> 2) - gq * bpg;
+      szv = my_sz[(size_t)gq * 64];
+    }
+    for (; c < end;) {
+      const int lo = c & 3, hi = min(end - (c & ~3), 4);
+      c = (c & ~3) + hi;
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        ru32x4v e = next[i];
+        if constexpr (IS_INT) {
+          constexpr short be = (short)rows_int_bias(4);
+#pragma unroll
+          for (int d = 0; d < 4; ++d) e[d] = __builtin_bit_cast(uint32_t, (rs2v)(__builtin_bit_cast(rs2v, (uint32_t)e[d]) + rs2v{be, be}));
+        }
+        *reinterpret_cast<ru32x4v*>(tab + (i >> 1) * OSTRIDE + (i & 1) * 4096 + threadIdx.x * 16) = e;
+      }
+      __syncthreads();
+      if (c < end) request(set, c >> 2);
+      else if (left > 0) request(set_n, 0);
+      const uint32_t* const here = idx;
+      idx = c < end ? idx + 4 * 64 * BITS : left > 0 ? idx_n : idx;
+      // wavefronts that are behind come first (see above)
+      switch (4 * (todo - left - (end - c)) / (todo + 1)) {
+        case 0: __builtin_amdgcn_s_setprio(3); break;
+        case 1: __builtin_amdgcn_s_setprio(2); break;
+        case 2: __builtin_amdgcn_s_setprio(1); break;
+        default: __builtin_amdgcn_s_setprio(0); break;
+      }
+      if (enter) {  // a group starts, or the part starts inside one
+        enter = false;
+        const float s = __half2float(__ushort_as_half((uint16_t)(szv & 0xffffu)));
+        const float z = __half2float(__ushort_as_half((uint16_t)(szv >> 16)));
+        hs = 0.5f * s;
+        if (bg == 0 && lo == 0) {  // bias term of Section 4's linear transform: with the group's first chunk
+          const float bz = s * (p.mid - z);
+#pragma unroll
+          for (int t = 0; t < 16; ++t) acc[t] = fmaf(bz, sums[(size_t)gq * 16 + t], acc[t]);
+        }
+      }
+      float unit[16];  // value of one unit (wave-uniform); -0 where entries are not finite
+      if constexpr (!IS_INT) {
+#pragma unroll
+        for (int t = 0; t < 16; ++t) unit[t] = fix_scale[t];
+        fix_scale += 16;
+#pragma unroll
+        for (int t = 0; t < 16; ++t) L[t] = (lo - hi) * (BIAS * ((1 << BITS) - 1));  // minus the biases of the chunks to come
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (i >= lo && i < hi) {
+          if constexpr (IS_INT) rows_chunk_int<BITS, 2, OSTRIDE>(x[i & (AHEAD - 1)], lds0 + (uint32_t)i * CB, L);
+          else rows_chunk_fix<BITS, OSTRIDE, false>(x[i & (AHEAD - 1)], lds0 + (uint32_t)i * CB, L);
+        }
+        if (i >= (lo & (4 - AHEAD))) load_idx(i + AHEAD < 4 ? here + (i + AHEAD) * 64 * BITS : idx + (i + AHEAD - 4) * 64 * BITS, x[i & (AHEAD - 1)]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if constexpr (!IS_INT) {
+#pragma unroll
+        for (int t = 0; t < 16; ++t) {
+          flag |= __float_as_int(unit[t]);
+          acc[t] = fmaf((float)L[t], unit[t] * hs, acc[t]);
+        }
+        if (p.grouped && ++bg == bpg) {
+          bg = 0;
+          ++gq;
+          enter = true;
+          szv = my_sz[(size_t)min(gq, p.nq - 1) * 64];
+        }
+      }
+    }
+    if (tile_raw < p.n_tiles) {
+      const uint32_t slot = wg - p.share.first((uint32_t)(set * row_blocks + rb));
+      float* const part = p.ws_part + ((size_t)slot * p.N + n0) * p.Mp + tile_raw * 64 + lane;
+#pragma unroll
+      for (int t = 0; t < 16; ++t)
+        if (n0 + t < p.N) part[(size_t)t * p.Mp] = IS_INT ? __int_as_float(L[t]) : acc[t];
+    }
+    if (left <= 0) break;
+    c = 0;
+    rb = rb_n;
+    set = set_n;
+  }
+  if constexpr (!IS_INT) {
+    if (flag >= 0) return;
+    // the parts again, for the blocks whose entries are not finite
+    left = todo;
+    set = pair0 / row_blocks;
+    rb = pair0 - set * row_blocks;
+    c = c00;
+    while (left > 0) {
+      const int end = min(chunks, c + left), tile_raw = rb * ROWS_WAVES + wave;
+      if (tile_raw < p.n_tiles) {
+        const uint32_t slot = wg - p.share.first((uint32_t)(set * row_blocks + rb));
+        rows_add_raw<BITS>(p, p.fix_scale + (size_t)set * (chunks >> 2) * 16, p.idx + ((size_t)tile_raw * chunks * 64 + lane) * BITS,
+                           p.sz + (size_t)tile_raw * p.nq * 64 + lane, set * 16, c, end,
+                           p.ws_part + ((size_t)slot * p.N + set * 16) * p.Mp + tile_raw * 64 + lane, tile_raw * 64 + lane < p.M);
+      }
+      left -= end - c;
+      c = 0;
+      if (++rb == row_blocks) {
+        rb = 0;
+        ++set;
+      }
+    }
+  }
+}
+
+static RowsShare rows_share(int wgs, int total, int row_blocks, int chunks) {
+  return RowsShare{(uint32_t)wgs, (uint32_t)(total / wgs), (uint32_t)(total % wgs), (uint32_t)row_blocks, (uint32_t)chunks,
+                   rows_inverse((uint32_t)row_blocks), rows_inverse((uint32_t)chunks)};
+}
+
+template <bool IS_INT>
+static const void* rows_run_kernel(int bits) {
+  if constexpr (IS_INT) {
+    if (bits == 1) return reinterpret_cast<const void*>(mpgemm_run_kernel<1, IS_INT>);
+  }
+  return bits == 2   ? reinterpret_cast<const void*>(mpgemm_run_kernel<2, IS_INT>)
+         : bits == 3 ? reinterpret_cast<const void*>(mpgemm_run_kernel<3, IS_INT>)
+                     : reinterpret_cast<const void*>(mpgemm_run_kernel<4, IS_INT>);
+}
+
 template <bool SOLO>
 static const void* rows_fix_lookup(int bits) {
   return bits == 2   ? reinterpret_cast<const void*>(mpgemm_fix_kernel<2, SOLO>)
@@ -1399,6 +1654,13 @@ static hipError_t launch_rows_fix(const RowsParams& p, const RowsPlan& pl, int b
   local.tables = reinterpret_cast<const uint16_t*>(fix);
   local.fix_scale = scale;
   local.S = sums;
+  if (pl.fix_wgs) {
+    local.share = rows_share(pl.fix_wgs, pl.fix_total, pl.row_blocks, p.n_chunks);
+    void* args1[] = {&local};
+    e = hipLaunchKernel(rows_run_kernel<false>(bits), dim3((pl.fix_wgs + 7) / 8 * 8), dim3(64 * ROWS_WAVES), args1, 0, st);
+    if (e != hipSuccess) return e;
+    return launch_rows_sum<false, true>(local, 0, st);
+  }
   local.cps = pl.fix_cps;
   const void* fn = (p.grouped && p.cpg == 1) ? rows_fix_lookup<true>(bits) : rows_fix_lookup<false>(bits);
   void* args2[] = {&local};
@@ -1473,7 +1735,7 @@ static RowsPlan rows_plan_oct(const tmac_wdesc* desc, int N, int oct) {
   pl.part_bytes = pl.slices > 1 ? ((size_t)pl.slices * N * ge.Mp * 4 + 255) / 256 * 256 : 0;
   pl.ctr_bytes = 0;  // (no arrival counters: the slices meet in rows_sum_kernel)
   pl.fix = false;
-  pl.fix_cps = pl.fix_slices = pl.fix_tiles = pl.fix_shift = 0;
+  pl.fix_cps = pl.fix_slices = pl.fix_tiles = pl.fix_shift = pl.fix_wgs = pl.fix_total = pl.run_wgs = pl.run_total = 0;
   pl.fix_part_bytes = pl.fix_tab_bytes = pl.fix_scale_bytes = pl.fix_sums_bytes = 0;
   pl.srow_bytes = pl.eight ? ((size_t)pl.slices * N * 4 + 255) / 256 * 256 : 0;
   return pl;
@@ -1490,8 +1752,42 @@ static RowsPlan rows_plan_plain(const tmac_wdesc* desc, int N) {
   return one;
 }
 
-// Fixed-point tables (fp16 tables only) serve calls whose partial sums would not fit the library's own
-// array: tmac_mpgemm_noalloc, whose results are tmac_mpgemm's bit for bit, refuses exactly these.  (Calls
+// The run of chunks (RowsShare) for a call of `pairs` pairs: workgroups, chunks in all, most parts of a pair.
+struct RunPlan {
+  int wgs, total, parts;
+};
+static RunPlan rows_run(int64_t pairs, int row_blocks, int n_chunks) {
+  RunPlan r = {0, 0, 0};
+  const int64_t total = pairs * n_chunks;
+  // (the kernel's 32-bit arithmetic)
+  if (total >= (1 << 22) || total * n_chunks >= 0x100000000ll || pairs * row_blocks >= 0x100000000ll) return r;
+  r.wgs = (int)(total < ROWS_RUN_WGS ? total : ROWS_RUN_WGS);
+  r.total = (int)total;
+  const int per = r.total / r.wgs;  // at least this many chunks each
+  r.parts = r.total % r.wgs == 0 && n_chunks % per == 0 ? n_chunks / per : (n_chunks - 1) / per + 2;
+  return r;
+}
+
+// Which calls are served by a run of chunks (RowsShare), and which fp16 tables become fixed-point numbers.
+//
+// Run of chunks, integer tables (one scale per row or tensor, more than 32 rows): from ROWS_RUN_INT_CHUNKS on, twelve
+// for each workgroup.  Times as fast as K slices of equal length: 1.10 at 12288 chunks (96 rows x 4096 x 4096), 1.16 at
+// 16512 (48 x 11008 x 4096), 1.05 to 1.18 at 14000 to 57000; below, 1.00 at 8192 (64 x 4096 x 4096), 1.00 at 6144
+// (33 x 4096 x 4096), 0.96 at 5504 (16 x 11008 x 4096).
+// Run of chunks, fp16 tables and 2 to 4 bits, every 128-k block in one group, as fixed-point numbers:
+//   * built from activations (tmac_mpgemm_fused; the conversion takes the place of the precompute): from
+//     ROWS_RUN_ACT_CHUNKS on, 1.03 (320 x 5000 x 512, 2 bit) to 1.30 (48 x 11008 x 4096, 4 bit) times as fast as fp16
+//     sums.  Up to 32 rows the other side builds its tables in the look-up kernel and saves a launch: chunks times
+//     bits from ROWS_RUN_ACT_FEW on: 1.12 at 28672 (16 x 28672 x 2048, 4 bit), 1.00 and 0.96 at 22016 (16 and 12 x
+//     11008 x 4096, 4 bit), 0.95 at 16384 (32 x 4096 x 4096, 4 bit).
+//   * from a LUT buffer the conversion is one more launch: look-ups from ROWS_RUN_LUT_LOOKUPS on: 1.07 at 1.07e9 (64 x
+//     4096 x 4096, 4 bit), 1.05 at 0.8e9 (64 x 2048 x 8192, 3 bit), 1.09 (96 x 4096 x 4096, 2 bit); 0.89 to 1.01 at 0.3e9
+//     to 0.7e9; and ROWS_RUN_LUT_ROWS weight rows times bits for each table: 1.07 at 2100 (300 x 700 x 8192, 3 bit),
+//     0.86 at 768 (511 x 256 x 13760, 3 bit).  Within the library's own array where the plain plan is, because
+//     tmac_mpgemm_noalloc gives tmac_mpgemm's results bit for bit.
+// Other fp16 calls, and those of the rule that follows: K slices of equal length, or again a run of chunks.
+//
+// Fixed-point tables in K slices serve calls whose partial sums would not fit the library's own array.  (Calls
 // with so many workgroups that the plain plan leaves K whole have no partial sums and keep fp16 tables, as do
 // calls whose tables would not fit into the partial sums' room beside one slice's and those that would fill
 // less than two thirds of the chip there: K long against M, where the tables weigh most.)
@@ -1510,23 +1806,53 @@ static RowsPlan rows_plan_plain(const tmac_wdesc* desc, int N) {
 // 96 rows (1.1e9, 1.3e9, 1.6e9 look-ups), 0.985 at 130 rows and 2 bit against the general kernel (1.1e9);
 // with 40 rows there are too few workgroups (0.77 to 1.02), and at 1 bit it is 0.93 to 1.05 times as fast:
 // tables and launches weigh four times as much there.
-RowsPlan rows_plan(const tmac_wdesc* desc, int N) {
+RowsPlan rows_plan(const tmac_wdesc* desc, int N, bool from_act) {
   RowsPlan pl = rows_plan_plain(desc, N);
+  if (desc->g != 4 || N <= 8) return pl;
   const size_t room = pl.part_bytes + pl.ctr_bytes + pl.srow_bytes;
-  if (pl.nt != ROWS_NT_WIDE || desc->g != 4 || desc->bits < 2 || N < ROWS_FIX_MIN_N || room <= (size_t)TMAC_NOALLOC_MAX_WORKSPACE) return pl;
   const Geometry ge = geometry(desc);
-  if ((double)N * ge.Mp * (ge.Kp / 4) * desc->bits < (pl.eight ? 1.5e9 : 1.1e9)) return pl;
   const bool one_group = (desc->group == 0 || desc->group == desc->K);
   const int cpg = (one_group || desc->group < 32) ? 1 : desc->group / 32;
-  int unit = 4;  // whole 128-k blocks, whole groups
-  while (unit % cpg) unit += 4;
   const int tiles = (N + 15) / 16;
   const int64_t pairs = (int64_t)tiles * pl.row_blocks;
   const size_t slice = (size_t)N * ge.Mp * 4;
+  const RunPlan run = rows_run(pairs, pl.row_blocks, ge.n_chunks);
+  if (one_group && N > 32 && pl.nt == ROWS_NT_WIDE && run.total >= ROWS_RUN_INT_CHUNKS && (size_t)run.parts * slice <= room) {
+    pl.run_wgs = run.wgs;
+    pl.run_total = run.total;
+  }
+  if (desc->bits < 2) return pl;
+  int unit = 4;  // whole 128-k blocks, whole groups
+  while (unit % cpg) unit += 4;
   // units: one per 128-k block where no block holds parts of two groups, else one per chunk
   const int shift = (one_group || cpg % 4 == 0) ? 2 : 0;
   const size_t tab = (size_t)((N + 7) / 8) * (ge.Kp / 4) * 256, scale = (size_t)tiles * (ge.n_chunks >> 2) * 64;
   const size_t sums = (size_t)tiles * (one_group ? 1 : desc->K / desc->group) * 64;
+  const double lookups = (double)N * ge.Mp * (ge.Kp / 4) * desc->bits;
+  auto fixed = [&](size_t part_bytes) {
+    pl.fix = true;
+    pl.fix_tiles = tiles;
+    pl.fix_shift = shift;
+    pl.fix_part_bytes = part_bytes;
+    pl.fix_tab_bytes = tab;
+    pl.fix_scale_bytes = scale * (shift == 0 ? 4 : 1);
+    pl.fix_sums_bytes = sums;
+  };
+  const size_t run_parts = ((size_t)run.parts * slice + 255) / 256 * 256;
+  if (shift == 2 && run.wgs) {
+    bool take;
+    if (from_act) take = N > 32 ? run.total >= ROWS_RUN_ACT_CHUNKS : (int64_t)run.total * desc->bits >= ROWS_RUN_ACT_FEW;
+    else take = lookups >= ROWS_RUN_LUT_LOOKUPS && (int64_t)desc->M * desc->bits >= ROWS_RUN_LUT_ROWS && run.total >= ROWS_RUN_ACT_CHUNKS;
+    // (within the library's own array where the plain plan is)
+    if (!from_act && room <= (size_t)TMAC_NOALLOC_MAX_WORKSPACE && run_parts + tab + scale + sums > (size_t)TMAC_NOALLOC_MAX_WORKSPACE) take = false;
+    if (take) {
+      pl.fix_wgs = run.wgs;
+      pl.fix_total = run.total;
+      fixed(run_parts);
+      return pl;
+    }
+  }
+  if (pl.nt != ROWS_NT_WIDE || N < ROWS_FIX_MIN_N || room <= (size_t)TMAC_NOALLOC_MAX_WORKSPACE || lookups < (pl.eight ? 1.5e9 : 1.1e9)) return pl;
   const int want = (int)((ROWS_FIX_TARGET_WGS + pairs - 1) / pairs);
   const int cps = ((ge.n_chunks + want - 1) / want + unit - 1) / unit * unit;
   auto slices_of = [&](int c) { return (ge.n_chunks + c - 1) / c; };
@@ -1537,28 +1863,34 @@ RowsPlan rows_plan(const tmac_wdesc* desc, int N) {
     least += unit;
   }
   if (pairs * slices_of(least) < ROWS_FIX_LEAST_WGS) return pl;
+  if (shift == 2 && run.wgs) {
+    pl.fix_wgs = run.wgs;
+    pl.fix_total = run.total;
+    fixed(run_parts);
+    return pl;
+  }
   int use = least;
   while (use > cps && use > ROWS_FIX_SPLIT) use -= unit;
-  pl.fix = true;
   pl.fix_cps = use;
   pl.fix_slices = slices_of(use);
-  pl.fix_tiles = tiles;
-  pl.fix_part_bytes = part_of(use);
-  pl.fix_tab_bytes = tab;
-  pl.fix_scale_bytes = scale * (shift == 0 ? 4 : 1);
-  pl.fix_sums_bytes = sums;
-  pl.fix_shift = shift;
+  fixed(part_of(use));
   return pl;
 }
 
-bool rows_fixed_point(const tmac_wdesc* desc, int N) { return desc->g == 4 && rows_plan(desc, N).fix; }
+bool rows_fixed_from_act(const tmac_wdesc* desc, int N) { return desc->g == 4 && rows_plan(desc, N, true).fix; }
+
+// Whether the eight-chunk kernel could build the tables of a call that brings activations; such calls need a
+// leading dimension that is a multiple of eight, whichever kernel serves them.
+bool rows_reads_eight(const tmac_wdesc* desc, int N) {
+  return N <= 32 && desc->K % 8 == 0 && rows_plan_plain(desc, N).eight;  // (activations are summed eight at a time)
+}
 
 // Whether a call builds its tables inside the lookup kernel when it is given activations instead
 // of a LUT buffer: the eight-chunk kernel, up to 32 activation rows (every
 // block of 256 weight rows builds the tables again: from 64 rows on that costs more than the
 // launch of the precompute kernel it saves).
-bool rows_builds_tables(const tmac_wdesc* desc, int N) {
-  return N <= 32 && desc->K % 8 == 0 && rows_plan(desc, N).eight;  // (activations are summed eight at a time)
+bool rows_builds_tables(const tmac_wdesc* desc, int N, bool is_int) {
+  return rows_reads_eight(desc, N) && (is_int || !rows_fixed_from_act(desc, N));  // (activations are summed eight at a time)
 }
 
 // lut_dev: buffer of tmac_precompute_lut, or NULL with A_dev / lda given (only where
@@ -1569,14 +1901,14 @@ int launch_rows_gemm(const tmac_wdesc* desc, const void* packed_dev, const void*
   if (lut_t != TMAC_LUT_F16 && lut_t != TMAC_LUT_I16) return TMAC_EUNSUPPORTED;
   const bool from_act = fixed_from_act;  // fixed-point tables from the activations; lut_dev: room for a LUT buffer
   const bool fused = (lut_dev == nullptr);
-  if (fused && (!A_dev || !rows_builds_tables(desc, N))) return TMAC_EUNSUPPORTED;
-  if (from_act && (!lut_dev || !A_dev || lut_t != TMAC_LUT_F16 || !rows_fixed_point(desc, N))) return TMAC_EUNSUPPORTED;
+  if (fused && (!A_dev || !rows_builds_tables(desc, N, lut_t == TMAC_LUT_I16))) return TMAC_EUNSUPPORTED;
+  if (from_act && (!lut_dev || !A_dev || lut_t != TMAC_LUT_F16 || !rows_fixed_from_act(desc, N))) return TMAC_EUNSUPPORTED;
   const Geometry ge = geometry(desc);
   LutGeom lg;
   if (!lut_geom(N, desc->K, desc->g, desc->group, lut_t, &lg)) return TMAC_EINVAL;
   const bool is_int = (lut_t == TMAC_LUT_I16);
   const bool one_group = (desc->group == 0 || desc->group == desc->K);
-  const RowsPlan pl = rows_plan(desc, N);
+  const RowsPlan pl = rows_plan(desc, N, from_act);
   if (pl.n_tiles_n > 0x7fffffff || pl.row_blocks > 65535 || pl.slices > 65535) return TMAC_EUNSUPPORTED;
   if (pl.bytes() > 0) {
     if (!workspace_dev) return TMAC_EINVAL;
@@ -1626,6 +1958,9 @@ int launch_rows_gemm(const tmac_wdesc* desc, const void* packed_dev, const void*
   hipStream_t st = static_cast<hipStream_t>(stream);
   hipError_t e;
   p.fix_scale = nullptr;
+  p.lut_nt = pl.nt;
+  p.raw_nt = from_act ? 8 : pl.nt;
+  p.share = RowsShare{};
   p.fix_shift = pl.fix_shift;
   p.raw = nullptr;
   if (pl.fix && !is_int && !fused) {
@@ -1633,6 +1968,11 @@ int launch_rows_gemm(const tmac_wdesc* desc, const void* packed_dev, const void*
     e = launch_rows_fix(p, pl, desc->bits, from_act, lg.Geff, reinterpret_cast<uint32_t*>(tab),
                         reinterpret_cast<float*>(tab + pl.fix_tab_bytes),
                         reinterpret_cast<float*>(tab + pl.fix_tab_bytes + pl.fix_scale_bytes), st);
+  } else if (pl.run_wgs && is_int) {
+    p.share = rows_share(pl.run_wgs, pl.run_total, pl.row_blocks, p.n_chunks);
+    void* args[] = {&p};
+    e = hipLaunchKernel(rows_run_kernel<true>(desc->bits), dim3((pl.run_wgs + 7) / 8 * 8), dim3(64 * ROWS_WAVES), args, 0, st);
+    if (e == hipSuccess) e = launch_rows_sum<true, true>(p, 0, st);
   } else if (fused) e = is_int ? launch_rows8_nt<true, true>(p, pl.nt, desc->bits, st) : launch_rows8_nt<false, true>(p, pl.nt, desc->bits, st);
   else if (pl.eight) e = is_int ? launch_rows8_nt<true>(p, pl.nt, desc->bits, st) : launch_rows8_nt<false>(p, pl.nt, desc->bits, st);
   else e = is_int ? launch_rows_nt<true>(p, desc->g, pl.nt, pl.oct, desc->bits, st) : launch_rows_nt<false>(p, desc->g, pl.nt, pl.oct, desc->bits, st);

@@ -1328,6 +1328,65 @@ def test_fixed_point_rows_do_not_depend_on_rows_that_are_not_finite(T, torch, bi
     assert torch.equal(torch.nan_to_num(two, nan=1e30), torch.nan_to_num(one, nan=1e30))
 
 
+@pytest.mark.parametrize("N,M,K,bits,group,one_call", [
+    (40, 4999, 4000, 3, -1, True), (33, 5121, 4096, 2, 256, True), (511, 300, 4096, 2, 128, True), (200, 801, 4000, 4, 0, True),
+    (17, 20001, 2048, 4, 512, True), (12, 20481, 4096, 4, 128, False), (41, 8201, 4096, 4, 256, False),
+    (36, 9000, 4128, 3, -1, False)])
+def test_runs_of_chunks_with_fixed_point_tables(T, torch, N, M, K, bits, group, one_call):
+    """Calls dealt out as one run of chunks (RowsShare): workgroups whose share begins and ends inside a 128-k block, a
+    group and a pair, spans several pairs, sets of 16 rows that are not full, blocks of 256 weight rows that are not
+    full, LUT buffers four rows wide; the arithmetic of the rounding model on rows and columns at both ends and in the
+    middle (fp32 sums of at most K / 32 terms: 3e-6; fp16 sums are 3e-4 off it), every output against the oracle,
+    the same bits twice, rows that are not finite like a small call's and without effect on the others.  (K in whole
+    chunks: with one scale per row the model puts a chunk that K ends in into a stretch of its own.)"""
+    from paper_2407_00088_amd.runner import from_problem
+    rng = np.random.default_rng(1800 + N)
+    if group == 0:
+        p = wl.Problem("run", 0, N, M, K, bits, 0, wl.uniform_codes(rng, M, K, bits), None, None, weight_scale=0.05,
+                       zero_point=1.5, act=wl.gaussian_act(rng, N, K))
+    else:
+        p = wl.make_grouped(0, 1800 + N, N, M, K, bits, K if group < 0 else group, name="run")
+    lin = from_problem(p, layout=L3)
+    run = lin.forward_one_call if one_call else lin.forward
+    A = torch.from_numpy(p.act).cuda()
+    clean = run(A)
+    assert torch.equal(run(A), clean)
+    got, ref = clean.cpu().numpy(), oracle_fp(p)
+    assert_elementwise(got, ref, p)
+    rows, cols = sorted({0, 7, N // 2, N - 1}), np.r_[0:40, M // 2:M // 2 + 40, M - 40:M]
+    sub = lambda x: None if x is None else x[cols]
+    model = rm.lut_mpgemm_fixed(p.act[rows], p.q[cols], bits, sub(p.scales), sub(p.zeros), p.group, p.weight_scale, p.zero_point)
+    off = orc.rel_frobenius(got[np.ix_(rows, cols)], model)
+    print(f"run {N}x{M}x{K} w{bits} g{group}: from the model {off:.2e}", flush=True)
+    assert off <= 3e-6
+    assert torch.equal(run(A, out_t=T.TMAC_OUT_F16), clean.half())
+    B_ = A.clone()
+    B_[1, 100], B_[4, K - 1], B_[5, 132:136], B_[N - 1, K // 2] = float("inf"), float("nan"), 30000.0, -float("inf")
+    odd = [1, 4, 5, N - 1]
+    rest = [n for n in range(N) if n not in odd]
+    bad, small = run(B_), lin.forward(B_[odd].contiguous())
+    assert torch.equal(bad[rest], clean[rest])
+    for kind in (torch.isnan, torch.isposinf, torch.isneginf):
+        assert torch.equal(kind(bad[odd]), kind(small))
+    fin = torch.isfinite(small)
+    if bool(fin.any()):
+        assert float((bad[odd][fin].double() - small[fin].double()).norm() / small[fin].double().norm()) <= 1e-3
+
+
+@pytest.mark.parametrize("N,M,K", [(50, 8641, 4096), (300, 1999, 3232), (130, 4163, 2080)])
+def test_runs_of_chunks_with_integer_tables(T, torch, N, M, K):
+    """The same for integer tables with one scale per tensor: exact, in all output types."""
+    p = wl.make_ternary(0, 1850 + N, N, M, K, name="run_int")
+    lin = make_lin(p, L3)
+    A, s_a = torch.from_numpy(p.act_q).cuda(), torch.from_numpy(p.act_scale).cuda()
+    ref_i = orc.ternary_int_matmul(p.act_q, p.q, 1)
+    ref_f = orc.int_path_output_f32(ref_i, p.act_scale, p.weight_scale)
+    for run in (lin.forward, lin.forward_one_call):
+        assert np.array_equal(run(A, out_t=T.TMAC_OUT_I32, act_scale=s_a).cpu().numpy(), ref_i.astype(np.int32))
+        assert np.array_equal(run(A, act_scale=s_a).cpu().numpy().view(np.uint32), ref_f.view(np.uint32))
+        assert np.array_equal(run(A, out_t=T.TMAC_OUT_F16, act_scale=s_a).cpu().numpy(), ref_f.astype(np.float16))
+
+
 def test_large_call_takes_two_row_tiles_per_workgroup_by_default(T, torch):
     """From about 8000 wavefronts on (here 8192 x 8192: 1024 row tiles x 8 waves) the register-table
     kernel serves 16 rows per workgroup unless told otherwise: the default call, the call with 8 rows
