@@ -114,6 +114,19 @@ def _load() -> C.CDLL:
 lib = _load()
 
 
+def _load_calls():
+    """The native side of runner.LinearLUT's calls (csrc/tmac_python.cpp), given the library's functions."""
+    from . import _tmac_calls as calls
+    addr = [C.cast(getattr(lib, f), C.c_void_p).value for f in (
+        "tmac_mpgemv_fused", "tmac_precompute_lut", "tmac_mpgemm", "tmac_mpgemm_fused", "tmac_fused_workspace_bytes",
+        "tmac_mpgemv_fused_multi")]
+    calls.bind(TmacError, tmac_wdesc, *addr)
+    return calls
+
+
+calls = _load_calls()
+
+
 def status_str(status: int) -> str:
     return lib.tmac_status_str(int(status)).decode()
 
@@ -275,6 +288,8 @@ def tmac_mpgemv_fused_multi(items, N: int, out_t: int, act: Optional[int] = None
                             tuning: Optional[tmac_tuning] = None) -> None:
     """items: sequence of (desc, packed, A, out[, act_scale[, weight_scale]]) with device tensors;
     one launch serves them all."""
+    if stream is None and tuning is None and calls.multi(items, N, out_t, act):
+        return
     n = len(items)
     items = list(items)  # a sequence may make its tuples on access: what the library reads by address lives until it returns
     arr = (tmac_gemv_item * max(n, 1))()

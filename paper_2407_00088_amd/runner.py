@@ -81,14 +81,25 @@ class LinearLUT:
         B.tmac_mpgemm_fused(self.desc, self.packed if packed is None else packed, A, N, out, out_t, self.fused_ws,
                             act_scale=act_scale, weight_scale=self.weight_scale, stream=stream)
 
+    # The three forward_ calls go through the native side of the binding (B.calls), which answers None for what is
+    # not the ordinary case; then the same is done here, step by step.
+
     def forward_one_call(self, A, out_t: int = B.TMAC_OUT_F32, act_scale=None):
         N = A.shape[0]
         assert N <= self.max_N
+        out = B.calls.forward_one_call(self.desc, self.packed, A, self.M, out_t, None, act_scale, self.weight_scale, self.device,
+                                       getattr(self, "fused_ws", None))
+        if out is not None:
+            return out
         out = torch.empty((N, self.M), dtype=_OUT_DTYPE[out_t], device=self.device)
         self.mpgemm_fused(A, N, out, out_t, act_scale=act_scale)
         return out
 
     def forward_fused(self, A, out_t: int = B.TMAC_OUT_F32, act_scale=None, tuning=None, act=None):
+        if tuning is None:
+            out = B.calls.forward_fused(self.desc, self.packed, A, self.M, out_t, act, act_scale, self.weight_scale, self.device)
+            if out is not None:
+                return out
         N = A.shape[0]
         out = torch.empty((N, self.M), dtype=_OUT_DTYPE[out_t], device=self.device)
         self.mpgemv_fused(A, N, out, out_t, act_scale=act_scale, tuning=tuning, act=act)
@@ -97,6 +108,11 @@ class LinearLUT:
     def forward(self, A, out_t: int = B.TMAC_OUT_F32, act_scale=None, tuning=None):
         N = A.shape[0]
         assert N <= self.max_N
+        if tuning is None:
+            out = B.calls.forward(self.desc, self.packed, A, self.M, out_t, None, act_scale, self.weight_scale, self.device,
+                                  self.lut, self.lut_t, self.workspace, self.K, self.group, self.g)
+            if out is not None:
+                return out
         out = torch.empty((N, self.M), dtype=_OUT_DTYPE[out_t], device=self.device)
         self.precompute(A, N)
         self.mpgemm(N, out, out_t, act_scale=act_scale, tuning=tuning)

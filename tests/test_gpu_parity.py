@@ -1407,6 +1407,61 @@ def test_large_call_takes_two_row_tiles_per_workgroup_by_default(T, torch):
     assert np.array_equal(auto.view(np.uint32), fused.view(np.uint32))
 
 
+# ------------------------------------------------ native side of the binding ----
+
+class _NoCalls:
+    """Stands in for the native side: nothing is the ordinary case."""
+
+    def __getattr__(self, name):
+        return lambda *a: None
+
+
+@pytest.mark.parametrize("i8,out", [(False, 0), (False, 1), (True, 0), (True, 1), (True, 2)])
+def test_native_calls_give_the_bits_of_the_step_by_step_path(T, torch, monkeypatch, i8, out):
+    """runner's forward calls and the multi-matrix call through the native side and without it: both layouts, output
+    types, activation scales, leading dimensions, a workspace that is made on first use, refused arguments."""
+    from paper_2407_00088_amd import binding as B
+    from paper_2407_00088_amd.runner import from_problem
+    p = wl.make_ternary(0, 1900, 3, 200, 640) if i8 else wl.make_grouped(0, 1900, 3, 200, 640, 4, 64, name="native")
+    wide = torch.zeros((3, 656), dtype=torch.int8 if i8 else torch.float16, device="cuda")
+    A = wide[:, :640]
+    A.copy_(torch.from_numpy(p.act_q if i8 else p.act))
+    s_a = torch.from_numpy(p.act_scale).cuda() if i8 else torch.rand(3, device="cuda") + 0.5
+    lins = [from_problem(p, layout=L2), from_problem(p, layout=L3)]
+    dt = (torch.float32, torch.float16, torch.int32)[out]
+
+    def all_calls():
+        res = []
+        for lin in lins:
+            res.append(lin.forward(A, out_t=out, act_scale=s_a))
+            res += [lin.forward_one_call(A, out_t=out, act_scale=s_a) for _ in range(2)]
+        res.append(lins[0].forward_fused(A, out_t=out, act_scale=s_a))
+        outs = [torch.empty((3, 200), dtype=dt, device="cuda") for _ in range(2)]
+        items = [(lins[0].desc, lins[0].packed, A, o, s_a, lins[0].weight_scale) for o in outs]
+        T.tmac_mpgemv_fused_multi(items, 3, out)
+        return res + outs
+
+    native = all_calls()
+    assert B.calls.forward_fused(lins[0].desc, lins[0].packed, A, 200, out, None, s_a, lins[0].weight_scale, "cuda") is not None
+    other = torch.zeros((3, 640), dtype=torch.float16 if i8 else torch.int8, device="cuda")
+    errors = []
+    for _ in range(2):
+        for f in (lambda: lins[0].forward_fused(A, out_t=7), lambda: lins[0].forward_fused(A[:, :320].contiguous()),
+                  lambda: lins[0].forward_fused(other, act=B.TMAC_ACT_F16 if not i8 else B.TMAC_ACT_I8),
+                  lambda: lins[1].forward_fused(A), lambda: lins[1].forward(other, act_scale=s_a)):
+            with pytest.raises(Exception) as e:
+                f()
+            errors.append((type(e.value), str(e.value)))
+        with torch.cuda.stream(torch.cuda.Stream()):
+            streamed = lins[0].forward_fused(A, out_t=out, act_scale=s_a)
+            torch.cuda.current_stream().synchronize()
+        assert torch.equal(streamed, native[6])
+        monkeypatch.setattr(B, "calls", _NoCalls())
+    assert errors[:5] == errors[5:]
+    for a, b in zip(native, all_calls()):
+        assert a.dtype == b.dtype and torch.equal(a, b)
+
+
 # ------------------------------------------------------ measurement helpers ----
 
 def test_measurement_helpers_run_and_check_their_arguments(T, torch):
