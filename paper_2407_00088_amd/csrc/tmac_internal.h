@@ -159,28 +159,44 @@ __device__ inline __attribute__((always_inline)) float sum4_f16(uint32_t x01, ui
   asm("v_dot2_f32_f16 %0, %1, %2, 0" : "=v"(s) : "v"(x01), "s"(0x3C003C00u));
   return __builtin_amdgcn_fdot2(__builtin_bit_cast(tmac_h2, x23), ones, s, false);
 }
-// One wavefront per (n, quantisation group): the group sum S[n][gq] = sum of its activations,
-// four elements per lane and step (the row base, lda and the group size are multiples of 4),
-// then a butterfly.
+// Group sums S[n][gq] = sum of the activations of a quantisation group, four elements per lane and step (the row base,
+// lda and the group size are multiples of 4), then a butterfly.  Groups whose lanes fill a power of two share a
+// wavefront (the butterfly's other additions would be of zeros); group_sums_waves gives the number of wavefronts:
+// 45 rows of 101 groups of 32 took 4545 wavefronts with eight lanes at work in each.  Up to a thousand groups, a
+// wavefront per SIMD, have one each (one row of K = 4096 in groups of 128: 2.4 us for the whole precompute against 2.5).
 // BY16: stored as [set of 16 rows][group][16 rows] instead of [row][group].
+TMAC_HD inline int group_sum_lanes(int groups, int Geff) {
+  const int lanes = Geff / 4;
+  return groups > 1024 && lanes < 64 && (lanes & (lanes - 1)) == 0 ? lanes : 64;
+}
+inline int64_t group_sums_waves(int N, int nq, int Geff) {
+  const int per = 64 / group_sum_lanes(N * nq, Geff);
+  return ((int64_t)N * nq + per - 1) / per;
+}
 template <bool IS_INT, bool BY16 = false>
 __device__ inline __attribute__((always_inline)) void group_sums_wave(const void* __restrict__ A_, int N, int64_t lda,
                                                 void* __restrict__ S_, int Geff, int nq, int wave) {
-  const int lane = threadIdx.x & 63;
-  if (wave >= N * nq) return;
-  const int n = wave / nq, gq = wave % nq;
-  const size_t at = BY16 ? ((size_t)(n >> 4) * nq + gq) * 16 + (n & 15) : (size_t)wave;
+  const int lanes = group_sum_lanes(N * nq, Geff), log2 = 31 - __builtin_clz((unsigned)lanes);
+  const int lane = (int)(threadIdx.x & 63) & (lanes - 1);
+  const uint32_t id32 = ((uint32_t)wave << (6 - log2)) + ((threadIdx.x & 63) >> log2);  // (N nq stays far below 2^32)
+  const bool live = id32 < (uint32_t)(N * nq);
+  const int id = live ? (int)id32 : 0;
+  const int n = id / nq, gq = id % nq;
+  const size_t at = BY16 ? ((size_t)(n >> 4) * nq + gq) * 16 + (n & 15) : (size_t)id;
   const int64_t base = n * lda + (int64_t)gq * Geff;
   if constexpr (IS_INT) {
     const uint32_t* a = reinterpret_cast<const uint32_t*>(static_cast<const int8_t*>(A_) + base);
     int s = 0;
+#pragma unroll 4
     for (int k4 = lane; 4 * k4 < Geff; k4 += 64) s = __builtin_amdgcn_sdot4((int)a[k4], 0x01010101, s, false);
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-    if (lane == 0) static_cast<int*>(S_)[at] = s;
+    for (int o = 32; o > 0; o >>= 1)
+      if (o < lanes) s += __shfl_xor(s, o);
+    if (live && lane == 0) static_cast<int*>(S_)[at] = s;
   } else {
     const uint2* a = reinterpret_cast<const uint2*>(static_cast<const __half*>(A_) + base);
     float s = 0.f;
+#pragma unroll 4
     for (int k4 = lane; 4 * k4 < Geff; k4 += 64) {
       const uint2 v = a[k4];
       const float a0 = __half2float(__ushort_as_half((uint16_t)(v.x & 0xffffu)));
@@ -190,8 +206,9 @@ __device__ inline __attribute__((always_inline)) void group_sums_wave(const void
       s += (a0 + a1) + (a2 + a3);
     }
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-    if (lane == 0) static_cast<float*>(S_)[at] = s;
+    for (int o = 32; o > 0; o >>= 1)
+      if (o < lanes) s += __shfl_xor(s, o);
+    if (live && lane == 0) static_cast<float*>(S_)[at] = s;
   }
 }
 #endif

@@ -18,6 +18,7 @@
 #include <cstdint>
 #include <cstring>
 #include <tuple>
+#include <type_traits>
 #include <utility>
 
 #include "tmac.h"
@@ -125,21 +126,78 @@ __device__ __forceinline__ void staged_tables(const void* __restrict__ A_, int N
   }
 }
 
+// The same for n tiles of eight rows, a workgroup at a time: 32 tables of two neighbouring n tiles, thread = one table
+// of a pair of rows.  The two rows' terms sit side by side in a dword from the start, so that the eight entries of
+// the mirror half (Section 3.3) are twelve packed additions and leave for LDS in the order of the buffer; from there
+// 16 bytes a thread and store.  Bound by launch and memory.  256 rows of K = 5120: 5.1 us against 7.2 with one thread
+// for two entries of eight rows; 511 of K = 13760 16.8 against 33.5; 128 of K = 3200, int8, 3.3 against 4.7 (the group
+// sums' share of that: group_sums_wave); 45 of K = 3232, groups of 32, 3.0 against 4.2.
+constexpr int STAGE_TABLE = 64 + 4, STAGE_TILE = 32 * STAGE_TABLE + 32;  // dwords from table to table, n tile to n tile: no bank conflicts
 template <bool IS_INT>
+__device__ __forceinline__ void staged_block(const void* __restrict__ A_, int N, int K, int64_t lda, int KG,
+                                             uint4* __restrict__ tables, int block, uint32_t* stage) {
+  typedef short s2 __attribute__((ext_vector_type(2)));
+  using T2 = typename std::conditional<IS_INT, s2, tmac_h2>::type;
+  const int blocks = KG / 32, set = block / blocks, kg0 = block % blocks * 32;
+  const int u = threadIdx.x & 7, tb = threadIdx.x >> 3, kg = kg0 + tb, n = set * 16 + 2 * u;
+  T2 a[4];
+  if constexpr (IS_INT) {
+    uint32_t x = 0u, y = 0u;
+    if (4 * kg < K) {
+      const int8_t* const at = static_cast<const int8_t*>(A_) + 4 * kg;
+      if (n < N) x = *reinterpret_cast<const uint32_t*>(at + n * lda);
+      if (n + 1 < N) y = *reinterpret_cast<const uint32_t*>(at + (n + 1) * lda);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) a[j] = s2{(short)(int8_t)(x >> (8 * j)), (short)(int8_t)(y >> (8 * j))};
+  } else {
+    uint2 x = {0u, 0u}, y = {0u, 0u};
+    if (4 * kg < K) {
+      const __half* const at = static_cast<const __half*>(A_) + 4 * kg;
+      if (n < N) x = *reinterpret_cast<const uint2*>(at + n * lda);
+      if (n + 1 < N) y = *reinterpret_cast<const uint2*>(at + (n + 1) * lda);
+    }
+    a[0] = __builtin_bit_cast(T2, __builtin_amdgcn_perm(y.x, x.x, 0x05040100u));
+    a[1] = __builtin_bit_cast(T2, __builtin_amdgcn_perm(y.x, x.x, 0x07060302u));
+    a[2] = __builtin_bit_cast(T2, __builtin_amdgcn_perm(y.y, x.y, 0x05040100u));
+    a[3] = __builtin_bit_cast(T2, __builtin_amdgcn_perm(y.y, x.y, 0x07060302u));
+  }
+  // the additions of half_table_f16: pair sums first, then their sum
+  const T2 p = a[0] + a[1], m = a[0] - a[1], q = a[2] + a[3], w = a[2] - a[3];
+  const T2 e[8] = {-p - q, m - q, -m - q, p - q, w - p, m + w, w - m, p + w};
+  uint32_t* const dst = stage + (u >> 2) * STAGE_TILE + tb * STAGE_TABLE + (u & 3);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    dst[i * 4] = __builtin_bit_cast(uint32_t, e[i]);
+    dst[(15 - i) * 4] = IS_INT ? __builtin_bit_cast(uint32_t, (T2)(-e[i])) : __builtin_bit_cast(uint32_t, e[i]) ^ 0x80008000u;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int o = i >> 1, at = (i & 1) * 256 + (int)threadIdx.x, t8 = set * 2 + o;  // 16-byte piece of the n tile's 32 tables
+    if (t8 * 8 < N)
+      tables[((size_t)t8 * KG + kg0) * 16 + at] = *reinterpret_cast<const uint4*>(stage + o * STAGE_TILE + (at >> 4) * STAGE_TABLE + (at & 15) * 4);
+  }
+}
+
+// NT: activation rows of an n tile, 4 or 8
+template <bool IS_INT, int NT>
 __global__ __launch_bounds__(256) void precompute_kernel(const void* __restrict__ A_, int N, int K,
                                                          int64_t lda, int KG,
                                                          uint4* __restrict__ tables,
                                                          void* __restrict__ S_, void* __restrict__ S16_,
                                                          void* __restrict__ S128_,
                                                          uint4* __restrict__ HT, int U, int Geff, int nq,
-                                                         int n_tab_blocks, int n_stage_blocks, int NT) {
+                                                         int n_tab_blocks, int n_stage_blocks) {
   if ((int)blockIdx.x >= n_tab_blocks && (int)blockIdx.x < n_tab_blocks + n_stage_blocks) {
-    // the tables of the batched kernels, one thread per two entries of an n tile
-    const int64_t id = (int64_t)((int)blockIdx.x - n_tab_blocks) * 256 + threadIdx.x;
-    const int64_t n_ids = (int64_t)((N + NT - 1) / NT) * KG * 8;
-    if (id >= n_ids) return;
-    if (NT == 8) staged_tables<IS_INT, 4, 8>(A_, N, K, lda, KG, tables, id);
-    else staged_tables<IS_INT, 4, 4>(A_, N, K, lda, KG, tables, id);
+    // the tables of the batched kernels
+    if constexpr (NT == 8) {
+      __shared__ __attribute__((aligned(16))) uint32_t stage[2 * STAGE_TILE];
+      staged_block<IS_INT>(A_, N, K, lda, KG, tables, (int)blockIdx.x - n_tab_blocks, stage);
+    } else {  // one thread per two entries of an n tile
+      const int64_t id = (int64_t)((int)blockIdx.x - n_tab_blocks) * 256 + threadIdx.x;
+      if (id < (int64_t)((N + 3) / 4) * KG * 8) staged_tables<IS_INT, 4, 4>(A_, N, K, lda, KG, tables, id);
+    }
     return;
   }
   if ((int)blockIdx.x < n_tab_blocks) {
@@ -388,13 +446,13 @@ extern "C" tmac_status tmac_precompute_lut(const void* A_dev, tmac_act_t act, in
   if ((reinterpret_cast<uintptr_t>(A_dev) & a_align) != 0 || (lda % 4) != 0) return TMAC_EINVAL;
   if (lut_bytes < lg.total) return TMAC_ESIZE;
 
-  const int64_t n_sum_blocks64 = ((int64_t)N * lg.nq + 3) / 4;
+  const int64_t n_sum_blocks64 = (group_sums_waves(N, lg.nq, lg.Geff) + 3) / 4;
   const int64_t n_stage_ids = (int64_t)((N + lg.NT - 1) / lg.NT) * lg.KG * ((1 << g) / 2);
   const int64_t n_items = (int64_t)N * lg.KG;  // tables (g = 4: one lane each in the half-table part)
   // every part of the grid, and their sum, must fit the 32-bit block index
   if (n_sum_blocks64 + (n_stage_ids + 255) / 256 + (n_items + 255) / 256 > 0x7fffffff) return TMAC_EUNSUPPORTED;
   const int n_sum_blocks = (int)n_sum_blocks64;
-  const int n_stage_blocks = (int)((n_stage_ids + 255) / 256);
+  const int n_stage_blocks = (int)(g == 4 && lg.NT == 8 ? (int64_t)((N + 15) / 16) * (lg.KG / 32) : (n_stage_ids + 255) / 256);
   if (g != 4) {
     uint4* tables = static_cast<uint4*>(lut_dev);
     void* S = static_cast<char*>(lut_dev) + lg.s_off;
@@ -438,12 +496,10 @@ extern "C" tmac_status tmac_precompute_lut(const void* A_dev, tmac_act_t act, in
   uint4* HT = reinterpret_cast<uint4*>(static_cast<char*>(lut_dev) + lg.ht_off);
   hipStream_t st = static_cast<hipStream_t>(stream);
   const dim3 grid(n_tab_blocks + n_stage_blocks + n_sum_blocks), block(256);
-  const hipError_t e =
-      (act == TMAC_ACT_F16)
-          ? launch(precompute_kernel<false>, grid, block, 0, st, A_dev, N, K, lda, lg.KG, tables, S, S16, S128, HT,
-                   lg.U, lg.Geff, lg.nq, n_tab_blocks, n_stage_blocks, lg.NT)
-          : launch(precompute_kernel<true>, grid, block, 0, st, A_dev, N, K, lda, lg.KG, tables, S, S16, S128, HT,
-                   lg.U, lg.Geff, lg.nq, n_tab_blocks, n_stage_blocks, lg.NT);
+  const auto kernel = act == TMAC_ACT_F16 ? (lg.NT == 8 ? precompute_kernel<false, 8> : precompute_kernel<false, 4>)
+                                          : (lg.NT == 8 ? precompute_kernel<true, 8> : precompute_kernel<true, 4>);
+  const hipError_t e = launch(kernel, grid, block, 0, st, A_dev, N, K, lda, lg.KG, tables, S, S16, S128, HT, lg.U, lg.Geff, lg.nq,
+                              n_tab_blocks, n_stage_blocks);
   return e == hipSuccess ? TMAC_OK : TMAC_EHIP;
 }
 

@@ -1644,7 +1644,7 @@ static hipError_t launch_rows_fix(const RowsParams& p, const RowsPlan& pl, int b
   RowsParams local = p;
   local.raw = const_cast<uint16_t*>(p.tables);  // (written only where the tables are built here)
   int n_fix = pl.fix_tiles * (p.KG / 32);
-  const int64_t blocks = n_fix + (from_act ? ((int64_t)p.N * p.nq + 3) / 4 : 0);
+  const int64_t blocks = n_fix + (from_act ? (group_sums_waves(p.N, p.nq, Geff) + 3) / 4 : 0);
   if (blocks > 0x7fffffff) return hipErrorInvalidValue;
   void* args[] = {&local, &fix, &scale, &sums, &Geff, &n_fix};
   hipError_t e = hipLaunchKernel(from_act ? reinterpret_cast<const void*>(rows_fix_kernel<true>)
