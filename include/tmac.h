@@ -60,10 +60,9 @@ typedef enum { TMAC_ACT_F16 = 0, TMAC_ACT_I8 = 1, TMAC_ACT_F16_TQ = 2 } tmac_act
  *                 tmac_precompute_lut; results within 2e-3 relative Frobenius error of the fp64
  *                 product).
  *                 Calls of the batched kernels with g = 4, 2 to 4 bits, nine activation rows or more
- *                 and more than about 0.75e9 look-ups (N M K bits / 4; tmac_mpgemm_fused: 0.3e9), or
- *                 1.1e9 with groups that are no multiple of 128, look (unless K is so long against M
- *                 that the tables would weigh most; see rows_plan in csrc/tmac_rows.hip for the exact
- *                 lines) the entries up as 16-bit integers, rounded once to 2^-15 of the largest sum of
+ *                 and more than about 0.75e9 look-ups (N M K bits / 4; tmac_mpgemm_fused: 0.3e9) look
+ *                 (unless K is so long against M that the tables would weigh most; see rows_plan in
+ *                 csrc/tmac_rows.hip for the exact lines) the entries up as 16-bit integers, rounded once to 2^-15 of the largest sum of
  *                 eight entries in each (activation row, quantisation group of at most 128 k), whose
  *                 sums are exact: closer to the product than sums in fp16, unless those are exact
  *                 (small whole numbers).  Where a row's entries are not all finite, that row's

@@ -237,9 +237,9 @@ struct RowsPlan {
   size_t srow_bytes;             // ... and the slices' sums of every activation row (eight-chunk plans)
   // fp16 tables as fixed-point numbers (see rows_fix_kernel); fix == false: none of it
   bool fix;
-  int fix_cps, fix_slices, fix_tiles;               // chunks per K slice, K slices, sets of 16 activation rows
+  int fix_tiles;                                    // sets of 16 activation rows
   int run_wgs, run_total;                           // the same for integer tables
-  int fix_wgs, fix_total;                           // workgroups and chunks of the run (RowsShare); 0: K slices
+  int fix_wgs, fix_total;                           // workgroups and chunks of the run (RowsShare)
   int fix_shift;                                    // 2: a unit per 128-k block, 0: per chunk
   // inside the same workspace: partial sums, tables, their units, the group sums
   size_t fix_part_bytes, fix_tab_bytes, fix_scale_bytes, fix_sums_bytes;

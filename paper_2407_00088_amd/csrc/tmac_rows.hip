@@ -69,12 +69,12 @@ constexpr int ROWS_LDS = 32768;     // bytes of tables per LDS slice: 1024 k for
 constexpr int ROWS_FIX_TARGET_WGS = 2048;  // eight workgroups per CU
 constexpr int ROWS_FIX_LEAST_WGS = 640;    // fewer leave the chip idle
 constexpr int ROWS_RUN_WGS = 1024;         // four workgroups (one wavefront per SIMD each) per CU: what the chip holds at once
+constexpr int ROWS_RUN_LONG = 106496;      // chunks from which there are twice as many
 constexpr int ROWS_RUN_INT_CHUNKS = 12288; // chunks of pairs (RowsShare) from which the run serves a call: integer tables,
 constexpr int ROWS_RUN_ACT_CHUNKS = 5000;  // ... fp16 tables built from activations, more than 32 rows,
 constexpr int ROWS_RUN_ACT_FEW = 24576;    // ... times the bits, up to 32 rows,
 constexpr double ROWS_RUN_LUT_LOOKUPS = 0.75e9;  // ... fp16 tables from a LUT buffer: look-ups,
 constexpr int ROWS_RUN_LUT_ROWS = 1536;    // ... and weight rows times bits (rows_plan)
-constexpr int ROWS_FIX_SPLIT = 16;         // chunks: a longer K slice is split even if the workspace grows (rows_plan)
 constexpr int ROWS_FIX_MIN_N = 64;  // activation rows from which tables are turned into fixed-point numbers (rows_plan)
 constexpr int ROWS_NT_WIDE = 8;     // activation rows per workgroup when there are enough of them
 constexpr int ROWS_NT_NARROW = 4;   // ... and otherwise
@@ -99,9 +99,9 @@ struct RowsShare {
   __device__ uint32_t first(uint32_t pair) const { return owner(pair * chunks); }
   __device__ int parts(uint32_t pair) const { return (int)(owner((pair + 1) * chunks - 1) - first(pair)) + 1; }
 };
-// n / d = the high half of n * rows_inverse(d) for n d < 2^32 and d > 1; d == 1: 0, which rows_div takes for it
-inline uint32_t rows_inverse(uint32_t d) { return (uint32_t)((0x100000000ull + d - 1) / d); }
-__device__ __forceinline__ uint32_t rows_div(uint32_t n, uint32_t inverse) { return inverse ? __umulhi(n, inverse) : n; }
+// n / d = the high half of n * rows_inverse(d, n) for n d < 2^32 and d > 1; 0 else, for a division
+inline uint32_t rows_inverse(uint32_t d, uint64_t n) { return d > 1 && n * d < 0x100000000ull ? (uint32_t)((0x100000000ull + d - 1) / d) : 0u; }
+__device__ __forceinline__ uint32_t rows_div(uint32_t n, uint32_t d, uint32_t inverse) { return inverse ? __umulhi(n, inverse) : n / d; }
 
 struct RowsParams {
   const uint32_t* idx;     // [n_tiles][n_chunks][64][bits] dwords
@@ -1024,7 +1024,7 @@ static hipError_t launch_rows_sum(const RowsParams& p, int nz, hipStream_t st) {
 // ROWS_FIX_BIAS): additions of whole dwords are exact, and the sum of a chunk's eight pairs has two
 // clean halves, sum + 32768.
 // Where an activation row's entries are not all finite, the chunks of that unit hold zeros for this row and
-// the unit is -0; mpgemm_fix_kernel adds what their fp16 entries give, with fp16 additions, so that
+// the unit is -0; mpgemm_run_kernel adds what their fp16 entries give, with fp16 additions, so that
 // infinities and NaNs come out as they do in the general kernel (rows_add_raw).  Other rows do not notice.
 // The fp16 entries are read from the LUT buffer; a call that builds the integers from the activations writes
 // those blocks into the buffer's place in its workspace.
@@ -1273,167 +1273,35 @@ __device__ __forceinline__ void rows_add_raw(const RowsParams& p, const float* u
   }
 }
 
-// mpgemm_rows_kernel for fixed-point tables: two sets of eight activation rows per workgroup, tables
-// from the workspace (written by rows_fix_kernel), results through the workspace to rows_sum_kernel even
-// where there is one K slice only (finishing here as well costs 40 registers).  The integer sums of a
-// quantisation group and 128-k block are converted once and multiplied by their unit and half the group's
-// scale.  Bound by the look-up rate of LDS and the vector ALUs about equally, each about 70 % busy (see
-// rows_chunk_int).  The whole call at 256 rows x 5120 x 5120, 4 bit: 141 us against 164 with fp16 tables;
-// 511 rows x 13824 x 5120, 2 bit: 365 against 449.  (Tables of eight chunks staged with a wait: 143, 401;
-// five wavefronts per SIMD: 141, 391 -> 157, 440; next round's reads ahead: 160, 455.)
-// SOLO: groups of 32 k, every chunk a group and a unit of its own.  The first plane starts from the constant
-// and units and group sums are asked for before the chunk's look-ups and used after them: 511 rows x 13824 x
-// 5120 at 2 bit 424 us against 460 with the general loop (fp16 tables 499), 295 x 8881 x 6496 260 against 293
-// (272), 256 x 5120 x 13824 at 4 bit 377 against 399 (413).
-template <int BITS, bool SOLO>
-__global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_fix_kernel(const RowsParams p) {
-  using Sh = RowsShape<8, 4>;
-  constexpr int CB = Sh::CB, OSTRIDE = 4 * CB;
-  __shared__ __attribute__((aligned(2048))) char tab[2 * OSTRIDE];
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int n0 = blockIdx.x * 16;
-  const int tile_raw = blockIdx.y * ROWS_WAVES + wave;
-  const bool tile_ok = tile_raw < p.n_tiles;
-  const int tile = tile_ok ? tile_raw : p.n_tiles - 1;  // clamped: loads stay in range, stores are masked
-  const uint32_t* my_idx = p.idx + ((size_t)tile * p.n_chunks * 64 + lane) * BITS;
-  const uint32_t* my_sz = p.sz + (size_t)tile * p.nq * 64 + lane;
-  const uint32_t lds0 = (uint32_t)(uintptr_t)((rows_lds_char*)tab);
-  const int shift = SOLO ? 0 : p.fix_shift;
-  rows_const_float* const fix_scale = rows_const(p.fix_scale) + (size_t)blockIdx.x * (p.n_chunks >> shift) * 16;
-  rows_const_float* const sums = rows_const(p.S) + (size_t)blockIdx.x * p.nq * 16;
-  const int cz0 = blockIdx.z * p.cps, cz1 = min(cz0 + p.cps, p.n_chunks);
+// Which tables a run of chunks looks up: integer ones (one scale per row or tensor), or fixed-point ones with a unit
+// for each 128-k block, for each chunk where a group is one, or for each chunk else.
+enum { RUN_INT, RUN_BLOCK, RUN_SOLO, RUN_CHUNK };
 
-  float acc[16];
-#pragma unroll
-  for (int t = 0; t < 16; ++t) acc[t] = 0.f;
-  auto load_idx = [&](int c, uint32_t (&x)[BITS]) {
-    const uint32_t* src = my_idx + (size_t)c * 64 * BITS;
-    if constexpr (BITS == 4) {
-      const ru32x4v v = *reinterpret_cast<const ru32x4v*>(src);
-      x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
-    } else if constexpr (BITS == 2) {
-      const ru32x2v v = *reinterpret_cast<const ru32x2v*>(src);
-      x[0] = v.x; x[1] = v.y;
-    } else {
-#pragma unroll
-      for (int b = 0; b < BITS; ++b) x[b] = src[b];
-    }
-  };
-  int gq = p.grouped ? cz0 / p.cpg : 0, cg = 0;  // current quantisation group, chunks done in it (wave-uniform)
-  float hs = 1.f;                                // half the group's scale (1: one scale per row or tensor, applied at the end)
-  uint32_t szv_next = p.grouped ? my_sz[(size_t)min(gq, p.nq - 1) * 64] : 0u;
-  float unit[16];  // units of the sums in progress (wave-uniform); -0 where entries are not finite
-  int flag = 0;    // negative once there was such a unit
-  uint32_t xn[BITS];
-  load_idx(cz0, xn);
-
-  // the tables of a 128-k block, 8 KB for each set of eight rows, are requested while the block before it
-  // is looked up
-  const int last8 = (p.N + 7) / 8 - 1;  // (a second row set past it repeats it)
-  const char* const src0 = reinterpret_cast<const char*>(p.tables) + (size_t)(blockIdx.x * 2) * p.KG * Sh::TB + threadIdx.x * 16;
-  const char* const src1 = reinterpret_cast<const char*>(p.tables) + (size_t)min((int)blockIdx.x * 2 + 1, last8) * p.KG * Sh::TB + threadIdx.x * 16;
-  ru32x4v next[4];
-  auto request = [&](int c) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      next[i] = *reinterpret_cast<const ru32x4v*>(src0 + (size_t)c * CB + i * 4096);
-      next[2 + i] = *reinterpret_cast<const ru32x4v*>(src1 + (size_t)c * CB + i * 4096);
-    }
-  };
-  request(cz0);
-  for (int c0 = cz0; c0 < cz1; c0 += 4) {
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < 4; ++i) *reinterpret_cast<ru32x4v*>(tab + (i >> 1) * OSTRIDE + (i & 1) * 4096 + threadIdx.x * 16) = next[i];
-    __syncthreads();
-    if (c0 + 4 < cz1) request(c0 + 4);
-    int L[16];
-    bool first = true;
-    for (int c = c0; c < c0 + 4; ++c) {
-      uint32_t x[BITS];
-#pragma unroll
-      for (int b = 0; b < BITS; ++b) x[b] = xn[b];
-      load_idx(min(c + 1, cz1 - 1), xn);  // next chunk's indices, one chunk ahead
-      if constexpr (SOLO) {
-        if (c >= p.nq) break;  // (chunks in the K padding belong to no group)
-        const float s = __half2float(__ushort_as_half((uint16_t)(szv_next & 0xffffu)));
-        const float z = __half2float(__ushort_as_half((uint16_t)(szv_next >> 16)));
-        szv_next = my_sz[(size_t)min(c + 1, p.nq - 1) * 64];
-        float sum[16];
-#pragma unroll
-        for (int t = 0; t < 16; ++t) {
-          flag |= __float_as_int(unit[t] = fix_scale[(size_t)c * 16 + t]);
-          sum[t] = sums[(size_t)c * 16 + t];
-        }
-        rows_chunk_fix<BITS, OSTRIDE, true>(x, lds0 + (uint32_t)(c - c0) * (uint32_t)CB, L, -32768 * ((1 << BITS) - 1));
-        // half the scale times (look-ups + bias term), the latter as in Section 4's linear transform
-        const float bz = 2.f * (p.mid - z);
-        hs = 0.5f * s;
-#pragma unroll
-        for (int t = 0; t < 16; ++t) acc[t] = fmaf(hs, fmaf((float)L[t], unit[t], bz * sum[t]), acc[t]);
-        continue;
-      }
-      if (p.grouped && cg == 0 && gq < p.nq) {  // a group starts (chunks in the K padding belong to none)
-        const float s = __half2float(__ushort_as_half((uint16_t)(szv_next & 0xffffu)));
-        const float z = __half2float(__ushort_as_half((uint16_t)(szv_next >> 16)));
-        hs = 0.5f * s;
-        const float bz = s * (p.mid - z);
-#pragma unroll
-        for (int t = 0; t < 16; ++t)  // bias term of Section 4's linear transform
-          acc[t] = fmaf(bz, sums[(size_t)gq * 16 + t], acc[t]);
-        szv_next = my_sz[(size_t)min(gq + 1, p.nq - 1) * 64];
-      }
-      if (first) {  // sums start at minus the biases of the chunks they will hold
-#pragma unroll
-        for (int t = 0; t < 16; ++t) flag |= __float_as_int(unit[t] = fix_scale[(c >> shift) * 16 + t]);
-        int chunks = 4 - (c & 3);
-        if (p.grouped && gq < p.nq) chunks = min(chunks, p.cpg - cg);
-        const int L0 = -chunks * (32768 * ((1 << BITS) - 1));
-#pragma unroll
-        for (int t = 0; t < 16; ++t) L[t] = L0;
-      }
-      rows_chunk_fix<BITS, OSTRIDE, false>(x, lds0 + (uint32_t)(c - c0) * (uint32_t)CB, L);
-      const bool group_ends = p.grouped && gq < p.nq && ++cg == p.cpg;
-      first = group_ends || (c & 3) == 3;
-      if (first) {
-#pragma unroll
-        for (int t = 0; t < 16; ++t) acc[t] = fmaf((float)L[t], unit[t] * hs, acc[t]);
-      }
-      if (group_ends) {
-        cg = 0;
-        ++gq;
-      }
-    }
-  }
-
-  const int m = tile_raw * 64 + lane;
-  if (!tile_ok) return;
-#pragma unroll
-  for (int t = 0; t < 16; ++t)
-    if (n0 + t < p.N) p.ws_part[((size_t)blockIdx.z * p.N + n0 + t) * p.Mp + (size_t)m] = acc[t];
-  if (flag < 0)
-    rows_add_raw<BITS>(p, p.fix_scale + (size_t)blockIdx.x * (p.n_chunks >> shift) * 16, my_idx, my_sz, n0,
-                       cz0, cz1, p.ws_part + ((size_t)blockIdx.z * p.N + n0) * p.Mp + m, m < p.M);
-}
-
-// The same where every 128-k block lies in one quantisation group (or there is one scale per row or tensor), and
-// for integer tables with one scale per row or tensor: the call as one run of chunks (RowsShare), an equal share
-// for each of the 1024 workgroups that the chip holds at once, instead of two to four rounds of workgroups whose
-// last is nearly empty.  Bound by the look-up rate of LDS (rows_chunk_int); what a call takes beyond it is the
-// start of the stream (9 us of a 16 row call without any look-up), the tables and the slice sums.
-// Shares alone are slower than rounds (256 rows x 5120 x 5120, 4 bit: 148 us against 137; 511 x 13824 x 5120, 2 bit:
-// 388 against 365; no matter how the pairs are ordered): a SIMD serves its oldest wavefront first, so one workgroup
-// of a CU is done after three quarters of the time and its place stays empty (12.2 wavefronts per CU on average, of
-// 16).  Wavefronts that are behind therefore get a higher priority.  Indices are requested two chunks ahead, at one
-// and two bits, whose chunks are over sooner, four (511 x 13824 x 5120: 351 us, two 356).
-// Us before (K slices of equal length) and now: 256 x 5120 x 5120, 4 bit 135.8, 132.3; 511 x 13824 x 5120, 2 bit
-// 362.4, 351; ternary 128 x 8640 x 3200 56.4, 50.2, 256 x 3200 x 8640 99.1, 94.2; against fp16 sums 48 x 11008 x
-// 4096, 4 bit 75.0, 57.9, 64 x 4096 x 4096 43.5, 36.1, 300 x 700 x 8192 71.8, 59.5.
+// Look-ups in fixed-point tables (from the workspace, written by rows_fix_kernel), and in integer tables with one scale
+// per row or tensor: two sets of eight activation rows per workgroup, the call as one run of chunks (RowsShare), an
+// equal share for each of the 1024 workgroups that the chip holds at once; results through the workspace to
+// rows_sum_kernel even where a pair has one part only (finishing here as well costs 40 registers).  The integer sums
+// of a quantisation group and 128-k block are converted once and multiplied by their unit and half the group's scale;
+// RUN_SOLO starts every chunk's sum from the constant and asks for units and group sums before its look-ups.
+// Bound by the look-up rate of LDS (rows_chunk_int): with tables and indices at hand the loop runs at 84 % of it at 4
+// bit (81 at 2 bit) with four wavefronts per SIMD, 86 with five, and neither earlier reads nor fewer additions change
+// that; what a call takes beyond it is the start of the stream (9 us of a 16 row call without any look-up), the tables
+// and the slice sums.
+// Shares alone are slower than two to four rounds of workgroups with K slices of equal length (256 rows x 5120 x 5120,
+// 4 bit: 148 us against 137; 511 x 13824 x 5120, 2 bit: 388 against 365; no matter how the pairs are ordered): a SIMD
+// serves its oldest wavefront first, so one workgroup of a CU is done after three quarters of the time and its place
+// stays empty (12.2 wavefronts per CU on average, of 16).  Wavefronts that are behind therefore get a higher priority.
+// Indices are requested two chunks ahead, at one and two bits, whose chunks are over sooner, four (511 x 13824 x 5120:
+// 351 us, two 356).
+// Us, K slices of equal length and now: 256 x 5120 x 5120, 4 bit 135.8, 132.3; 511 x 13824 x 5120, 2 bit 373, 356,
+// groups of 32 436, 417; 256 x 5120 x 5120 in groups of 32, 2 bit 102.1, 95.7; ternary 128 x 8640 x 3200 56.4, 50.2,
+// 256 x 3200 x 8640 99.1, 94.2; against fp16 sums 48 x 11008 x 4096, 4 bit 75.0, 57.9, in groups of 32 79.4, 60.5, 64 x
+// 4096 x 4096 43.5, 36.1, 300 x 700 x 8192 71.8, 59.5.
 // (The chunk loop not unrolled, indices handed from register to register: 53 and 382 us for the ternary and the 2-bit
 // call of 511 rows; a copy of it without the bounds of a share: 53.7 and 353.)
-template <int BITS, bool IS_INT>
+template <int BITS, int MODE>
 __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_run_kernel(const RowsParams p) {
+  constexpr bool IS_INT = MODE == RUN_INT;
   using Sh = RowsShape<8, 4>;
   constexpr int CB = Sh::CB, OSTRIDE = 4 * CB;
   constexpr int BIAS = IS_INT ? ROWS_CHUNK_BIAS : 32768;  // of a chunk's sum, per plane weight
@@ -1447,7 +1315,7 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_run_kernel(const Ro
   const int todo = (int)(p.share.start(wg + 1) - at0);
   if (todo <= 0) return;
   const int chunks = (int)p.share.chunks, row_blocks = (int)p.share.row_blocks;
-  const int pair0 = (int)rows_div(at0, p.share.inv_chunks), c00 = (int)(at0 - (uint32_t)pair0 * p.share.chunks);
+  const int pair0 = (int)rows_div(at0, p.share.chunks, p.share.inv_chunks), c00 = (int)(at0 - (uint32_t)pair0 * p.share.chunks);
   const uint32_t lds0 = (uint32_t)(uintptr_t)((rows_lds_char*)tab);
   const int last8 = (p.N + 7) / 8 - 1;  // (a second row set past it repeats it)
   const int bpg = p.cpg >> 2;           // blocks per quantisation group
@@ -1479,7 +1347,7 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_run_kernel(const Ro
       next[2 + i] = *reinterpret_cast<const ru32x4v*>(b1 + o + i * 4096);
     }
   };
-  int set = (int)rows_div((uint32_t)pair0, p.share.inv_row_blocks), rb = pair0 - set * row_blocks, c = c00, left = todo, flag = 0;
+  int set = (int)rows_div((uint32_t)pair0, p.share.row_blocks, p.share.inv_row_blocks), rb = pair0 - set * row_blocks, c = c00, left = todo, flag = 0;
   const uint32_t* idx = p.idx + ((size_t)tile_of(rb) * chunks + (c & ~3)) * 64 * BITS;
   constexpr int AHEAD = BITS <= 2 ? 4 : 2;
   uint32_t x[AHEAD][BITS];
@@ -1491,7 +1359,8 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_run_kernel(const Ro
     left -= end - c;
     const int n0 = set * 16, tile_raw = rb * ROWS_WAVES + wave;
     const uint32_t* const my_sz = p.sz + (size_t)tile_of(rb) * p.nq * 64 + lane;
-    rows_const_float* fix_scale = rows_const(p.fix_scale) + ((size_t)set * (chunks >> 2) + (c >> 2)) * 16;
+    constexpr int SHIFT = MODE == RUN_BLOCK ? 2 : 0;  // a unit for each block, or for each chunk
+    rows_const_float* fix_scale = rows_const(p.fix_scale) + ((size_t)set * (chunks >> SHIFT) + (c >> SHIFT)) * 16;
     rows_const_float* const sums = rows_const(p.S) + (size_t)set * p.nq * 16;
     const int rb_n = rb + 1 == row_blocks ? 0 : rb + 1, set_n = rb + 1 == row_blocks ? set + 1 : set;  // the next pair
     const uint32_t* const idx_n = p.idx + (size_t)tile_of(rb_n) * chunks * 64 * BITS;
@@ -1502,15 +1371,17 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_run_kernel(const Ro
       acc[t] = 0.f;
       L[t] = -(end - c) * (BIAS * ((1 << BITS) - 1));  // (fixed point: set anew in every block)
     }
-    int gq = 0, bg = 0;  // quantisation group, its block
+    int gq = 0, bg = 0;  // quantisation group, its block or chunk
     float hs = 1.f;      // half the group's scale (1: one scale per row or tensor, applied at the end)
     uint32_t szv = 0;
     bool enter = !IS_INT && p.grouped != 0;
     if (enter) {
-      gq = (c >> 2) / bpg;
-      bg = (c >> 2) - gq * bpg;
-      szv = my_sz[(size_t)gq * 64];
+      const int at = MODE == RUN_BLOCK ? c >> 2 : c, per = MODE == RUN_BLOCK ? bpg : p.cpg;
+      gq = at / per;  // (RUN_CHUNK: chunks in the K padding belong to no group)
+      bg = at - gq * per;
+      szv = my_sz[(size_t)min(gq, p.nq - 1) * 64];
     }
+    bool first = true;  // RUN_CHUNK: a sum starts
     for (; c < end;) {
       const int lo = c & 3, hi = min(end - (c & ~3), 4);
       c = (c & ~3) + hi;
@@ -1537,19 +1408,21 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_run_kernel(const Ro
         case 2: __builtin_amdgcn_s_setprio(1); break;
         default: __builtin_amdgcn_s_setprio(0); break;
       }
-      if (enter) {  // a group starts, or the part starts inside one
+      // half the scale of the group; its bias term (Section 4's linear transform) goes with its first chunk
+      auto enter_group = [&](bool starts) {
         enter = false;
         const float s = __half2float(__ushort_as_half((uint16_t)(szv & 0xffffu)));
         const float z = __half2float(__ushort_as_half((uint16_t)(szv >> 16)));
         hs = 0.5f * s;
-        if (bg == 0 && lo == 0) {  // bias term of Section 4's linear transform: with the group's first chunk
+        if (starts) {
           const float bz = s * (p.mid - z);
 #pragma unroll
           for (int t = 0; t < 16; ++t) acc[t] = fmaf(bz, sums[(size_t)gq * 16 + t], acc[t]);
         }
-      }
+      };
       float unit[16];  // value of one unit (wave-uniform); -0 where entries are not finite
-      if constexpr (!IS_INT) {
+      if constexpr (MODE == RUN_BLOCK) {
+        if (enter) enter_group(bg == 0 && lo == 0);  // a group starts, or the part starts inside one
 #pragma unroll
         for (int t = 0; t < 16; ++t) unit[t] = fix_scale[t];
         fix_scale += 16;
@@ -1559,13 +1432,68 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_run_kernel(const Ro
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         if (i >= lo && i < hi) {
-          if constexpr (IS_INT) rows_chunk_int<BITS, 2, OSTRIDE>(x[i & (AHEAD - 1)], lds0 + (uint32_t)i * CB, L);
-          else rows_chunk_fix<BITS, OSTRIDE, false>(x[i & (AHEAD - 1)], lds0 + (uint32_t)i * CB, L);
+          const uint32_t cbase = lds0 + (uint32_t)i * CB;
+          uint32_t (&xi)[BITS] = x[i & (AHEAD - 1)];
+          if constexpr (IS_INT) {
+            rows_chunk_int<BITS, 2, OSTRIDE>(xi, cbase, L);
+          } else if constexpr (MODE == RUN_BLOCK) {
+            rows_chunk_fix<BITS, OSTRIDE, false>(xi, cbase, L);
+          } else if constexpr (MODE == RUN_SOLO) {
+            if (gq < p.nq) {  // (chunks in the K padding belong to no group)
+              const float s = __half2float(__ushort_as_half((uint16_t)(szv & 0xffffu)));
+              const float z = __half2float(__ushort_as_half((uint16_t)(szv >> 16)));
+              szv = my_sz[(size_t)min(gq + 1, p.nq - 1) * 64];
+              float sum[16];
+#pragma unroll
+              for (int t = 0; t < 16; ++t) {
+                unit[t] = fix_scale[t];
+                sum[t] = sums[(size_t)gq * 16 + t];
+              }
+              fix_scale += 16;
+              rows_chunk_fix<BITS, OSTRIDE, true>(xi, cbase, L, -BIAS * ((1 << BITS) - 1));
+              const float bz = 2.f * (p.mid - z);
+              hs = 0.5f * s;
+#pragma unroll
+              for (int t = 0; t < 16; ++t) {
+                flag |= __float_as_int(unit[t]);
+                acc[t] = fmaf(hs, fmaf((float)L[t], unit[t], bz * sum[t]), acc[t]);
+              }
+              ++gq;
+            }
+          } else if (gq < p.nq) {
+            if (enter) {
+              enter_group(bg == 0);
+              szv = my_sz[(size_t)min(gq + 1, p.nq - 1) * 64];
+            }
+            if (first) {  // the chunks of this group left in this block and part
+#pragma unroll
+              for (int t = 0; t < 16; ++t) unit[t] = fix_scale[t];
+              const int n = min(hi - i, p.cpg - bg);
+#pragma unroll
+              for (int t = 0; t < 16; ++t) L[t] = -n * (BIAS * ((1 << BITS) - 1));
+            }
+            fix_scale += 16;
+            rows_chunk_fix<BITS, OSTRIDE, false>(xi, cbase, L);
+            const bool ends = ++bg == p.cpg;
+            first = ends || i + 1 == hi;
+            if (first) {
+#pragma unroll
+              for (int t = 0; t < 16; ++t) {
+                flag |= __float_as_int(unit[t]);
+                acc[t] = fmaf((float)L[t], unit[t] * hs, acc[t]);
+              }
+            }
+            if (ends) {
+              bg = 0;
+              ++gq;
+              enter = true;
+            }
+          }
         }
         if (i >= (lo & (4 - AHEAD))) load_idx(i + AHEAD < 4 ? here + (i + AHEAD) * 64 * BITS : idx + (i + AHEAD - 4) * 64 * BITS, x[i & (AHEAD - 1)]);
         __builtin_amdgcn_sched_barrier(0);
       }
-      if constexpr (!IS_INT) {
+      if constexpr (MODE == RUN_BLOCK) {
 #pragma unroll
         for (int t = 0; t < 16; ++t) {
           flag |= __float_as_int(unit[t]);
@@ -1602,7 +1530,7 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_run_kernel(const Ro
       const int end = min(chunks, c + left), tile_raw = rb * ROWS_WAVES + wave;
       if (tile_raw < p.n_tiles) {
         const uint32_t slot = wg - p.share.first((uint32_t)(set * row_blocks + rb));
-        rows_add_raw<BITS>(p, p.fix_scale + (size_t)set * (chunks >> 2) * 16, p.idx + ((size_t)tile_raw * chunks * 64 + lane) * BITS,
+        rows_add_raw<BITS>(p, p.fix_scale + (size_t)set * (chunks >> p.fix_shift) * 16, p.idx + ((size_t)tile_raw * chunks * 64 + lane) * BITS,
                            p.sz + (size_t)tile_raw * p.nq * 64 + lane, set * 16, c, end,
                            p.ws_part + ((size_t)slot * p.N + set * 16) * p.Mp + tile_raw * 64 + lane, tile_raw * 64 + lane < p.M);
       }
@@ -1618,24 +1546,17 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_run_kernel(const Ro
 
 static RowsShare rows_share(int wgs, int total, int row_blocks, int chunks) {
   return RowsShare{(uint32_t)wgs, (uint32_t)(total / wgs), (uint32_t)(total % wgs), (uint32_t)row_blocks, (uint32_t)chunks,
-                   rows_inverse((uint32_t)row_blocks), rows_inverse((uint32_t)chunks)};
+                   rows_inverse((uint32_t)row_blocks, (uint64_t)(total / chunks)), rows_inverse((uint32_t)chunks, (uint64_t)total)};
 }
 
-template <bool IS_INT>
+template <int MODE>
 static const void* rows_run_kernel(int bits) {
-  if constexpr (IS_INT) {
-    if (bits == 1) return reinterpret_cast<const void*>(mpgemm_run_kernel<1, IS_INT>);
+  if constexpr (MODE == RUN_INT) {
+    if (bits == 1) return reinterpret_cast<const void*>(mpgemm_run_kernel<1, MODE>);
   }
-  return bits == 2   ? reinterpret_cast<const void*>(mpgemm_run_kernel<2, IS_INT>)
-         : bits == 3 ? reinterpret_cast<const void*>(mpgemm_run_kernel<3, IS_INT>)
-                     : reinterpret_cast<const void*>(mpgemm_run_kernel<4, IS_INT>);
-}
-
-template <bool SOLO>
-static const void* rows_fix_lookup(int bits) {
-  return bits == 2   ? reinterpret_cast<const void*>(mpgemm_fix_kernel<2, SOLO>)
-         : bits == 3 ? reinterpret_cast<const void*>(mpgemm_fix_kernel<3, SOLO>)
-                     : reinterpret_cast<const void*>(mpgemm_fix_kernel<4, SOLO>);
+  return bits == 2   ? reinterpret_cast<const void*>(mpgemm_run_kernel<2, MODE>)
+         : bits == 3 ? reinterpret_cast<const void*>(mpgemm_run_kernel<3, MODE>)
+                     : reinterpret_cast<const void*>(mpgemm_run_kernel<4, MODE>);
 }
 
 // Tables to fixed point, look-ups, slice sums.
@@ -1654,20 +1575,12 @@ static hipError_t launch_rows_fix(const RowsParams& p, const RowsPlan& pl, int b
   local.tables = reinterpret_cast<const uint16_t*>(fix);
   local.fix_scale = scale;
   local.S = sums;
-  if (pl.fix_wgs) {
-    local.share = rows_share(pl.fix_wgs, pl.fix_total, pl.row_blocks, p.n_chunks);
-    void* args1[] = {&local};
-    e = hipLaunchKernel(rows_run_kernel<false>(bits), dim3((pl.fix_wgs + 7) / 8 * 8), dim3(64 * ROWS_WAVES), args1, 0, st);
-    if (e != hipSuccess) return e;
-    return launch_rows_sum<false, true>(local, 0, st);
-  }
-  local.cps = pl.fix_cps;
-  const void* fn = (p.grouped && p.cpg == 1) ? rows_fix_lookup<true>(bits) : rows_fix_lookup<false>(bits);
+  local.share = rows_share(pl.fix_wgs, pl.fix_total, pl.row_blocks, p.n_chunks);
+  const void* fn = pl.fix_shift == 2 ? rows_run_kernel<RUN_BLOCK>(bits) : p.cpg == 1 ? rows_run_kernel<RUN_SOLO>(bits) : rows_run_kernel<RUN_CHUNK>(bits);
   void* args2[] = {&local};
-  e = hipLaunchKernel(fn, dim3(pl.fix_tiles, (p.n_tiles + ROWS_WAVES - 1) / ROWS_WAVES, pl.fix_slices), dim3(64 * ROWS_WAVES),
-                      args2, 0, st);
+  e = hipLaunchKernel(fn, dim3((pl.fix_wgs + 7) / 8 * 8), dim3(64 * ROWS_WAVES), args2, 0, st);
   if (e != hipSuccess) return e;
-  return launch_rows_sum<false>(local, pl.fix_slices, st);
+  return launch_rows_sum<false, true>(local, 0, st);
 }
 
 template <bool IS_INT, int BITS, int NT, bool FUSED>
@@ -1735,7 +1648,7 @@ static RowsPlan rows_plan_oct(const tmac_wdesc* desc, int N, int oct) {
   pl.part_bytes = pl.slices > 1 ? ((size_t)pl.slices * N * ge.Mp * 4 + 255) / 256 * 256 : 0;
   pl.ctr_bytes = 0;  // (no arrival counters: the slices meet in rows_sum_kernel)
   pl.fix = false;
-  pl.fix_cps = pl.fix_slices = pl.fix_tiles = pl.fix_shift = pl.fix_wgs = pl.fix_total = pl.run_wgs = pl.run_total = 0;
+  pl.fix_tiles = pl.fix_shift = pl.fix_wgs = pl.fix_total = pl.run_wgs = pl.run_total = 0;
   pl.fix_part_bytes = pl.fix_tab_bytes = pl.fix_scale_bytes = pl.fix_sums_bytes = 0;
   pl.srow_bytes = pl.eight ? ((size_t)pl.slices * N * 4 + 255) / 256 * 256 : 0;
   return pl;
@@ -1756,12 +1669,15 @@ static RowsPlan rows_plan_plain(const tmac_wdesc* desc, int N) {
 struct RunPlan {
   int wgs, total, parts;
 };
-static RunPlan rows_run(int64_t pairs, int row_blocks, int n_chunks) {
+static RunPlan rows_run(int64_t pairs, int n_chunks) {
   RunPlan r = {0, 0, 0};
   const int64_t total = pairs * n_chunks;
-  // (the kernel's 32-bit arithmetic)
-  if (total >= (1 << 22) || total * n_chunks >= 0x100000000ll || pairs * row_blocks >= 0x100000000ll) return r;
-  r.wgs = (int)(total < ROWS_RUN_WGS ? total : ROWS_RUN_WGS);
+  if (total >= (1 << 30)) return r;  // (32-bit arithmetic in the kernel)
+  // (a second round of workgroups for long runs, whose shares drift apart all the same: 511 x 13824 x 5120, 276480 chunks,
+  // 2 bit, 359 -> 356 us, in groups of 32 434 -> 417; 511 x 8640 x 3200, 108800, ternary 141 -> 137; 460 x 2836 x 9536, 104400
+  // chunks, 228 -> 230; 256 x 5120 x 5120, 51200, 136 -> 139)
+  const int wgs = total >= ROWS_RUN_LONG ? 2 * ROWS_RUN_WGS : ROWS_RUN_WGS;
+  r.wgs = (int)(total < wgs ? total : wgs);
   r.total = (int)total;
   const int per = r.total / r.wgs;  // at least this many chunks each
   r.parts = r.total % r.wgs == 0 && n_chunks % per == 0 ? n_chunks / per : (n_chunks - 1) / per + 2;
@@ -1774,38 +1690,25 @@ static RunPlan rows_run(int64_t pairs, int row_blocks, int n_chunks) {
 // for each workgroup.  Times as fast as K slices of equal length: 1.10 at 12288 chunks (96 rows x 4096 x 4096), 1.16 at
 // 16512 (48 x 11008 x 4096), 1.05 to 1.18 at 14000 to 57000; below, 1.00 at 8192 (64 x 4096 x 4096), 1.00 at 6144
 // (33 x 4096 x 4096), 0.96 at 5504 (16 x 11008 x 4096).
-// Run of chunks, fp16 tables and 2 to 4 bits, every 128-k block in one group, as fixed-point numbers:
+// Run of chunks, fp16 tables and 2 to 4 bits, as fixed-point numbers (groups of 128 unless said otherwise):
 //   * built from activations (tmac_mpgemm_fused; the conversion takes the place of the precompute): from
-//     ROWS_RUN_ACT_CHUNKS on, 1.03 (320 x 5000 x 512, 2 bit) to 1.30 (48 x 11008 x 4096, 4 bit) times as fast as fp16
-//     sums.  Up to 32 rows the other side builds its tables in the look-up kernel and saves a launch: chunks times
+//     ROWS_RUN_ACT_CHUNKS on, 1.03 (320 x 5000 x 512, 2 bit) to 1.31 (48 x 11008 x 4096, 4 bit) times as fast as fp16
+//     sums, in groups of 32 1.07 (150 x 1000 x 4096, 2 bit) to 1.31.  Up to 32 rows the other side builds its tables in the look-up kernel and saves a launch: chunks times
 //     bits from ROWS_RUN_ACT_FEW on: 1.12 at 28672 (16 x 28672 x 2048, 4 bit), 1.00 and 0.96 at 22016 (16 and 12 x
 //     11008 x 4096, 4 bit), 0.95 at 16384 (32 x 4096 x 4096, 4 bit).
 //   * from a LUT buffer the conversion is one more launch: look-ups from ROWS_RUN_LUT_LOOKUPS on: 1.07 at 1.07e9 (64 x
 //     4096 x 4096, 4 bit), 1.05 at 0.8e9 (64 x 2048 x 8192, 3 bit), 1.09 (96 x 4096 x 4096, 2 bit); 0.89 to 1.01 at 0.3e9
 //     to 0.7e9; and ROWS_RUN_LUT_ROWS weight rows times bits for each table: 1.07 at 2100 (300 x 700 x 8192, 3 bit),
-//     0.86 at 768 (511 x 256 x 13760, 3 bit).  Within the library's own array where the plain plan is, because
+//     0.86 at 768 (511 x 256 x 13760, 3 bit).  Up to 32 rows twice the look-ups (20 x 12000 x 5120, 3 and 4 bit: 0.985),
+//     and where more than 15 % of the sets' rows do not exist, as many chunks as for integer tables (40 x 2700 x 8192, 4
+//     bit, 8448 chunks: 0.94).  Within the library's own array where the plain plan is, because
 //     tmac_mpgemm_noalloc gives tmac_mpgemm's results bit for bit.
-// Other fp16 calls, and those of the rule that follows: K slices of equal length, or again a run of chunks.
-//
-// Fixed-point tables in K slices serve calls whose partial sums would not fit the library's own array.  (Calls
-// with so many workgroups that the plain plan leaves K whole have no partial sums and keep fp16 tables, as do
-// calls whose tables would not fit into the partial sums' room beside one slice's and those that would fill
-// less than two thirds of the chip there: K long against M, where the tables weigh most.)
-//
-// The tables take the room of partial sums: K is split into fewer slices, about eight workgroups per CU.  Where
-// that room allows fewer still, slices of more than ROWS_FIX_SPLIT chunks are split all the same and the
-// workspace grows: two to five slices where eight workgroups per CU wanted seven to eighteen took up to 15 %
-// longer than fp16 tables (460 rows x 2836 x 9536, 3 bit, groups of 64: 293 us in three slices, 250 in six, 271
-// with fp16 tables; 539 x 1386 x 7872, 4 bit, groups of 64: 200, 180, 183).  Eighty such calls: 1.03 times as fast
-// as fp16 tables without it, 1.09 with it.  Shorter slices are not worth it (255 x 15975 x 320: 46 us with
-// what the room allows, 50 in three slices).
-//
-// The extra launch that converts the tables wants look-ups to pay for it.  Measured against the general
-// kernels: 64 rows x 11008 x 4096 at 4 bit 70.0 us against 79.0, 80 rows 84.0 against 96.3; at 4096 x
-// 4096, where the eight-chunk kernel pair is the other side, 1.00 / 0.98 / 1.09 times as fast at 64 / 80 /
-// 96 rows (1.1e9, 1.3e9, 1.6e9 look-ups), 0.985 at 130 rows and 2 bit against the general kernel (1.1e9);
-// with 40 rows there are too few workgroups (0.77 to 1.02), and at 1 bit it is 0.93 to 1.05 times as fast:
-// tables and launches weigh four times as much there.
+//   * else by the older line for calls whose partial sums would not fit the library's own array: 64 rows, 1.1e9
+//     look-ups (1.5e9 where the eight-chunk kernel pair is the other side), tables that fit into the room of the plain
+//     plan's partial sums beside those of K slices for about eight workgroups per CU or longer ones, and enough slices
+//     to fill two thirds of the chip.  (Calls with so many workgroups that the plain plan leaves K whole have no
+//     partial sums and keep fp16 tables.)  At 1 bit fixed point is 0.93 to 1.05 times as fast: tables and launches weigh
+//     four times as much there.
 RowsPlan rows_plan(const tmac_wdesc* desc, int N, bool from_act) {
   RowsPlan pl = rows_plan_plain(desc, N);
   if (desc->g != 4 || N <= 8) return pl;
@@ -1816,7 +1719,7 @@ RowsPlan rows_plan(const tmac_wdesc* desc, int N, bool from_act) {
   const int tiles = (N + 15) / 16;
   const int64_t pairs = (int64_t)tiles * pl.row_blocks;
   const size_t slice = (size_t)N * ge.Mp * 4;
-  const RunPlan run = rows_run(pairs, pl.row_blocks, ge.n_chunks);
+  const RunPlan run = rows_run(pairs, ge.n_chunks);
   if (one_group && N > 32 && pl.nt == ROWS_NT_WIDE && run.total >= ROWS_RUN_INT_CHUNKS && (size_t)run.parts * slice <= room) {
     pl.run_wgs = run.wgs;
     pl.run_total = run.total;
@@ -1829,28 +1732,32 @@ RowsPlan rows_plan(const tmac_wdesc* desc, int N, bool from_act) {
   const size_t tab = (size_t)((N + 7) / 8) * (ge.Kp / 4) * 256, scale = (size_t)tiles * (ge.n_chunks >> 2) * 64;
   const size_t sums = (size_t)tiles * (one_group ? 1 : desc->K / desc->group) * 64;
   const double lookups = (double)N * ge.Mp * (ge.Kp / 4) * desc->bits;
-  auto fixed = [&](size_t part_bytes) {
+  const size_t run_parts = ((size_t)run.parts * slice + 255) / 256 * 256;
+  auto fixed = [&]() {
     pl.fix = true;
+    pl.fix_wgs = run.wgs;
+    pl.fix_total = run.total;
     pl.fix_tiles = tiles;
     pl.fix_shift = shift;
-    pl.fix_part_bytes = part_bytes;
+    pl.fix_part_bytes = run_parts;
     pl.fix_tab_bytes = tab;
     pl.fix_scale_bytes = scale * (shift == 0 ? 4 : 1);
     pl.fix_sums_bytes = sums;
   };
-  const size_t run_parts = ((size_t)run.parts * slice + 255) / 256 * 256;
-  if (shift == 2 && run.wgs) {
-    bool take;
-    if (from_act) take = N > 32 ? run.total >= ROWS_RUN_ACT_CHUNKS : (int64_t)run.total * desc->bits >= ROWS_RUN_ACT_FEW;
-    else take = lookups >= ROWS_RUN_LUT_LOOKUPS && (int64_t)desc->M * desc->bits >= ROWS_RUN_LUT_ROWS && run.total >= ROWS_RUN_ACT_CHUNKS;
-    // (within the library's own array where the plain plan is)
-    if (!from_act && room <= (size_t)TMAC_NOALLOC_MAX_WORKSPACE && run_parts + tab + scale + sums > (size_t)TMAC_NOALLOC_MAX_WORKSPACE) take = false;
-    if (take) {
-      pl.fix_wgs = run.wgs;
-      pl.fix_total = run.total;
-      fixed(run_parts);
-      return pl;
-    }
+  if (!run.wgs) return pl;
+  bool take;
+  if (from_act) {
+    take = N > 32 ? run.total >= ROWS_RUN_ACT_CHUNKS : (int64_t)run.total * desc->bits >= ROWS_RUN_ACT_FEW;
+  } else {
+    const bool part_full = pl.nt == ROWS_NT_WIDE && N * 20 < tiles * 16 * 17;  // sets with many rows that do not exist
+    take = lookups >= (N > 32 ? 1 : 2) * ROWS_RUN_LUT_LOOKUPS && (int64_t)desc->M * desc->bits >= ROWS_RUN_LUT_ROWS &&
+           run.total >= (part_full ? ROWS_RUN_INT_CHUNKS : ROWS_RUN_ACT_CHUNKS);
+    const size_t own = (size_t)TMAC_NOALLOC_MAX_WORKSPACE;  // within the library's own array where the plain plan is
+    if (room <= own && run_parts + tab + scale * (shift == 0 ? 4 : 1) + sums > own) take = false;
+  }
+  if (take) {
+    fixed();
+    return pl;
   }
   if (pl.nt != ROWS_NT_WIDE || N < ROWS_FIX_MIN_N || room <= (size_t)TMAC_NOALLOC_MAX_WORKSPACE || lookups < (pl.eight ? 1.5e9 : 1.1e9)) return pl;
   const int want = (int)((ROWS_FIX_TARGET_WGS + pairs - 1) / pairs);
@@ -1863,17 +1770,7 @@ RowsPlan rows_plan(const tmac_wdesc* desc, int N, bool from_act) {
     least += unit;
   }
   if (pairs * slices_of(least) < ROWS_FIX_LEAST_WGS) return pl;
-  if (shift == 2 && run.wgs) {
-    pl.fix_wgs = run.wgs;
-    pl.fix_total = run.total;
-    fixed(run_parts);
-    return pl;
-  }
-  int use = least;
-  while (use > cps && use > ROWS_FIX_SPLIT) use -= unit;
-  pl.fix_cps = use;
-  pl.fix_slices = slices_of(use);
-  fixed(part_of(use));
+  fixed();
   return pl;
 }
 
@@ -1971,7 +1868,7 @@ int launch_rows_gemm(const tmac_wdesc* desc, const void* packed_dev, const void*
   } else if (pl.run_wgs && is_int) {
     p.share = rows_share(pl.run_wgs, pl.run_total, pl.row_blocks, p.n_chunks);
     void* args[] = {&p};
-    e = hipLaunchKernel(rows_run_kernel<true>(desc->bits), dim3((pl.run_wgs + 7) / 8 * 8), dim3(64 * ROWS_WAVES), args, 0, st);
+    e = hipLaunchKernel(rows_run_kernel<RUN_INT>(desc->bits), dim3((pl.run_wgs + 7) / 8 * 8), dim3(64 * ROWS_WAVES), args, 0, st);
     if (e == hipSuccess) e = launch_rows_sum<true, true>(p, 0, st);
   } else if (fused) e = is_int ? launch_rows8_nt<true, true>(p, pl.nt, desc->bits, st) : launch_rows8_nt<false, true>(p, pl.nt, desc->bits, st);
   else if (pl.eight) e = is_int ? launch_rows8_nt<true>(p, pl.nt, desc->bits, st) : launch_rows8_nt<false>(p, pl.nt, desc->bits, st);

@@ -1330,8 +1330,10 @@ def test_fixed_point_rows_do_not_depend_on_rows_that_are_not_finite(T, torch, bi
 
 @pytest.mark.parametrize("N,M,K,bits,group,one_call", [
     (40, 4999, 4000, 3, -1, True), (33, 5121, 4096, 2, 256, True), (511, 300, 4096, 2, 128, True), (200, 801, 4000, 4, 0, True),
-    (17, 20001, 2048, 4, 512, True), (12, 20481, 4096, 4, 128, False), (41, 8201, 4096, 4, 256, False),
-    (36, 9000, 4128, 3, -1, False)])
+    (17, 20001, 2048, 4, 512, True), (12, 30721, 4128, 4, -1, False), (41, 8201, 4096, 4, 256, False),
+    (36, 9000, 4128, 3, -1, False),
+    (40, 4999, 4000, 3, 32, True), (33, 5121, 4128, 2, 96, True), (200, 801, 4032, 4, 64, True), (41, 8201, 4096, 4, 64, False),
+    (36, 9000, 4128, 4, 96, False)])
 def test_runs_of_chunks_with_fixed_point_tables(T, torch, N, M, K, bits, group, one_call):
     """Calls dealt out as one run of chunks (RowsShare): workgroups whose share begins and ends inside a 128-k block, a
     group and a pair, spans several pairs, sets of 16 rows that are not full, blocks of 256 weight rows that are not
