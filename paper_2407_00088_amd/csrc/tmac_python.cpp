@@ -17,6 +17,7 @@
 #include <torch/csrc/Device.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/csrc/utils/object_ptr.h>
 
 #include <cstdint>
 #include <cstring>
@@ -192,7 +193,11 @@ PyObject* forward_one_call(PyObject*, PyObject* const* a, Py_ssize_t n) {
 PyObject* multi(PyObject*, PyObject* const* a, Py_ssize_t n) {
   HANDLE_TH_ERRORS
   if (n != 4 || modes_active() || !(PyList_CheckExact(a[0]) || PyTuple_CheckExact(a[0]))) return ordinary_only();
-  const Py_ssize_t count = PySequence_Fast_GET_SIZE(a[0]);
+  // a tuple of its own: another thread may change a list while the library runs, and what it reads by address lives until
+  // it returns
+  const THPObjectPtr held(PySequence_Tuple(a[0]));
+  if (!held) return nullptr;
+  const Py_ssize_t count = PyTuple_GET_SIZE(held.get());
   if (count < 1 || count > TMAC_MULTI_MAX || !PyLong_CheckExact(a[1]) || !PyLong_CheckExact(a[2])) return ordinary_only();
   const long long N = PyLong_AsLongLong(a[1]), out_t = PyLong_AsLongLong(a[2]);
   long long act = -1;
@@ -205,7 +210,7 @@ PyObject* multi(PyObject*, PyObject* const* a, Py_ssize_t n) {
   tmac_wdesc descs[TMAC_MULTI_MAX];
   tmac_gemv_item items[TMAC_MULTI_MAX];
   for (Py_ssize_t i = 0; i < count; ++i) {
-    PyObject* const t = PySequence_Fast_GET_ITEM(a[0], i);
+    PyObject* const t = PyTuple_GET_ITEM(held.get(), i);
     if (!PyTuple_CheckExact(t) || PyTuple_GET_SIZE(t) < 4 || PyTuple_GET_SIZE(t) > 6) return ordinary_only();
     const Py_ssize_t len = PyTuple_GET_SIZE(t);
     const at::Tensor *packed = plain(PyTuple_GET_ITEM(t, 1)), *A = plain(PyTuple_GET_ITEM(t, 2)), *out = plain(PyTuple_GET_ITEM(t, 3));
