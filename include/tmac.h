@@ -64,8 +64,9 @@ typedef enum { TMAC_ACT_F16 = 0, TMAC_ACT_I8 = 1, TMAC_ACT_F16_TQ = 2 } tmac_act
  *                 (unless K is so long against M that the tables would weigh most; see rows_plan in
  *                 csrc/tmac_rows.hip for the exact lines) the entries up as 16-bit integers, rounded once to 2^-15 of the largest sum of
  *                 eight entries in each (activation row, quantisation group of at most 128 k), whose
- *                 sums are exact: closer to the product than sums in fp16, unless those are exact
- *                 (small whole numbers).  Where a row's entries are not all finite, that row's
+ *                 sums are exact: closer to the product than sums in fp16.  Entries that are multiples
+ *                 of a power of two not below that unit's size (whole numbers, fractions, subnormal
+ *                 numbers whose fp16 sums are exact) are not rounded.  Where a row's entries are not all finite, that row's
  *                 fp16 entries are looked up; other rows' results do not change.
  *   TMAC_LUT_I16: entries are exact int16 sums of int8 activations (|T| <= 4*127); all
  *                 aggregation is int32 and the result is bit-exact.

@@ -13,7 +13,8 @@ the 2e-3 bar" (which a wrong kernel could also be):
   32-k chunk gives one bit plane in fp16 before widening.  This is the library's own choice and it
   is lossy; the paper's "fast 8-bit aggregation" (Section 4) is a different, integer technique.
 * ``lut_mpgemm_fixed``: large calls round the entries once more, to 16-bit integers with one unit per
-  activation row and quantisation group of at most 128 k; every sum is exact from there on.
+  activation row and quantisation group of at most 128 k (a power of two where that holds the entries as
+  they are); every sum is exact from there on.
 
 They build on the oracle's exact steps (bit planes, indices, group sums) and are pinned by
 ``tests/test_rounding_models.py``.
@@ -125,19 +126,30 @@ def _scales_and_zeros(M, K, scales, zeros, group, weight_scale, zero_point):
 def fixed_point_tables(act, group, g=4):
     """fp16 tables rounded to multiples of one unit per (activation row, stretch of K that lies in one
     quantisation group and one 128-k block): the largest sum of eight entries a 32-k chunk of the stretch
-    can reach, divided by 32700 (fp32); nearest integer, ties to even.  K is padded to 128 with zeros."""
+    can reach, divided by 32700 (fp32), or the power of two from there on if all entries of the stretch are
+    multiples of it; nearest integer, ties to even.  K is padded to 128 with zeros."""
     lut = precompute_lut_fp16_tree(act, g).astype(np.float64)
     N, KG, E = lut.shape
     lut = np.concatenate([lut, np.zeros((N, -KG % 32, E))], axis=1)
     C, cpg = lut.shape[1] // 8, max(group // 32, 1)
     sums = np.abs(lut).max(2).reshape(N, C, 8).sum(2).astype(np.float32)
     top = sums.copy()
+
+    def same_unit(c):
+        return [d for d in range(c // 4 * 4, c // 4 * 4 + 4) if d // cpg == c // cpg]
     for c in range(C):
-        same = [d for d in range(c // 4 * 4, c // 4 * 4 + 4) if d // cpg == c // cpg]
-        top[:, c] = sums[:, same].max(1)
+        top[:, c] = sums[:, same_unit(c)].max(1)
     with np.errstate(divide="ignore"):
         factor = np.where(top > 0, np.float32(32700) / top, np.float32(0))
-    unit = (top / np.float32(32700)).astype(np.float64)
+        unit = (top / np.float32(32700)).astype(np.float64)
+        least = (top * np.float32(1 / 32700)).astype(np.float64)
+        power = np.where(top > 0, 2.0 ** np.ceil(np.log2(least)), 1.0)
+    whole = lut.reshape(N, C, 8 * E) / power[:, :, None]
+    whole = (whole == np.rint(whole)).all(2)
+    held = whole.copy()
+    for c in range(C):
+        held[:, c] = whole[:, same_unit(c)].all(1)
+    unit, factor = np.where(held, power, unit), np.where(held, 1.0 / power, factor)
     ints = np.rint(lut * np.repeat(factor.astype(np.float64), 8, axis=1)[:, :, None])
     assert np.abs(np.abs(ints).max(2).reshape(N, C, 8).sum(2)).max() < 32768
     return (ints * np.repeat(unit, 8, axis=1)[:, :, None])[:, :KG]

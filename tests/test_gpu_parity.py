@@ -1375,6 +1375,34 @@ def test_runs_of_chunks_with_fixed_point_tables(T, torch, N, M, K, bits, group, 
         assert float((bad[odd][fin].double() - small[fin].double()).norm() / small[fin].double().norm()) <= 1e-3
 
 
+@pytest.mark.parametrize("N,M,K,bits,group,one_call", [
+    (40, 4999, 4000, 3, -1, True), (40, 4999, 4000, 2, 32, True), (200, 801, 4032, 4, 64, True), (64, 4096, 4096, 4, 128, False),
+    (41, 8201, 4096, 4, 256, False), (130, 2700, 8160, 3, 96, False)])
+def test_fixed_point_tables_hold_few_bits_as_they_are(T, torch, N, M, K, bits, group, one_call):
+    """Rows of whole numbers, quarters, powers of two, subnormal numbers and ones, whose chunk sums fp16 holds exactly, are
+    exact in fixed point too but for the fp32 sums of at most K / 32 terms (3e-6; units that are no power of two:
+    9e-5); rows of four significant bits, and rows that are whole numbers in part, have some such units and others: the
+    arithmetic of the rounding model."""
+    from test_rounding_models import coarse_activations
+    from paper_2407_00088_amd.runner import from_problem
+    rng = np.random.default_rng(1900 + N)
+    p = wl.make_grouped(0, 1900 + N, N, M, K, bits, K if group < 0 else group, name="coarse")
+    kinds = ["+-10", "+-127", "quarters", "subnormal", "2^0..7", "ones", "mantissa4"]
+    for i, kind in enumerate(kinds):
+        p.act[i::8] = coarse_activations(rng, kind, len(p.act[i::8]), K)
+    p.act[7::8, : K // 3] = coarse_activations(rng, "+-127", len(p.act[7::8]), K)[:, : K // 3]
+    lin = from_problem(p, layout=L3)
+    got = (lin.forward_one_call if one_call else lin.forward)(torch.from_numpy(p.act).cuda()).cpu().numpy()
+    ref = oracle_fp(p)
+    for n in range(N):
+        if n % 8 < 6:
+            assert orc.rel_frobenius(got[n:n + 1], ref[n:n + 1]) <= 3e-6, (n, kinds[n % 8])
+    rows, cols = [5, 6, 7, 14, 15], np.r_[0:40, M - 40:M]
+    model = rm.lut_mpgemm_fixed(p.act[rows], p.q[cols], bits, p.scales[cols], p.zeros[cols], p.group)
+    for i, n in enumerate(rows):
+        assert orc.rel_frobenius(got[n:n + 1][:, cols], model[i:i + 1]) <= 3e-6, n
+
+
 @pytest.mark.parametrize("N,M,K", [(50, 8641, 4096), (300, 1999, 3232), (130, 4163, 2080)])
 def test_runs_of_chunks_with_integer_tables(T, torch, N, M, K):
     """The same for integer tables with one scale per tensor: exact, in all output types."""

@@ -1,5 +1,6 @@
 """Pins of the kernel-rounding models in tests/rounding_models.py (CPU only)."""
 import numpy as np
+import pytest
 
 import tmac_workloads as wl
 from oracle import tmac_oracle as orc
@@ -128,3 +129,42 @@ def test_fixed_point_tables_err_less_than_fp16_sums():
             fixed = orc.rel_frobenius(rm.lut_mpgemm_fixed(act, q, bits, s, z, group), ref)
             narrow = orc.rel_frobenius(rm.lut_mpgemm_narrow(act, q, bits, s, z, group), ref)
             assert fixed < narrow and fixed < 4e-4, (bits, group, ratio, fixed, narrow)
+
+
+def coarse_activations(rng, kind, N, K):
+    """Activations with few significant bits, or with sums that fp16 holds as they are."""
+    sign = rng.choice([-1.0, 1.0], size=(N, K))
+    normal = rng.standard_normal((N, K))
+    if kind.startswith("mantissa"):
+        m, e = np.frexp(normal)
+        bits = int(kind[8:])
+        return np.ldexp(np.round(m * 2 ** bits), e - bits).astype(np.float16)
+    return {"+-10": lambda: rng.integers(-10, 11, size=(N, K)), "+-127": lambda: rng.integers(-127, 128, size=(N, K)),
+            "quarters": lambda: rng.integers(-40, 41, size=(N, K)) / 4,
+            "subnormal": lambda: rng.integers(-500, 501, size=(N, K)) * 2.0 ** -24,
+            "1e-6": lambda: normal * 1e-6, "2^0..7": lambda: sign * 2.0 ** rng.integers(0, 8, size=(N, K)),
+            "2^-12..12": lambda: sign * 2.0 ** rng.integers(-12, 13, size=(N, K)),
+            "sparse": lambda: normal * (rng.random((N, K)) < 0.01), "relu": lambda: np.maximum(normal, 0),
+            "ones": lambda: np.ones((N, K))}[kind]().astype(np.float16)
+
+
+@pytest.mark.parametrize("kind,exact", [("+-10", True), ("+-127", True), ("quarters", True), ("subnormal", True), ("1e-6", True),
+                                        ("2^0..7", True), ("ones", True), ("2^-12..12", False), ("sparse", False),
+                                        ("relu", False), ("mantissa3", False), ("mantissa4", False), ("mantissa8", False)])
+def test_fixed_point_tables_are_no_further_off_on_activations_with_few_bits(kind, exact):
+    """Where the entries of a unit are multiples of a power of two that is a unit too, they are held as they are: whole
+    numbers, fractions of a power of two and subnormal numbers keep the exact sums that fp16 gives them, and nothing
+    with few significant bits is further from the product than with fp16 sums."""
+    rng = np.random.default_rng(97)
+    N, M, K = 3, 40, 2048
+    for bits, group in ((2, 32), (4, 128), (3, 96), (4, 2048)):
+        K_ = K // group * group
+        act = coarse_activations(rng, kind, N, K_)
+        q = rng.integers(0, 1 << bits, size=(M, K_), dtype=np.uint8)
+        s = rng.uniform(0.01, 0.1, size=(M, K_ // group)).astype(np.float16)
+        z = rng.uniform(0, 2 ** bits - 1, size=(M, K_ // group)).astype(np.float16)
+        ref = orc.mpgemm_definition(act, q, s, z, group)
+        fixed = orc.rel_frobenius(rm.lut_mpgemm_fixed(act, q, bits, s, z, group), ref)
+        narrow = orc.rel_frobenius(rm.lut_mpgemm_narrow(act, q, bits, s, z, group), ref)
+        assert fixed <= max(narrow, 1e-12), (kind, bits, group, fixed, narrow)
+        assert not exact or fixed <= 1e-12, (kind, bits, group, fixed)
