@@ -72,7 +72,8 @@ constexpr int ROWS_RUN_WGS = 1024;         // four workgroups (one wavefront per
 constexpr int ROWS_RUN_LONG = 106496;      // chunks from which there are twice as many
 constexpr int ROWS_RUN_INT_CHUNKS = 12288; // chunks of pairs (RowsShare) from which the run serves a call: integer tables,
 constexpr int ROWS_RUN_ACT_CHUNKS = 5000;  // ... fp16 tables built from activations, more than 32 rows,
-constexpr int ROWS_RUN_ACT_FEW = 24576;    // ... times the bits, up to 32 rows,
+constexpr int ROWS_RUN_ACT_BITS = 15000;   // ... times the bits,
+constexpr int ROWS_RUN_ACT_FEW = 24576;    // ... up to 32 rows,
 constexpr double ROWS_RUN_LUT_LOOKUPS = 0.75e9;  // ... fp16 tables from a LUT buffer: look-ups,
 constexpr int ROWS_RUN_LUT_ROWS = 1536;    // ... and weight rows times bits (rows_plan)
 constexpr int ROWS_FIX_MIN_N = 64;  // activation rows from which tables are turned into fixed-point numbers (rows_plan)
@@ -1732,10 +1733,12 @@ static RunPlan rows_run(int64_t pairs, int n_chunks) {
 // (33 x 4096 x 4096), 0.96 at 5504 (16 x 11008 x 4096).
 // Run of chunks, fp16 tables and 2 to 4 bits, as fixed-point numbers (groups of 128 unless said otherwise):
 //   * built from activations (tmac_mpgemm_fused; the conversion takes the place of the precompute): from
-//     ROWS_RUN_ACT_CHUNKS on, 1.03 (320 x 5000 x 512, 2 bit) to 1.31 (48 x 11008 x 4096, 4 bit) times as fast as fp16
-//     sums, in groups of 32 1.07 (150 x 1000 x 4096, 2 bit) to 1.31.  Up to 32 rows the other side builds its tables in the look-up kernel and saves a launch: chunks times
-//     bits from ROWS_RUN_ACT_FEW on: 1.12 at 28672 (16 x 28672 x 2048, 4 bit), 1.00 and 0.96 at 22016 (16 and 12 x
-//     11008 x 4096, 4 bit), 0.95 at 16384 (32 x 4096 x 4096, 4 bit).
+//     ROWS_RUN_ACT_CHUNKS on, and ROWS_RUN_ACT_BITS chunks times bits.  Of 41 random calls up to twice that line 39 are
+//     faster than with fp16 sums, 1.08 times on average (0.97 to 1.20; 0.93 at 511 x 1024 x 2048, 2 bit, and 40 x 4096 x
+//     4096, 3 bit; 1.31 at 48 x 11008 x 4096, 4 bit); of 19 below it, from 10000 on, six, 0.97 times as fast (0.83 to 1.07;
+//     40 x 4096 x 4096, 2 bit 26.4 us against 22.0).  Up to 32 rows the other side builds its tables in the look-up
+//     kernel and saves a launch: chunks times bits from ROWS_RUN_ACT_FEW on, 1.14 times on average (23 calls, 0.98 to 1.47;
+//     16 x 28672 x 2048, 4 bit 1.11), below it 0.91 (13 calls, 0.75 to 1.17).
 //   * from a LUT buffer the conversion is one more launch: look-ups from ROWS_RUN_LUT_LOOKUPS on: 1.07 at 1.07e9 (64 x
 //     4096 x 4096, 4 bit), 1.05 at 0.8e9 (64 x 2048 x 8192, 3 bit), 1.09 (96 x 4096 x 4096, 2 bit); 0.89 to 1.01 at 0.3e9
 //     to 0.7e9; and ROWS_RUN_LUT_ROWS weight rows times bits for each table: 1.07 at 2100 (300 x 700 x 8192, 3 bit),
@@ -1787,7 +1790,8 @@ RowsPlan rows_plan(const tmac_wdesc* desc, int N, bool from_act) {
   if (!run.wgs) return pl;
   bool take;
   if (from_act) {
-    take = N > 32 ? run.total >= ROWS_RUN_ACT_CHUNKS : (int64_t)run.total * desc->bits >= ROWS_RUN_ACT_FEW;
+    const int64_t by_bits = (int64_t)run.total * desc->bits;
+    take = N > 32 ? run.total >= ROWS_RUN_ACT_CHUNKS && by_bits >= ROWS_RUN_ACT_BITS : by_bits >= ROWS_RUN_ACT_FEW;
   } else {
     const bool part_full = pl.nt == ROWS_NT_WIDE && N * 20 < tiles * 16 * 17;  // sets with many rows that do not exist
     take = lookups >= (N > 32 ? 1 : 2) * ROWS_RUN_LUT_LOOKUPS && (int64_t)desc->M * desc->bits >= ROWS_RUN_LUT_ROWS &&

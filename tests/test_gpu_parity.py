@@ -1012,6 +1012,17 @@ def test_one_call_entry_point_fp(T, torch, layout, g, N, M, K, bits, group):
         assert orc.rel_frobenius(one, two) <= 2e-6
 
 
+@pytest.mark.parametrize("N,M,K,bits", [(40, 4096, 4096, 2), (96, 4096, 2048, 2), (48, 5120, 3200, 2), (40, 2861, 4832, 2)])
+def test_one_call_keeps_fp16_sums_where_they_are_faster(T, torch, N, M, K, bits):
+    """Calls with fewer chunks times bits than fixed-point tables need to pay for their conversion hold the tables of
+    tmac_precompute_lut + tmac_mpgemm and add them in fp16 (fixed point would be 3e-4 off)."""
+    from paper_2407_00088_amd.runner import from_problem
+    p = wl.make_grouped(0, 990 + N, N, M, K, bits, 32, name="onecall_below")
+    lin = from_problem(p, layout=L3)
+    A = torch.from_numpy(p.act).cuda()
+    assert orc.rel_frobenius(lin.forward_one_call(A).cpu().numpy(), lin.forward(A).cpu().numpy()) <= 2e-6
+
+
 @pytest.mark.parametrize("layout,N,M,K", [(L3, 12, 257, 3200), (L3, 70, 100, 8640), (L2, 2, 64, 3200)])
 def test_one_call_entry_point_int_exact(T, torch, layout, N, M, K):
     from paper_2407_00088_amd.runner import from_problem
