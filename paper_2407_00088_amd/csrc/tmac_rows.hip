@@ -69,7 +69,7 @@ constexpr int ROWS_LDS = 32768;     // bytes of tables per LDS slice: 1024 k for
 constexpr int ROWS_FIX_TARGET_WGS = 2048;  // eight workgroups per CU
 constexpr int ROWS_FIX_LEAST_WGS = 640;    // fewer leave the chip idle
 constexpr int ROWS_RUN_WGS = 1024;         // four workgroups (one wavefront per SIMD each) per CU: what the chip holds at once
-constexpr int ROWS_RUN_LONG = 106496;      // chunks from which there are twice as many
+constexpr int ROWS_RUN_LONG = 163840;      // chunks from which there are twice as many
 constexpr int ROWS_RUN_INT_CHUNKS = 12288; // chunks of pairs (RowsShare) from which the run serves a call: integer tables,
 constexpr int ROWS_RUN_ACT_CHUNKS = 5000;  // ... fp16 tables built from activations, more than 32 rows,
 constexpr int ROWS_RUN_ACT_BITS = 15000;   // ... times the bits,
@@ -1714,9 +1714,9 @@ static RunPlan rows_run(int64_t pairs, int n_chunks) {
   RunPlan r = {0, 0, 0};
   const int64_t total = pairs * n_chunks;
   if (total >= (1 << 30)) return r;  // (32-bit arithmetic in the kernel)
-  // (a second round of workgroups for long runs, whose shares drift apart all the same: 511 x 13824 x 5120, 276480 chunks,
-  // 2 bit, 359 -> 356 us, in groups of 32 434 -> 417; 511 x 8640 x 3200, 108800, ternary 141 -> 137; 460 x 2836 x 9536, 104400
-  // chunks, 228 -> 230; 256 x 5120 x 5120, 51200, 136 -> 139)
+  // (a second round of workgroups for long runs, whose shares drift apart all the same.  Times as fast as one round: of 17
+  // calls of 65536 to 138240 chunks 16 at 0.98 to 1.00, one at 1.005; of 14 of 163840 to 276480 nine at 1.004 to 1.05 (511 x 13824
+  // x 5120, 2 bit 356.5 -> 352.8 us, in groups of 32 435 -> 414), five at 0.99 to 1.00)
   const int wgs = total >= ROWS_RUN_LONG ? 2 * ROWS_RUN_WGS : ROWS_RUN_WGS;
   r.wgs = (int)(total < wgs ? total : wgs);
   r.total = (int)total;

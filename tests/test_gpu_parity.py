@@ -8,6 +8,9 @@ Every case runs in both packed layouts where both apply: layout 3 feeds the batc
 with one lane per weight row ("rows"), layout 2 the register-table decode kernel, called either as
 tmac_precompute_lut + tmac_mpgemm ("regs") or as the single fused launch tmac_mpgemv_fused
 ("fused")."""
+import os
+import re
+
 import numpy as np
 import pytest
 
@@ -1412,6 +1415,37 @@ def test_fixed_point_tables_hold_few_bits_as_they_are(T, torch, N, M, K, bits, g
     model = rm.lut_mpgemm_fixed(p.act[rows], p.q[cols], bits, p.scales[cols], p.zeros[cols], p.group)
     for i, n in enumerate(rows):
         assert orc.rel_frobenius(got[n:n + 1][:, cols], model[i:i + 1]) <= 3e-6, n
+
+
+def rows_constant(name):
+    """A constant of csrc/tmac_rows.hip: the lines between routes, so that a test says which side of one it is on."""
+    src = open(os.path.join(os.path.dirname(os.path.abspath(__file__)), "..", "paper_2407_00088_amd", "csrc", "tmac_rows.hip")).read()
+    return int(re.search(r"constexpr int %s = (\d+);" % name, src).group(1))
+
+
+def run_chunks(N, M, K):
+    """Chunks of a call's run: sets of 16 rows x blocks of 256 weight rows x 32-k chunks of K padded to 128."""
+    return -(-N // 16) * -(-M // 256) * -(-K // 128) * 4
+
+
+@pytest.mark.parametrize("N,M,K,bits,group,rounds", [(509, 13801, 3072, 2, 32, 2), (500, 14081, 3072, 3, 128, 2),
+                                                     (400, 6011, 7904, 2, 32, 1)])
+def test_long_runs_of_chunks_in_one_round_and_in_two(T, torch, N, M, K, bits, group, rounds):
+    """The longest runs have two workgroups for each place on the chip: every output against the oracle, the arithmetic
+    of the rounding model (fp32 sums of at most K / 32 terms: 3e-6), the same bits twice and from both entry points."""
+    from paper_2407_00088_amd.runner import from_problem
+    line = rows_constant("ROWS_RUN_LONG")
+    assert (run_chunks(N, M, K) >= line) == (rounds == 2) and run_chunks(N, M, K) >= line // 2
+    p = wl.make_grouped(0, 1880 + bits, N, M, K, bits, group, name="long")
+    lin = from_problem(p, layout=L3)
+    A = torch.from_numpy(p.act).cuda()
+    got = lin.forward(A)
+    assert torch.equal(lin.forward(A), got) and torch.equal(lin.forward_one_call(A), got)
+    got = got.cpu().numpy()
+    assert_elementwise(got, oracle_fp(p), p)
+    rows, cols = [0, N // 2, N - 1], np.r_[0:40, M // 2:M // 2 + 40, M - 40:M]
+    model = rm.lut_mpgemm_fixed(p.act[rows], p.q[cols], bits, p.scales[cols], p.zeros[cols], group)
+    assert orc.rel_frobenius(got[np.ix_(rows, cols)], model) <= 3e-6
 
 
 @pytest.mark.parametrize("N,M,K", [(50, 8641, 4096), (300, 1999, 3232), (130, 4163, 2080)])
