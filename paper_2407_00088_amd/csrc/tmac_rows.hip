@@ -66,8 +66,6 @@ typedef __attribute__((address_space(3))) const ru32x4v rows_lds_u32x4;
 constexpr int ROWS_WAVES = TMAC_ROWS_WAVES;  // 64-row tiles per workgroup
 constexpr int ROWS_TARGET_WGS = TMAC_ROWS_TARGET_WGS;  // K is split until a call has about this many workgroups
 constexpr int ROWS_LDS = 32768;     // bytes of tables per LDS slice: 1024 k for 4 activation rows, 512 k for 8
-constexpr int ROWS_FIX_TARGET_WGS = 2048;  // eight workgroups per CU
-constexpr int ROWS_FIX_LEAST_WGS = 640;    // fewer leave the chip idle
 constexpr int ROWS_RUN_WGS = 1024;         // four workgroups (one wavefront per SIMD each) per CU: what the chip holds at once
 constexpr int ROWS_RUN_LONG = 163840;      // chunks from which there are twice as many
 constexpr int ROWS_RUN_INT_CHUNKS = 12288; // chunks of pairs (RowsShare) from which the run serves a call: integer tables,
@@ -76,7 +74,6 @@ constexpr int ROWS_RUN_ACT_BITS = 15000;   // ... times the bits,
 constexpr int ROWS_RUN_ACT_FEW = 24576;    // ... up to 32 rows,
 constexpr double ROWS_RUN_LUT_LOOKUPS = 0.75e9;  // ... fp16 tables from a LUT buffer: look-ups,
 constexpr int ROWS_RUN_LUT_ROWS = 1536;    // ... and weight rows times bits (rows_plan)
-constexpr int ROWS_FIX_MIN_N = 64;  // activation rows from which tables are turned into fixed-point numbers (rows_plan)
 constexpr int ROWS_NT_WIDE = 8;     // activation rows per workgroup when there are enough of them
 constexpr int ROWS_NT_NARROW = 4;   // ... and otherwise
 constexpr int64_t ROWS_SUM_WIDE = 1 << 19;  // outputs from which the slice sums go four to a thread (two wavefronts per SIMD)
@@ -1741,17 +1738,12 @@ static RunPlan rows_run(int64_t pairs, int n_chunks) {
 //     16 x 28672 x 2048, 4 bit 1.11), below it 0.91 (13 calls, 0.75 to 1.17).
 //   * from a LUT buffer the conversion is one more launch: look-ups from ROWS_RUN_LUT_LOOKUPS on: 1.07 at 1.07e9 (64 x
 //     4096 x 4096, 4 bit), 1.05 at 0.8e9 (64 x 2048 x 8192, 3 bit), 1.09 (96 x 4096 x 4096, 2 bit); 0.89 to 1.01 at 0.3e9
-//     to 0.7e9; and ROWS_RUN_LUT_ROWS weight rows times bits for each table: 1.07 at 2100 (300 x 700 x 8192, 3 bit),
-//     0.86 at 768 (511 x 256 x 13760, 3 bit).  Up to 32 rows twice the look-ups (20 x 12000 x 5120, 3 and 4 bit: 0.985),
+//     to 0.7e9; and ROWS_RUN_LUT_ROWS weight rows times bits for each table: 1.05 at 2100 (300 x 700 x 8192, 3 bit), 0.90 to
+//     1.07 at 1200 to 1536 (eleven calls, seven below 1), 0.88 at 768 (511 x 256 x 13824, 3 bit).  Up to 32 rows twice the look-ups (20 x 12000 x 5120, 3 and 4 bit: 0.985),
 //     and where more than 15 % of the sets' rows do not exist, as many chunks as for integer tables (40 x 2700 x 8192, 4
 //     bit, 8448 chunks: 0.94).  Within the library's own array where the plain plan is, because
 //     tmac_mpgemm_noalloc gives tmac_mpgemm's results bit for bit.
-//   * else by the older line for calls whose partial sums would not fit the library's own array: 64 rows, 1.1e9
-//     look-ups (1.5e9 where the eight-chunk kernel pair is the other side), tables that fit into the room of the plain
-//     plan's partial sums beside those of K slices for about eight workgroups per CU or longer ones, and enough slices
-//     to fill two thirds of the chip.  (Calls with so many workgroups that the plain plan leaves K whole have no
-//     partial sums and keep fp16 tables.)  At 1 bit fixed point is 0.93 to 1.05 times as fast: tables and launches weigh
-//     four times as much there.
+// At 1 bit fixed point is 0.93 to 1.05 times as fast as fp16 sums: tables and launches weigh four times as much there.
 RowsPlan rows_plan(const tmac_wdesc* desc, int N, bool from_act) {
   RowsPlan pl = rows_plan_plain(desc, N);
   if (desc->g != 4 || N <= 8) return pl;
@@ -1768,25 +1760,12 @@ RowsPlan rows_plan(const tmac_wdesc* desc, int N, bool from_act) {
     pl.run_total = run.total;
   }
   if (desc->bits < 2) return pl;
-  int unit = 4;  // whole 128-k blocks, whole groups
-  while (unit % cpg) unit += 4;
   // units: one per 128-k block where no block holds parts of two groups, else one per chunk
   const int shift = (one_group || cpg % 4 == 0) ? 2 : 0;
-  const size_t tab = (size_t)((N + 7) / 8) * (ge.Kp / 4) * 256, scale = (size_t)tiles * (ge.n_chunks >> 2) * 64;
+  const size_t tab = (size_t)((N + 7) / 8) * (ge.Kp / 4) * 256, scale = (size_t)tiles * (ge.n_chunks >> shift) * 64;
   const size_t sums = (size_t)tiles * (one_group ? 1 : desc->K / desc->group) * 64;
   const double lookups = (double)N * ge.Mp * (ge.Kp / 4) * desc->bits;
   const size_t run_parts = ((size_t)run.parts * slice + 255) / 256 * 256;
-  auto fixed = [&]() {
-    pl.fix = true;
-    pl.fix_wgs = run.wgs;
-    pl.fix_total = run.total;
-    pl.fix_tiles = tiles;
-    pl.fix_shift = shift;
-    pl.fix_part_bytes = run_parts;
-    pl.fix_tab_bytes = tab;
-    pl.fix_scale_bytes = scale * (shift == 0 ? 4 : 1);
-    pl.fix_sums_bytes = sums;
-  };
   if (!run.wgs) return pl;
   bool take;
   if (from_act) {
@@ -1797,24 +1776,18 @@ RowsPlan rows_plan(const tmac_wdesc* desc, int N, bool from_act) {
     take = lookups >= (N > 32 ? 1 : 2) * ROWS_RUN_LUT_LOOKUPS && (int64_t)desc->M * desc->bits >= ROWS_RUN_LUT_ROWS &&
            run.total >= (part_full ? ROWS_RUN_INT_CHUNKS : ROWS_RUN_ACT_CHUNKS);
     const size_t own = (size_t)TMAC_NOALLOC_MAX_WORKSPACE;  // within the library's own array where the plain plan is
-    if (room <= own && run_parts + tab + scale * (shift == 0 ? 4 : 1) + sums > own) take = false;
+    if (room <= own && run_parts + tab + scale + sums > own) take = false;
   }
-  if (take) {
-    fixed();
-    return pl;
-  }
-  if (pl.nt != ROWS_NT_WIDE || N < ROWS_FIX_MIN_N || room <= (size_t)TMAC_NOALLOC_MAX_WORKSPACE || lookups < (pl.eight ? 1.5e9 : 1.1e9)) return pl;
-  const int want = (int)((ROWS_FIX_TARGET_WGS + pairs - 1) / pairs);
-  const int cps = ((ge.n_chunks + want - 1) / want + unit - 1) / unit * unit;
-  auto slices_of = [&](int c) { return (ge.n_chunks + c - 1) / c; };
-  auto part_of = [&](int c) { return ((size_t)slices_of(c) * slice + 255) / 256 * 256; };
-  int least = cps;  // the least chunks per slice that leave room for the tables
-  while (part_of(least) + tab + scale + sums > room) {
-    if (slices_of(least) == 1) return pl;
-    least += unit;
-  }
-  if (pairs * slices_of(least) < ROWS_FIX_LEAST_WGS) return pl;
-  fixed();
+  if (!take) return pl;
+  pl.fix = true;
+  pl.fix_wgs = run.wgs;
+  pl.fix_total = run.total;
+  pl.fix_tiles = tiles;
+  pl.fix_shift = shift;
+  pl.fix_part_bytes = run_parts;
+  pl.fix_tab_bytes = tab;
+  pl.fix_scale_bytes = scale;
+  pl.fix_sums_bytes = sums;
   return pl;
 }
 

@@ -1417,6 +1417,18 @@ def test_fixed_point_tables_hold_few_bits_as_they_are(T, torch, N, M, K, bits, g
         assert orc.rel_frobenius(got[n:n + 1][:, cols], model[i:i + 1]) <= 3e-6, n
 
 
+@pytest.mark.parametrize("N,M,K,bits,group", [(252, 747, 13312, 2, 32), (486, 727, 6528, 2, 64), (511, 256, 13824, 3, 128)])
+def test_few_weight_rows_keep_fp16_sums(T, torch, N, M, K, bits, group):
+    """Where few weight rows share each table its conversion does not pay, however many look-ups the call has: the
+    arithmetic of the model of fp16 sums (fp32 sums of the groups and slices: 3e-6; fixed point is 3e-4 off it)."""
+    from paper_2407_00088_amd.runner import from_problem
+    p = wl.make_grouped(0, 1890 + N, N, M, K, bits, group, name="few_rows")
+    got = from_problem(p, layout=L3).forward(torch.from_numpy(p.act).cuda()).cpu().numpy()
+    rows, cols = [0, N // 2, N - 1], np.r_[0:40, M - 40:M]
+    model = rm.lut_mpgemm_narrow(p.act[rows], p.q[cols], bits, p.scales[cols], p.zeros[cols], group)
+    assert orc.rel_frobenius(got[np.ix_(rows, cols)], model) <= 3e-6
+
+
 def rows_constant(name):
     """A constant of csrc/tmac_rows.hip: the lines between routes, so that a test says which side of one it is on."""
     src = open(os.path.join(os.path.dirname(os.path.abspath(__file__)), "..", "paper_2407_00088_amd", "csrc", "tmac_rows.hip")).read()
