@@ -82,21 +82,28 @@ class LinearLUT:
                             act_scale=act_scale, weight_scale=self.weight_scale, stream=stream)
 
     # The three forward_ calls go through the native side of the binding (B.calls), which answers None for what is
-    # not the ordinary case; then the same is done here, step by step.
+    # not the ordinary case; then the same is done here, step by step, as where a derived class has steps of its own.
+    _native = True
+
+    def __init_subclass__(cls, **kw):
+        super().__init_subclass__(**kw)
+        steps = ("precompute", "mpgemm", "mpgemv_fused", "mpgemm_fused")
+        cls._native = all(getattr(cls, step) is getattr(LinearLUT, step) for step in steps)
 
     def forward_one_call(self, A, out_t: int = B.TMAC_OUT_F32, act_scale=None):
         N = A.shape[0]
         assert N <= self.max_N
-        out = B.calls.forward_one_call(self.desc, self.packed, A, self.M, out_t, None, act_scale, self.weight_scale, self.device,
-                                       getattr(self, "fused_ws", None))
-        if out is not None:
-            return out
+        if self._native:
+            out = B.calls.forward_one_call(self.desc, self.packed, A, self.M, out_t, None, act_scale, self.weight_scale, self.device,
+                                           getattr(self, "fused_ws", None))
+            if out is not None:
+                return out
         out = torch.empty((N, self.M), dtype=_OUT_DTYPE[out_t], device=self.device)
         self.mpgemm_fused(A, N, out, out_t, act_scale=act_scale)
         return out
 
     def forward_fused(self, A, out_t: int = B.TMAC_OUT_F32, act_scale=None, tuning=None, act=None):
-        if tuning is None:
+        if tuning is None and self._native:
             out = B.calls.forward_fused(self.desc, self.packed, A, self.M, out_t, act, act_scale, self.weight_scale, self.device)
             if out is not None:
                 return out
@@ -108,7 +115,7 @@ class LinearLUT:
     def forward(self, A, out_t: int = B.TMAC_OUT_F32, act_scale=None, tuning=None):
         N = A.shape[0]
         assert N <= self.max_N
-        if tuning is None:
+        if tuning is None and self._native:
             out = B.calls.forward(self.desc, self.packed, A, self.M, out_t, None, act_scale, self.weight_scale, self.device,
                                   self.lut, self.lut_t, self.workspace, self.K, self.group, self.g)
             if out is not None:

@@ -1549,6 +1549,41 @@ def test_native_calls_give_the_bits_of_the_step_by_step_path(T, torch, monkeypat
         assert a.dtype == b.dtype and torch.equal(a, b)
 
 
+def test_forward_calls_take_the_steps_that_a_subclass_defines(T, torch):
+    """precompute, mpgemm, mpgemv_fused and mpgemm_fused of a class derived from LinearLUT are what its forward calls
+    go through."""
+    from paper_2407_00088_amd.runner import LinearLUT
+    seen = []
+
+    class Logged(LinearLUT):
+        def precompute(self, *a, **kw):
+            seen.append("precompute")
+            return super().precompute(*a, **kw)
+
+        def mpgemm(self, *a, **kw):
+            seen.append("mpgemm")
+            return super().mpgemm(*a, **kw)
+
+        def mpgemv_fused(self, *a, **kw):
+            seen.append("mpgemv_fused")
+            return super().mpgemv_fused(*a, **kw)
+
+        def mpgemm_fused(self, *a, **kw):
+            seen.append("mpgemm_fused")
+            return super().mpgemm_fused(*a, **kw)
+
+    p = wl.make_grouped(0, 1910, 2, 100, 512, 4, 128, name="derived")
+    args = (p.M, p.K, p.bits, p.group, p.q, p.scales, p.zeros)
+    A = torch.from_numpy(p.act).cuda()
+    plain, logged = LinearLUT(*args, max_N=2), Logged(*args, max_N=2)
+    for _ in range(2):                                            # (forward_one_call makes its workspace on first use)
+        for call, steps in (("forward", ["precompute", "mpgemm"]), ("forward_fused", ["mpgemv_fused"]),
+                            ("forward_one_call", ["mpgemm_fused"])):
+            seen.clear()
+            assert torch.equal(getattr(logged, call)(A), getattr(plain, call)(A))
+            assert seen == steps, call
+
+
 # ------------------------------------------------------ measurement helpers ----
 
 def test_measurement_helpers_run_and_check_their_arguments(T, torch):
