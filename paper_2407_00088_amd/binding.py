@@ -3,13 +3,15 @@
 Every step of the path (table precompute, lookup, accumulate, scale, reduce) runs in
 the library's HIP kernels; the offline packer runs in the library's host code.  torch
 is used for device memory and streams only.  There is no fallback: if the shared
-library is missing, importing this module raises.
+library is missing, importing this module raises.  (Without _tmac_calls.so, which only
+marshals arguments, it warns.)
 """
 from __future__ import annotations
 
 import ctypes as C
 import os
 import struct
+import warnings
 from dataclasses import dataclass
 from typing import Optional
 
@@ -21,6 +23,7 @@ import torch
 
 _PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG_DIR, "libtmac_hip.so")
+CALLS_LIB_PATH = os.path.join(_PKG_DIR, "_tmac_calls.so")
 
 TMAC_OK, TMAC_EINVAL, TMAC_EUNSUPPORTED, TMAC_ESIZE, TMAC_EHIP = range(5)
 TMAC_ACT_F16, TMAC_ACT_I8, TMAC_ACT_F16_TQ = 0, 1, 2
@@ -114,9 +117,27 @@ def _load() -> C.CDLL:
 lib = _load()
 
 
+class _NoCalls:
+    """In place of the native side where it cannot be loaded: no call is the ordinary case."""
+
+    @staticmethod
+    def _refuse(*args):
+        return None
+    forward_fused = forward = forward_one_call = multi = _refuse
+
+
 def _load_calls():
-    """The native side of runner.LinearLUT's calls (csrc/tmac_python.cpp), given the library's functions."""
-    from . import _tmac_calls as calls
+    """The native side of runner.LinearLUT's calls (csrc/tmac_python.cpp), given the library's functions.  It belongs to
+    the torch it was built with; without it every call goes through the functions below, as what is not the ordinary case
+    always does."""
+    try:
+        from . import _tmac_calls as calls
+        if calls.torch_version != torch.__version__:
+            raise ImportError(f"built with torch {calls.torch_version}")
+    except ImportError as e:
+        warnings.warn(f"{CALLS_LIB_PATH} is not used ({e}): calls take about 3 us more of host time; run "
+                      "`python -c 'import __graft_entry__ as g; g.build()'`", RuntimeWarning, stacklevel=2)
+        return _NoCalls()
     addr = [C.cast(getattr(lib, f), C.c_void_p).value for f in (
         "tmac_mpgemv_fused", "tmac_precompute_lut", "tmac_mpgemm", "tmac_mpgemm_fused", "tmac_fused_workspace_bytes",
         "tmac_mpgemv_fused_multi")]

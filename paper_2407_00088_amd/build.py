@@ -46,7 +46,7 @@ def _compile_calls(verbose: bool) -> None:
     import torch
     inc, lib = (os.path.join(os.path.dirname(torch.__file__), d) for d in ("include", "lib"))
     cmd = [os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "-x", "hip", "--offload-host-only", "-no-hip-rt", "-O2", "-std=c++17",
-           "-fPIC", "-shared", "-Wall", "-DUSE_ROCM", "-I" + os.path.join(ROOT, "include"), "-isystem", inc, "-isystem",
+           "-fPIC", "-shared", "-Wall", "-DUSE_ROCM", f'-DTMAC_TORCH_VERSION="{torch.__version__}"', "-I" + os.path.join(ROOT, "include"), "-isystem", inc, "-isystem",
            os.path.join(inc, "torch", "csrc", "api", "include"), "-isystem", sysconfig.get_path("include"),
            os.path.join(CSRC, "tmac_python.cpp"), "-o", CALLS_LIB_PATH, "-L" + lib, "-ltorch_python", "-ltorch_cpu", "-lc10",
            "-lc10_hip", "-Wl,-rpath," + lib]

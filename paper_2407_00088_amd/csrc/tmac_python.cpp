@@ -270,4 +270,12 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_tmac_calls", nullptr, -1, methods
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__tmac_calls() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__tmac_calls() {
+  PyObject* const m = PyModule_Create(&module);
+  // (torch's classes are compiled in: binding.py uses the module with this version only)
+  if (m && PyModule_AddStringConstant(m, "torch_version", TMAC_TORCH_VERSION) != 0) {
+    Py_DECREF(m);
+    return nullptr;
+  }
+  return m;
+}

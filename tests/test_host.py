@@ -355,6 +355,30 @@ def test_multi_keeps_items_made_on_access_alive_until_the_library_returns(monkey
     assert seen == [256, 320, 384]
 
 
+@pytest.mark.parametrize("how", ["sys.modules['paper_2407_00088_amd._tmac_calls'] = None", "torch.__version__ = '0.0'"])
+def test_package_imports_without_the_native_side_of_the_binding(how):
+    """_tmac_calls.so missing, or built with another torch: the package imports with a warning that says what to build, and
+    its calls take the path through ctypes."""
+    import subprocess
+    import sys
+    code = f"""
+import sys, warnings, torch
+{how}
+with warnings.catch_warnings(record=True) as seen:
+    warnings.simplefilter("always")
+    import paper_2407_00088_amd as T
+assert any("_tmac_calls.so" in str(w.message) and "build()" in str(w.message) for w in seen), [str(w.message) for w in seen]
+from paper_2407_00088_amd import binding as B
+assert B.calls.forward(1, 2) is None and B.calls.multi([], 1, 0, None) is None and T.tmac_version() >= 1
+try:
+    T.tmac_mpgemv_fused_multi([], 1, B.TMAC_OUT_F32, stream=type("S", (), dict(cuda_stream=0)))
+except B.TmacError as e:
+    print("refused by the library:", e.status)
+"""
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=300, cwd=ROOT)
+    assert r.returncode == 0 and "refused by the library" in r.stdout, r.stdout + r.stderr
+
+
 def test_bench_refuses_more_than_one_gpu():
     """bench.py measures one GPU's throughput; --gpus N with N > 1 ends with a message and a
     non-zero status before anything touches a device."""
