@@ -57,6 +57,13 @@ bool take_desc(PyObject* o, tmac_wdesc* desc) {
 
 bool modes_active() { return at::impl::torch_function_mode_enabled() || c10::impl::TorchDispatchModeTLS::any_modes_set(); }
 
+// Without the interpreter's lock, as in torch's own functions: a call's allocation may wait for the device, and what it
+// waits for may need another Python thread.
+struct Unlocked {
+  PyThreadState* const state = PyEval_SaveThread();
+  ~Unlocked() { PyEval_RestoreThread(state); }
+};
+
 // What all calls have in common.
 struct Call {
   tmac_wdesc desc;
@@ -65,6 +72,8 @@ struct Call {
   tmac_act_t act;
   tmac_out_t out_t;
   float weight_scale;
+  at::TensorOptions options;
+  int64_t width;
   at::Tensor out;
   void* stream;
 
@@ -94,10 +103,13 @@ struct Call {
     if (THPDevice_Check(a[8])) device = reinterpret_cast<THPDevice*>(a[8])->device;
     else if (!PyUnicode_Check(a[8]) || PyUnicode_CompareWithASCIIString(a[8], "cuda") != 0) return false;
     const at::ScalarType dt = out_t == TMAC_OUT_F32 ? at::kFloat : out_t == TMAC_OUT_F16 ? at::kHalf : at::kInt;
-    out = at::empty({A->size(0), (int64_t)M}, at::TensorOptions().dtype(dt).device(device));
+    options = at::TensorOptions().dtype(dt).device(device);
+    width = M;
     stream = c10::hip::getCurrentHIPStream().stream();
     return true;
   }
+
+  void allocate() { out = at::empty({A->size(0), width}, options); }
 };
 
 PyObject* refuse(tmac_status status, const char* where) {
@@ -122,12 +134,13 @@ PyObject* forward_fused(PyObject*, PyObject* const* a, Py_ssize_t n) {
   const void* packed = c.packed->data_ptr();
   const void* A = c.A->data_ptr();
   const float* scale = c.scale();
-  void* out = c.out.data_ptr();
-  const int64_t lda = c.A->stride(0), ldo = c.out.stride(0);
+  const int64_t lda = c.A->stride(0);
   tmac_status st;
-  Py_BEGIN_ALLOW_THREADS
-  st = g_mpgemv_fused(&c.desc, packed, A, c.act, c.N, lda, scale, c.weight_scale, out, c.out_t, ldo, c.stream);
-  Py_END_ALLOW_THREADS
+  {
+    const Unlocked unlocked;
+    c.allocate();
+    st = g_mpgemv_fused(&c.desc, packed, A, c.act, c.N, lda, scale, c.weight_scale, c.out.data_ptr(), c.out_t, c.out.stride(0), c.stream);
+  }
   return st == TMAC_OK ? THPVariable_Wrap(std::move(c.out)) : refuse(st, "tmac_mpgemv_fused");
   END_HANDLE_TH_ERRORS
 }
@@ -150,16 +163,19 @@ PyObject* forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
   const void* packed = c.packed->data_ptr();
   const void* A = c.A->data_ptr();
   const float* scale = c.scale();
-  void *out = c.out.data_ptr(), *lut_ptr = lut->data_ptr(), *ws_ptr = ws->data_ptr();
+  void *lut_ptr = lut->data_ptr(), *ws_ptr = ws->data_ptr();
   const size_t lut_bytes = lut->nbytes(), ws_bytes = ws->nbytes();
-  const int64_t lda = c.A->stride(0), ldo = c.out.stride(0);
+  const int64_t lda = c.A->stride(0);
   const tmac_lut_t lut_t = (tmac_lut_t)v[0];
   tmac_status first, second = TMAC_OK;
-  Py_BEGIN_ALLOW_THREADS
-  first = g_precompute_lut(A, c.act, c.N, (int32_t)v[1], lda, (int32_t)v[3], (int32_t)v[2], lut_t, lut_ptr, lut_bytes, c.stream);
-  if (first == TMAC_OK)
-    second = g_mpgemm(&c.desc, packed, lut_ptr, lut_t, c.N, scale, c.weight_scale, out, c.out_t, ldo, ws_ptr, ws_bytes, c.stream);
-  Py_END_ALLOW_THREADS
+  {
+    const Unlocked unlocked;
+    c.allocate();
+    first = g_precompute_lut(A, c.act, c.N, (int32_t)v[1], lda, (int32_t)v[3], (int32_t)v[2], lut_t, lut_ptr, lut_bytes, c.stream);
+    if (first == TMAC_OK)
+      second = g_mpgemm(&c.desc, packed, lut_ptr, lut_t, c.N, scale, c.weight_scale, c.out.data_ptr(), c.out_t, c.out.stride(0), ws_ptr,
+                        ws_bytes, c.stream);
+  }
   if (first != TMAC_OK) return refuse(first, "tmac_precompute_lut");
   return second == TMAC_OK ? THPVariable_Wrap(std::move(c.out)) : refuse(second, "tmac_mpgemm");
   END_HANDLE_TH_ERRORS
@@ -178,13 +194,16 @@ PyObject* forward_one_call(PyObject*, PyObject* const* a, Py_ssize_t n) {
   const void* packed = c.packed->data_ptr();
   const void* A = c.A->data_ptr();
   const float* scale = c.scale();
-  void *out = c.out.data_ptr(), *ws_ptr = ws->data_ptr();
+  void* const ws_ptr = ws->data_ptr();
   const size_t ws_bytes = ws->nbytes();
-  const int64_t lda = c.A->stride(0), ldo = c.out.stride(0);
+  const int64_t lda = c.A->stride(0);
   tmac_status st;
-  Py_BEGIN_ALLOW_THREADS
-  st = g_mpgemm_fused(&c.desc, packed, A, c.act, c.N, lda, scale, c.weight_scale, out, c.out_t, ldo, ws_ptr, ws_bytes, c.stream);
-  Py_END_ALLOW_THREADS
+  {
+    const Unlocked unlocked;
+    c.allocate();
+    st = g_mpgemm_fused(&c.desc, packed, A, c.act, c.N, lda, scale, c.weight_scale, c.out.data_ptr(), c.out_t, c.out.stride(0), ws_ptr,
+                        ws_bytes, c.stream);
+  }
   return st == TMAC_OK ? THPVariable_Wrap(std::move(c.out)) : refuse(st, "tmac_mpgemm_fused");
   END_HANDLE_TH_ERRORS
 }
@@ -231,9 +250,10 @@ PyObject* multi(PyObject*, PyObject* const* a, Py_ssize_t n) {
   }
   void* const stream = c10::hip::getCurrentHIPStream().stream();
   tmac_status st;
-  Py_BEGIN_ALLOW_THREADS
-  st = g_mpgemv_fused_multi(items, (int32_t)count, (tmac_act_t)act, (int32_t)N, (tmac_out_t)out_t, stream, nullptr);
-  Py_END_ALLOW_THREADS
+  {
+    const Unlocked unlocked;
+    st = g_mpgemv_fused_multi(items, (int32_t)count, (tmac_act_t)act, (int32_t)N, (tmac_out_t)out_t, stream, nullptr);
+  }
   if (st != TMAC_OK) return refuse(st, "tmac_mpgemv_fused_multi");
   Py_RETURN_TRUE;
   END_HANDLE_TH_ERRORS

@@ -1549,6 +1549,43 @@ def test_native_calls_give_the_bits_of_the_step_by_step_path(T, torch, monkeypat
         assert a.dtype == b.dtype and torch.equal(a, b)
 
 
+def test_native_calls_from_two_threads(T, torch):
+    """The native calls allocate and launch without the interpreter's lock: two threads, each with its matrices, stream and
+    changing numbers of rows, an emptied cache in between, get what one thread gets."""
+    import threading
+    from paper_2407_00088_amd.runner import from_problem
+    probs = [wl.make_grouped(0, 1920 + i, 40, 900 + i, 1024, 4, 128, name=f"thread{i}") for i in range(2)]
+    lins = [[from_problem(p, layout=L) for L in (L2, L3)] for p in probs]
+    acts = [torch.from_numpy(p.act).cuda() for p in probs]
+    sizes = (1, 8, 3, 40, 17)
+
+    def calls(i, n):
+        A = acts[i][:n].contiguous()
+        return [lins[i][0].forward_fused(A), lins[i][0].forward(A), lins[i][1].forward(A), lins[i][1].forward_one_call(A)]
+    want = [[calls(i, n) for n in sizes] for i in range(2)]
+    torch.cuda.synchronize()
+    failed = []
+
+    def work(i):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                for _ in range(8):
+                    for n, w in zip(sizes, want[i]):
+                        got = calls(i, n)
+                        torch.cuda.current_stream().synchronize()
+                        assert all(torch.equal(a, b) for a, b in zip(got, w)), (i, n)
+                    del got
+                    torch.cuda.empty_cache()
+        except BaseException as e:
+            failed.append(e)
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not failed, failed
+
+
 def test_forward_calls_take_the_steps_that_a_subclass_defines(T, torch):
     """precompute, mpgemm, mpgemv_fused and mpgemm_fused of a class derived from LinearLUT are what its forward calls
     go through."""
