@@ -671,9 +671,9 @@ extern "C" tmac_status tmac_mpgemm_fused(const tmac_wdesc* desc, const void* pac
   if (out != TMAC_OUT_F32 && out != TMAC_OUT_F16 && out != TMAC_OUT_I32) return TMAC_EINVAL;
   if (!aligned16(packed_dev) || !aligned16(A_dev) || !aligned16(workspace_dev)) return TMAC_EINVAL;
   if (ldo < desc->M || lda < desc->K) return TMAC_EINVAL;
+  if (!group_supported(desc)) return TMAC_EUNSUPPORTED;
   // the kernels that build tables in place read eight activations per load
   if ((lutb == 0 || (desc->layout == TMAC_LAYOUT_R64K32 && rows_reads_eight(desc, N))) && lda % 8 != 0) return TMAC_EINVAL;
-  if (!group_supported(desc)) return TMAC_EUNSUPPORTED;
   if (workspace_bytes < ws + lutb) return TMAC_ESIZE;
   const tmac_lut_t lt = (act == TMAC_ACT_I8) ? TMAC_LUT_I16 : TMAC_LUT_F16;
   if (lutb == 0) {

@@ -204,6 +204,11 @@ def test_device_entry_points_reject_bad_arguments_before_launch():
     assert call(a0=C.byref(bad)) == B.TMAC_EINVAL
     g48 = _desc(M=16, K=192, bits=2, group=48)          # layout 3 needs whole 32-k chunks per group
     assert call(a0=C.byref(g48), a9=16) == B.TMAC_EUNSUPPORTED
+    # the one-call entry point: a group size without a kernel is that, whatever the leading dimension
+    big48 = _desc(M=4096, K=4608, bits=4, group=48)
+    for lda in (4608, 4612):
+        assert lib.tmac_mpgemm_fused(C.byref(big48), fake, fake, 0, 16, lda, None, C.c_float(1.0), fake, 0, 4096, fake, 1 << 40,
+                                     None) == B.TMAC_EUNSUPPORTED
     assert T.status_str(B.TMAC_ESIZE) == "buffer too small"
 
 
