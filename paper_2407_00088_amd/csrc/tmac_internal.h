@@ -261,6 +261,8 @@ int launch_rows_gemm(const tmac_wdesc* desc, const void* packed_dev, const void*
                      bool fixed_from_act = false);
 // Whether a call that brings fp16 activations builds fixed-point tables from them.
 bool rows_fixed_from_act(const tmac_wdesc* desc, int N);
+// ... and the room it needs for fp16 tables (of rows that are not finite): whole n tiles of eight rows.
+size_t rows_raw_bytes(const tmac_wdesc* desc, int N);
 
 // Records the last HIP error of this thread (diagnostics for TMAC_EHIP).
 void note_hip_error(int hip_error);

@@ -14,6 +14,7 @@
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstring>
@@ -650,6 +651,9 @@ static bool fused_regions(const tmac_wdesc* desc, int N, tmac_act_t act, size_t*
   // (the register-table kernel reads its tables from a LUT buffer for at most TMAC_DECODE_MAX_ROWS rows)
   if (!in_kernel && desc->layout == TMAC_LAYOUT_R8U16 && N > TMAC_DECODE_MAX_ROWS) return false;
   *lut = in_kernel ? 0 : tmac_lut_bytes(N, desc->K, desc->g, desc->group, lt);
+  // (fixed-point calls put the fp16 tables of rows that are not finite there, in n tiles of eight rows whatever the LUT
+  // buffer's are)
+  if (fixed) *lut = std::max(*lut, rows_raw_bytes(desc, N));
   return true;
 }
 

@@ -1762,7 +1762,7 @@ RowsPlan rows_plan(const tmac_wdesc* desc, int N, bool from_act) {
   if (desc->bits < 2) return pl;
   // units: one per 128-k block where no block holds parts of two groups, else one per chunk
   const int shift = (one_group || cpg % 4 == 0) ? 2 : 0;
-  const size_t tab = (size_t)((N + 7) / 8) * (ge.Kp / 4) * 256, scale = (size_t)tiles * (ge.n_chunks >> shift) * 64;
+  const size_t tab = rows_raw_bytes(desc, N), scale = (size_t)tiles * (ge.n_chunks >> shift) * 64;
   const size_t sums = (size_t)tiles * (one_group ? 1 : desc->K / desc->group) * 64;
   const double lookups = (double)N * ge.Mp * (ge.Kp / 4) * desc->bits;
   const size_t run_parts = ((size_t)run.parts * slice + 255) / 256 * 256;
@@ -1790,6 +1790,9 @@ RowsPlan rows_plan(const tmac_wdesc* desc, int N, bool from_act) {
   pl.fix_sums_bytes = sums;
   return pl;
 }
+
+// (as many as the fixed-point tables themselves take)
+size_t rows_raw_bytes(const tmac_wdesc* desc, int N) { return (size_t)((N + 7) / 8) * (geometry(desc).Kp / 4) * 256; }
 
 bool rows_fixed_from_act(const tmac_wdesc* desc, int N) { return desc->g == 4 && rows_plan(desc, N, true).fix; }
 

@@ -1429,6 +1429,28 @@ def test_few_weight_rows_keep_fp16_sums(T, torch, N, M, K, bits, group):
     assert orc.rel_frobenius(got[np.ix_(rows, cols)], model) <= 3e-6
 
 
+@pytest.mark.parametrize("N,M,K", [(9, 12545, 4096), (12, 12289, 4128), (20, 6401, 4128), (36, 4097, 4096)])
+def test_one_call_writes_nothing_past_its_workspace_for_rows_that_are_not_finite(T, torch, N, M, K):
+    """Fixed-point calls write the fp16 tables of such rows as n tiles of eight rows, also where a LUT buffer's are four
+    rows wide (9 to 12, 17 to 20, 33 to 36 rows: four rows that do not exist); the same rows in a small call agree."""
+    from paper_2407_00088_amd import binding as B
+    from paper_2407_00088_amd.runner import from_problem
+    p = wl.make_grouped(0, 1895 + N, N, M, K, 4, 32, name="raw_room")
+    p.act[0, 5], p.act[N - 1, K - 1] = np.inf, np.nan
+    p.act[N - 2, 512:516] = 30000.0
+    lin = from_problem(p, layout=L3)
+    A, out = torch.from_numpy(p.act).cuda(), torch.empty((N, M), dtype=torch.float32, device="cuda")
+    need = B.tmac_fused_workspace_bytes(lin.desc, N, B.TMAC_ACT_F16)
+    room = torch.full((need + 65536,), 0xA5, dtype=torch.uint8, device="cuda")
+    B.tmac_mpgemm_fused(lin.desc, lin.packed, A, N, out, B.TMAC_OUT_F32, room[:need])
+    assert bool((room[need:] == 0xA5).all())
+    small = lin.forward(A[[0, N - 2, N - 1]].contiguous())
+    for kind in (torch.isnan, torch.isposinf, torch.isneginf):
+        assert torch.equal(kind(out[[0, N - 2, N - 1]]), kind(small))
+    ref = orc.mpgemm_definition(p.act[1:N - 2], p.q, p.scales, p.zeros, 32)
+    assert orc.rel_frobenius(out[1:N - 2].cpu().numpy(), ref) <= 4e-4
+
+
 def rows_constant(name):
     """A constant of csrc/tmac_rows.hip: the lines between routes, so that a test says which side of one it is on."""
     src = open(os.path.join(os.path.dirname(os.path.abspath(__file__)), "..", "paper_2407_00088_amd", "csrc", "tmac_rows.hip")).read()
