@@ -1484,7 +1484,8 @@ def test_long_runs_of_chunks_in_one_round_and_in_two(T, torch, N, M, K, bits, gr
 
 @pytest.mark.parametrize("N,M,K", [(50, 8641, 4096), (300, 1999, 3232), (130, 4163, 2080)])
 def test_runs_of_chunks_with_integer_tables(T, torch, N, M, K):
-    """The same for integer tables with one scale per tensor: exact, in all output types."""
+    """The same for integer tables with one scale per tensor: exact, in all output types.  (The third shape has too few
+    chunks for a run and keeps K slices.)"""
     p = wl.make_ternary(0, 1850 + N, N, M, K, name="run_int")
     lin = make_lin(p, L3)
     A, s_a = torch.from_numpy(p.act_q).cuda(), torch.from_numpy(p.act_scale).cuda()
@@ -1494,6 +1495,42 @@ def test_runs_of_chunks_with_integer_tables(T, torch, N, M, K):
         assert np.array_equal(run(A, out_t=T.TMAC_OUT_I32, act_scale=s_a).cpu().numpy(), ref_i.astype(np.int32))
         assert np.array_equal(run(A, act_scale=s_a).cpu().numpy().view(np.uint32), ref_f.view(np.uint32))
         assert np.array_equal(run(A, out_t=T.TMAC_OUT_F16, act_scale=s_a).cpu().numpy(), ref_f.astype(np.float16))
+
+
+@pytest.mark.parametrize("N,M,K,bits,per_row", [
+    (130, 5301, 2080, 2, False), (50, 8641, 4096, 1, False), (300, 1999, 3232, 3, False), (61, 8640, 3208, 4, False),
+    (40, 11008, 3200, 1, True), (130, 5301, 2080, 2, True), (300, 1999, 3232, 3, True), (50, 8641, 4096, 4, True),
+    (509, 13801, 3072, 2, False), (500, 14081, 3072, 4, True)])
+def test_runs_of_chunks_with_integer_tables_of_all_widths(T, torch, N, M, K, bits, per_row):
+    """Integer tables dealt out as one run of chunks, in one round of workgroups and in two: 1 to 4 bits, one scale per
+    tensor (exact, in all output types) and one per row (the exact integer, then a handful of fp32 operations on terms
+    that may be larger than their sum: 1e-5 of the results' root mean square).  The integers are a product in float64, exact."""
+    from paper_2407_00088_amd.runner import from_problem
+    assert N > 32 and run_chunks(N, M, K) >= rows_constant("ROWS_RUN_INT_CHUNKS")
+    rng = np.random.default_rng(1860 + N + bits)
+    q = wl.uniform_codes(rng, M, K, bits)
+    a_q, s_a = wl.absmax_int8(wl.gaussian_act(rng, N, K))
+    a, w = torch.from_numpy(a_q).cuda().double(), torch.from_numpy(q).cuda().double()
+    A, sa = torch.from_numpy(a_q).cuda(), torch.from_numpy(s_a).cuda()
+    if per_row:
+        s, z = wl.group_scales(rng, M, 1), wl.group_zeros(rng, M, 1, bits)
+        p = wl.Problem("run_int", 0, N, M, K, bits, K, q, s, z, act_q=a_q, act_scale=s_a)
+        lin = from_problem(p, layout=L3)
+        s64, z64 = (torch.from_numpy(t.astype(np.float64)).cuda()[:, 0] for t in (s, z))
+        ref = (a @ w.t() - a.sum(1)[:, None] * z64[None, :]) * s64[None, :] * sa.double()[:, None]
+        for run in (lin.forward, lin.forward_one_call):
+            assert float((run(A, act_scale=sa).double() - ref).abs().max()) <= 1e-5 * float(ref.pow(2).mean().sqrt())
+        return
+    zero = 1 << (bits - 1)
+    p = wl.Problem("run_int", 0, N, M, K, bits, 0, q, None, None, weight_scale=float(np.float32(0.02)), zero_point=float(zero),
+                   act_q=a_q, act_scale=s_a)
+    lin = from_problem(p, layout=L3)
+    ref_i = (a @ (w - zero).t()).cpu().numpy().astype(np.int64)
+    ref_f = orc.int_path_output_f32(ref_i, s_a, p.weight_scale)
+    for run in (lin.forward, lin.forward_one_call):
+        assert np.array_equal(run(A, out_t=T.TMAC_OUT_I32, act_scale=sa).cpu().numpy(), ref_i.astype(np.int32))
+        assert np.array_equal(run(A, act_scale=sa).cpu().numpy().view(np.uint32), ref_f.view(np.uint32))
+        assert np.array_equal(run(A, out_t=T.TMAC_OUT_F16, act_scale=sa).cpu().numpy(), ref_f.astype(np.float16))
 
 
 def test_large_call_takes_two_row_tiles_per_workgroup_by_default(T, torch):
@@ -1569,6 +1606,33 @@ def test_native_calls_give_the_bits_of_the_step_by_step_path(T, torch, monkeypat
     assert errors[:5] == errors[5:]
     for a, b in zip(native, all_calls()):
         assert a.dtype == b.dtype and torch.equal(a, b)
+
+
+@pytest.mark.parametrize("i8", [False, True])
+def test_every_native_call_serves_the_ordinary_case(T, torch, i8):
+    """forward_fused, forward, forward_one_call and multi are taken for plain tensors (a comparison of both paths could
+    not tell if one of them always refused), and give what runner and binding give."""
+    from paper_2407_00088_amd import binding as B
+    from paper_2407_00088_amd.runner import from_problem
+    p = wl.make_ternary(0, 1905, 3, 200, 640) if i8 else wl.make_grouped(0, 1905, 3, 200, 640, 4, 64, name="ordinary")
+    A = torch.from_numpy(p.act_q if i8 else p.act).cuda()
+    s_a = torch.from_numpy(p.act_scale).cuda() if i8 else None
+    for layout in (L2, L3):
+        lin = from_problem(p, layout=layout)
+        want = lin.forward(A, act_scale=s_a)
+        args = (lin.desc, lin.packed, A, lin.M, B.TMAC_OUT_F32, None, s_a, lin.weight_scale, lin.device)
+        two = B.calls.forward(*args, lin.lut, lin.lut_t, lin.workspace, lin.K, lin.group, lin.g)
+        assert two is not None and torch.equal(two, want)
+        assert B.calls.forward_one_call(*args, getattr(lin, "fused_ws", None)) is None       # no workspace yet
+        want = lin.forward_one_call(A, act_scale=s_a)
+        one = B.calls.forward_one_call(*args, lin.fused_ws)
+        assert one is not None and torch.equal(one, want)
+        if layout == L2:
+            fused = B.calls.forward_fused(*args)
+            assert fused is not None and torch.equal(fused, lin.forward_fused(A, act_scale=s_a))
+            out = torch.empty_like(fused)
+            assert B.calls.multi([(lin.desc, lin.packed, A, out, s_a, lin.weight_scale)], 3, B.TMAC_OUT_F32, None) is True
+            assert torch.equal(out, fused)
 
 
 def test_native_calls_from_two_threads(T, torch):
