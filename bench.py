@@ -204,7 +204,8 @@ def main():
             stream.synchronize()
             for _ in range(launches):
                 replay.run()  # untimed lead-in as long as the timed region: the GPU is busy while the host
-                              # enqueues, and the clocks have recovered from the idle gap of the synchronize()
+                              # enqueues (its clocks go on rising for about 20 ms after an idle gap: the prefill
+                              # calls, a few ms into it, read up to a fifth more than in continuous work)
             t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
             t0.record(stream)
             for _ in range(launches):

@@ -59,15 +59,21 @@ typedef enum { TMAC_ACT_F16 = 0, TMAC_ACT_I8 = 1, TMAC_ACT_F16_TQ = 2 } tmac_act
  *   TMAC_LUT_F16: entries are signed sums of fp16 activations formed with fp16 additions (see
  *                 tmac_precompute_lut; results within 2e-3 relative Frobenius error of the fp64
  *                 product).
- *                 Calls of the batched kernels with g = 4, 2 to 4 bits, nine activation rows or more
- *                 and more than about 0.75e9 look-ups (N M K bits / 4; tmac_mpgemm_fused: 0.3e9) look
- *                 (unless K is so long against M that the tables would weigh most; see rows_plan in
- *                 csrc/tmac_rows.hip for the exact lines) the entries up as 16-bit integers, rounded once to 2^-15 of the largest sum of
- *                 eight entries in each (activation row, quantisation group of at most 128 k), whose
- *                 sums are exact: closer to the product than sums in fp16.  Entries that are multiples
- *                 of a power of two not below that unit's size (whole numbers, fractions, subnormal
- *                 numbers whose fp16 sums are exact) are not rounded.  Where a row's entries are not all finite, that row's
- *                 fp16 entries are looked up; other rows' results do not change.
+ *                 Large calls of the batched kernels with g = 4, 2 to 4 bits and nine activation rows
+ *                 or more look the entries up as 16-bit integers, rounded once to 2^-15 of the largest
+ *                 sum of eight entries in each (activation row, quantisation group of at most 128 k),
+ *                 whose sums are exact: closer to the product than sums in fp16.  Entries that are
+ *                 multiples of a power of two not below that unit's size (whole numbers, fractions,
+ *                 subnormal numbers whose fp16 sums are exact) are not rounded.  Where a row's
+ *                 entries are not all finite, that row's fp16 entries are looked up; other rows'
+ *                 results do not change.  Which calls these are decides how results are rounded; with
+ *                 chunks = ceil(N / 16) ceil(M / 256) 4 ceil(K / 128):
+ *                   tmac_mpgemm_fused: 5000 chunks and 15000 chunks times bits; up to 32 rows 24576
+ *                   chunks times bits.
+ *                   tmac_mpgemm: 0.75e9 look-ups (N M K bits / 4, M padded to 64 and K to 128), up to 32
+ *                   rows 1.5e9; M bits >= 1536; 5000 chunks, or 12288 at most N that leave more than
+ *                   15 % of ceil(N / 16) sets of 16 rows empty; and tmac_mpgemm_noalloc takes the call
+ *                   if it would with sums in fp16 (rows_plan in csrc/tmac_rows.hip).
  *   TMAC_LUT_I16: entries are exact int16 sums of int8 activations (|T| <= 4*127); all
  *                 aggregation is int32 and the result is bit-exact.
  *   TMAC_LUT_I8Q: table quantisation (Section 3.3): entries of fp16 activations' tables rounded
@@ -261,9 +267,11 @@ tmac_status tmac_mpgemv_fused(const tmac_wdesc* desc, const void* packed_dev, co
                               float weight_scale, void* out_dev, tmac_out_t out, int64_t ldo,
                               void* stream);
 
-/* One call for either layout and any N: the result of tmac_precompute_lut followed by
- * tmac_mpgemm (fp16 tables for TMAC_ACT_F16, exact integer tables for TMAC_ACT_I8), computed
- * from the activations.  The tables are built inside the lookup kernel where a kernel does that
+/* One call for either layout and any N: tmac_precompute_lut followed by tmac_mpgemm (fp16 tables for
+ * TMAC_ACT_F16, exact integer tables for TMAC_ACT_I8), from the activations themselves.  The same
+ * table entries, added in the same way, except where this entry point looks fp16 entries up as integers
+ * and tmac_mpgemm does not yet (TMAC_LUT_F16 above): those results are the closer ones, about 4e-4 apart.
+ * The tables are built inside the lookup kernel where a kernel does that
  * (Algorithm 1 Precompute next to the look-ups that use it: no second launch and no table
  * traffic): layout 2 with K % 16 == 0 (this is then tmac_mpgemv_fused), and layout 3 with g = 4,
  * K % 8 == 0, a group size that divides 256 (or one scale per row or tensor), and at most 32
@@ -271,8 +279,7 @@ tmac_status tmac_mpgemv_fused(const tmac_wdesc* desc, const void* packed_dev, co
  * launch costs most).  Every other call runs tmac_precompute_lut into the second region of the
  * workspace and tmac_mpgemm after it, or, where the entries are looked up as integers
  * (TMAC_LUT_F16 above), builds those from the activations and uses the second region only for tables
- * that are not finite; it does so from fewer look-ups on than tmac_mpgemm, which reads its tables from
- * a LUT buffer: between the two lines its results are the closer ones (layout 2 with K % 16 != 0 or an unsupported group size: at most 64 activation
+ * that are not finite (layout 2 with K % 16 != 0 or an unsupported group size: at most 64 activation
  * rows, beyond that TMAC_EUNSUPPORTED and a size of 0).
  *   A_dev          [N,K] fp16 or int8, 16-byte aligned; leading dimension lda a multiple of 8
  *                  where a kernel could build the tables as above (16 for int8 with layout 2), else

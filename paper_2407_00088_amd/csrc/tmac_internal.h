@@ -238,8 +238,8 @@ struct RowsPlan {
   // fp16 tables as fixed-point numbers (see rows_fix_kernel); fix == false: none of it
   bool fix;
   int fix_tiles;                                    // sets of 16 activation rows
-  int run_wgs, run_total;                           // the same for integer tables
   int fix_wgs, fix_total;                           // workgroups and chunks of the run (RowsShare)
+  int run_wgs, run_total;                           // those of a run with integer tables (run_wgs == 0: K slices)
   int fix_shift;                                    // 2: a unit per 128-k block, 0: per chunk
   // inside the same workspace: partial sums, tables, their units, the group sums
   size_t fix_part_bytes, fix_tab_bytes, fix_scale_bytes, fix_sums_bytes;
@@ -254,7 +254,7 @@ bool rows_reads_eight(const tmac_wdesc* desc, int N);
 bool rows_builds_tables(const tmac_wdesc* desc, int N, bool is_int);
 // Returns a tmac_status value.  lut_dev NULL: tables built in the kernel from A_dev (where
 // rows_builds_tables(desc, N, is_int) holds).  fixed_from_act: fixed-point tables built from A_dev (where
-// rows_fixed_from_act(desc, N) holds); lut_dev is room of a LUT buffer's size.
+// rows_fixed_from_act(desc, N) holds); lut_dev is room of at least rows_raw_bytes(desc, N).
 int launch_rows_gemm(const tmac_wdesc* desc, const void* packed_dev, const void* lut_dev, const void* A_dev,
                      int64_t lda, int lut_t, int N, const float* act_scale_dev, float weight_scale, void* out_dev,
                      int out_t, int64_t ldo, void* workspace_dev, size_t workspace_bytes, void* stream,

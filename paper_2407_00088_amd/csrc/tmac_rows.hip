@@ -130,7 +130,8 @@ struct RowsParams {
   int fix_shift;           // 2: one unit per 128-k block, 0: one per chunk (see rows_fix_kernel)
   uint16_t* raw;           // ... and the fp16 tables, as in a LUT buffer, where a unit is -0
   int lut_nt, raw_nt;      // activation rows of an n tile of the LUT buffer, 4 or 8 (rows_nt), and of raw
-  RowsShare share;         // ... and which part of the call a workgroup serves (wgs == 0: K slices of equal length)
+  RowsShare share;         // mpgemm_run_kernel and its sums: which part of the call a workgroup serves (the other kernels, which
+                           // take K slices of equal length, do not read it)
 };
 
 // 32-k chunks of tables one LDS slice holds, for LUT group size g and nt activation rows
@@ -1337,6 +1338,8 @@ enum { RUN_INT, RUN_BLOCK, RUN_SOLO, RUN_CHUNK };
 // 4096 x 4096 43.5, 36.1, 300 x 700 x 8192 71.8, 59.5.
 // (The chunk loop not unrolled, indices handed from register to register: 53 and 382 us for the ternary and the 2-bit
 // call of 511 rows; a copy of it without the bounds of a share: 53.7 and 353.)
+// The fixed-point variants keep 60 to 67 of their scalars (parameters, 16 units, addresses) in lanes of a vector register
+// (integer tables: none, two at 3 bit); they are read back once per 128-k block or part, not within a chunk's look-ups.
 template <int BITS, int MODE>
 __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_run_kernel(const RowsParams p) {
   constexpr bool IS_INT = MODE == RUN_INT;
@@ -1736,13 +1739,17 @@ static RunPlan rows_run(int64_t pairs, int n_chunks) {
 //     40 x 4096 x 4096, 2 bit 26.4 us against 22.0).  Up to 32 rows the other side builds its tables in the look-up
 //     kernel and saves a launch: chunks times bits from ROWS_RUN_ACT_FEW on, 1.14 times on average (23 calls, 0.98 to 1.47;
 //     16 x 28672 x 2048, 4 bit 1.11), below it 0.91 (13 calls, 0.75 to 1.17).
-//   * from a LUT buffer the conversion is one more launch: look-ups from ROWS_RUN_LUT_LOOKUPS on: 1.07 at 1.07e9 (64 x
-//     4096 x 4096, 4 bit), 1.05 at 0.8e9 (64 x 2048 x 8192, 3 bit), 1.09 (96 x 4096 x 4096, 2 bit); 0.89 to 1.01 at 0.3e9
-//     to 0.7e9; and ROWS_RUN_LUT_ROWS weight rows times bits for each table: 1.05 at 2100 (300 x 700 x 8192, 3 bit), 0.90 to
-//     1.07 at 1200 to 1536 (eleven calls, seven below 1), 0.88 at 768 (511 x 256 x 13824, 3 bit).  Up to 32 rows twice the look-ups (20 x 12000 x 5120, 3 and 4 bit: 0.985),
-//     and where more than 15 % of the sets' rows do not exist, as many chunks as for integer tables (40 x 2700 x 8192, 4
-//     bit, 8448 chunks: 0.94).  Within the library's own array where the plain plan is, because
-//     tmac_mpgemm_noalloc gives tmac_mpgemm's results bit for bit.
+//   * from a LUT buffer the conversion is one more launch: look-ups from ROWS_RUN_LUT_LOOKUPS on, twice as many up to 32
+//     rows, ROWS_RUN_LUT_ROWS weight rows times bits for each table, and ROWS_RUN_ACT_CHUNKS, where more than 15 % of the
+//     sets' rows do not exist ROWS_RUN_INT_CHUNKS.  Of 64 random calls that these lines take 55 are faster than with fp16
+//     sums, 1.06 times on average (0.94 to 1.21); of 46 that they leave, from 0.4e9 look-ups on, 14, 0.95 (0.72 to 1.08).
+//     At the lines: 1.05 and 1.07 at 0.8e9 and 1.07e9 look-ups (64 x 4096 x 4096, 3 and 4 bit), 0.94 and 0.96 at 0.6e9 (48 x
+//     4096 x 4096 and 64 x 3072 x 4096, 3 bit); up to 32 rows 0.94 (20 x 12000 x 5120, 3 and 4 bit) to 1.20 (28 x 16384 x 4096,
+//     2 bit) below, 1.16 and 1.18 above (32 x 28672 x 2048, 16 x 28672 x 4096, 4 bit); weight rows times bits 1.05 at 2100 (300 x 700 x
+//     8192, 3 bit), 0.90 to 1.07 at 1200 to 1536 (eleven calls, seven below 1), 0.88 at 768 (511 x 256 x 13824, 3 bit);
+//     sets that are not full 0.92, 1.00 and 1.05 at 8448, 11264 and 10240 chunks (40 x 2700 x 8192, 52 x 2800 x 8192, 65 x 2048
+//     x 8192).  Within the library's own array where the plain plan is, because tmac_mpgemm_noalloc gives tmac_mpgemm's
+//     results bit for bit.
 // At 1 bit fixed point is 0.93 to 1.05 times as fast as fp16 sums: tables and launches weigh four times as much there.
 RowsPlan rows_plan(const tmac_wdesc* desc, int N, bool from_act) {
   RowsPlan pl = rows_plan_plain(desc, N);
