@@ -84,15 +84,21 @@ typedef short rs2v __attribute__((ext_vector_type(2)));
 // The call as one run of chunks, dealt out evenly.  A pair is a block of 256 weight rows and a set of 16
 // activation rows; the pairs' chunks follow each other, weight rows fastest, and workgroup w takes the chunks
 // [w total / wgs, (w + 1) total / wgs) of the run, whatever pairs they belong to.  What it has of one pair is
-// one part of that pair's sums; a pair's parts are numbered from its first workgroup.
+// one part of that pair's sums; a pair's parts are numbered from its first workgroup.  The workgroups with one
+// chunk more than others are spread evenly: the first ones of the run would all sit on the same XCDs, which then
+// end last (16 x 11008 x 4096, 5504 chunks: three XCDs at 18.3 us, the others at 16.2).
 struct RowsShare {
-  uint32_t wgs, per, more;      // workgroups, chunks of each; the first `more` take one more
+  uint32_t wgs, per, more;      // workgroups, chunks of each; `more` of them take one more
+  uint32_t log2;                // logarithm of wgs, which is a power of two (or more is 0)
+  float wgs_per_chunk;
   uint32_t row_blocks, chunks;  // blocks of 256 weight rows, chunks of a pair
   uint32_t inv_row_blocks, inv_chunks;  // rows_inverse() of the two
-  __device__ uint32_t start(uint32_t wg) const { return wg * per + min(wg, more); }
+  __device__ uint32_t start(uint32_t wg) const { return wg * per + (wg * more >> log2); }
   __device__ uint32_t owner(uint32_t chunk) const {
-    const uint32_t head = more * (per + 1);
-    return chunk < head ? chunk / (per + 1) : more + (chunk - head) / per;
+    uint32_t wg = min((uint32_t)((float)chunk * wgs_per_chunk), wgs - 1u);  // (at most one off)
+    if (start(wg) > chunk) --wg;
+    else if (start(wg + 1u) <= chunk) ++wg;
+    return wg;
   }
   __device__ uint32_t first(uint32_t pair) const { return owner(pair * chunks); }
   __device__ int parts(uint32_t pair) const { return (int)(owner((pair + 1) * chunks - 1) - first(pair)) + 1; }
@@ -1201,6 +1207,11 @@ __global__ __launch_bounds__(256) void rows_fix_kernel(const RowsParams p, uint3
   }
 }
 
+// A sum of at most four chunks, |sum| < 2^21, that starts from ROWS_FLOAT_ZERO is the bit pattern of 1.5 2^23 plus it:
+// as a number by one subtraction (1.1 ns per wavefront and SIMD; a conversion takes 1.8)
+constexpr int ROWS_FLOAT_ZERO = 0x4B400000;
+__device__ __forceinline__ float rows_float(int l) { return __int_as_float(l) - 12582912.f; }
+
 // The look-ups of one 32-k chunk for two sets of eight activation rows, in rounds of the eight reads of
 // one plane and row set (see rows_chunk_int): L += the planes' sums, and their biases, times the planes'
 // weights.  START: L begins at `start`.
@@ -1390,11 +1401,11 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_run_kernel(const Ro
   };
   int set = (int)rows_div((uint32_t)pair0, p.share.row_blocks, p.share.inv_row_blocks), rb = pair0 - set * row_blocks, c = c00, left = todo, flag = 0;
   const uint32_t* idx = p.idx + ((size_t)tile_of(rb) * chunks + (c & ~3)) * 64 * BITS;
+  request(set, c >> 2);
   constexpr int AHEAD = BITS <= 2 ? 4 : 2;
   uint32_t x[AHEAD][BITS];
 #pragma unroll
   for (int i = 0; i < AHEAD; ++i) load_idx(idx + ((c & (4 - AHEAD)) + i) * 64 * BITS, x[i]);
-  request(set, c >> 2);
   while (true) {  // the parts of this workgroup, pair by pair
     const int end = min(chunks, c + left);
     left -= end - c;
@@ -1443,12 +1454,11 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_run_kernel(const Ro
       const uint32_t* const here = idx;
       idx = c < end ? idx + 4 * 64 * BITS : left > 0 ? idx_n : idx;
       // wavefronts that are behind come first (see above)
-      switch (4 * (todo - left - (end - c)) / (todo + 1)) {
-        case 0: __builtin_amdgcn_s_setprio(3); break;
-        case 1: __builtin_amdgcn_s_setprio(2); break;
-        case 2: __builtin_amdgcn_s_setprio(1); break;
-        default: __builtin_amdgcn_s_setprio(0); break;
-      }
+      const int done4 = 4 * (todo - left - (end - c));
+      if (done4 <= todo) __builtin_amdgcn_s_setprio(3);
+      else if (done4 <= 2 * todo + 1) __builtin_amdgcn_s_setprio(2);
+      else if (done4 <= 3 * todo + 2) __builtin_amdgcn_s_setprio(1);
+      else __builtin_amdgcn_s_setprio(0);
       // half the scale of the group; its bias term (Section 4's linear transform) goes with its first chunk
       auto enter_group = [&](bool starts) {
         enter = false;
@@ -1467,18 +1477,20 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_run_kernel(const Ro
 #pragma unroll
         for (int t = 0; t < 16; ++t) unit[t] = fix_scale[t];
         fix_scale += 16;
+        if (lo != 0) {  // (else the first chunk starts the sums)
 #pragma unroll
-        for (int t = 0; t < 16; ++t) L[t] = (lo - hi) * (BIAS * ((1 << BITS) - 1));  // minus the biases of the chunks to come
+          for (int t = 0; t < 16; ++t) L[t] = ROWS_FLOAT_ZERO + (lo - hi) * (BIAS * ((1 << BITS) - 1));
+        }
       }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
+      auto chunk = [&](auto ic) {
+        constexpr int i = decltype(ic)::value;
         if (i >= lo && i < hi) {
           const uint32_t cbase = lds0 + (uint32_t)i * CB;
           uint32_t (&xi)[BITS] = x[i & (AHEAD - 1)];
           if constexpr (IS_INT) {
             rows_chunk_int<BITS, 2, OSTRIDE>(xi, cbase, L);
           } else if constexpr (MODE == RUN_BLOCK) {
-            rows_chunk_fix<BITS, OSTRIDE, false>(xi, cbase, L);
+            rows_chunk_fix<BITS, OSTRIDE, i == 0>(xi, cbase, L, ROWS_FLOAT_ZERO - hi * (BIAS * ((1 << BITS) - 1)));
           } else if constexpr (MODE == RUN_SOLO) {
             if (gq < p.nq) {  // (chunks in the K padding belong to no group)
               const float s = __half2float(__ushort_as_half((uint16_t)(szv & 0xffffu)));
@@ -1491,13 +1503,13 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_run_kernel(const Ro
                 sum[t] = sums[(size_t)gq * 16 + t];
               }
               fix_scale += 16;
-              rows_chunk_fix<BITS, OSTRIDE, true>(xi, cbase, L, -BIAS * ((1 << BITS) - 1));
+              rows_chunk_fix<BITS, OSTRIDE, true>(xi, cbase, L, ROWS_FLOAT_ZERO - BIAS * ((1 << BITS) - 1));
               const float bz = 2.f * (p.mid - z);
               hs = 0.5f * s;
 #pragma unroll
               for (int t = 0; t < 16; ++t) {
                 flag |= __float_as_int(unit[t]);
-                acc[t] = fmaf(hs, fmaf((float)L[t], unit[t], bz * sum[t]), acc[t]);
+                acc[t] = fmaf(hs, fmaf(rows_float(L[t]), unit[t], bz * sum[t]), acc[t]);
               }
               ++gq;
             }
@@ -1511,7 +1523,7 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_run_kernel(const Ro
               for (int t = 0; t < 16; ++t) unit[t] = fix_scale[t];
               const int n = min(hi - i, p.cpg - bg);
 #pragma unroll
-              for (int t = 0; t < 16; ++t) L[t] = -n * (BIAS * ((1 << BITS) - 1));
+              for (int t = 0; t < 16; ++t) L[t] = ROWS_FLOAT_ZERO - n * (BIAS * ((1 << BITS) - 1));
             }
             fix_scale += 16;
             rows_chunk_fix<BITS, OSTRIDE, false>(xi, cbase, L);
@@ -1521,7 +1533,7 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_run_kernel(const Ro
 #pragma unroll
               for (int t = 0; t < 16; ++t) {
                 flag |= __float_as_int(unit[t]);
-                acc[t] = fmaf((float)L[t], unit[t] * hs, acc[t]);
+                acc[t] = fmaf(rows_float(L[t]), unit[t] * hs, acc[t]);
               }
             }
             if (ends) {
@@ -1533,12 +1545,16 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_run_kernel(const Ro
         }
         if (i >= (lo & (4 - AHEAD))) load_idx(i + AHEAD < 4 ? here + (i + AHEAD) * 64 * BITS : idx + (i + AHEAD - 4) * 64 * BITS, x[i & (AHEAD - 1)]);
         __builtin_amdgcn_sched_barrier(0);
-      }
+      };
+      chunk(std::integral_constant<int, 0>());
+      chunk(std::integral_constant<int, 1>());
+      chunk(std::integral_constant<int, 2>());
+      chunk(std::integral_constant<int, 3>());
       if constexpr (MODE == RUN_BLOCK) {
 #pragma unroll
         for (int t = 0; t < 16; ++t) {
           flag |= __float_as_int(unit[t]);
-          acc[t] = fmaf((float)L[t], unit[t] * hs, acc[t]);
+          acc[t] = fmaf(rows_float(L[t]), unit[t] * hs, acc[t]);
         }
         if (p.grouped && ++bg == bpg) {
           bg = 0;
@@ -1586,7 +1602,9 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_run_kernel(const Ro
 }
 
 static RowsShare rows_share(int wgs, int total, int row_blocks, int chunks) {
-  return RowsShare{(uint32_t)wgs, (uint32_t)(total / wgs), (uint32_t)(total % wgs), (uint32_t)row_blocks, (uint32_t)chunks,
+  uint32_t log2 = 0;
+  while ((2 << log2) <= wgs) ++log2;
+  return RowsShare{(uint32_t)wgs, (uint32_t)(total / wgs), (uint32_t)(total % wgs), log2, (float)wgs / (float)total, (uint32_t)row_blocks, (uint32_t)chunks,
                    rows_inverse((uint32_t)row_blocks, (uint64_t)(total / chunks)), rows_inverse((uint32_t)chunks, (uint64_t)total)};
 }
 
