@@ -107,6 +107,12 @@ struct RowsShare {
 inline uint32_t rows_inverse(uint32_t d, uint64_t n) { return d > 1 && n * d < 0x100000000ull ? (uint32_t)((0x100000000ull + d - 1) / d) : 0u; }
 __device__ __forceinline__ uint32_t rows_div(uint32_t n, uint32_t d, uint32_t inverse) { return inverse ? __umulhi(n, inverse) : n / d; }
 
+// Grid of the eight-chunk kernel (n tiles, row blocks, K slices): slices of equal length, but for one chunk.
+struct Rows8Grid {
+  int per, more;          // chunks of a slice; the first `more` take one more
+  uint32_t inv_x, inv_y;  // rows_inverse() of n tiles and row blocks
+};
+
 struct RowsParams {
   const uint32_t* idx;     // [n_tiles][n_chunks][64][bits] dwords
   const uint32_t* sz;      // [n_tiles][nq][64] {fp16 scale, fp16 zero}
@@ -119,6 +125,8 @@ struct RowsParams {
   int cpg;                 // 32-k chunks per quantisation group (grouped mode)
   int cpg_log2;            // its logarithm when it is a power of two (the eight-chunk kernel needs one)
   int cps;                 // 32-k chunks per workgroup along K (a multiple of cpg); gridDim.z slices
+  int slices;              // K slices of the eight-chunk kernel (gridDim.z)
+  Rows8Grid grid8;
   int Mp;                  // M rounded up to 64
   float* ws_part;          // split K: [slices][N][Mp] partial sums (fp32, or int32 bit patterns)
   float* ws_srow;          // fused table build, one scale per row or tensor: [slices][N] sums of the
@@ -154,13 +162,16 @@ __device__ __forceinline__ void tree_sum(T (&a)[N]) {
 }
 
 
-template <int NT, int G>
+// PAD: bytes from table to table beyond its own, for kernels that build the tables a table per lane: without them
+// all tables start at the same LDS bank and the lanes' stores come one after the other.  A look-up reads one table,
+// wherever it starts.
+template <int NT, int G, int PAD = 0>
 struct RowsShape {
   static constexpr int ENT = 1 << G;          // entries per table
   static constexpr int ES = 2 * NT;           // bytes per entry: NT 16-bit values
-  static constexpr int TB = ENT * ES;         // bytes per table
+  static constexpr int TB = ENT * ES + PAD;   // bytes per table
   static constexpr int TPC = 32 / G;          // tables, i.e. lookups per plane, of a 32-k chunk
-  static constexpr int CB = TPC * TB;         // bytes per chunk
+  static constexpr int CB = (TPC * TB + 255) / 256 * 256;  // bytes per chunk
   static constexpr int HD = NT / 2;           // dwords per entry
 };
 
@@ -188,39 +199,22 @@ __device__ __forceinline__ void rows_widen_from(int& l0, int& l1, uint32_t pair,
   asm("v_mad_u32_u16 %0, %1, %2, %3 op_sel:[1,0,0,0]" : "=v"(l1) : "v"(pair), "n"(W), "s"(start));
 }
 
-// Algorithm 1 Precompute for one (activation row, LUT group of four) inside a lookup kernel: the
-// eight entries 8h..8h+7 of the table, as four dwords of two 16-bit entries, with the arithmetic
+// Algorithm 1 Precompute for one (activation row, LUT group of four) inside a lookup kernel:
+// entries 0..7 of the table, as four dwords of two 16-bit entries, with the arithmetic
 // of the stand-alone precompute kernel ((+-a0 +- a1) + (+-a2 - a3), every addition in fp16;
 // entries 8..15 are the negated entries 7..0: mirror consolidation, Section 3.3).  Integer entries come
-// with their bias (rows_int_bias).
+// with their bias (rows_int_bias).  a: the four activations, int8 in the first dword.
 template <bool IS_INT>
-__device__ __forceinline__ ru32x4v rows_build_half_table(const void* A, int64_t lda, int n, int kg, int h, bool live) {
-  uint32_t low[4];  // entries 0..7
+__device__ __forceinline__ void rows_half_table(ru32x2v a, uint32_t (&low)[4]) {
   if constexpr (IS_INT) {
-    int a0 = 0, a1 = 0, a2 = 0, a3 = 0;
-    if (live) {
-      const uint32_t v = *reinterpret_cast<const uint32_t*>(static_cast<const int8_t*>(A) + n * lda + 4 * kg);
-      a0 = (int8_t)(v & 0xff); a1 = (int8_t)((v >> 8) & 0xff); a2 = (int8_t)((v >> 16) & 0xff); a3 = (int8_t)(v >> 24);
-    }
+    const int a0 = (int8_t)(a.x & 0xff), a1 = (int8_t)((a.x >> 8) & 0xff), a2 = (int8_t)((a.x >> 16) & 0xff), a3 = (int8_t)(a.x >> 24);
     int e[8];
 #pragma unroll
     for (int q = 0; q < 8; ++q) e[q] = ((q & 1) ? a0 : -a0) + ((q & 2) ? a1 : -a1) + ((q & 4) ? a2 : -a2) - a3;
 #pragma unroll
-    for (int d = 0; d < 4; ++d) {
-      const int x = h ? -e[7 - 2 * d] : e[2 * d], y = h ? -e[6 - 2 * d] : e[2 * d + 1];
-      low[d] = ((uint32_t)x + ((uint32_t)y << 16)) + (uint32_t)rows_int_bias(4) * 0x10001u;
-    }
-    return ru32x4v{low[0], low[1], low[2], low[3]};
+    for (int d = 0; d < 4; ++d) low[d] = ((uint32_t)e[2 * d] + ((uint32_t)e[2 * d + 1] << 16)) + (uint32_t)rows_int_bias(4) * 0x10001u;
   } else {
-    ru32x2v v = {0u, 0u};
-    if (live) v = *reinterpret_cast<const ru32x2v*>(static_cast<const __half*>(A) + n * lda + 4 * kg);
-    half_table_f16(v.x, v.y, low);
-    if (!h) return ru32x4v{low[0], low[1], low[2], low[3]};
-    // entries 8 + q = -(entry 7 - q): halves swapped, order reversed, sign bits flipped
-    ru32x4v r;
-#pragma unroll
-    for (int d = 0; d < 4; ++d) r[d] = __builtin_amdgcn_alignbit(low[3 - d], low[3 - d], 16) ^ 0x80008000u;
-    return r;
+    half_table_f16(a.x, a.y, low);
   }
 }
 
@@ -257,36 +251,48 @@ __device__ __forceinline__ void rows_stage_copy(const RowsParams& p, char* tab, 
   }
 }
 
-// Build and stage tables in one go (tables from the activations, g = 4): item `it` is eight
-// consecutive entries (half a table) counted from table kg0, built for the NT activation rows n0..
-// and written entry-major [table][entry][n].  Tables from kg_end on are written as zeros.
-template <int NT, int G, bool IS_INT>
-__device__ __forceinline__ void rows_stage_item(const RowsParams& p, char* tab, int it, int n0, int kg0, int kg_end) {
-  using Sh = RowsShape<NT, G>;
-  static_assert(G == 4, "tables are built in the kernel for g = 4 only");
-  const int flat = it * 8;
-  const int kg = kg0 + (flat >> G);
-  ru32x4v v[NT];
+// Build and stage tables in one go (tables from the activations, g = 4): item `it` is a table, counted from table
+// kg0, of four activation rows (of eight, the first or second four), written entry-major [table][entry][n], eight bytes
+// an entry.  Tables from kg_end on are written as zeros.
+// First the activations are requested, without a branch in between (clamped addresses): loads behind a
+// branch each come one after the other.  us from the start of the kernel until all tables are there, 16 rows x 11008 x
+// 4096, 4 bit: 9.5 with a branch before each load, half a table of eight rows for each lane and the tables' first
+// entries in the same LDS bank, 4.5 like this.
+template <int NT, bool IS_INT>
+__device__ __forceinline__ void rows_item_load(const RowsParams& p, ru32x2v (&a)[4], int it, int n0, int kg0) {
+  const int k = min(4 * (kg0 + it / (NT / 4)), p.K - 4), n = n0 + it % (NT / 4) * 4;
 #pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    const bool live = n0 + t < p.N && kg < kg_end && 4 * kg < p.K;
-    v[t] = rows_build_half_table<IS_INT>(p.A, p.lda, min(n0 + t, p.N - 1), kg, it & 1, live);
+  for (int t = 0; t < 4; ++t) {
+    const int64_t at = min(n + t, p.N - 1) * p.lda + k;
+    if constexpr (IS_INT) a[t] = ru32x2v{*reinterpret_cast<const uint32_t*>(static_cast<const int8_t*>(p.A) + at), 0u};
+    else a[t] = *reinterpret_cast<const ru32x2v*>(static_cast<const __half*>(p.A) + at);
   }
-  ru32x4v* dst = reinterpret_cast<ru32x4v*>(tab + flat * Sh::ES);
+}
+
+template <int NT, bool IS_INT, int PAD>
+__device__ __forceinline__ void rows_stage_item(const RowsParams& p, char* tab, const ru32x2v (&a)[4], int it, int n0, int kg0, int kg_end) {
+  using Sh = RowsShape<NT, 4, PAD>;
+  const int table = it / (NT / 4), kg = kg0 + table, n = n0 + it % (NT / 4) * 4;
+  uint32_t low[4][4];
 #pragma unroll
-  for (int d = 0; d < 4; ++d) {  // dword d of every row holds entries 2d, 2d+1 of the item
-    uint32_t lo[Sh::HD], hi[Sh::HD];
+  for (int t = 0; t < 4; ++t) {
+    const bool live = n + t < p.N && kg < kg_end && 4 * kg < p.K;
+    rows_half_table<IS_INT>(live ? a[t] : ru32x2v{0u, 0u}, low[t]);
+  }
+  char* const dst = tab + table / Sh::TPC * Sh::CB + table % Sh::TPC * Sh::TB + it % (NT / 4) * 8;
 #pragma unroll
-    for (int u = 0; u < Sh::HD; ++u) {
-      lo[u] = __builtin_amdgcn_perm(v[2 * u + 1][d], v[2 * u][d], 0x05040100u);  // entry 2d: rows 2u, 2u+1
-      hi[u] = __builtin_amdgcn_perm(v[2 * u + 1][d], v[2 * u][d], 0x07060302u);  // entry 2d+1
-    }
-    if constexpr (NT == 4) {
-      dst[d] = ru32x4v{lo[0], lo[1], hi[0], hi[1]};
-    } else {
-      dst[2 * d] = ru32x4v{lo[0], lo[1], lo[2], lo[3]};
-      dst[2 * d + 1] = ru32x4v{hi[0], hi[1], hi[2], hi[3]};
-    }
+  for (int d = 0; d < 4; ++d) {  // dword d of every row holds entries 2d, 2d+1
+    const ru32x2v even = {__builtin_amdgcn_perm(low[1][d], low[0][d], 0x05040100u), __builtin_amdgcn_perm(low[3][d], low[2][d], 0x05040100u)};
+    const ru32x2v odd = {__builtin_amdgcn_perm(low[1][d], low[0][d], 0x07060302u), __builtin_amdgcn_perm(low[3][d], low[2][d], 0x07060302u)};
+    // entry 15 - e = -(entry e): sign bits flipped, or subtracted from twice the bias
+    auto mirror = [](ru32x2v e) {
+      if constexpr (IS_INT) return (2u * (uint32_t)rows_int_bias(4) * 0x10001u) - e;
+      else return e ^ 0x80008000u;
+    };
+    *reinterpret_cast<ru32x2v*>(dst + (2 * d) * Sh::ES) = even;
+    *reinterpret_cast<ru32x2v*>(dst + (2 * d + 1) * Sh::ES) = odd;
+    *reinterpret_cast<ru32x2v*>(dst + (15 - 2 * d) * Sh::ES) = mirror(even);
+    *reinterpret_cast<ru32x2v*>(dst + (14 - 2 * d) * Sh::ES) = mirror(odd);
   }
 }
 
@@ -295,15 +301,16 @@ __device__ __forceinline__ void rows_stage_item(const RowsParams& p, char* tab, 
 // entries), per activation row.
 // With OCT = 2 the workgroup serves two sets of NT activation rows whose tables sit OSTRIDE bytes
 // apart in LDS: one address (one permute) then feeds two reads, and L holds 2 NT sums.
-template <bool IS_INT, int BITS, int NT, int G, typename AccT, int OCT = 1, int OSTRIDE = 0>
+// ROUND: reads that are in flight at once.
+template <bool IS_INT, int BITS, int NT, int G, typename AccT, int OCT = 1, int OSTRIDE = 0, int PAD = 0, int ROUND = 16>
 __device__ __forceinline__ void rows_chunk(const uint32_t (&x)[BITS], uint32_t cbase, AccT (&L)[NT * OCT],
                                            const float (&pw)[4]) {
-  using Sh = RowsShape<NT, G>;
+  using Sh = RowsShape<NT, G, PAD>;
   constexpr int TPC = Sh::TPC, HD = Sh::HD, TB = Sh::TB;
   static_assert(OCT == 1 || (OCT == 2 && NT == 8 && TPC * OCT <= 16), "two row sets: eight rows each, g = 4");
   // rounds of 16 LDS reads (one, two or four planes at g = 2, 4, 8): the hardware counts at
   // most 15 outstanding LDS operations exactly, so a round's reads can be consumed as they return
-  constexpr int PL = 16 / (TPC * OCT);
+  constexpr int PL = ROUND / (TPC * OCT);
   uint32_t c[OCT * HD];  // integer tables: planes 0..2 with their weights, as biased 16-bit pairs
 #pragma unroll
   for (int b0 = 0; b0 < BITS; b0 += PL) {
@@ -711,7 +718,8 @@ static hipError_t launch_rows_nt(const RowsParams& p, int g, int nt, int oct, in
 // scales and zeros, tables, group sums) is requested in one go at the start, the chunk loop is
 // straight-line code, and the partial sums are written with plain stores; rows_sum_kernel, the
 // next kernel on the stream, adds the slices in slice order and finishes.
-constexpr int R8_CH = 8;
+constexpr int R8_CH = 8;     // chunks whose indices a wavefront holds at once
+constexpr int R8_MOST = 16;  // most chunks of a slice: four workgroups' tables of eight activation rows fill 128 KB of LDS
 
 // Which (n tile, row block, K slice) a workgroup serves.  The hardware hands workgroups to the
 // chip's eight XCDs (one L2 each) round-robin by linear id; with the plain blockIdx mapping the
@@ -724,36 +732,32 @@ constexpr int R8_CH = 8;
 struct RowsUnit {
   int nt, rb, kz;
 };
-__device__ __forceinline__ RowsUnit rows_unit() {
+__device__ __forceinline__ RowsUnit rows_unit(const Rows8Grid& g) {
   const uint32_t gx = gridDim.x, gy = gridDim.y, groups = gy * gridDim.z;
   const uint32_t lin = (blockIdx.z * gy + blockIdx.y) * gx + blockIdx.x;
   const uint32_t whole = (groups & ~7u) * gx;  // ids of the groups that fill all eight XCDs evenly
-  uint32_t grp = lin / gx, nt = lin % gx;      // the few groups left over keep the plain order
-  if (lin < whole) {
-    const uint32_t xcd = lin & 7u, slot = lin >> 3;
-    grp = xcd + 8u * (slot / gx);
-    nt = slot % gx;
-  }
+  const bool even = lin < whole;               // the few groups left over keep the plain order
+  const uint32_t n = even ? lin >> 3 : lin, quot = rows_div(n, gx, g.inv_x), grp = even ? (lin & 7u) + 8u * quot : quot;
   RowsUnit r;
-  r.nt = (int)nt;
-  r.rb = (int)(grp % gy);
-  r.kz = (int)(grp / gy);
+  r.nt = (int)(n - quot * gx);
+  r.kz = (int)rows_div(grp, gy, g.inv_y);
+  r.rb = (int)(grp - (uint32_t)r.kz * gy);
   return r;
 }
 
 
 template <bool IS_INT, int BITS, int NT, bool FUSED>
-__global__ __launch_bounds__(64 * ROWS_WAVES) void mpgemm_rows8_kernel(const RowsParams p) {
-  static_assert(ROWS_WAVES * 64 >= 32 * NT, "one thread per eight activations of the slice");
-  constexpr int G = 4;
-  using Sh = RowsShape<NT, G>;
-  __shared__ __attribute__((aligned(2048))) char tab[R8_CH * Sh::CB];
-  __shared__ float sS[R8_CH][NT];  // per chunk: the sum of activations of its quantisation group
+__global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_rows8_kernel(const RowsParams p) {
+  static_assert(64 * 8 >= 32 * R8_MOST, "a lane for eight activations of a row's slice");
+  constexpr int G = 4, PAD = FUSED ? 2 * NT : 0;
+  using Sh = RowsShape<NT, G, PAD>;
+  __shared__ __attribute__((aligned(2048))) char tab[R8_MOST * Sh::CB];
+  __shared__ float sS[R8_MOST][NT];  // [chunk]: sum of activations for the bias term added after it (see 2.)
   using AccT = typename std::conditional<IS_INT, int, float>::type;
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const RowsUnit un = rows_unit();
+  const RowsUnit un = rows_unit(p.grid8);
   const int n0 = un.nt * NT;
   const int tile_raw = un.rb * ROWS_WAVES + wave;
   const bool tile_ok = tile_raw < p.n_tiles;
@@ -761,98 +765,147 @@ __global__ __launch_bounds__(64 * ROWS_WAVES) void mpgemm_rows8_kernel(const Row
   const uint32_t* my_idx = p.idx + ((size_t)tile * p.n_chunks * 64 + lane) * BITS;
   const uint32_t* my_sz = p.sz + (size_t)tile * p.nq * 64 + lane;
   const uint32_t lds0 = (uint32_t)(uintptr_t)((rows_lds_char*)tab);
-  const int cz0 = un.kz * R8_CH;
-  const int nc = min(R8_CH, p.n_chunks - cz0);  // chunks of this workgroup (at least one)
+  const int cz0 = un.kz * p.grid8.per + min(un.kz, p.grid8.more);
+  const int nc = p.grid8.per + (un.kz < p.grid8.more ? 1 : 0);  // chunks of this workgroup, 1 to R8_MOST
 
-  // 1. all global loads, unconditional (clamped addresses): indices, {scale, zero} of every chunk's group
-  uint32_t x[R8_CH][BITS];
+  // 1. all global loads, unconditional (clamped addresses): activations, indices, {scale, zero} of every chunk's group;
+  // those of chunks 8 to 15 follow when their places are free
+  constexpr int ITEMS = Sh::TPC * NT / 4;  // tables of four rows in a chunk
+  static_assert(!FUSED || R8_MOST * ITEMS <= 64 * ROWS_WAVES, "one item for each thread");
+  constexpr int SUM_ROWS = (NT + ROWS_WAVES - 1) / ROWS_WAVES;  // rows whose sums a wavefront makes: wave, wave + 4
+  using SumT = typename std::conditional<IS_INT, ru32x2v, ru32x4v>::type;
+  ru32x2v build[4];
+  SumT act[SUM_ROWS];  // eight activations for each lane
+  if constexpr (FUSED) {
+    rows_item_load<NT, IS_INT>(p, build, threadIdx.x, n0, cz0 * Sh::TPC);
 #pragma unroll
-  for (int c = 0; c < R8_CH; ++c) {
+    for (int i = 0; i < SUM_ROWS; ++i) {
+      const int64_t at = min(n0 + wave + i * ROWS_WAVES, p.N - 1) * p.lda + min((cz0 << 5) + 8 * lane, p.K - 8);
+      act[i] = *reinterpret_cast<const SumT*>(static_cast<const char*>(p.A) + at * (IS_INT ? 1 : 2));
+    }
+  }
+  const int cmask = (1 << p.cpg_log2) - 1;
+  uint32_t x[R8_CH][BITS];
+  uint32_t szv[R8_CH];
+  auto load_chunk = [&](int c, uint32_t (&xc)[BITS], uint32_t& sz) {
     const uint32_t* src = my_idx + (size_t)min(cz0 + c, p.n_chunks - 1) * 64 * BITS;
     if constexpr (BITS == 4) {
       const ru32x4v v = *reinterpret_cast<const ru32x4v*>(src);
-      x[c][0] = v.x; x[c][1] = v.y; x[c][2] = v.z; x[c][3] = v.w;
+      xc[0] = v.x; xc[1] = v.y; xc[2] = v.z; xc[3] = v.w;
     } else if constexpr (BITS == 2) {
       const ru32x2v v = *reinterpret_cast<const ru32x2v*>(src);
-      x[c][0] = v.x; x[c][1] = v.y;
+      xc[0] = v.x; xc[1] = v.y;
     } else {
 #pragma unroll
-      for (int b = 0; b < BITS; ++b) x[c][b] = src[b];
+      for (int b = 0; b < BITS; ++b) xc[b] = src[b];
     }
-  }
-  uint32_t szv[R8_CH];
-#pragma unroll
-  for (int c = 0; c < R8_CH; ++c) {
     const int gq = p.grouped ? min((cz0 + c) >> p.cpg_log2, p.nq - 1) : 0;
-    szv[c] = (p.grouped || !p.per_tensor) ? my_sz[(size_t)gq * 64] : 0u;
-  }
+    sz = *(p.per_tensor ? my_idx : my_sz + (size_t)gq * 64);  // (per tensor: there are none; not used)
+  };
+#pragma unroll
+  for (int c = 0; c < R8_CH; ++c) load_chunk(c, x[c], szv[c]);
+  const uint32_t sz_row = szv[0];
 
-  // 2. tables of the eight chunks, and the group sums, into LDS
+  // 2. tables of the chunks, and the sums of activations, into LDS.  A slice may begin and end inside a quantisation
+  // group.  From a LUT buffer the bias term of the whole group goes with the slice that holds its first chunk; from
+  // the activations every slice adds the term of its own chunks.
   const int kg_end = min((cz0 + nc) * Sh::TPC, p.KG);
   if constexpr (FUSED) {
-    // sums of the quantisation groups of the slice, from the activations: thread
-    // i takes eight activations of row i / 32, the 4 cpg threads of a group add up by butterfly
-    // (they sit in one half of a wavefront), and one thread per chunk publishes the group's sum
-    const int t = threadIdx.x >> 5, seg = threadIdx.x & 31;
-    float ssum = 0.f;
-    const int n = n0 + t, k0 = (cz0 << 5) + 8 * seg;
-    if (t < NT && n < p.N && k0 < p.K) {
+    if ((int)threadIdx.x < nc * ITEMS) rows_stage_item<NT, IS_INT, PAD>(p, tab, build, threadIdx.x, n0, cz0 * Sh::TPC, kg_end);
+    // lane: eight activations of a row, four lanes a chunk, whose sum by butterfly; then the sums up to each chunk from
+    // the group's start (or the slice's)
+    float ssum[SUM_ROWS];
+    const int k0 = (cz0 << 5) + 8 * lane, c = lane >> 2;
+#pragma unroll
+    for (int r = 0; r < SUM_ROWS; ++r) {
+      const SumT v = act[r];
       if constexpr (IS_INT) {
-        const ru32x2v v = *reinterpret_cast<const ru32x2v*>(static_cast<const int8_t*>(p.A) + n * p.lda + k0);
         int si = __builtin_amdgcn_sdot4((int)v.x, 0x01010101, 0, false);
         si = __builtin_amdgcn_sdot4((int)v.y, 0x01010101, si, false);
-        ssum = (float)si;  // sums of a group stay below 2^24: exact
+        ssum[r] = (float)si;  // sums of a group stay below 2^24: exact
       } else {
-        const ru32x4v v = *reinterpret_cast<const ru32x4v*>(static_cast<const __half*>(p.A) + n * p.lda + k0);
         float f[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) f[i] = __half2float(__ushort_as_half((uint16_t)(v[i >> 1] >> (16 * (i & 1)))));
-        ssum = ((f[0] + f[1]) + (f[2] + f[3])) + ((f[4] + f[5]) + (f[6] + f[7]));
+        ssum[r] = ((f[0] + f[1]) + (f[2] + f[3])) + ((f[4] + f[5]) + (f[6] + f[7]));
+      }
+      if (n0 + wave + r * ROWS_WAVES >= p.N || c >= nc || k0 >= p.K) ssum[r] = 0.f;
+      ssum[r] += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(ssum[r]), 0xB1, 0xf, 0xf, true));  // lane ^ 1
+      ssum[r] += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(ssum[r]), 0x4E, 0xf, 0xf, true));  // lane ^ 2
+    }
+    if (p.grouped) {
+      const int back = min((cz0 + c) & cmask, c);  // chunks before c in the same group and slice
+      for (int o = 1; o <= cmask; o <<= 1) {
+#pragma unroll
+        for (int r = 0; r < SUM_ROWS; ++r) {
+          const float before = __shfl_up(ssum[r], 4 * o);
+          if (o <= back) ssum[r] += before;
+        }
+      }
+      if ((lane & 3) == 0) {
+#pragma unroll
+        for (int r = 0; r < SUM_ROWS; ++r) sS[c][wave + r * ROWS_WAVES] = ssum[r];
+      }
+    } else if (un.rb == 0) {
+      // (one scale per row or tensor: the whole slice's sum per row, for rows_sum_kernel)
+#pragma unroll
+      for (int r = 0; r < SUM_ROWS; ++r) {
+#pragma unroll
+        for (int o = 4; o < 64; o <<= 1) ssum[r] += __shfl_xor(ssum[r], o);
+        const int n = n0 + wave + r * ROWS_WAVES;
+        if (n < p.N && lane == 0) p.ws_srow[(size_t)un.kz * p.N + n] = IS_INT ? __int_as_float((int)ssum[r]) : ssum[r];
       }
     }
-    // (one scale per row or per tensor: the whole slice's sum per row, for rows_sum_kernel)
-    const int span = p.grouped ? (4 << p.cpg_log2) : 32;
-    for (int o = 1; o < span; o <<= 1) ssum += __shfl_xor(ssum, o);
-    if (p.grouped) {
-      if (t < NT && (seg & 3) == 0) sS[seg >> 2][t] = ssum;
-    } else if (un.rb == 0 && t < NT && n < p.N && seg == 0) {
-      p.ws_srow[(size_t)un.kz * p.N + n] = IS_INT ? __int_as_float((int)ssum) : ssum;
-    }
-    for (int it = threadIdx.x; it < R8_CH * Sh::CB / (8 * Sh::ES); it += 64 * ROWS_WAVES)
-      rows_stage_item<NT, G, IS_INT>(p, tab, it, n0, cz0 * Sh::TPC, kg_end);
   } else {
-  rows_stage_copy<IS_INT, NT, G, R8_CH * Sh::CB>(p, tab, un.nt, cz0 * Sh::TPC, kg_end);
-  if (p.grouped && threadIdx.x < R8_CH * NT) {
-    const int c = threadIdx.x / NT, t = threadIdx.x % NT;
-    const int gq = min((cz0 + c) >> p.cpg_log2, p.nq - 1);
-    const int n = min(n0 + t, p.N - 1);
-    if constexpr (IS_INT) sS[c][t] = (float)static_cast<const int*>(p.S)[(size_t)n * p.nq + gq];
-    else sS[c][t] = static_cast<const float*>(p.S)[(size_t)n * p.nq + gq];
-  }
+    rows_stage_copy<IS_INT, NT, G, R8_CH * Sh::CB>(p, tab, un.nt, cz0 * Sh::TPC, kg_end);
+    if (nc > R8_CH) rows_stage_copy<IS_INT, NT, G, R8_CH * Sh::CB>(p, tab + R8_CH * Sh::CB, un.nt, (cz0 + R8_CH) * Sh::TPC, kg_end);
+    if (p.grouped && threadIdx.x < R8_MOST * NT) {
+      const int c = threadIdx.x / NT, t = threadIdx.x % NT;
+      const int gq = min((cz0 + c) >> p.cpg_log2, p.nq - 1);
+      const int n = min(n0 + t, p.N - 1);
+      const bool whole = gq << p.cpg_log2 >= cz0;  // the group begins in this slice
+      if constexpr (IS_INT) sS[c][t] = whole ? (float)static_cast<const int*>(p.S)[(size_t)n * p.nq + gq] : 0.f;
+      else sS[c][t] = whole ? static_cast<const float*>(p.S)[(size_t)n * p.nq + gq] : 0.f;
+    }
   }
   __syncthreads();
 
-  // 3. the chunks, straight-line
+  // 3. the chunks, eight at a time straight-line
   float acc[NT];
   AccT L[NT];
-  // (integer tables: minus the biases of the chunks that enter one sum, a group's or this workgroup's)
-  const AccT L0 = IS_INT ? (AccT)(-ROWS_CHUNK_BIAS * ((1 << BITS) - 1) * (p.grouped ? 1 << p.cpg_log2 : nc)) : (AccT)0;
+  // (integer tables: minus the biases of the chunks that enter one sum, a group's in this slice or the slice's)
+  auto start_sum = [&](int c) {
+    const AccT L0 = IS_INT ? (AccT)(-ROWS_CHUNK_BIAS * ((1 << BITS) - 1) * (p.grouped ? min(cmask + 1 - ((cz0 + c) & cmask), nc - c) : nc)) : (AccT)0;
 #pragma unroll
-  for (int t = 0; t < NT; ++t) { acc[t] = 0.f; L[t] = L0; }
-  const int cmask = (1 << p.cpg_log2) - 1;
+    for (int t = 0; t < NT; ++t) L[t] = L0;
+  };
 #pragma unroll
-  for (int c = 0; c < R8_CH; ++c) {
-    if (c < nc) {
-      rows_chunk<IS_INT, BITS, NT, G>(x[c], lds0 + (uint32_t)c * (uint32_t)Sh::CB, L, p.pw);
-      // a quantisation group ends with this chunk (chunks in the K padding belong to no group)
-      if (p.grouped && ((cz0 + c + 1) & cmask) == 0 && ((cz0 + c) >> p.cpg_log2) < p.nq) {
-        const float s = __half2float(__ushort_as_half((uint16_t)(szv[c] & 0xffffu)));
-        const float z = __half2float(__ushort_as_half((uint16_t)(szv[c] >> 16)));
+  for (int t = 0; t < NT; ++t) acc[t] = 0.f;
+  start_sum(0);
+#pragma unroll 1
+  for (int c0 = 0; c0 < nc; c0 += R8_CH) {
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
-          acc[t] = fmaf(s, fmaf(p.mid - z, sS[c][t], 0.5f * (float)L[t]), acc[t]);
-          L[t] = L0;
+    for (int i = 0; i < R8_CH; ++i) {
+      const int c = c0 + i;
+      if (c < nc) {
+        // wavefronts that are behind come first (see mpgemm_run_kernel)
+        if (c0 == 0) {
+          if (i == 0) __builtin_amdgcn_s_setprio(3);
+          if (i == 3) __builtin_amdgcn_s_setprio(2);
+          if (i == 6) __builtin_amdgcn_s_setprio(1);
+        } else if (i == 0) {
+          __builtin_amdgcn_s_setprio(0);
         }
+        rows_chunk<IS_INT, BITS, NT, G, AccT, 1, 0, PAD, NT == 8 ? 8 : 16>(x[i], lds0 + (uint32_t)c * (uint32_t)Sh::CB, L, p.pw);
+        // a quantisation group, or its part in this slice, ends with this chunk (chunks in the K padding belong to no group)
+        if (p.grouped && (((cz0 + c + 1) & cmask) == 0 || c + 1 == nc) && ((cz0 + c) >> p.cpg_log2) < p.nq) {
+          const float s = __half2float(__ushort_as_half((uint16_t)(szv[i] & 0xffffu)));
+          const float z = __half2float(__ushort_as_half((uint16_t)(szv[i] >> 16)));
+#pragma unroll
+          for (int t = 0; t < NT; ++t) acc[t] = fmaf(s, fmaf(p.mid - z, sS[c][t], 0.5f * (float)L[t]), acc[t]);
+          start_sum(c + 1);
+        }
+        if (c + R8_CH < nc) load_chunk(c + R8_CH, x[i], szv[i]);
       }
     }
   }
@@ -863,8 +916,8 @@ __global__ __launch_bounds__(64 * ROWS_WAVES) void mpgemm_rows8_kernel(const Row
     if (!tile_ok || m >= p.M) return;
     float s = p.wscale, z = p.zero_point;
     if (!p.grouped && !p.per_tensor) {
-      s = __half2float(__ushort_as_half((uint16_t)(szv[0] & 0xffffu)));
-      z = __half2float(__ushort_as_half((uint16_t)(szv[0] >> 16)));
+      s = __half2float(__ushort_as_half((uint16_t)(sz_row & 0xffffu)));
+      z = __half2float(__ushort_as_half((uint16_t)(sz_row >> 16)));
     }
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
@@ -1645,9 +1698,11 @@ static hipError_t launch_rows_fix(const RowsParams& p, const RowsPlan& pl, int b
 template <bool IS_INT, int BITS, int NT, bool FUSED>
 static hipError_t launch_rows8_one(const RowsParams& p, hipStream_t st) {
   RowsParams local = p;
-  const int nz = (p.n_chunks + R8_CH - 1) / R8_CH;
+  const int nz = p.slices;
   void* args[] = {&local};
   const dim3 grid((p.N + NT - 1) / NT, (p.n_tiles + ROWS_WAVES - 1) / ROWS_WAVES, nz);
+  const uint64_t units = (uint64_t)grid.x * grid.y * grid.z;
+  local.grid8 = Rows8Grid{p.n_chunks / nz, p.n_chunks % nz, rows_inverse(grid.x, units), rows_inverse(grid.y, units / grid.x)};
   hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(mpgemm_rows8_kernel<IS_INT, BITS, NT, FUSED>), grid,
                                  dim3(64 * ROWS_WAVES), args, 0, st);
   if (e != hipSuccess || nz == 1) return e;
@@ -1669,6 +1724,20 @@ template <bool IS_INT, bool FUSED = false>
 static hipError_t launch_rows8_nt(const RowsParams& p, int nt, int bits, hipStream_t st) {
   return nt == ROWS_NT_WIDE ? launch_rows8_bits<IS_INT, ROWS_NT_WIDE, FUSED>(p, bits, st)
                             : launch_rows8_bits<IS_INT, ROWS_NT_NARROW, FUSED>(p, bits, st);
+}
+
+static int rows8_slices(int64_t pairs, int n_chunks) {
+  const int most = (n_chunks + R8_CH - 1) / R8_CH, least = (n_chunks + R8_MOST - 1) / R8_MOST;
+  int best = most;
+  int64_t least_time = INT64_MAX;
+  for (int s = least; s <= most; ++s) {
+    const int64_t time = (pairs * s + ROWS_RUN_WGS - 1) / ROWS_RUN_WGS * ((n_chunks + s - 1) / s);
+    if (time < least_time) {
+      least_time = time;
+      best = s;
+    }
+  }
+  return best;
 }
 
 // How a call is split: workgroups along N and M, and the number of K slices (1 when the (row block,
@@ -1710,6 +1779,7 @@ static RowsPlan rows_plan_oct(const tmac_wdesc* desc, int N, int oct) {
   pl.fix_tiles = pl.fix_shift = pl.fix_wgs = pl.fix_total = pl.run_wgs = pl.run_total = 0;
   pl.fix_part_bytes = pl.fix_tab_bytes = pl.fix_scale_bytes = pl.fix_sums_bytes = 0;
   pl.srow_bytes = pl.eight ? ((size_t)pl.slices * N * 4 + 255) / 256 * 256 : 0;
+  if (pl.eight) pl.slices = rows8_slices(pairs, ge.n_chunks);
   return pl;
 }
 
@@ -1877,6 +1947,7 @@ int launch_rows_gemm(const tmac_wdesc* desc, const void* packed_dev, const void*
   p.cpg_log2 = 0;
   while ((2 << p.cpg_log2) <= p.cpg) ++p.cpg_log2;
   p.cps = pl.cps;
+  p.slices = pl.slices;
   p.Mp = ge.Mp;
   p.ws_part = static_cast<float*>(workspace_dev);
   p.ws_srow = (fused && one_group) ? reinterpret_cast<float*>(static_cast<char*>(workspace_dev) + pl.part_bytes + pl.ctr_bytes)
