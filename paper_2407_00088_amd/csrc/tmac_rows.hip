@@ -301,8 +301,7 @@ __device__ __forceinline__ void rows_stage_item(const RowsParams& p, char* tab, 
 // entries), per activation row.
 // With OCT = 2 the workgroup serves two sets of NT activation rows whose tables sit OSTRIDE bytes
 // apart in LDS: one address (one permute) then feeds two reads, and L holds 2 NT sums.
-// ROUND: reads that are in flight at once.
-template <bool IS_INT, int BITS, int NT, int G, typename AccT, int OCT = 1, int OSTRIDE = 0, int PAD = 0, int ROUND = 16>
+template <bool IS_INT, int BITS, int NT, int G, typename AccT, int OCT = 1, int OSTRIDE = 0, int PAD = 0>
 __device__ __forceinline__ void rows_chunk(const uint32_t (&x)[BITS], uint32_t cbase, AccT (&L)[NT * OCT],
                                            const float (&pw)[4]) {
   using Sh = RowsShape<NT, G, PAD>;
@@ -310,7 +309,7 @@ __device__ __forceinline__ void rows_chunk(const uint32_t (&x)[BITS], uint32_t c
   static_assert(OCT == 1 || (OCT == 2 && NT == 8 && TPC * OCT <= 16), "two row sets: eight rows each, g = 4");
   // rounds of 16 LDS reads (one, two or four planes at g = 2, 4, 8): the hardware counts at
   // most 15 outstanding LDS operations exactly, so a round's reads can be consumed as they return
-  constexpr int PL = ROUND / (TPC * OCT);
+  constexpr int PL = 16 / (TPC * OCT);
   uint32_t c[OCT * HD];  // integer tables: planes 0..2 with their weights, as biased 16-bit pairs
 #pragma unroll
   for (int b0 = 0; b0 < BITS; b0 += PL) {
@@ -719,7 +718,11 @@ static hipError_t launch_rows_nt(const RowsParams& p, int g, int nt, int oct, in
 // straight-line code, and the partial sums are written with plain stores; rows_sum_kernel, the
 // next kernel on the stream, adds the slices in slice order and finishes.
 constexpr int R8_CH = 8;     // chunks whose indices a wavefront holds at once
-constexpr int R8_MOST = 16;  // most chunks of a slice: four workgroups' tables of eight activation rows fill 128 KB of LDS
+constexpr int R8_MOST = 16;  // most chunks of a slice: four workgroups' tables of eight activation rows take 147 KB of LDS
+// LDS bytes of a chunk's tables (those built in the kernel lie further apart: RowsShape)
+constexpr int rows8_chunk_bytes(int nt, bool fused) {
+  return nt == 8 ? (fused ? RowsShape<8, 4, 16>::CB : RowsShape<8, 4>::CB) : (fused ? RowsShape<4, 4, 8>::CB : RowsShape<4, 4>::CB);
+}
 
 // Which (n tile, row block, K slice) a workgroup serves.  The hardware hands workgroups to the
 // chip's eight XCDs (one L2 each) round-robin by linear id; with the plain blockIdx mapping the
@@ -751,8 +754,9 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_rows8_kernel(const 
   static_assert(64 * 8 >= 32 * R8_MOST, "a lane for eight activations of a row's slice");
   constexpr int G = 4, PAD = FUSED ? 2 * NT : 0;
   using Sh = RowsShape<NT, G, PAD>;
-  __shared__ __attribute__((aligned(2048))) char tab[R8_MOST * Sh::CB];
-  __shared__ float sS[R8_MOST][NT];  // [chunk]: sum of activations for the bias term added after it (see 2.)
+  extern __shared__ __attribute__((aligned(2048))) char rows8_lds[];  // as many chunks as the longest slice has (launch_rows8_one)
+  float (*const sS)[NT] = reinterpret_cast<float (*)[NT]>(rows8_lds);  // [chunk]: sum of activations for the bias term added after it (see 2.)
+  char* const tab = rows8_lds + R8_MOST * NT * 4;
   using AccT = typename std::conditional<IS_INT, int, float>::type;
 
   const int lane = threadIdx.x & 63;
@@ -768,8 +772,8 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_rows8_kernel(const 
   const int cz0 = un.kz * p.grid8.per + min(un.kz, p.grid8.more);
   const int nc = p.grid8.per + (un.kz < p.grid8.more ? 1 : 0);  // chunks of this workgroup, 1 to R8_MOST
 
-  // 1. all global loads, unconditional (clamped addresses): activations, indices, {scale, zero} of every chunk's group;
-  // those of chunks 8 to 15 follow when their places are free
+  // 1. all global loads, unconditional (clamped addresses): activations, indices, {scale, zero} of the first groups;
+  // indices of chunks 8 to 15 follow when their places are free, scales one group ahead
   constexpr int ITEMS = Sh::TPC * NT / 4;  // tables of four rows in a chunk
   static_assert(!FUSED || R8_MOST * ITEMS <= 64 * ROWS_WAVES, "one item for each thread");
   constexpr int SUM_ROWS = (NT + ROWS_WAVES - 1) / ROWS_WAVES;  // rows whose sums a wavefront makes: wave, wave + 4
@@ -786,8 +790,7 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_rows8_kernel(const 
   }
   const int cmask = (1 << p.cpg_log2) - 1;
   uint32_t x[R8_CH][BITS];
-  uint32_t szv[R8_CH];
-  auto load_chunk = [&](int c, uint32_t (&xc)[BITS], uint32_t& sz) {
+  auto load_chunk = [&](int c, uint32_t (&xc)[BITS]) {
     const uint32_t* src = my_idx + (size_t)min(cz0 + c, p.n_chunks - 1) * 64 * BITS;
     if constexpr (BITS == 4) {
       const ru32x4v v = *reinterpret_cast<const ru32x4v*>(src);
@@ -799,12 +802,14 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_rows8_kernel(const 
 #pragma unroll
       for (int b = 0; b < BITS; ++b) xc[b] = src[b];
     }
-    const int gq = p.grouped ? min((cz0 + c) >> p.cpg_log2, p.nq - 1) : 0;
-    sz = *(p.per_tensor ? my_idx : my_sz + (size_t)gq * 64);  // (per tensor: there are none; not used)
   };
+  // {scale, zero} of a group (per tensor: there are none; not used): the present one and the next
+  auto load_sz = [&](int gq) { return *(p.per_tensor ? my_idx : my_sz + (size_t)min(gq, p.nq - 1) * 64); };
+  int gq = p.grouped ? cz0 >> p.cpg_log2 : 0;
+  load_chunk(0, x[0]);
+  uint32_t szv = load_sz(gq), szv_next = load_sz(gq + 1);
 #pragma unroll
-  for (int c = 0; c < R8_CH; ++c) load_chunk(c, x[c], szv[c]);
-  const uint32_t sz_row = szv[0];
+  for (int c = 1; c < R8_CH; ++c) load_chunk(c, x[c]);
 
   // 2. tables of the chunks, and the sums of activations, into LDS.  A slice may begin and end inside a quantisation
   // group.  From a LUT buffer the bias term of the whole group goes with the slice that holds its first chunk; from
@@ -896,16 +901,19 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_rows8_kernel(const 
         } else if (i == 0) {
           __builtin_amdgcn_s_setprio(0);
         }
-        rows_chunk<IS_INT, BITS, NT, G, AccT, 1, 0, PAD, NT == 8 ? 8 : 16>(x[i], lds0 + (uint32_t)c * (uint32_t)Sh::CB, L, p.pw);
+        rows_chunk<IS_INT, BITS, NT, G, AccT, 1, 0, PAD>(x[i], lds0 + (uint32_t)c * (uint32_t)Sh::CB, L, p.pw);
         // a quantisation group, or its part in this slice, ends with this chunk (chunks in the K padding belong to no group)
-        if (p.grouped && (((cz0 + c + 1) & cmask) == 0 || c + 1 == nc) && ((cz0 + c) >> p.cpg_log2) < p.nq) {
-          const float s = __half2float(__ushort_as_half((uint16_t)(szv[i] & 0xffffu)));
-          const float z = __half2float(__ushort_as_half((uint16_t)(szv[i] >> 16)));
+        if (p.grouped && (((cz0 + c + 1) & cmask) == 0 || c + 1 == nc) && gq < p.nq) {
+          const float s = __half2float(__ushort_as_half((uint16_t)(szv & 0xffffu)));
+          const float z = __half2float(__ushort_as_half((uint16_t)(szv >> 16)));
+          szv = szv_next;
+          ++gq;
+          szv_next = load_sz(gq + 1);
 #pragma unroll
           for (int t = 0; t < NT; ++t) acc[t] = fmaf(s, fmaf(p.mid - z, sS[c][t], 0.5f * (float)L[t]), acc[t]);
           start_sum(c + 1);
         }
-        if (c + R8_CH < nc) load_chunk(c + R8_CH, x[i], szv[i]);
+        if (c + R8_CH < nc) load_chunk(c + R8_CH, x[i]);
       }
     }
   }
@@ -916,8 +924,8 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_rows8_kernel(const 
     if (!tile_ok || m >= p.M) return;
     float s = p.wscale, z = p.zero_point;
     if (!p.grouped && !p.per_tensor) {
-      s = __half2float(__ushort_as_half((uint16_t)(sz_row & 0xffffu)));
-      z = __half2float(__ushort_as_half((uint16_t)(sz_row >> 16)));
+      s = __half2float(__ushort_as_half((uint16_t)(szv & 0xffffu)));
+      z = __half2float(__ushort_as_half((uint16_t)(szv >> 16)));
     }
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
@@ -1703,8 +1711,9 @@ static hipError_t launch_rows8_one(const RowsParams& p, hipStream_t st) {
   const dim3 grid((p.N + NT - 1) / NT, (p.n_tiles + ROWS_WAVES - 1) / ROWS_WAVES, nz);
   const uint64_t units = (uint64_t)grid.x * grid.y * grid.z;
   local.grid8 = Rows8Grid{p.n_chunks / nz, p.n_chunks % nz, rows_inverse(grid.x, units), rows_inverse(grid.y, units / grid.x)};
+  const int lds = R8_MOST * NT * 4 + (local.grid8.per + (local.grid8.more > 0)) * rows8_chunk_bytes(NT, FUSED);
   hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(mpgemm_rows8_kernel<IS_INT, BITS, NT, FUSED>), grid,
-                                 dim3(64 * ROWS_WAVES), args, 0, st);
+                                 dim3(64 * ROWS_WAVES), args, lds, st);
   if (e != hipSuccess || nz == 1) return e;
   return launch_rows_sum<IS_INT>(p, nz, st);
 }
@@ -1726,14 +1735,20 @@ static hipError_t launch_rows8_nt(const RowsParams& p, int nt, int bits, hipStre
                             : launch_rows8_bits<IS_INT, ROWS_NT_NARROW, FUSED>(p, bits, st);
 }
 
-static int rows8_slices(int64_t pairs, int n_chunks) {
+// K slices of the eight-chunk kernel, eight to sixteen chunks each: as many as fill the chip once, where that many
+// fill it; a second, partly empty round costs as much as the first (16 rows x 11008 x 4096, 4 bit: 1376 workgroups of
+// eight chunks 30.0 us, 946 of eleven or twelve 27.0).  Workgroups per CU by registers (four wavefronts each) and LDS.
+static int rows8_slices(int64_t pairs, int n_chunks, int nt, int bits) {
+  const int by_regs = nt == 8 ? (bits == 1 ? 6 : 4) : (bits == 1 ? 8 : bits == 2 ? 6 : 5);
   const int most = (n_chunks + R8_CH - 1) / R8_CH, least = (n_chunks + R8_MOST - 1) / R8_MOST;
   int best = most;
-  int64_t least_time = INT64_MAX;
-  for (int s = least; s <= most; ++s) {
-    const int64_t time = (pairs * s + ROWS_RUN_WGS - 1) / ROWS_RUN_WGS * ((n_chunks + s - 1) / s);
-    if (time < least_time) {
-      least_time = time;
+  double best_time = 1e300;
+  for (int s = most; s >= least; --s) {
+    const int len = (n_chunks + s - 1) / s, by_lds = 163840 / (R8_MOST * nt * 4 + len * rows8_chunk_bytes(nt, true));
+    const double rounds = (double)(pairs * s) / (256 * (by_regs < by_lds ? by_regs : by_lds));
+    const double time = (len + 2) * (rounds <= 1. ? 1. : rounds + 0.5);  // (starts and ends weigh about two chunks)
+    if (time < best_time) {
+      best_time = time;
       best = s;
     }
   }
@@ -1779,7 +1794,7 @@ static RowsPlan rows_plan_oct(const tmac_wdesc* desc, int N, int oct) {
   pl.fix_tiles = pl.fix_shift = pl.fix_wgs = pl.fix_total = pl.run_wgs = pl.run_total = 0;
   pl.fix_part_bytes = pl.fix_tab_bytes = pl.fix_scale_bytes = pl.fix_sums_bytes = 0;
   pl.srow_bytes = pl.eight ? ((size_t)pl.slices * N * 4 + 255) / 256 * 256 : 0;
-  if (pl.eight) pl.slices = rows8_slices(pairs, ge.n_chunks);
+  if (pl.eight) pl.slices = rows8_slices(pairs, ge.n_chunks, pl.nt, desc->bits);
   return pl;
 }
 
