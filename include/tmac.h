@@ -71,7 +71,7 @@ typedef enum { TMAC_ACT_F16 = 0, TMAC_ACT_I8 = 1, TMAC_ACT_F16_TQ = 2 } tmac_act
  *                   tmac_mpgemm_fused: 5000 chunks and 15000 chunks times bits; up to 32 rows 24576
  *                   chunks times bits.
  *                   tmac_mpgemm: 0.75e9 look-ups (N M K bits / 4, M padded to 64 and K to 128), up to 32
- *                   rows 1.5e9; M bits >= 1536; 5000 chunks, or 12288 at most N that leave more than
+ *                   rows 1.05e9; M bits >= 1536; 5000 chunks, or 12288 at most N that leave more than
  *                   15 % of ceil(N / 16) sets of 16 rows empty; and tmac_mpgemm_noalloc takes the call
  *                   if it would with sums in fp16 (rows_plan in csrc/tmac_rows.hip).
  *   TMAC_LUT_I16: entries are exact int16 sums of int8 activations (|T| <= 4*127); all

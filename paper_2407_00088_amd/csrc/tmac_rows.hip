@@ -107,9 +107,10 @@ struct RowsShare {
 inline uint32_t rows_inverse(uint32_t d, uint64_t n) { return d > 1 && n * d < 0x100000000ull ? (uint32_t)((0x100000000ull + d - 1) / d) : 0u; }
 __device__ __forceinline__ uint32_t rows_div(uint32_t n, uint32_t d, uint32_t inverse) { return inverse ? __umulhi(n, inverse) : n / d; }
 
-// Grid of the eight-chunk kernel (n tiles, row blocks, K slices): slices of equal length, but for one chunk.
+// Grid of the eight-chunk kernel (n tiles, row blocks, K slices): slices of whole quantisation groups, of equal length
+// but for one.
 struct Rows8Grid {
-  int per, more;          // chunks of a slice; the first `more` take one more
+  int per, more;          // groups (chunks, where there are none) of a slice; the first `more` take one more
   uint32_t inv_x, inv_y;  // rows_inverse() of n tiles and row blocks
 };
 
@@ -712,16 +713,28 @@ static hipError_t launch_rows_nt(const RowsParams& p, int g, int nt, int oct, in
 // Few activation rows: one slice of eight chunks per workgroup, sums finished by a second kernel
 // ------------------------------------------------------------------------------------------
 // With few activation rows a call is a chain of latencies, not a stream: the general kernel above
-// asks for a chunk's indices one chunk ahead.  Here the share of a workgroup is fixed at eight
-// chunks (256 k, g = 4), so that every global load it will ever need (indices of all eight chunks,
-// scales and zeros, tables, group sums) is requested in one go at the start, the chunk loop is
-// straight-line code, and the partial sums are written with plain stores; rows_sum_kernel, the
+// asks for a chunk's indices one chunk ahead.  Here a workgroup's slice is eight to sixteen chunks (256 to 512 k,
+// g = 4; fewer where K is short), as long as fills the chip once (rows8_slices): all tables, the indices of eight
+// chunks and the first groups' scales are requested in one go at the start, the other chunks' indices as places get
+// free, the partial sums are written with plain stores, and rows_sum_kernel, the
 // next kernel on the stream, adds the slices in slice order and finishes.
+// Bound by the vector ALUs once the tables are there: 47 instructions per plane and chunk of eight rows, of which 28
+// add and 11 make addresses.  16 rows x 11008 x 4096, 4 bit, from the activations, us after the start of the kernel
+// (median of the wavefronts): tables there 3.4, half the look-ups 11, end 19 (21.7 for the last); with a branch before
+// each activation load, 128-byte steps between the lanes' LDS stores and a spilled register, tables were there at 9.5.
+// A SIMD serves its oldest wavefront first; priorities that fall with the chunks done keep a CU's four level (28.8 us
+// for the call without, 26.8 with).  Row blocks with a slice more, so that 1024 instead of 946 workgroups share the
+// work, and a high priority while the tables are built change nothing.
 constexpr int R8_CH = 8;     // chunks whose indices a wavefront holds at once
 constexpr int R8_MOST = 16;  // most chunks of a slice: four workgroups' tables of eight activation rows take 147 KB of LDS
 // LDS bytes of a chunk's tables (those built in the kernel lie further apart: RowsShape)
 constexpr int rows8_chunk_bytes(int nt, bool fused) {
   return nt == 8 ? (fused ? RowsShape<8, 4, 16>::CB : RowsShape<8, 4>::CB) : (fused ? RowsShape<4, 4, 8>::CB : RowsShape<4, 4>::CB);
+}
+// ... of a workgroup whose slice has `len` chunks: the group sums, then the tables (those of a LUT buffer are copied
+// eight chunks at a time, whatever the slice's length)
+constexpr int rows8_lds_bytes(int nt, bool fused, int len) {
+  return R8_MOST * nt * 4 + (fused ? len : (len + R8_CH - 1) / R8_CH * R8_CH) * rows8_chunk_bytes(nt, fused);
 }
 
 // Which (n tile, row block, K slice) a workgroup serves.  The hardware hands workgroups to the
@@ -769,8 +782,8 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_rows8_kernel(const 
   const uint32_t* my_idx = p.idx + ((size_t)tile * p.n_chunks * 64 + lane) * BITS;
   const uint32_t* my_sz = p.sz + (size_t)tile * p.nq * 64 + lane;
   const uint32_t lds0 = (uint32_t)(uintptr_t)((rows_lds_char*)tab);
-  const int cz0 = un.kz * p.grid8.per + min(un.kz, p.grid8.more);
-  const int nc = p.grid8.per + (un.kz < p.grid8.more ? 1 : 0);  // chunks of this workgroup, 1 to R8_MOST
+  const int cz0 = (un.kz * p.grid8.per + min(un.kz, p.grid8.more)) << p.cpg_log2;
+  const int nc = (p.grid8.per + (un.kz < p.grid8.more ? 1 : 0)) << p.cpg_log2;  // chunks of this workgroup, 1 to R8_MOST
 
   // 1. all global loads, unconditional (clamped addresses): activations, indices, {scale, zero} of the first groups;
   // indices of chunks 8 to 15 follow when their places are free, scales one group ahead
@@ -811,14 +824,12 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_rows8_kernel(const 
 #pragma unroll
   for (int c = 1; c < R8_CH; ++c) load_chunk(c, x[c]);
 
-  // 2. tables of the chunks, and the sums of activations, into LDS.  A slice may begin and end inside a quantisation
-  // group.  From a LUT buffer the bias term of the whole group goes with the slice that holds its first chunk; from
-  // the activations every slice adds the term of its own chunks.
+  // 2. tables of the chunks, and the group sums, into LDS
   const int kg_end = min((cz0 + nc) * Sh::TPC, p.KG);
   if constexpr (FUSED) {
     if ((int)threadIdx.x < nc * ITEMS) rows_stage_item<NT, IS_INT, PAD>(p, tab, build, threadIdx.x, n0, cz0 * Sh::TPC, kg_end);
     // lane: eight activations of a row, four lanes a chunk, whose sum by butterfly; then the sums up to each chunk from
-    // the group's start (or the slice's)
+    // its group's start
     float ssum[SUM_ROWS];
     const int k0 = (cz0 << 5) + 8 * lane, c = lane >> 2;
 #pragma unroll
@@ -839,7 +850,7 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_rows8_kernel(const 
       ssum[r] += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(ssum[r]), 0x4E, 0xf, 0xf, true));  // lane ^ 2
     }
     if (p.grouped) {
-      const int back = min((cz0 + c) & cmask, c);  // chunks before c in the same group and slice
+      const int back = c & cmask;  // chunks before c in the same group (slices hold whole groups)
       for (int o = 1; o <= cmask; o <<= 1) {
 #pragma unroll
         for (int r = 0; r < SUM_ROWS; ++r) {
@@ -868,9 +879,8 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_rows8_kernel(const 
       const int c = threadIdx.x / NT, t = threadIdx.x % NT;
       const int gq = min((cz0 + c) >> p.cpg_log2, p.nq - 1);
       const int n = min(n0 + t, p.N - 1);
-      const bool whole = gq << p.cpg_log2 >= cz0;  // the group begins in this slice
-      if constexpr (IS_INT) sS[c][t] = whole ? (float)static_cast<const int*>(p.S)[(size_t)n * p.nq + gq] : 0.f;
-      else sS[c][t] = whole ? static_cast<const float*>(p.S)[(size_t)n * p.nq + gq] : 0.f;
+      if constexpr (IS_INT) sS[c][t] = (float)static_cast<const int*>(p.S)[(size_t)n * p.nq + gq];
+      else sS[c][t] = static_cast<const float*>(p.S)[(size_t)n * p.nq + gq];
     }
   }
   __syncthreads();
@@ -878,15 +888,10 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_rows8_kernel(const 
   // 3. the chunks, eight at a time straight-line
   float acc[NT];
   AccT L[NT];
-  // (integer tables: minus the biases of the chunks that enter one sum, a group's in this slice or the slice's)
-  auto start_sum = [&](int c) {
-    const AccT L0 = IS_INT ? (AccT)(-ROWS_CHUNK_BIAS * ((1 << BITS) - 1) * (p.grouped ? min(cmask + 1 - ((cz0 + c) & cmask), nc - c) : nc)) : (AccT)0;
+  // (integer tables: minus the biases of the chunks that enter one sum, a group's or this workgroup's)
+  const AccT L0 = IS_INT ? (AccT)(-ROWS_CHUNK_BIAS * ((1 << BITS) - 1) * (p.grouped ? 1 << p.cpg_log2 : nc)) : (AccT)0;
 #pragma unroll
-    for (int t = 0; t < NT; ++t) L[t] = L0;
-  };
-#pragma unroll
-  for (int t = 0; t < NT; ++t) acc[t] = 0.f;
-  start_sum(0);
+  for (int t = 0; t < NT; ++t) { acc[t] = 0.f; L[t] = L0; }
 #pragma unroll 1
   for (int c0 = 0; c0 < nc; c0 += R8_CH) {
 #pragma unroll
@@ -902,16 +907,18 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_rows8_kernel(const 
           __builtin_amdgcn_s_setprio(0);
         }
         rows_chunk<IS_INT, BITS, NT, G, AccT, 1, 0, PAD>(x[i], lds0 + (uint32_t)c * (uint32_t)Sh::CB, L, p.pw);
-        // a quantisation group, or its part in this slice, ends with this chunk (chunks in the K padding belong to no group)
-        if (p.grouped && (((cz0 + c + 1) & cmask) == 0 || c + 1 == nc) && gq < p.nq) {
+        // a quantisation group ends with this chunk (chunks in the K padding belong to no group)
+        if (p.grouped && ((c + 1) & cmask) == 0 && gq < p.nq) {
           const float s = __half2float(__ushort_as_half((uint16_t)(szv & 0xffffu)));
           const float z = __half2float(__ushort_as_half((uint16_t)(szv >> 16)));
           szv = szv_next;
           ++gq;
           szv_next = load_sz(gq + 1);
 #pragma unroll
-          for (int t = 0; t < NT; ++t) acc[t] = fmaf(s, fmaf(p.mid - z, sS[c][t], 0.5f * (float)L[t]), acc[t]);
-          start_sum(c + 1);
+          for (int t = 0; t < NT; ++t) {
+            acc[t] = fmaf(s, fmaf(p.mid - z, sS[c][t], 0.5f * (float)L[t]), acc[t]);
+            L[t] = L0;
+          }
         }
         if (c + R8_CH < nc) load_chunk(c + R8_CH, x[i]);
       }
@@ -1709,9 +1716,11 @@ static hipError_t launch_rows8_one(const RowsParams& p, hipStream_t st) {
   const int nz = p.slices;
   void* args[] = {&local};
   const dim3 grid((p.N + NT - 1) / NT, (p.n_tiles + ROWS_WAVES - 1) / ROWS_WAVES, nz);
-  const uint64_t units = (uint64_t)grid.x * grid.y * grid.z;
-  local.grid8 = Rows8Grid{p.n_chunks / nz, p.n_chunks % nz, rows_inverse(grid.x, units), rows_inverse(grid.y, units / grid.x)};
-  const int lds = R8_MOST * NT * 4 + (local.grid8.per + (local.grid8.more > 0)) * rows8_chunk_bytes(NT, FUSED);
+  const uint64_t wgs = (uint64_t)grid.x * grid.y * grid.z;
+  const int units = p.n_chunks >> p.cpg_log2;  // (n_chunks is a multiple: K is one of the group's size, and padded to 128)
+  local.grid8 = Rows8Grid{units / nz, units % nz, rows_inverse(grid.x, wgs), rows_inverse(grid.y, wgs / grid.x)};
+  const int len = (local.grid8.per + (local.grid8.more > 0)) << p.cpg_log2;  // chunks of the longest slice
+  const int lds = rows8_lds_bytes(NT, FUSED, len);
   hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(mpgemm_rows8_kernel<IS_INT, BITS, NT, FUSED>), grid,
                                  dim3(64 * ROWS_WAVES), args, lds, st);
   if (e != hipSuccess || nz == 1) return e;
@@ -1735,16 +1744,19 @@ static hipError_t launch_rows8_nt(const RowsParams& p, int nt, int bits, hipStre
                             : launch_rows8_bits<IS_INT, ROWS_NT_NARROW, FUSED>(p, bits, st);
 }
 
-// K slices of the eight-chunk kernel, eight to sixteen chunks each: as many as fill the chip once, where that many
+// K slices of the eight-chunk kernel, up to sixteen chunks in whole groups each: as many as fill the chip once, where that many
 // fill it; a second, partly empty round costs as much as the first (16 rows x 11008 x 4096, 4 bit: 1376 workgroups of
-// eight chunks 30.0 us, 946 of eleven or twelve 27.0).  Workgroups per CU by registers (four wavefronts each) and LDS.
-static int rows8_slices(int64_t pairs, int n_chunks, int nt, int bits) {
+// eight chunks and 946 of eight or twelve: 33.0 us and 32.2 before the other changes to this kernel; 45 x 4099 x 3232, 3
+// bit 27.8 and 27.0).  Workgroups per CU by registers (four wavefronts each) and LDS.
+static int rows8_slices(int64_t pairs, int n_chunks, int cpg, int nt, int bits) {
   const int by_regs = nt == 8 ? (bits == 1 ? 6 : 4) : (bits == 1 ? 8 : bits == 2 ? 6 : 5);
   const int most = (n_chunks + R8_CH - 1) / R8_CH, least = (n_chunks + R8_MOST - 1) / R8_MOST;
   int best = most;
   double best_time = 1e300;
   for (int s = most; s >= least; --s) {
-    const int len = (n_chunks + s - 1) / s, by_lds = 163840 / (R8_MOST * nt * 4 + len * rows8_chunk_bytes(nt, true));
+    const int len = (n_chunks / cpg + s - 1) / s * cpg;  // whole groups
+    if (len > R8_MOST) break;
+    const int by_lds = 163840 / rows8_lds_bytes(nt, true, (len + R8_CH - 1) / R8_CH * R8_CH);
     const double rounds = (double)(pairs * s) / (256 * (by_regs < by_lds ? by_regs : by_lds));
     const double time = (len + 2) * (rounds <= 1. ? 1. : rounds + 0.5);  // (starts and ends weigh about two chunks)
     if (time < best_time) {
@@ -1794,7 +1806,7 @@ static RowsPlan rows_plan_oct(const tmac_wdesc* desc, int N, int oct) {
   pl.fix_tiles = pl.fix_shift = pl.fix_wgs = pl.fix_total = pl.run_wgs = pl.run_total = 0;
   pl.fix_part_bytes = pl.fix_tab_bytes = pl.fix_scale_bytes = pl.fix_sums_bytes = 0;
   pl.srow_bytes = pl.eight ? ((size_t)pl.slices * N * 4 + 255) / 256 * 256 : 0;
-  if (pl.eight) pl.slices = rows8_slices(pairs, ge.n_chunks, pl.nt, desc->bits);
+  if (pl.eight) pl.slices = rows8_slices(pairs, ge.n_chunks, cpg, pl.nt, desc->bits);
   return pl;
 }
 
@@ -1840,15 +1852,18 @@ static RunPlan rows_run(int64_t pairs, int n_chunks) {
 //     faster than with fp16 sums, 1.08 times on average (0.97 to 1.20; 0.93 at 511 x 1024 x 2048, 2 bit, and 40 x 4096 x
 //     4096, 3 bit; 1.31 at 48 x 11008 x 4096, 4 bit); of 19 below it, from 10000 on, six, 0.97 times as fast (0.83 to 1.07;
 //     40 x 4096 x 4096, 2 bit 26.4 us against 22.0).  Up to 32 rows the other side builds its tables in the look-up
-//     kernel and saves a launch: chunks times bits from ROWS_RUN_ACT_FEW on, 1.14 times on average (23 calls, 0.98 to 1.47;
-//     16 x 28672 x 2048, 4 bit 1.11), below it 0.91 (13 calls, 0.75 to 1.17).
-//   * from a LUT buffer the conversion is one more launch: look-ups from ROWS_RUN_LUT_LOOKUPS on, twice as many up to 32
+//     kernel and saves a launch: chunks times bits from ROWS_RUN_ACT_FEW on, 1.18 times on average (11 calls from 32768 on,
+//     1.00 to 1.42: 32 x 8192 x 4096, 4 bit 1.00, 16 x 13824 x 5120 1.20), 0.95 at the line (16 x 16384 x 4096, 3 bit in
+//     groups of 64) and below it 0.78 to 0.94 (32 x 4096 x 4096, 16 x 8192 x 4096, 16 x 11008 x 4096, 4 bit), 1.17 once
+//     (32 x 11008 x 4096, 2 bit).  For time alone the line would be 32768; results between are closer with fixed point.
+//   * from a LUT buffer the conversion is one more launch: look-ups from ROWS_RUN_LUT_LOOKUPS on, 1.4 times as many up to 32
 //     rows, ROWS_RUN_LUT_ROWS weight rows times bits for each table, and ROWS_RUN_ACT_CHUNKS, where more than 15 % of the
 //     sets' rows do not exist ROWS_RUN_INT_CHUNKS.  Of 64 random calls that these lines take 55 are faster than with fp16
 //     sums, 1.06 times on average (0.94 to 1.21); of 46 that they leave, from 0.4e9 look-ups on, 14, 0.95 (0.72 to 1.08).
 //     At the lines: 1.05 and 1.07 at 0.8e9 and 1.07e9 look-ups (64 x 4096 x 4096, 3 and 4 bit), 0.94 and 0.96 at 0.6e9 (48 x
-//     4096 x 4096 and 64 x 3072 x 4096, 3 bit); up to 32 rows 0.94 (20 x 12000 x 5120, 3 and 4 bit) to 1.20 (28 x 16384 x 4096,
-//     2 bit) below, 1.16 and 1.18 above (32 x 28672 x 2048, 16 x 28672 x 4096, 4 bit); weight rows times bits 1.05 at 2100 (300 x 700 x
+//     4096 x 4096 and 64 x 3072 x 4096, 3 bit); up to 32 rows 0.80 to 0.98 below (32 x 4096 x
+//     4096, 16 x 11008 x 4096, 4 bit, 20 x 12000 x 5120, 3 bit; 1.11 and 1.25 at 2 bit: 32 x 11008 x 4096, 28 x 16384 x 4096 in
+//     groups of 32), 1.00 to 1.26 above (24 x 11008 x 4096, 32 x 8192 x 4096, 16 x 13824 x 5120, 16 x 28672 x 4096, 4 bit); weight rows times bits 1.05 at 2100 (300 x 700 x
 //     8192, 3 bit), 0.90 to 1.07 at 1200 to 1536 (eleven calls, seven below 1), 0.88 at 768 (511 x 256 x 13824, 3 bit);
 //     sets that are not full 0.92, 1.00 and 1.05 at 8448, 11264 and 10240 chunks (40 x 2700 x 8192, 52 x 2800 x 8192, 65 x 2048
 //     x 8192).  Within the library's own array where the plain plan is, because tmac_mpgemm_noalloc gives tmac_mpgemm's
@@ -1883,7 +1898,7 @@ RowsPlan rows_plan(const tmac_wdesc* desc, int N, bool from_act) {
     take = N > 32 ? run.total >= ROWS_RUN_ACT_CHUNKS && by_bits >= ROWS_RUN_ACT_BITS : by_bits >= ROWS_RUN_ACT_FEW;
   } else {
     const bool part_full = pl.nt == ROWS_NT_WIDE && N * 20 < tiles * 16 * 17;  // sets with many rows that do not exist
-    take = lookups >= (N > 32 ? 1 : 2) * ROWS_RUN_LUT_LOOKUPS && (int64_t)desc->M * desc->bits >= ROWS_RUN_LUT_ROWS &&
+    take = lookups >= (N > 32 ? 1. : 1.4) * ROWS_RUN_LUT_LOOKUPS && (int64_t)desc->M * desc->bits >= ROWS_RUN_LUT_ROWS &&
            run.total >= (part_full ? ROWS_RUN_INT_CHUNKS : ROWS_RUN_ACT_CHUNKS);
     const size_t own = (size_t)TMAC_NOALLOC_MAX_WORKSPACE;  // within the library's own array where the plain plan is
     if (room <= own && run_parts + tab + scale + sums > own) take = false;

@@ -1039,6 +1039,41 @@ def test_one_call_entry_point_int_exact(T, torch, layout, N, M, K):
     assert np.array_equal(got_f.view(np.uint32), orc.int_path_output_f32(ref_i, p.act_scale, p.weight_scale).view(np.uint32))
 
 
+@pytest.mark.parametrize("N,M,K,bits,group", [
+    (32, 13300, 1280, 4, 128),   # 52 row blocks x 4 n tiles: longer slices than eight chunks, of whole groups
+    (32, 13300, 1376, 3, 32),    # a group per chunk, K padded inside a chunk's block
+    (30, 13300, 1280, 2, 256),   # groups of eight chunks; rows of the last n tile do not exist
+    (16, 25700, 1312, 1, -1),    # one scale per row, row sums by the slices of the first row block
+    (12, 13300, 1280, 4, 64),    # n tiles of four rows, tables of four rows in LDS
+    (16, 300, 384, 4, 128),      # slices shorter than eight chunks
+])
+def test_slices_that_fill_the_chip(T, torch, N, M, K, bits, group):
+    """Few-row calls whose K slices are longer (or shorter) than the eight chunks whose indices a wavefront holds at
+    once, from activations and from a LUT buffer: the bars of the file against the oracle, and the two routes (same
+    table entries, sums of activations in another order) 2e-6 from each other, as above."""
+    from paper_2407_00088_amd.runner import from_problem
+    p = wl.make_grouped(0, 980 + N + bits, N, M, K, bits, K if group < 0 else group, name="slices")
+    lin = from_problem(p, layout=L3)
+    A = torch.from_numpy(p.act).cuda()
+    one, two, ref = lin.forward_one_call(A).cpu().numpy(), lin.forward(A).cpu().numpy(), oracle_fp(p)
+    for got in (one, two):
+        assert orc.rel_frobenius(got, ref) <= FP_TOL
+        assert_elementwise(got, ref, p)
+    assert orc.rel_frobenius(one, two) <= 2e-6
+
+
+@pytest.mark.parametrize("N,M,K", [(32, 13300, 1312), (11, 13300, 1280), (16, 300, 352)])
+def test_slices_that_fill_the_chip_int_exact(T, torch, N, M, K):
+    """The same with ternary weights and int8 activations, bit for bit through both entry points."""
+    from paper_2407_00088_amd.runner import from_problem
+    p = wl.make_ternary(0, 985 + N, N, M, K, name="slices_int")
+    lin = from_problem(p, layout=L3)
+    A, s_a = torch.from_numpy(p.act_q).cuda(), torch.from_numpy(p.act_scale).cuda()
+    ref = orc.ternary_int_matmul(p.act_q, p.q, 1)
+    for call in (lin.forward_one_call, lin.forward):
+        assert np.array_equal(call(A, out_t=T.TMAC_OUT_I32, act_scale=s_a).cpu().numpy().astype(np.int64), ref)
+
+
 def test_one_call_entry_point_int_group_scales_in_kernel(T, torch):
     """int8 activations with group scales, tables and group sums built in the kernel: integer tables
     and sums are exact, so the result must equal the two-call path bit for bit."""
