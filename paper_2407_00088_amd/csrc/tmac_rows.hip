@@ -258,7 +258,7 @@ __device__ __forceinline__ void rows_stage_copy(const RowsParams& p, char* tab, 
 // First the activations are requested, without a branch in between (clamped addresses): loads behind a
 // branch each come one after the other.  us from the start of the kernel until all tables are there, 16 rows x 11008 x
 // 4096, 4 bit: 9.5 with a branch before each load, half a table of eight rows for each lane and the tables' first
-// entries in the same LDS bank, 4.5 like this.
+// entries in the same LDS bank, 3.4 like this.
 template <int NT, bool IS_INT>
 __device__ __forceinline__ void rows_item_load(const RowsParams& p, ru32x2v (&a)[4], int it, int n0, int kg0) {
   const int k = min(4 * (kg0 + it / (NT / 4)), p.K - 4), n = n0 + it % (NT / 4) * 4;
