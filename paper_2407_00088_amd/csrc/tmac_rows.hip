@@ -39,6 +39,7 @@
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <type_traits>
@@ -1748,9 +1749,10 @@ static hipError_t launch_rows8_nt(const RowsParams& p, int nt, int bits, hipStre
 // fill it; a second, partly empty round costs as much as the first (16 rows x 11008 x 4096, 4 bit: 1376 workgroups of
 // eight chunks and 946 of eight or twelve: 33.0 us and 32.2 before the other changes to this kernel; 45 x 4099 x 3232, 3
 // bit 27.8 and 27.0).  Workgroups per CU by registers (four wavefronts each) and LDS.
-static int rows8_slices(int64_t pairs, int n_chunks, int cpg, int nt, int bits) {
+// `fewest`: see rows_plan_oct.
+static int rows8_slices(int64_t pairs, int n_chunks, int cpg, int nt, int bits, int fewest) {
   const int by_regs = nt == 8 ? (bits == 1 ? 6 : 4) : (bits == 1 ? 8 : bits == 2 ? 6 : 5);
-  const int most = (n_chunks + R8_CH - 1) / R8_CH, least = (n_chunks + R8_MOST - 1) / R8_MOST;
+  const int most = (n_chunks + R8_CH - 1) / R8_CH, least = std::max((n_chunks + R8_MOST - 1) / R8_MOST, fewest);
   int best = most;
   double best_time = 1e300;
   for (int s = most; s >= least; --s) {
@@ -1766,6 +1768,9 @@ static int rows8_slices(int64_t pairs, int n_chunks, int cpg, int nt, int bits) 
   }
   return best;
 }
+
+// Calls that may build their tables inside the eight-chunk kernel, where it serves them (rows_builds_tables).
+static bool rows_may_build(const tmac_wdesc* desc, int N) { return N <= 32 && desc->K % 8 == 0; }
 
 // How a call is split: workgroups along N and M, and the number of K slices (1 when the (row block,
 // n tile) pairs alone fill the chip; otherwise enough slices of at least 256 k, whole quantisation
@@ -1806,7 +1811,9 @@ static RowsPlan rows_plan_oct(const tmac_wdesc* desc, int N, int oct) {
   pl.fix_tiles = pl.fix_shift = pl.fix_wgs = pl.fix_total = pl.run_wgs = pl.run_total = 0;
   pl.fix_part_bytes = pl.fix_tab_bytes = pl.fix_scale_bytes = pl.fix_sums_bytes = 0;
   pl.srow_bytes = pl.eight ? ((size_t)pl.slices * N * 4 + 255) / 256 * 256 : 0;
-  if (pl.eight) pl.slices = rows8_slices(pairs, ge.n_chunks, cpg, pl.nt, desc->bits);
+  // (tables built in the kernel and one scale per row or tensor: the sums of the activations are in ws_srow, a part from
+  // each slice, for rows_sum_kernel to add, which is launched from two slices on)
+  if (pl.eight) pl.slices = rows8_slices(pairs, ge.n_chunks, cpg, pl.nt, desc->bits, one_group && rows_may_build(desc, N) ? 2 : 1);
   return pl;
 }
 
@@ -1924,7 +1931,7 @@ bool rows_fixed_from_act(const tmac_wdesc* desc, int N) { return desc->g == 4 &&
 // Whether the eight-chunk kernel could build the tables of a call that brings activations; such calls need a
 // leading dimension that is a multiple of eight, whichever kernel serves them.
 bool rows_reads_eight(const tmac_wdesc* desc, int N) {
-  return N <= 32 && desc->K % 8 == 0 && rows_plan_plain(desc, N).eight;  // (activations are summed eight at a time)
+  return rows_may_build(desc, N) && rows_plan_plain(desc, N).eight;  // (activations are summed eight at a time)
 }
 
 // Whether a call builds its tables inside the lookup kernel when it is given activations instead
@@ -1951,6 +1958,7 @@ int launch_rows_gemm(const tmac_wdesc* desc, const void* packed_dev, const void*
   const bool is_int = (lut_t == TMAC_LUT_I16);
   const bool one_group = (desc->group == 0 || desc->group == desc->K);
   const RowsPlan pl = rows_plan(desc, N, from_act);
+  if (fused && one_group && pl.slices < 2) return TMAC_EUNSUPPORTED;  // (no buffer of row sums to finish from)
   if (pl.n_tiles_n > 0x7fffffff || pl.row_blocks > 65535 || pl.slices > 65535) return TMAC_EUNSUPPORTED;
   if (pl.bytes() > 0) {
     if (!workspace_dev) return TMAC_EINVAL;

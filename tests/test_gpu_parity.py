@@ -15,6 +15,7 @@ import numpy as np
 import pytest
 
 import rounding_models as rm
+from plan_probe import rows_plan
 import tmac_workloads as wl
 from oracle import tmac_oracle as orc
 
@@ -1067,6 +1068,45 @@ def test_slices_that_fill_the_chip_int_exact(T, torch, N, M, K):
     """The same with ternary weights and int8 activations, bit for bit through both entry points."""
     from paper_2407_00088_amd.runner import from_problem
     p = wl.make_ternary(0, 985 + N, N, M, K, name="slices_int")
+    lin = from_problem(p, layout=L3)
+    A, s_a = torch.from_numpy(p.act_q).cuda(), torch.from_numpy(p.act_scale).cuda()
+    ref = orc.ternary_int_matmul(p.act_q, p.q, 1)
+    for call in (lin.forward_one_call, lin.forward):
+        assert np.array_equal(call(A, out_t=T.TMAC_OUT_I32, act_scale=s_a).cpu().numpy().astype(np.int64), ref)
+
+
+@pytest.mark.parametrize("N,M,K,bits,group,slices", [
+    (32, 43000, 512, 4, 128, 1),    # group scales, sixteen chunks, tables built in the kernel
+    (29, 41216, 288, 3, 32, 1),     # K padded by three chunks that belong to no group; the last n tile is not full
+    (9, 82500, 512, 3, 256, 1),     # n tiles of four rows
+    (64, 28672, 384, 4, -1, 1),     # one scale per row, row sums from the LUT buffer
+    (32, 43000, 512, 2, -1, 2),     # ... and built in the kernel: their parts meet in the second kernel
+    (9, 82500, 512, 4, -1, 2),
+])
+def test_short_k_with_many_weight_rows(T, torch, N, M, K, bits, group, slices):
+    """K of 288 to 512 with so many weight rows that one K slice fills the chip: the kernel finishes its results itself,
+    except where it builds the tables and there is one scale per row."""
+    from paper_2407_00088_amd.runner import from_problem
+    p = wl.make_grouped(0, 990 + N + bits, N, M, K, bits, K if group < 0 else group, name="short_k")
+    plan = rows_plan(N, M, K, bits, p.group)
+    assert plan.eight and not plan.fix and plan.slices == slices and plan.builds_f16 == (N <= 32)
+    lin = from_problem(p, layout=L3)
+    A = torch.from_numpy(p.act).cuda()
+    one, two, ref = lin.forward_one_call(A).cpu().numpy(), lin.forward(A).cpu().numpy(), oracle_fp(p)
+    for got in (one, two):
+        assert orc.rel_frobenius(got, ref) <= FP_TOL
+        assert_elementwise(got, ref, p)
+    # (more than 32 rows: the one call may look the entries up as integers, 4e-4 from fp16 sums)
+    assert orc.rel_frobenius(one, two) <= (2e-6 if N <= 32 else 1e-3)
+
+
+@pytest.mark.parametrize("N,M,K,slices", [(30, 41300, 384, 2), (9, 82500, 504, 2), (40, 43000, 512, 1)])
+def test_short_k_with_many_weight_rows_int_exact(T, torch, N, M, K, slices):
+    """The same with ternary weights and int8 activations, bit for bit."""
+    from paper_2407_00088_amd.runner import from_problem
+    plan = rows_plan(N, M, K, 2, 0)
+    assert plan.eight and not plan.run_wgs and plan.slices == slices and plan.builds_i8 == (N <= 32)
+    p = wl.make_ternary(0, 995 + N, N, M, K, name="short_k_int")
     lin = from_problem(p, layout=L3)
     A, s_a = torch.from_numpy(p.act_q).cuda(), torch.from_numpy(p.act_scale).cuda()
     ref = orc.ternary_int_matmul(p.act_q, p.q, 1)

@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 
 from blob_unpack import unpack_layout3
+from plan_probe import rows_plan
 
 import paper_2407_00088_amd as T
 from paper_2407_00088_amd import binding as B
@@ -121,3 +122,25 @@ def test_fused_workspace_regions():
     assert B.tmac_fused_workspace_bytes(d2b, 65, F16) == 0     # LUT-buffer route of the register-table kernel: 64 rows at most
     assert B.tmac_fused_workspace_bytes(d2, 65, F16) == 256     # tables built in the kernel: any number of rows
     assert B.tmac_fused_workspace_bytes(d, 0, F16) == 0 and B.tmac_fused_workspace_bytes(d, 1, 7) == 0
+
+
+def test_slices_of_the_eight_chunk_kernel():
+    """K slices of the few-row kernel: at most sixteen chunks, within the workspace, and at least two where the tables may
+    be built in the kernel and there is one scale per row or tensor: the sums of the activations are then known to
+    rows_sum_kernel only, which needs a second slice to be launched."""
+    seen = ones = 0
+    for N in (1, 4, 5, 8, 9, 12, 16, 21, 24, 29, 32, 33, 48, 64, 100):
+        for M in (1, 300, 4096, 13300, 28672, 41216, 42752, 43000, 54784, 68352, 82176, 100000, 164096, 200000):
+            for K, groups in ((264, (0, 264)), (288, (0, 32, 96, 288)), (384, (0, 32, 64, 128, 384)), (504, (0, 504)),
+                              (512, (0, 32, 64, 128, 256, 512)), (640, (0, 64, 128, 640)), (4096, (0, 32, 256, 4096))):
+                for group in groups:
+                    for bits in (1, 2, 3, 4):
+                        p = rows_plan(N, M, K, bits, group)
+                        if not p.eight:
+                            assert not (p.builds_f16 or p.builds_i8)
+                            continue
+                        seen += 1
+                        ones += p.slices == 1
+                        assert 1 <= p.slices and p.longest <= 16 and p.slices * N * p.Mp * 4 <= p.part_bytes
+                        assert p.slices >= 2 or not (p.one_group and (p.builds_f16 or p.builds_i8)), (N, M, K, bits, group)
+    assert seen > 2000 and ones > 50    # (one slice is taken where it can be finished)
