@@ -312,7 +312,7 @@ __device__ __forceinline__ void rows_chunk(const uint32_t (&x)[BITS], uint32_t c
   // rounds of 16 LDS reads (one, two or four planes at g = 2, 4, 8): the hardware counts at
   // most 15 outstanding LDS operations exactly, so a round's reads can be consumed as they return
   constexpr int PL = 16 / (TPC * OCT);
-  uint32_t c[OCT * HD];  // integer tables: planes 0..2 with their weights, as biased 16-bit pairs
+  uint32_t c[OCT * HD];  // integer tables: the planes of a widening with their weights, as biased 16-bit pairs
 #pragma unroll
   for (int b0 = 0; b0 < BITS; b0 += PL) {
     uint32_t e[PL][TPC][OCT * HD];
@@ -374,12 +374,12 @@ __device__ __forceinline__ void rows_chunk(const uint32_t (&x)[BITS], uint32_t c
           uint32_t q = e[bb][0][u];
 #pragma unroll
           for (int j = 1; j < TPC; ++j) q += e[bb][j][u];
-          if (b < 3) {
-            c[u] = b == 0 ? q : c[u] + (q << b);
-            if (b == (BITS < 3 ? BITS - 1 : 2)) rows_widen<1>(L[2 * u], L[2 * u + 1], c[u]);
-          } else {
-            rows_widen<8>(L[2 * u], L[2 * u + 1], q);
-          }
+          // (four planes: two and two, so that no sum stays in registers through the next round of reads; three and one made
+          // the eight-chunk kernel spill 13 registers)
+          constexpr int PLANES = BITS == 4 ? 2 : 3;
+          c[u] = b % PLANES == 0 ? q : c[u] + (q << (b % PLANES));
+          if (b == PLANES - 1 || (b < PLANES && b == BITS - 1)) rows_widen<1>(L[2 * u], L[2 * u + 1], c[u]);
+          else if (b == BITS - 1) rows_widen<1 << PLANES>(L[2 * u], L[2 * u + 1], c[u]);
         } else {
           rh2v q[TPC];
 #pragma unroll
