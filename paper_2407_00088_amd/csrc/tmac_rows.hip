@@ -1465,11 +1465,11 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_run_kernel(const Ro
   };
   int set = (int)rows_div((uint32_t)pair0, p.share.row_blocks, p.share.inv_row_blocks), rb = pair0 - set * row_blocks, c = c00, left = todo, flag = 0;
   const uint32_t* idx = p.idx + ((size_t)tile_of(rb) * chunks + (c & ~3)) * 64 * BITS;
-  request(set, c >> 2);
   constexpr int AHEAD = BITS <= 2 ? 4 : 2;
   uint32_t x[AHEAD][BITS];
 #pragma unroll
   for (int i = 0; i < AHEAD; ++i) load_idx(idx + ((c & (4 - AHEAD)) + i) * 64 * BITS, x[i]);
+  request(set, c >> 2);  // (after the indices: before them 1.005 to 1.02 times the time)
   while (true) {  // the parts of this workgroup, pair by pair
     const int end = min(chunks, c + left);
     left -= end - c;
