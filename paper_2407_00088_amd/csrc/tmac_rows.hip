@@ -34,7 +34,7 @@
 //   * Few activation rows (batched decode) leave too few (row block, n tile) pairs to fill the
 //     chip: K is then also split over gridDim.z workgroups, whose partial sums meet in the
 //     workspace; rows_sum_kernel, the next kernel on the stream, adds them in slice order (fixed
-//     order again) and writes the result.  When the slices are as short as eight chunks (a handful
+//     order again) and writes the result.  Where that asks for slices of eight chunks (a handful
 //     of activation rows), mpgemm_rows8_kernel further down takes the call instead.
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
@@ -706,14 +706,18 @@ static hipError_t launch_rows_nt(const RowsParams& p, int g, int nt, int oct, in
 
 
 // ------------------------------------------------------------------------------------------
-// Few activation rows: one slice of eight chunks per workgroup, sums finished by a second kernel
+// Few activation rows: a slice of at most sixteen chunks per workgroup, sums finished by a second kernel
 // ------------------------------------------------------------------------------------------
 // With few activation rows a call is a chain of latencies, not a stream: the general kernel above
-// asks for a chunk's indices one chunk ahead.  Here a workgroup's slice is eight to sixteen chunks (256 to 512 k,
-// g = 4; fewer where K is short), as long as fills the chip once (rows8_slices): all tables, the indices of eight
-// chunks and the first groups' scales are requested in one go at the start, the other chunks' indices as places get
-// free, the partial sums are written with plain stores, and rows_sum_kernel, the
+// asks for a chunk's indices one chunk ahead.  Here a workgroup's slice is at most sixteen chunks (512 k, g = 4;
+// rows8_slices): all tables and the indices of eight chunks are requested in one go at the start, their scales next, the
+// partial sums are written with plain stores, and rows_sum_kernel, the
 // next kernel on the stream, adds the slices in slice order and finishes.
+// Slices of at most eight chunks are straight-line code.  Longer ones have a variant of their own: indices as places get
+// free, scales two chunks ahead.  Where one variant with scales one group ahead served both, its waits for scales and
+// the registers of its loop made short slices slow.  us, that variant and now (before there were longer slices): 2 x 1680 x
+// 6112, 3 bit in groups of 32 12.8, 10.7 (10.6); 2 x 3692 x 6976, 2 bit in groups of 32 13.0, 11.3 (11.7); 4 x 4096 x 4096, 4
+// bit 11.7, 11.5 (11.7).  A copy of the straight-line code inside the variant with the loop spills registers.
 // Bound by the vector ALUs once the tables are there: 47 instructions per plane and chunk of eight rows, of which 28
 // add and 11 make addresses.  16 rows x 11008 x 4096, 4 bit, from the activations, us after the start of the kernel
 // (median of the wavefronts): tables there 3.4, half the look-ups 11, end 19 (21.7 for the last); with a branch before
@@ -722,6 +726,7 @@ static hipError_t launch_rows_nt(const RowsParams& p, int g, int nt, int oct, in
 // for the call without, 26.8 with).  Row blocks with a slice more, so that 1024 instead of 946 workgroups share the
 // work, and a high priority while the tables are built change nothing.
 constexpr int R8_CH = 8;     // chunks whose indices a wavefront holds at once
+enum { R8_SHORT, R8_LONG };  // variants: slices of at most eight chunks, longer slices
 constexpr int R8_MOST = 16;  // most chunks of a slice: four workgroups' tables of eight activation rows take 147 KB of LDS
 // LDS bytes of a chunk's tables (those built in the kernel lie further apart: RowsShape)
 constexpr int rows8_chunk_bytes(int nt, bool fused) {
@@ -758,9 +763,10 @@ __device__ __forceinline__ RowsUnit rows_unit(const Rows8Grid& g) {
 }
 
 
-template <bool IS_INT, int BITS, int NT, bool FUSED>
+template <bool IS_INT, int BITS, int NT, bool FUSED, int KIND>
 __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_rows8_kernel(const RowsParams p) {
   static_assert(64 * 8 >= 32 * R8_MOST, "a lane for eight activations of a row's slice");
+  constexpr bool LONG = KIND == R8_LONG;
   constexpr int G = 4, PAD = FUSED ? 2 * NT : 0;
   using Sh = RowsShape<NT, G, PAD>;
   extern __shared__ __attribute__((aligned(2048))) char rows8_lds[];  // as many chunks as the longest slice has (launch_rows8_one)
@@ -781,8 +787,7 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_rows8_kernel(const 
   const int cz0 = (un.kz * p.grid8.per + min(un.kz, p.grid8.more)) << p.cpg_log2;
   const int nc = (p.grid8.per + (un.kz < p.grid8.more ? 1 : 0)) << p.cpg_log2;  // chunks of this workgroup, 1 to R8_MOST
 
-  // 1. all global loads, unconditional (clamped addresses): activations, indices, {scale, zero} of the first groups;
-  // indices of chunks 8 to 15 follow when their places are free, scales one group ahead
+  // 1. all global loads, unconditional (clamped addresses): activations and indices of the first eight chunks
   constexpr int ITEMS = Sh::TPC * NT / 4;  // tables of four rows in a chunk
   static_assert(!FUSED || R8_MOST * ITEMS <= 64 * ROWS_WAVES, "one item for each thread");
   constexpr int SUM_ROWS = (NT + ROWS_WAVES - 1) / ROWS_WAVES;  // rows whose sums a wavefront makes: wave, wave + 4
@@ -812,18 +817,29 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_rows8_kernel(const 
       for (int b = 0; b < BITS; ++b) xc[b] = src[b];
     }
   };
-  // {scale, zero} of a group (per tensor: there are none; not used): the present one and the next
-  auto load_sz = [&](int gq) { return *(p.per_tensor ? my_idx : my_sz + (size_t)min(gq, p.nq - 1) * 64); };
-  int gq = p.grouped ? cz0 >> p.cpg_log2 : 0;
-  load_chunk(0, x[0]);
-  uint32_t szv = load_sz(gq), szv_next = load_sz(gq + 1);
 #pragma unroll
-  for (int c = 1; c < R8_CH; ++c) load_chunk(c, x[c]);
+  for (int c = 0; c < R8_CH; ++c) load_chunk(c, x[c]);
+  // {scale, zero} of a chunk's group; else of the row (per tensor: there are none).  Behind a branch, because eight loads that
+  // nobody needs cost 3 to 5 % of a call with one scale; requested after what must not wait for them: waits behind a
+  // branch with loads count as if there were none.
+  auto load_sz = [&](int c) { return my_sz[(size_t)min((cz0 + c) >> p.cpg_log2, p.nq - 1) * 64]; };
+  auto ends_group = [&](int c) { return ((c + 1) & cmask) == 0; };
+  constexpr int SZ = LONG ? 2 : R8_CH;
+  uint32_t szv[SZ] = {};
+  auto load_scales = [&] {
+    if (p.grouped) {
+#pragma unroll
+      for (int c = 0; c < SZ; ++c) szv[c] = load_sz(c);
+    } else if (!p.per_tensor) {
+      szv[0] = *my_sz;
+    }
+  };
 
   // 2. tables of the chunks, and the group sums, into LDS
   const int kg_end = min((cz0 + nc) * Sh::TPC, p.KG);
   if constexpr (FUSED) {
     if ((int)threadIdx.x < nc * ITEMS) rows_stage_item<NT, IS_INT, PAD>(p, tab, build, threadIdx.x, n0, cz0 * Sh::TPC, kg_end);
+    load_scales();
     // lane: eight activations of a row, four lanes a chunk, whose sum by butterfly; then the sums up to each chunk from
     // its group's start
     float ssum[SUM_ROWS];
@@ -869,8 +885,9 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_rows8_kernel(const 
       }
     }
   } else {
+    load_scales();
     rows_stage_copy<IS_INT, NT, G, R8_CH * Sh::CB>(p, tab, un.nt, cz0 * Sh::TPC, kg_end);
-    if (nc > R8_CH) rows_stage_copy<IS_INT, NT, G, R8_CH * Sh::CB>(p, tab + R8_CH * Sh::CB, un.nt, (cz0 + R8_CH) * Sh::TPC, kg_end);
+    if (LONG && nc > R8_CH) rows_stage_copy<IS_INT, NT, G, R8_CH * Sh::CB>(p, tab + R8_CH * Sh::CB, un.nt, (cz0 + R8_CH) * Sh::TPC, kg_end);
     if (p.grouped && threadIdx.x < R8_MOST * NT) {
       const int c = threadIdx.x / NT, t = threadIdx.x % NT;
       const int gq = min((cz0 + c) >> p.cpg_log2, p.nq - 1);
@@ -881,15 +898,14 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_rows8_kernel(const 
   }
   __syncthreads();
 
-  // 3. the chunks, eight at a time straight-line
+  // 3. the chunks, eight of them straight-line
   float acc[NT];
   AccT L[NT];
   // (integer tables: minus the biases of the chunks that enter one sum, a group's or this workgroup's)
   const AccT L0 = IS_INT ? (AccT)(-ROWS_CHUNK_BIAS * ((1 << BITS) - 1) * (p.grouped ? 1 << p.cpg_log2 : nc)) : (AccT)0;
 #pragma unroll
   for (int t = 0; t < NT; ++t) { acc[t] = 0.f; L[t] = L0; }
-#pragma unroll 1
-  for (int c0 = 0; c0 < nc; c0 += R8_CH) {
+  auto eight = [&](int c0) {
 #pragma unroll
     for (int i = 0; i < R8_CH; ++i) {
       const int c = c0 + i;
@@ -904,21 +920,27 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_rows8_kernel(const 
         }
         rows_chunk<IS_INT, BITS, NT, G, AccT, 1, 0, PAD>(x[i], lds0 + (uint32_t)c * (uint32_t)Sh::CB, L, p.pw);
         // a quantisation group ends with this chunk (chunks in the K padding belong to no group)
-        if (p.grouped && ((c + 1) & cmask) == 0 && gq < p.nq) {
-          const float s = __half2float(__ushort_as_half((uint16_t)(szv & 0xffffu)));
-          const float z = __half2float(__ushort_as_half((uint16_t)(szv >> 16)));
-          szv = szv_next;
-          ++gq;
-          szv_next = load_sz(gq + 1);
+        if (p.grouped && ends_group(c) && ((cz0 + c) >> p.cpg_log2) < p.nq) {
+          const float s = __half2float(__ushort_as_half((uint16_t)(szv[i % SZ] & 0xffffu)));
+          const float z = __half2float(__ushort_as_half((uint16_t)(szv[i % SZ] >> 16)));
 #pragma unroll
           for (int t = 0; t < NT; ++t) {
             acc[t] = fmaf(s, fmaf(p.mid - z, sS[c][t], 0.5f * (float)L[t]), acc[t]);
             L[t] = L0;
           }
         }
-        if (c + R8_CH < nc) load_chunk(c + R8_CH, x[i]);
+        if constexpr (LONG) {
+          if (p.grouped && ends_group(c + SZ) && c + SZ < nc) szv[i % SZ] = load_sz(c + SZ);
+          if (c + R8_CH < nc) load_chunk(c + R8_CH, x[i]);
+        }
       }
     }
+  };
+  if constexpr (LONG) {
+#pragma unroll 1
+    for (int c0 = 0; c0 < nc; c0 += R8_CH) eight(c0);
+  } else {
+    eight(0);
   }
 
   // 4. one slice: finish here; several: publish the partial sums for rows_sum_kernel
@@ -927,8 +949,8 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_rows8_kernel(const 
     if (!tile_ok || m >= p.M) return;
     float s = p.wscale, z = p.zero_point;
     if (!p.grouped && !p.per_tensor) {
-      s = __half2float(__ushort_as_half((uint16_t)(szv & 0xffffu)));
-      z = __half2float(__ushort_as_half((uint16_t)(szv >> 16)));
+      s = __half2float(__ushort_as_half((uint16_t)(szv[0] & 0xffffu)));
+      z = __half2float(__ushort_as_half((uint16_t)(szv[0] >> 16)));
     }
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
@@ -1715,8 +1737,9 @@ static hipError_t launch_rows8_one(const RowsParams& p, hipStream_t st) {
   local.grid8 = Rows8Grid{units / nz, units % nz, rows_inverse(grid.x, wgs), rows_inverse(grid.y, wgs / grid.x)};
   const int len = (local.grid8.per + (local.grid8.more > 0)) << p.cpg_log2;  // chunks of the longest slice
   const int lds = rows8_lds_bytes(NT, FUSED, len);
-  hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(mpgemm_rows8_kernel<IS_INT, BITS, NT, FUSED>), grid,
-                                 dim3(64 * ROWS_WAVES), args, lds, st);
+  const void* const kernel = len > R8_CH ? reinterpret_cast<const void*>(mpgemm_rows8_kernel<IS_INT, BITS, NT, FUSED, R8_LONG>)
+                                         : reinterpret_cast<const void*>(mpgemm_rows8_kernel<IS_INT, BITS, NT, FUSED, R8_SHORT>);
+  hipError_t e = hipLaunchKernel(kernel, grid, dim3(64 * ROWS_WAVES), args, lds, st);
   if (e != hipSuccess || nz == 1) return e;
   return launch_rows_sum<IS_INT>(p, nz, st);
 }
