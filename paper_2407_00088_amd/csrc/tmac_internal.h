@@ -226,6 +226,13 @@ int launch_perm_gemv(const tmac_wdesc* desc, const void* packed_dev, const void*
 int launch_perm_gemv_multi(const tmac_gemv_item* items, int count, int act_t, int N, int out_t, void* stream,
                            const tmac_tuning* tuning);
 
+// Workgroups of the eight-chunk kernel (four wavefronts each) that a CU's registers hold, by activation rows of an n tile,
+// bits and whether its slices are longer than eight chunks; the kernels are compiled for that many.
+constexpr int rows8_wgs_by_registers(int nt, int bits, bool longer) {
+  if (nt == 8) return bits == 1 ? 7 : 4;
+  return bits == 1 ? 8 : bits == 2 ? (longer ? 7 : 8) : bits == 3 ? 6 : (longer ? 5 : 6);
+}
+
 // Batched lookup kernel (layout 3); defined in tmac_rows.hip.
 struct RowsPlan {
   int nt;                     // activation rows per n tile of the LUT buffer (4 or 8)

@@ -738,6 +738,14 @@ constexpr int rows8_lds_bytes(int nt, bool fused, int len) {
   return R8_MOST * nt * 4 + (fused ? len : (len + R8_CH - 1) / R8_CH * R8_CH) * rows8_chunk_bytes(nt, fused);
 }
 
+// ... and how many such workgroups a CU holds.  (With the larger of both kinds of tables: how a call is split does not
+// depend on who builds them.)
+constexpr int rows8_wgs(int nt, int bits, int len) {
+  const int own = rows8_lds_bytes(nt, true, len), copied = rows8_lds_bytes(nt, false, len);
+  const int by_lds = 163840 / (own > copied ? own : copied), by_regs = rows8_wgs_by_registers(nt, bits, len > R8_CH);
+  return by_regs < by_lds ? by_regs : by_lds;
+}
+
 // Which (n tile, row block, K slice) a workgroup serves.  The hardware hands workgroups to the
 // chip's eight XCDs (one L2 each) round-robin by linear id; with the plain blockIdx mapping the
 // n tiles that share a block of packed indices would sit on eight different L2s and each would
@@ -764,7 +772,7 @@ __device__ __forceinline__ RowsUnit rows_unit(const Rows8Grid& g) {
 
 
 template <bool IS_INT, int BITS, int NT, bool FUSED, int KIND>
-__global__ __launch_bounds__(64 * ROWS_WAVES, 4) void mpgemm_rows8_kernel(const RowsParams p) {
+__global__ __launch_bounds__(64 * ROWS_WAVES, rows8_wgs_by_registers(NT, BITS, KIND == R8_LONG)) void mpgemm_rows8_kernel(const RowsParams p) {
   static_assert(64 * 8 >= 32 * R8_MOST, "a lane for eight activations of a row's slice");
   constexpr bool LONG = KIND == R8_LONG;
   constexpr int G = 4, PAD = FUSED ? 2 * NT : 0;
@@ -1765,28 +1773,23 @@ static hipError_t launch_rows8_nt(const RowsParams& p, int nt, int bits, hipStre
                             : launch_rows8_bits<IS_INT, ROWS_NT_NARROW, FUSED>(p, bits, st);
 }
 
-// K slices of the eight-chunk kernel, up to sixteen chunks in whole groups each: as many as fill the chip once, where that many
-// fill it; a second, partly empty round costs as much as the first (16 rows x 11008 x 4096, 4 bit: 1376 workgroups of
-// eight chunks and 946 of eight or twelve: 33.0 us and 32.2 before the other changes to this kernel; 45 x 4099 x 3232, 3
-// bit 27.8 and 27.0).  Workgroups per CU by registers (four wavefronts each) and LDS.
-// `fewest`: see rows_plan_oct.
+// K slices of the eight-chunk kernel, whole groups each, eight to sixteen chunks long: the most of which a CU gets at most
+// five workgroups (further wavefronts do not pay for their partial sums), else the most that the chip holds at once, and
+// slices of eight chunks if there is no such number.  Measured with every split of 90 random calls of 4 to 100 rows: where
+// this takes longer slices, ones of eight chunks take 0.94 to 1.19 times as long, 1.07 on average (40 calls; 25 x 3859 x 5600,
+// 4 bit 23.0 us, 27.2 with eight, 36 x 2267 x 4096, 2 bit 20.1, 18.8); where no split fits, longer ones take 0.99 to 1.14 times as long
+// as eight, 1.04 on average (29 calls; 100 x 1890 x 8704, 1 bit 30.3, 34.7 with sixteen).  The fastest split of each call is another 1.8 %
+// faster.  `fewest`: see rows_plan_oct.
 static int rows8_slices(int64_t pairs, int n_chunks, int cpg, int nt, int bits, int fewest) {
-  const int by_regs = nt == 8 ? (bits == 1 ? 6 : 4) : (bits == 1 ? 8 : bits == 2 ? 6 : 5);
   const int most = (n_chunks + R8_CH - 1) / R8_CH, least = std::max((n_chunks + R8_MOST - 1) / R8_MOST, fewest);
-  int best = most;
-  double best_time = 1e300;
-  for (int s = most; s >= least; --s) {
-    const int len = (n_chunks / cpg + s - 1) / s * cpg;  // whole groups
-    if (len > R8_MOST) break;
-    const int by_lds = 163840 / rows8_lds_bytes(nt, true, (len + R8_CH - 1) / R8_CH * R8_CH);
-    const double rounds = (double)(pairs * s) / (256 * (by_regs < by_lds ? by_regs : by_lds));
-    const double time = (len + 2) * (rounds <= 1. ? 1. : rounds + 0.5);  // (starts and ends weigh about two chunks)
-    if (time < best_time) {
-      best_time = time;
-      best = s;
+  for (const int per_cu : {5, 8}) {
+    for (int s = most; s >= least; --s) {
+      const int len = (n_chunks / cpg + s - 1) / s * cpg;
+      if (len > R8_MOST) break;
+      if (pairs * s <= 256 * std::min(rows8_wgs(nt, bits, len), per_cu)) return s;
     }
   }
-  return best;
+  return most;
 }
 
 // Calls that may build their tables inside the eight-chunk kernel, where it serves them (rows_builds_tables).

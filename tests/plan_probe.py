@@ -23,6 +23,7 @@ extern "C" void plan_probe(const tmac_wdesc* d, int N, int from_act, int* o, siz
   *part_bytes = p.part_bytes;
   *srow_bytes = p.srow_bytes;
 }
+extern "C" int wgs_by_registers(int nt, int bits, int longer) { return tmac::rows8_wgs_by_registers(nt, bits, longer != 0); }
 """
 
 
@@ -32,15 +33,20 @@ def _probe():
     subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-x", "c++", "-", "-x", "none", T.LIB_PATH,
                     "-I" + build.CSRC, "-I" + os.path.join(build.ROOT, "include"), "-o", out],
                    input=SOURCE.encode(), check=True)
-    return ctypes.CDLL(out).plan_probe
+    return ctypes.CDLL(out)
 
 
 def rows_plan(N, M, K, bits, group, g=4, from_act=False):
     """The plan of a layout-3 call, with `longest`: 32-k chunks of the longest K slice of the eight-chunk kernel."""
     d = T.wdesc(M, K, bits, group, g=g, layout=B.TMAC_LAYOUT_R64K32)
     o, part, srow = (ctypes.c_int * len(FIELDS))(), ctypes.c_size_t(), ctypes.c_size_t()
-    _probe()(ctypes.byref(d), N, int(from_act), o, ctypes.byref(part), ctypes.byref(srow))
+    _probe().plan_probe(ctypes.byref(d), N, int(from_act), o, ctypes.byref(part), ctypes.byref(srow))
     p = SimpleNamespace(**dict(zip(FIELDS, o)), part_bytes=part.value, srow_bytes=srow.value, one_group=group in (0, K))
     cpg = 1 if p.one_group else max(group // 32, 1)
     p.longest = -(-(p.n_chunks // cpg) // p.slices) * cpg
     return p
+
+
+def wgs_by_registers(nt, bits, longer):
+    """Workgroups of the eight-chunk kernel that the plan takes a CU's registers to hold."""
+    return _probe().wgs_by_registers(nt, bits, int(longer))

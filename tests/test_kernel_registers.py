@@ -1,5 +1,6 @@
 """Host-side check of what the compiler gives the few-row kernel (mpgemm_rows8_kernel): no variant spills vector
-registers.  Read from the kernel descriptions in the assembly.  No GPU needed."""
+registers, and a CU holds as many workgroups as the plan counts with.  Read from the kernel descriptions in the assembly.
+No GPU needed."""
 import os
 import re
 import subprocess
@@ -7,6 +8,7 @@ import subprocess
 import pytest
 
 from paper_2407_00088_amd import build as B
+from plan_probe import wgs_by_registers
 
 
 @pytest.fixture(scope="module")
@@ -28,3 +30,15 @@ def rows8(tmp_path_factory):
 
 def test_few_row_kernel_does_not_spill(rows8):
     assert not {k: v for k, v in rows8.items() if v["vgpr_spill_count"]}
+
+
+def test_plan_counts_with_the_registers_that_the_kernels_have(rows8):
+    """Workgroups of four wavefronts, one on each SIMD of 512 registers, handed out in eights, at most eight wavefronts; the
+    plan's number is that of the variant with most registers."""
+    variants = max(k[4] for k in rows8)    # (the last one is that of longer slices)
+    for nt in (4, 8):
+        for bits in (1, 2, 3, 4):
+            for longer in (False, True):
+                held = [min(512 // (-(-v["vgpr_count"] // 8) * 8), 8) for k, v in rows8.items()
+                        if k[1:3] == (bits, nt) and (k[4] == variants) == longer]
+                assert min(held) == wgs_by_registers(nt, bits, longer), (nt, bits, longer, held)
