@@ -723,10 +723,13 @@ static hipError_t launch_rows_nt(const RowsParams& p, int g, int nt, int oct, in
 // (median of the wavefronts): tables there 3.4, half the look-ups 11, end 19 (21.7 for the last); with a branch before
 // each activation load, 128-byte steps between the lanes' LDS stores and a spilled register, tables were there at 9.5.
 // A SIMD serves its oldest wavefront first; priorities that fall with the chunks done keep a CU's four level (28.8 us
-// for the call without, 26.8 with).  Row blocks with a slice more, so that 1024 instead of 946 workgroups share the
+// for the call without, 26.8 with; slices of eight chunks, 27 random calls 0.97 of the time on average).  Where workgroups
+// come in several rounds they would let the new ones overtake those about to end (63 calls: 1.02 on average; 64 x 3125 x
+// 8064, int8, 4 bit 52.3 us, 48.6 without).  Row blocks with a slice more, so that 1024 instead of 946 workgroups share the
 // work, and a high priority while the tables are built change nothing.
 constexpr int R8_CH = 8;     // chunks whose indices a wavefront holds at once
-enum { R8_SHORT, R8_LONG };  // variants: slices of at most eight chunks, longer slices
+// variants: slices of at most eight chunks that the chip holds all at once, or in several rounds; longer slices
+enum { R8_ONCE, R8_ROUNDS, R8_LONG };
 constexpr int R8_MOST = 16;  // most chunks of a slice: four workgroups' tables of eight activation rows take 147 KB of LDS
 // LDS bytes of a chunk's tables (those built in the kernel lie further apart: RowsShape)
 constexpr int rows8_chunk_bytes(int nt, bool fused) {
@@ -923,11 +926,11 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, rows8_wgs_by_registers(NT, BITS, K
       const int c = c0 + i;
       if (c < nc) {
         // wavefronts that are behind come first (see mpgemm_run_kernel)
-        if (c0 == 0) {
+        if (KIND != R8_ROUNDS && c0 == 0) {
           if (i == 0) __builtin_amdgcn_s_setprio(3);
           if (i == 3) __builtin_amdgcn_s_setprio(2);
           if (i == 6) __builtin_amdgcn_s_setprio(1);
-        } else if (i == 0) {
+        } else if (LONG && i == 0) {
           __builtin_amdgcn_s_setprio(0);
         }
         rows_chunk<IS_INT, BITS, NT, G, AccT, 1, 0, PAD>(x[i], lds0 + (uint32_t)c * (uint32_t)Sh::CB, L, p.pw);
@@ -1750,7 +1753,9 @@ static hipError_t launch_rows8_one(const RowsParams& p, hipStream_t st) {
   const int len = (local.grid8.per + (local.grid8.more > 0)) << p.cpg_log2;  // chunks of the longest slice
   const int lds = rows8_lds_bytes(NT, FUSED, len);
   const void* const kernel = len > R8_CH ? reinterpret_cast<const void*>(mpgemm_rows8_kernel<IS_INT, BITS, NT, FUSED, R8_LONG>)
-                                         : reinterpret_cast<const void*>(mpgemm_rows8_kernel<IS_INT, BITS, NT, FUSED, R8_SHORT>);
+                             : wgs > 256u * (unsigned)rows8_wgs(NT, BITS, len)
+                                 ? reinterpret_cast<const void*>(mpgemm_rows8_kernel<IS_INT, BITS, NT, FUSED, R8_ROUNDS>)
+                                 : reinterpret_cast<const void*>(mpgemm_rows8_kernel<IS_INT, BITS, NT, FUSED, R8_ONCE>);
   hipError_t e = hipLaunchKernel(kernel, grid, dim3(64 * ROWS_WAVES), args, lds, st);
   if (e != hipSuccess || nz == 1) return e;
   return launch_rows_sum<IS_INT>(p, nz, st);
