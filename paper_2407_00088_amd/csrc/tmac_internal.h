@@ -229,8 +229,9 @@ int launch_perm_gemv_multi(const tmac_gemv_item* items, int count, int act_t, in
 // Workgroups of the eight-chunk kernel (four wavefronts each) that a CU's registers hold, by activation rows of an n tile,
 // bits and whether its slices are longer than eight chunks; the kernels are compiled for that many.
 constexpr int rows8_wgs_by_registers(int nt, int bits, bool longer) {
-  if (nt == 8) return bits == 1 ? 7 : 4;
-  return bits == 1 ? 8 : bits == 2 ? (longer ? 7 : 8) : bits == 3 ? 6 : (longer ? 5 : 6);
+  if (nt == 8) return bits == 1 ? (longer ? 7 : 8) : 4;
+  if (bits == 1) return 8;
+  return (bits == 2 ? 8 : bits == 3 ? 7 : 6) - (longer ? 1 : 0);
 }
 
 // Batched lookup kernel (layout 3); defined in tmac_rows.hip.

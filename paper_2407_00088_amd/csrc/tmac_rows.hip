@@ -710,14 +710,14 @@ static hipError_t launch_rows_nt(const RowsParams& p, int g, int nt, int oct, in
 // ------------------------------------------------------------------------------------------
 // With few activation rows a call is a chain of latencies, not a stream: the general kernel above
 // asks for a chunk's indices one chunk ahead.  Here a workgroup's slice is at most sixteen chunks (512 k, g = 4;
-// rows8_slices): all tables and the indices of eight chunks are requested in one go at the start, their scales next, the
+// rows8_slices): all tables and the indices of eight chunks are requested in one go at the start, the
 // partial sums are written with plain stores, and rows_sum_kernel, the
 // next kernel on the stream, adds the slices in slice order and finishes.
-// Slices of at most eight chunks are straight-line code.  Longer ones have a variant of their own: indices as places get
-// free, scales two chunks ahead.  Where one variant with scales one group ahead served both, its waits for scales and
+// Slices of at most eight chunks are straight-line code; longer ones have a variant of their own that requests the other
+// chunks' indices as places get free.  Where one variant with scales one group ahead served both, its waits for scales and
 // the registers of its loop made short slices slow.  us, that variant and now (before there were longer slices): 2 x 1680 x
-// 6112, 3 bit in groups of 32 12.8, 10.7 (10.6); 2 x 3692 x 6976, 2 bit in groups of 32 13.0, 11.3 (11.7); 4 x 4096 x 4096, 4
-// bit 11.7, 11.5 (11.7).  A copy of the straight-line code inside the variant with the loop spills registers.
+// 6112, 3 bit in groups of 32 12.8, 10.9 (10.7); 2 x 3692 x 6976, 2 bit in groups of 32 13.0, 11.2 (11.7); 4 x 4096 x 4096, 4
+// bit 11.7, 10.7 (11.6).  A copy of the straight-line code inside the variant with the loop spills registers.
 // Bound by the vector ALUs once the tables are there: 47 instructions per plane and chunk of eight rows, of which 28
 // add and 11 make addresses.  16 rows x 11008 x 4096, 4 bit, from the activations, us after the start of the kernel
 // (median of the wavefronts): tables there 3.4, half the look-ups 11, end 19 (21.7 for the last); with a branch before
@@ -828,29 +828,23 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, rows8_wgs_by_registers(NT, BITS, K
       for (int b = 0; b < BITS; ++b) xc[b] = src[b];
     }
   };
-#pragma unroll
-  for (int c = 0; c < R8_CH; ++c) load_chunk(c, x[c]);
-  // {scale, zero} of a chunk's group; else of the row (per tensor: there are none).  Behind a branch, because eight loads that
-  // nobody needs cost 3 to 5 % of a call with one scale; requested after what must not wait for them: waits behind a
-  // branch with loads count as if there were none.
-  auto load_sz = [&](int c) { return my_sz[(size_t)min((cz0 + c) >> p.cpg_log2, p.nq - 1) * 64]; };
+  // {scale, zero} of a chunk's group, or of the row (per tensor: there are none; not used), two chunks ahead.  (All eight at
+  // the start cost calls with one scale 3 to 5 %; a branch around them costs more elsewhere, because waits after it count as
+  // if there were no loads in it: 4 x 4096 x 4096, 4 bit, one call 11.5 us, 10.7 like this.)
+  auto load_sz = [&](int c) { return *(p.per_tensor ? my_idx : p.grouped ? my_sz + (size_t)min((cz0 + c) >> p.cpg_log2, p.nq - 1) * 64 : my_sz); };
   auto ends_group = [&](int c) { return ((c + 1) & cmask) == 0; };
-  constexpr int SZ = LONG ? 2 : R8_CH;
-  uint32_t szv[SZ] = {};
-  auto load_scales = [&] {
-    if (p.grouped) {
+  constexpr int SZ = 2;  // (a divisor of R8_CH)
+  uint32_t szv[SZ];
+  load_chunk(0, x[0]);
 #pragma unroll
-      for (int c = 0; c < SZ; ++c) szv[c] = load_sz(c);
-    } else if (!p.per_tensor) {
-      szv[0] = *my_sz;
-    }
-  };
+  for (int c = 0; c < SZ; ++c) szv[c] = load_sz(c);
+#pragma unroll
+  for (int c = 1; c < R8_CH; ++c) load_chunk(c, x[c]);
 
   // 2. tables of the chunks, and the group sums, into LDS
   const int kg_end = min((cz0 + nc) * Sh::TPC, p.KG);
   if constexpr (FUSED) {
     if ((int)threadIdx.x < nc * ITEMS) rows_stage_item<NT, IS_INT, PAD>(p, tab, build, threadIdx.x, n0, cz0 * Sh::TPC, kg_end);
-    load_scales();
     // lane: eight activations of a row, four lanes a chunk, whose sum by butterfly; then the sums up to each chunk from
     // its group's start
     float ssum[SUM_ROWS];
@@ -896,9 +890,8 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, rows8_wgs_by_registers(NT, BITS, K
       }
     }
   } else {
-    load_scales();
     // (the group sums are requested before the tables; after them they were a round trip to memory of their own: 48 x 11008 x
-    // 4096, 1 bit, two calls 34.9 us against 34.1)
+    // 4096, 1 bit, two calls 35.3 us, 34.7 like this)
     const int c = threadIdx.x / NT, t = threadIdx.x % NT;
     const bool sums = p.grouped && c < R8_MOST;
     float sum = 0.f;
@@ -944,8 +937,8 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, rows8_wgs_by_registers(NT, BITS, K
             L[t] = L0;
           }
         }
+        if (p.grouped && (LONG || i + SZ < R8_CH) && ends_group(c + SZ) && c + SZ < nc) szv[i % SZ] = load_sz(c + SZ);
         if constexpr (LONG) {
-          if (p.grouped && ends_group(c + SZ) && c + SZ < nc) szv[i % SZ] = load_sz(c + SZ);
           if (c + R8_CH < nc) load_chunk(c + R8_CH, x[i]);
         }
       }
