@@ -71,9 +71,15 @@ typedef enum { TMAC_ACT_F16 = 0, TMAC_ACT_I8 = 1, TMAC_ACT_F16_TQ = 2 } tmac_act
  *                   tmac_mpgemm_fused: 5000 chunks and 15000 chunks times bits; up to 32 rows 24576
  *                   chunks times bits.
  *                   tmac_mpgemm: 0.75e9 look-ups (N M K bits / 4, M padded to 64 and K to 128), up to 32
- *                   rows 1.05e9; M bits >= 1536; 5000 chunks, or 12288 at most N that leave more than
- *                   15 % of ceil(N / 16) sets of 16 rows empty; and tmac_mpgemm_noalloc takes the call
- *                   if it would with sums in fp16 (rows_plan in csrc/tmac_rows.hip).
+ *                   rows 1.05e9, or 1.5e9 at N that leave more than 15 % of ceil(N / 16) sets of 16 rows
+ *                   empty; M bits >= 1536; 5000 chunks, or 12288 at most N that leave as much empty;
+ *                   and tmac_mpgemm_noalloc takes the call if it would with sums in fp16 (rows_plan in
+ *                   csrc/tmac_rows.hip).
+ *                 The lines may move from version to version, and with them the workspace a call needs
+ *                 (tmac_workspace_bytes, tmac_fused_workspace_bytes).  One kind of activations is further
+ *                 off than with sums in fp16: one large whole number in an otherwise empty chunk of 32 k,
+ *                 which fp16 adds exactly, gives its unit to the other chunks of its group (3e-5 instead of
+ *                 1e-6 and less).
  *   TMAC_LUT_I16: entries are exact int16 sums of int8 activations (|T| <= 4*127); all
  *                 aggregation is int32 and the result is bit-exact.
  *   TMAC_LUT_I8Q: table quantisation (Section 3.3): entries of fp16 activations' tables rounded

@@ -1885,13 +1885,15 @@ static RunPlan rows_run(int64_t pairs, int n_chunks) {
 //     groups of 64) and below it 0.78 to 0.94 (32 x 4096 x 4096, 16 x 8192 x 4096, 16 x 11008 x 4096, 4 bit), 1.17 once
 //     (32 x 11008 x 4096, 2 bit).  For time alone the line would be 32768; results between are closer with fixed point.
 //   * from a LUT buffer the conversion is one more launch: look-ups from ROWS_RUN_LUT_LOOKUPS on, 1.4 times as many up to 32
-//     rows, ROWS_RUN_LUT_ROWS weight rows times bits for each table, and ROWS_RUN_ACT_CHUNKS, where more than 15 % of the
-//     sets' rows do not exist ROWS_RUN_INT_CHUNKS.  Of 64 random calls that these lines take 55 are faster than with fp16
+//     rows, twice as many there where more than 15 % of the sets' rows do not exist; ROWS_RUN_LUT_ROWS weight rows times bits
+//     for each table; and ROWS_RUN_ACT_CHUNKS, in sets that are not full ROWS_RUN_INT_CHUNKS.  Of 64 random calls that these lines take 55 are faster than with fp16
 //     sums, 1.06 times on average (0.94 to 1.21); of 46 that they leave, from 0.4e9 look-ups on, 14, 0.95 (0.72 to 1.08).
 //     At the lines: 1.05 and 1.07 at 0.8e9 and 1.07e9 look-ups (64 x 4096 x 4096, 3 and 4 bit), 0.94 and 0.96 at 0.6e9 (48 x
 //     4096 x 4096 and 64 x 3072 x 4096, 3 bit); up to 32 rows 0.80 to 0.98 below (32 x 4096 x
 //     4096, 16 x 11008 x 4096, 4 bit, 20 x 12000 x 5120, 3 bit; 1.11 and 1.25 at 2 bit: 32 x 11008 x 4096, 28 x 16384 x 4096 in
-//     groups of 32), 1.00 to 1.26 above (24 x 11008 x 4096, 32 x 8192 x 4096, 16 x 13824 x 5120, 16 x 28672 x 4096, 4 bit); weight rows times bits 1.05 at 2100 (300 x 700 x
+//     groups of 32), between 1.4 and 2 times the line 1.07 on average in sets that are full (25 calls, 0.99 to 1.20; 16 x
+//     13824 x 5120 and 32 x 8192 x 4096, 4 bit 1.04 and 1.05) and 0.97 in others (18 calls, 0.91 to 1.07; 20 x 28512 x 1856, 4 bit
+//     46.8 us against 51.7), 1.26 above (16 x 28672 x 4096, 4 bit); weight rows times bits 1.05 at 2100 (300 x 700 x
 //     8192, 3 bit), 0.90 to 1.07 at 1200 to 1536 (eleven calls, seven below 1), 0.88 at 768 (511 x 256 x 13824, 3 bit);
 //     sets that are not full 0.92, 1.00 and 1.05 at 8448, 11264 and 10240 chunks (40 x 2700 x 8192, 52 x 2800 x 8192, 65 x 2048
 //     x 8192).  Within the library's own array where the plain plan is, because tmac_mpgemm_noalloc gives tmac_mpgemm's
@@ -1925,9 +1927,9 @@ RowsPlan rows_plan(const tmac_wdesc* desc, int N, bool from_act) {
     const int64_t by_bits = (int64_t)run.total * desc->bits;
     take = N > 32 ? run.total >= ROWS_RUN_ACT_CHUNKS && by_bits >= ROWS_RUN_ACT_BITS : by_bits >= ROWS_RUN_ACT_FEW;
   } else {
-    const bool part_full = pl.nt == ROWS_NT_WIDE && N * 20 < tiles * 16 * 17;  // sets with many rows that do not exist
-    take = lookups >= (N > 32 ? 1. : 1.4) * ROWS_RUN_LUT_LOOKUPS && (int64_t)desc->M * desc->bits >= ROWS_RUN_LUT_ROWS &&
-           run.total >= (part_full ? ROWS_RUN_INT_CHUNKS : ROWS_RUN_ACT_CHUNKS);
+    const bool part_full = N * 20 < tiles * 16 * 17;  // sets with many rows that do not exist
+    take = lookups >= (N > 32 ? 1. : part_full ? 2. : 1.4) * ROWS_RUN_LUT_LOOKUPS && (int64_t)desc->M * desc->bits >= ROWS_RUN_LUT_ROWS &&
+           run.total >= (part_full && pl.nt == ROWS_NT_WIDE ? ROWS_RUN_INT_CHUNKS : ROWS_RUN_ACT_CHUNKS);
     const size_t own = (size_t)TMAC_NOALLOC_MAX_WORKSPACE;  // within the library's own array where the plain plan is
     if (room <= own && run_parts + tab + scale + sums > own) take = false;
   }

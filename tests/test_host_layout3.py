@@ -144,3 +144,19 @@ def test_slices_of_the_eight_chunk_kernel():
                         assert 1 <= p.slices and p.longest <= 16 and p.slices * N * p.Mp * 4 <= p.part_bytes
                         assert p.slices >= 2 or not (p.one_group and (p.builds_f16 or p.builds_i8)), (N, M, K, bits, group)
     assert seen > 2000 and ones > 50    # (one slice is taken where it can be finished)
+
+
+@pytest.mark.parametrize("N,M,K,bits,fixed", [
+    (32, 8192, 4096, 4, True), (16, 13824, 5120, 4, True),         # 1.07e9 and 1.13e9 look-ups, sets of 16 rows full
+    (28, 15324, 6880, 2, True), (15, 13824, 5120, 4, True),        # ... at most 15 % empty
+    (20, 28512, 1856, 4, False), (24, 9020, 5824, 4, False), (12, 23391, 3904, 4, False), (9, 28672, 4096, 4, False),
+    (24, 11008, 5888, 4, True), (20, 16384, 4608, 4, True),        # 1.5e9 and more
+    (32, 8128, 4096, 4, True), (32, 7936, 4096, 4, False),         # beside the lower line
+])
+def test_fixed_point_line_up_to_32_rows(N, M, K, bits, fixed):
+    """Which calls of nine to 32 rows with a LUT buffer take fixed-point tables: from 1.05e9 look-ups on, and from 1.5e9 where more
+    than 15 % of the rows of their sets of 16 do not exist (the run looks those up as well)."""
+    lookups = N * (-(-M // 64) * 64) * (-(-K // 128) * 32) * bits
+    full = N * 20 >= -(-N // 16) * 16 * 17
+    assert (lookups >= (1.05e9 if full else 1.5e9)) == fixed
+    assert bool(rows_plan(N, M, K, bits, 32).fix) == fixed

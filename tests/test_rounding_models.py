@@ -153,8 +153,8 @@ def coarse_activations(rng, kind, N, K):
                                         ("relu", False), ("mantissa3", False), ("mantissa4", False), ("mantissa8", False)])
 def test_fixed_point_tables_are_no_further_off_on_activations_with_few_bits(kind, exact):
     """Where the entries of a unit are multiples of a power of two that is a unit too, they are held as they are: whole
-    numbers, fractions of a power of two and subnormal numbers keep the exact sums that fp16 gives them, and nothing
-    with few significant bits is further from the product than with fp16 sums."""
+    numbers, fractions of a power of two and subnormal numbers keep the exact sums that fp16 gives them, and none of
+    these kinds is further from the product than with fp16 sums (the next test has one that is)."""
     rng = np.random.default_rng(97)
     N, M, K = 3, 40, 2048
     for bits, group in ((2, 32), (4, 128), (3, 96), (4, 2048)):
@@ -168,3 +168,25 @@ def test_fixed_point_tables_are_no_further_off_on_activations_with_few_bits(kind
         narrow = orc.rel_frobenius(rm.lut_mpgemm_narrow(act, q, bits, s, z, group), ref)
         assert fixed <= max(narrow, 1e-12), (kind, bits, group, fixed, narrow)
         assert not exact or fixed <= 1e-12, (kind, bits, group, fixed)
+
+
+@pytest.mark.parametrize("big", [300, 3000, 30000])
+def test_a_large_number_alone_in_its_chunk_costs_the_rest_of_its_group(big):
+    """The kind of activations whose fixed-point tables are further off than fp16 sums: one large whole number in an otherwise
+    empty chunk of each group.  fp16 adds that chunk exactly; in fixed point the group's other entries take its unit, big / 32700,
+    and each is off by at most half of it: 24 entries of a plane add up to about sqrt(24 / 12) units, 4e-5 of what the large number
+    gives, and 1e-4 is allowed."""
+    rng = np.random.default_rng(98)
+    N, M, K, group = 3, 40, 2048, 128
+    act = rng.standard_normal((N, K)).reshape(N, K // group, group)
+    act[:, :, :32] = 0
+    act[:, :, 5] = big
+    act = act.reshape(N, K).astype(np.float16)
+    for bits in (2, 4):
+        q = rng.integers(0, 1 << bits, size=(M, K), dtype=np.uint8)
+        s = rng.uniform(0.01, 0.1, size=(M, K // group)).astype(np.float16)
+        z = rng.uniform(0, 2 ** bits - 1, size=(M, K // group)).astype(np.float16)
+        ref = orc.mpgemm_definition(act, q, s, z, group)
+        fixed = orc.rel_frobenius(rm.lut_mpgemm_fixed(act, q, bits, s, z, group), ref)
+        narrow = orc.rel_frobenius(rm.lut_mpgemm_narrow(act, q, bits, s, z, group), ref)
+        assert narrow < fixed <= 1e-4, (big, bits, narrow, fixed)
