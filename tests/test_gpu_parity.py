@@ -15,7 +15,7 @@ import numpy as np
 import pytest
 
 import rounding_models as rm
-from plan_probe import rows_plan
+from plan_probe import rows_plan, wgs_by_registers
 import tmac_workloads as wl
 from oracle import tmac_oracle as orc
 
@@ -1040,20 +1040,34 @@ def test_one_call_entry_point_int_exact(T, torch, layout, N, M, K):
     assert np.array_equal(got_f.view(np.uint32), orc.int_path_output_f32(ref_i, p.act_scale, p.weight_scale).view(np.uint32))
 
 
-@pytest.mark.parametrize("N,M,K,bits,group", [
-    (32, 13300, 1280, 4, 128),   # 52 row blocks x 4 n tiles: longer slices than eight chunks, of whole groups
-    (32, 13300, 1376, 3, 32),    # a group per chunk, K padded inside a chunk's block
-    (30, 13300, 1280, 2, 256),   # groups of eight chunks; rows of the last n tile do not exist
-    (16, 25700, 1312, 1, -1),    # one scale per row, row sums by the slices of the first row block
-    (12, 13300, 1280, 4, 64),    # n tiles of four rows, tables of four rows in LDS
-    (16, 300, 384, 4, 128),      # slices shorter than eight chunks
+@pytest.mark.parametrize("N,M,K,bits,group,longest", [
+    (32, 13300, 1280, 4, 128, 12),   # 52 row blocks x 4 n tiles: longer slices than eight chunks, of whole groups
+    (32, 13300, 1376, 3, 32, 11),    # a group per chunk, K padded inside a chunk's block
+    (30, 13300, 1280, 2, 256, 16),   # groups of eight chunks; rows of the last n tile do not exist
+    (40, 13300, 1280, 2, 128, 16),   # tables from a LUT buffer only
+    (9, 22000, 1376, 4, 32, 11),     # n tiles of four rows, the last one not full: tables of four rows in LDS
+    (12, 30000, 1536, 2, 64, 16),
+    (10, 30000, 1280, 3, 128, 16),
+    (9, 44000, 1280, 1, 128, 16),
+    (33, 9000, 1408, 2, 32, 15),     # ... from a LUT buffer only
+    (11, 22000, 1312, 3, -1, 11),    # one scale per row, row sums by the slices of the first row block
+    (16, 25700, 1312, 1, -1, 8),     # eight chunks: all at once
+    (31, 26000, 1312, 1, 32, 8),     # ... and in several rounds (no priorities)
+    (60, 13300, 1312, 1, -1, 8),
+    (12, 13300, 1280, 4, 64, 8),
+    (16, 300, 384, 4, 128, 8),
 ])
-def test_slices_that_fill_the_chip(T, torch, N, M, K, bits, group):
-    """Few-row calls whose K slices are longer (or shorter) than the eight chunks whose indices a wavefront holds at
-    once, from activations and from a LUT buffer: the bars of the file against the oracle, and the two routes (same
-    table entries, sums of activations in another order) 2e-6 from each other, as above."""
+def test_slices_that_fill_the_chip(T, torch, N, M, K, bits, group, longest):
+    """Few-row calls at each variant of the few-row kernel, by the plan that the library makes: K slices longer than the eight
+    chunks whose indices a wavefront holds at once, slices of eight, all at once and in several rounds; from activations and from
+    a LUT buffer: the bars of the file against the oracle, and the two routes (same table entries, sums of activations in another
+    order) 2e-6 from each other, as above."""
     from paper_2407_00088_amd.runner import from_problem
     p = wl.make_grouped(0, 980 + N + bits, N, M, K, bits, K if group < 0 else group, name="slices")
+    plan = rows_plan(N, M, K, bits, p.group)
+    assert plan.eight and plan.slices > 1 and plan.longest == longest and not plan.fix and plan.builds_f16 == (N <= 32)
+    rounds = plan.slices * plan.row_blocks * plan.n_tiles_n > 256 * wgs_by_registers(plan.nt, bits, longest > 8)
+    assert rounds == (N in (31, 60))
     lin = from_problem(p, layout=L3)
     A = torch.from_numpy(p.act).cuda()
     one, two, ref = lin.forward_one_call(A).cpu().numpy(), lin.forward(A).cpu().numpy(), oracle_fp(p)
@@ -1063,10 +1077,13 @@ def test_slices_that_fill_the_chip(T, torch, N, M, K, bits, group):
     assert orc.rel_frobenius(one, two) <= 2e-6
 
 
-@pytest.mark.parametrize("N,M,K", [(32, 13300, 1312), (11, 13300, 1280), (16, 300, 352)])
-def test_slices_that_fill_the_chip_int_exact(T, torch, N, M, K):
+@pytest.mark.parametrize("N,M,K,longest", [(32, 13300, 1312, 11), (9, 22000, 1312, 11), (45, 13300, 1280, 14), (11, 13300, 1280, 8),
+                                           (16, 300, 352, 6)])
+def test_slices_that_fill_the_chip_int_exact(T, torch, N, M, K, longest):
     """The same with ternary weights and int8 activations, bit for bit through both entry points."""
     from paper_2407_00088_amd.runner import from_problem
+    plan = rows_plan(N, M, K, 2, 0)
+    assert plan.eight and plan.slices > 1 and plan.longest == longest and not plan.run_wgs
     p = wl.make_ternary(0, 985 + N, N, M, K, name="slices_int")
     lin = from_problem(p, layout=L3)
     A, s_a = torch.from_numpy(p.act_q).cuda(), torch.from_numpy(p.act_scale).cuda()
@@ -1129,6 +1146,26 @@ def test_one_call_entry_point_int_group_scales_in_kernel(T, torch):
     two = lin.forward(A, act_scale=sa)
     one = lin.forward_one_call(A, act_scale=sa)
     assert torch.equal(one, two)
+    ref = orc.mpgemm_definition(a_q.astype(np.float64) * s_a[:, None].astype(np.float64), q, p.scales, p.zeros, G)
+    assert orc.rel_frobenius(one.cpu().numpy(), ref) <= 1e-5
+
+
+@pytest.mark.parametrize("N,M,K,bits,G,longest", [(32, 13300, 1280, 4, 128, 12), (16, 4096, 4096, 4, 64, 8), (12, 30000, 1536, 3, 32, 16)])
+def test_few_rows_int_group_scales_at_every_width(T, torch, N, M, K, bits, G, longest):
+    """The same in long slices and at 4 bit with eight activation rows, whose planes are widened two and two.  Both routes add the
+    same integers and the groups in the same order; the oracle's 1e-5 is that of the test above."""
+    from paper_2407_00088_amd.runner import from_problem
+    plan = rows_plan(N, M, K, bits, G)
+    assert plan.eight and plan.builds_i8 and plan.longest == longest
+    rng = np.random.default_rng(977 + N)
+    q = wl.uniform_codes(rng, M, K, bits)
+    a_q, s_a = wl.absmax_int8(wl.gaussian_act(rng, N, K))
+    p = wl.Problem("few_intg", 0, N, M, K, bits, G, q, wl.group_scales(rng, M, K // G), wl.group_zeros(rng, M, K // G, bits),
+                   act_q=a_q, act_scale=s_a)
+    lin = from_problem(p, layout=L3)
+    A, sa = torch.from_numpy(a_q).cuda(), torch.from_numpy(s_a).cuda()
+    one = lin.forward_one_call(A, act_scale=sa)
+    assert torch.equal(one, lin.forward(A, act_scale=sa))
     ref = orc.mpgemm_definition(a_q.astype(np.float64) * s_a[:, None].astype(np.float64), q, p.scales, p.zeros, G)
     assert orc.rel_frobenius(one.cpu().numpy(), ref) <= 1e-5
 
