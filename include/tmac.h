@@ -281,8 +281,8 @@ tmac_status tmac_mpgemv_fused(const tmac_wdesc* desc, const void* packed_dev, co
  * (Algorithm 1 Precompute next to the look-ups that use it: no second launch and no table
  * traffic): layout 2 with K % 16 == 0 (this is then tmac_mpgemv_fused), and layout 3 with g = 4,
  * K % 8 == 0, a group size that divides 256 (or one scale per row or tensor), and at most 32
- * activation rows in a call that is cut into K slices of 256 (the case a separate precompute
- * launch costs most).  Every other call runs tmac_precompute_lut into the second region of the
+ * activation rows in a call that is cut into K slices of 256 to 512 (the case a separate
+ * precompute launch costs most).  Every other call runs tmac_precompute_lut into the second region of the
  * workspace and tmac_mpgemm after it, or, where the entries are looked up as integers
  * (TMAC_LUT_F16 above), builds those from the activations and uses the second region only for tables
  * that are not finite (layout 2 with K % 16 != 0 or an unsupported group size: at most 64 activation

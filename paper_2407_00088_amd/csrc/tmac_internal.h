@@ -240,8 +240,10 @@ struct RowsPlan {
   int oct;                    // n tiles per workgroup (2 for many rows at g = 4, else 1)
   int n_tiles_n, row_blocks;  // workgroups along N (nt * oct activation rows each) and M (256 weight rows each)
   int cps, slices;            // 32-k chunks per K slice, number of K slices (gridDim.z)
-  bool eight;                 // slices of eight chunks: the kernel pair for few activation rows serves the call
-  size_t part_bytes, ctr_bytes;  // workspace: partial sums (0 when slices == 1); ctr_bytes is always 0
+  bool eight;                 // several slices of cps == 8 chunks: the kernel pair for few activation rows serves the call, with
+                              // `slices` of up to sixteen chunks (rows8_slices)
+  size_t part_bytes, ctr_bytes;  // workspace: partial sums (0 when K is not split; with `eight` of slices of cps chunks, of
+                                 // which there may be fewer); ctr_bytes is always 0
   size_t srow_bytes;             // ... and the slices' sums of every activation row (eight-chunk plans)
   // fp16 tables as fixed-point numbers (see rows_fix_kernel); fix == false: none of it
   bool fix;

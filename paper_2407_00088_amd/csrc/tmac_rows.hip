@@ -1823,7 +1823,8 @@ static RowsPlan rows_plan_oct(const tmac_wdesc* desc, int N, int oct) {
   if (cps < min_cps) cps = min_cps;
   pl.cps = cps;
   // eight-chunk slices, several of them, g = 4, a group size that divides 256 (or no groups):
-  // the kernel pair for few activation rows
+  // the kernel pair for few activation rows.  (Workspace sizes stay those of such slices also where rows8_slices takes fewer: which
+  // calls tmac_mpgemm_noalloc has room for and where a run of chunks fits (rows_plan) does not move with the split.)
   pl.eight = pl.oct == 1 && desc->g == 4 && cps == R8_CH && ge.n_chunks > R8_CH && (one_group || R8_CH % cpg == 0);
   pl.slices = (ge.n_chunks + cps - 1) / cps;
   pl.part_bytes = pl.slices > 1 ? ((size_t)pl.slices * N * ge.Mp * 4 + 255) / 256 * 256 : 0;
